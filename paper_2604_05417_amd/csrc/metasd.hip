@@ -19,6 +19,7 @@
 
 #include "kernels.h"
 #include "batch.h"
+#include "prefill.h"
 
 using namespace msd;
 
@@ -43,6 +44,7 @@ int fail_global(int code, const char* fmt, ...) {
 
 constexpr int PER_LAYER = 9;
 constexpr int MAX_ROWS = 16;
+constexpr int BIG_ROWS = 2048;                // most rows of one sequence that go through a model in one pass (forward_big)
 constexpr size_t ALIGN = 256;
 constexpr int LDS_BUDGET = 60 * 1024;
 constexpr int ROWS_PD = 2;                    // gemm_bf16_rows_kernel: stages (of two chunks) in flight
@@ -153,6 +155,10 @@ const char* check_model(const metasd_model_desc& d, const char* who, char* buf, 
     return nullptr;
 }
 
+// Models whose long blocks take forward_big, and the rows such a block can have in a context.
+bool big_ok(const metasd_model_desc& d) { return d.dtype == METASD_BF16 && d.d_model / d.n_heads >= 64; }
+int big_rows(const metasd_config& c) { return std::min(BIG_ROWS, c.max_ctx); }
+
 // Word the split-K siblings of a residual GEMM set when their bounded wait for each other runs out (read back with
 // the results of every accept).
 struct GridBar { int abort; int pad[3]; };
@@ -181,12 +187,18 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
         if (c.feature_heads && d.dtype == METASD_BF16)   // a drafter head's input projection: N = d, K = 2 d
             partmax = std::max(partmax, (size_t)std::max(choose_split(MAX_ROWS, d.d_model / 16, 2 * d.d_model / 32).ksplit, ks_cap()) *
                                             MAX_ROWS * d.d_model * sizeof(float));
+        if (c.feature_heads && big_ok(d))
+            for (int r = MAX_ROWS + 1; r <= big_rows(c); ++r)
+                partmax = std::max(partmax, (size_t)choose_split_rows(d.d_model / 16, 2 * d.d_model / 32, r, 0).ksplit * r * d.d_model * sizeof(float));
         for (int i = 0; i < 5; ++i) {
             int ksplit = 1;
             if (d.dtype == METASD_BF16) ksplit = choose_split(MAX_ROWS, ns[i] / 16, ks[i] / 32).ksplit;
             // a smaller m never needs more splits for LDS, but may use up to 8 for parallelism
             ksplit = std::max(ksplit, ks_cap());
             partmax = std::max(partmax, (size_t)ksplit * MAX_ROWS * ns[i] * sizeof(float));
+            if (big_ok(d) && i < 4)
+                for (int r = MAX_ROWS + 1; r <= big_rows(c); ++r)
+                    partmax = std::max(partmax, (size_t)choose_split_rows(ns[i] / 16, ks[i] / 32, r, 0).ksplit * r * ns[i] * sizeof(float));
             if (c.batch > 1) {
                 const int kr = d.dtype == METASD_BF16 ? std::min(8, std::max(1, ks[i] / 32 / 8)) : 1;   // any split choose_split_rows may take
                 partmax = std::max(partmax, (size_t)std::max(kr, ksplit) * MAX_ROWS * c.batch * ns[i] * sizeof(float));
@@ -199,7 +211,9 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
     Layout L{};
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
-    const size_t B = (size_t)c.batch, RM = (size_t)MAX_ROWS * B;   // sequences, rows of the largest block
+    bool big = big_ok(t);
+    for (int k = 0; k < c.K; ++k) big = big || big_ok(dr[k]);
+    const size_t B = (size_t)c.batch, RM = std::max((size_t)MAX_ROWS * B, big ? (size_t)big_rows(c) : 0);   // sequences, rows of the largest block
     L.hist = take(B * c.max_ctx * 4);
     L.h = take(RM * dmax * 4);
     L.h2 = take((size_t)MAX_ROWS * dmax * 4);
@@ -938,6 +952,7 @@ int upload_table(metasd_ctx* c, Model& M) {
 int model_index(const metasd_ctx* c, const Model& M) { return &M == &c->target ? -1 : (int)(&M - c->drafters.data()); }
 
 int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool want_all);
+int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n);
 
 // A drafter with a streaming cache attends to the sinks and to the last stream_window positions of its cache's tail: the
 // block mask of the attention kernels (TreeBlk, on == 2) carries that for the duration of its forward passes.
@@ -955,6 +970,11 @@ int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool
     c->cur_model = model_index(c, M);
     if (pos0 + n > c->cfg.max_ctx) return c->fail(METASD_E_OVERFLOW, "positions %d..%d exceed max_ctx %d", pos0, pos0 + n, c->cfg.max_ctx);
     int done = 0;
+    // long blocks: everything but the row that carries logits (and a last handful of rows) goes through in big blocks
+    if (big_ok(M.d) && !c->tree && n - (logits ? 1 : 0) > MAX_ROWS) {
+        done = n - (logits ? 1 : 0);
+        if (int rc = forward_big(c, M, 0, pos0, done)) return rc;
+    }
     while (done < n) {
         const int m = std::min(MAX_ROWS, n - done);
         const bool last = done + m == n;
@@ -1126,6 +1146,23 @@ int attention_seg(metasd_ctx* c, const Model& M, int L, const Segs& sg) {
     }
 }
 
+// Causal attention of the m rows of a long block (q in d_q, result in d_ao): 32 rows per wavefront where that still leaves a
+// workgroup for every CU, else 16.
+int attention_big(metasd_ctx* c, const metasd_model_desc& d, int hd, const bf16_t* kc, const bf16_t* vc, int pos0, int m) {
+    const float scale = 1.0f / sqrtf((float)hd);
+    const bool two = (size_t)((m + 127) / 128) * d.n_heads >= (size_t)c->n_cu;
+    const int nblk = two ? (m + 127) / 128 : (m + 63) / 64;
+    metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * (double)(pos0 + m) * hd * 2 + (double)m * d.n_heads * hd * 4);
+    hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
+#define BIG_GO(HD, RB) hipExtLaunchKernelGGL((attn_prefill_kernel<HD, RB>), dim3(nblk * d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u, \
+                                             (const bf16_t*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, (float*)c->d_ao())
+    if (hd == 128) { if (two) BIG_GO(128, 2); else BIG_GO(128, 1); }
+    else { if (two) BIG_GO(64, 2); else BIG_GO(64, 1); }
+#undef BIG_GO
+    LAUNCH_CHECK(c, "attn_prefill");
+    return 0;
+}
+
 // add the split-K partials to the residual rows and normalise: many rows of 2048 or 4096 columns go through the form that
 // keeps more requests in flight per CU (same arithmetic in the same order)
 template <typename T>
@@ -1193,6 +1230,78 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
         LAUNCH_CHECK(c, "sum_partials (segments)");
     }
     for (int s = 0; s < sg.n; ++s) M.kvl[sg.seq[s]] = sg.pos0[s] + sg.m[s];
+    return 0;
+}
+
+// n consecutive tokens of one sequence, hist[seq][pos0 .. pos0 + n), through model M in blocks of up to BIG_ROWS rows: what
+// they leave is their K/V (and, with drafter heads, the target's features).  bf16 models with head_dim >= 64; no tree or
+// streaming mask.  Every weight is read once per pass of 256 rows (gemm_rows) instead of once per 16 rows: a 1500-token query
+// start on the 7B shape took 362 ms in 16-row blocks and takes 63 ms, 512 tokens on the 1B shape 40.7 and 5.6 ms.  The last layer ends with its K/V: nothing
+// reads what follows, unless the features are wanted.
+int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
+    typedef bf16_t T;
+    const metasd_model_desc& d = M.d;
+    const int D = d.d_model, H = d.n_heads, KH = d.n_kv_heads, hd = M.hd, F = d.d_ffn;
+    const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV, NF = (d.act == METASD_SWIGLU ? 2 : 1) * F;
+    hipStream_t st = c->stream;
+    float* h = c->d_h();
+    float* xn = (float*)c->d_xn();
+    float* part = c->d_part();
+    const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
+    T* kv = (T*)M.kv + (size_t)seq * M.kv_layers * 2 * plane;
+    const bool features = &M == &c->target && c->cfg.feature_heads;
+    if (pos0 + n > c->cfg.max_ctx) return c->fail(METASD_E_OVERFLOW, "positions %d..%d exceed max_ctx %d", pos0, pos0 + n, c->cfg.max_ctx);
+    c->cur_model = model_index(c, M);
+    for (int done = 0; done < n;) {
+        const int m = std::min(big_rows(c->cfg), n - done), p0 = pos0 + done;
+        int ns = 0, rc;
+        hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, st, c->d_hist() + (size_t)seq * c->cfg.max_ctx + p0, (const T*)M.w[0], D,
+                           h, p0, hd, d.rope_theta, c->d_rope(), TreeBlk{});
+        LAUNCH_CHECK(c, "embed + rope table");
+        if (M.head) {   // W_fc . [embedding ; the target's feature of the position before]
+            float* cat = (float*)c->d_act();
+            hipLaunchKernelGGL(feat_cat_kernel, dim3(m), dim3(256), 0, st, (const float*)h, (const float*)c->d_feat(), (const float*)nullptr,
+                               FeatSrc{}, p0, D, cat, 1);
+            LAUNCH_CHECK(c, "feat_cat");
+            if ((rc = gemm_rows<T>(c, cat, 2 * D, m, 2 * D, M.fc, D, nullptr, 0, nullptr, 0, &ns))) return rc;
+            const size_t nh = (size_t)m * D;
+            hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((nh + 255) / 256)), dim3(256), 0, st, (const float*)part, ns, nh, nh, h,
+                               (const float*)nullptr, D);
+            LAUNCH_CHECK(c, "sum_partials");
+            ns = 0;
+        }
+        for (int L = 0; L < d.n_layers; ++L) {
+            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 0), d.rms_eps, xn, 1);
+            LAUNCH_CHECK(c, "addnorm");
+            if ((rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV, &ns))) return rc;
+            T* kc = kv + (size_t)L * 2 * plane;
+            hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, part, ns, (size_t)m * NQKV, NQKV, p0, H, KH, hd,
+                               (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, 1, (const float*)nullptr);
+            LAUNCH_CHECK(c, "rope_kv");
+            if (L + 1 == d.n_layers && !features) break;
+            if ((rc = attention_big(c, d, hd, kc, kc + plane, p0, m))) return rc;
+            if ((rc = gemm_rows<T>(c, c->d_ao(), DQ, m, DQ, M.layer_w(L, 4), D, nullptr, 0, nullptr, 0, &ns))) return rc;
+            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 5), d.rms_eps, xn, 1);
+            LAUNCH_CHECK(c, "addnorm");
+            if (d.act == METASD_SWIGLU) rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0, &ns);
+            else rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0, &ns);
+            if (rc) return rc;
+            const size_t nact = (size_t)m * F;
+            hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, st, part, ns, (size_t)m * NF, m, F, d.act,
+                               (float*)c->d_act(), 1, (const float*)nullptr);
+            LAUNCH_CHECK(c, "ffn_act");
+            if ((rc = gemm_rows<T>(c, c->d_act(), F, m, F, M.layer_w(L, 8), D, nullptr, 0, nullptr, 0, &ns))) return rc;
+        }
+        if (features) {
+            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.final_norm(), d.rms_eps, xn, 1);   // finishes the residual rows
+            LAUNCH_CHECK(c, "addnorm");
+            const unsigned n4 = (unsigned)((size_t)m * D / 4);
+            hipLaunchKernelGGL(copy_f4_kernel, dim3((n4 + 255) / 256), dim3(256), 0, st, (const float4*)h, (float4*)(c->d_feat() + (size_t)p0 * D), n4);
+            LAUNCH_CHECK(c, "feature rows");
+        }
+        done += m;
+    }
+    M.kvl[seq] = pos0 + n;
     return 0;
 }
 
@@ -1448,6 +1557,15 @@ int draft_batch(metasd_ctx* c, const int32_t* k, int gamma) {
     sync_shared_kv(c);
     SeqTab at{};
     const bool can_group = grouped_step_supported(c);
+    // A drafter that has a long backlog in some sequences reads all but its last token in big blocks, sequence by sequence.  A
+    // big block costs about as many launches as one 16-row block over all the sequences of the arm, so it wins once
+    // the backlog has more such blocks than the arm has sequences.
+    for (int b = 0; b < B; ++b) {
+        Model& D = c->drafters[k[b]];
+        const int pend = c->sq[b].l - D.kvl[b], nseq = (int)std::count(k, k + B, k[b]);
+        if (big_ok(D.d) && pend > MAX_ROWS && pend > MAX_ROWS * nseq)
+            if (int rc = forward_big(c, D, b, D.kvl[b], pend - 1)) return rc;
+    }
     for (int j = 0; j < gamma; ++j) {
         // one forward for all arms when more than one arm is in use and every sequence has 1..16 tokens to process in its
         // drafter (always so after the first step; in the first step unless a drafter was idle for many rounds)
@@ -1809,6 +1927,7 @@ int32_t metasd_set_context(metasd_ctx* c, int32_t seq, const int32_t* tokens, in
     for (auto& d : c->drafters) { d.kvl[seq] = (kv_prefilled || d.shared_kv) ? n - 1 : 0; d.tail = 0; }
     if (!kv_prefilled && n > 1) {
         if (c->cfg.batch == 1) { if (int rc = forward(c, c->target, 0, n - 1, nullptr, false)) return rc; }
+        else if (big_ok(c->target.d) && n - 1 > MAX_ROWS) { if (int rc = forward_big(c, c->target, seq, 0, n - 1)) return rc; }
         else if (int rc = catch_up(c, c->target, std::vector<int>{seq}, std::vector<int>{n - 1}, nullptr, 0, 0)) return rc;
     }
     return METASD_OK;

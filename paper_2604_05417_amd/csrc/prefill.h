@@ -1,0 +1,194 @@
+// Kernels for long blocks of consecutive rows of one sequence: the prefill of a prompt, and a drafter's catch-up over a
+// backlog of committed tokens.  Included after kernels.h and batch.h.
+#pragma once
+
+namespace msd {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// two floats -> two bf16 (round to nearest even) in one word, element 0 in the low half: one hardware instruction
+__device__ __forceinline__ uint32_t cvt_bf16x2(float a, float b) {
+    const bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+// the two-term form of a pair: hi = bf16(x), lo = bf16(x - hi)
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
+    hi = cvt_bf16x2(a, b);
+    lo = cvt_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+}
+// Transposing LDS read: the 16 lanes of a group give the addresses of a 4 x 16 block of 16-bit elements (lane i: row i / 4,
+// columns 4 (i % 4) .. + 3); lane i receives column i (rows 0 .. 3).
+__device__ __forceinline__ s16x4 lds_read_tr(const bf16_t* p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+}
+
+// ------------------------------------------------------------------------------------------
+// Causal attention of m consecutive rows (positions pos0 .. pos0 + m - 1; their K/V are in the cache already) over the cache.
+// A workgroup of 4 wavefronts takes 64 RB rows of one head, a wavefront 16 RB of them, and walks the positions in tiles of 64
+// with a running (max, sum, O) per row:
+//   S^T[pos][row] = K . q^T   A = K rows from LDS, B = q as two bf16 terms in registers;
+//   O^T[hd][row] += V^T . P^T A = V read through the transposing LDS read, B = P as two bf16 terms - straight from the registers
+//                             that held S^T: an MFMA sums over k in whatever order its two operands agree on, so slot 8 g + j
+//                             of a 32-position chunk stands for position 4 g + j (j < 4) or 16 + 4 g + j - 4, which is where
+//                             the lanes of group g already hold the scores.
+// What bounds it: the MFMAs (two terms for q and for P, 4 per 16 x 16 x 32 block) and the LDS reads of K and V, which RB = 2
+// halves per row (one tile of K and V feeds 32 rows of a wavefront).  The next tile is requested into registers while the
+// current one is multiplied.  Heads are dealt out over the 8 XCDs (workgroup id mod 8) so that the row blocks of one head share
+// that XCD's L2, the longest row blocks first.  Measured: 1499 rows x 32 heads of 128: 124 us per layer (18.4 GFLOP causal, twice
+// that with the second terms: 0.3 PFLOP/s), where 94 passes of the 16-row kernels took 94 x (7 + 5) us; 511 rows x 32 heads of
+// 64 on 8 KV heads: 12.8 us.
+//   grid (ceil(m / (64 RB)) * H), block 256.   out: two bf16 arrays [m][H HD], lo m H HD elements behind hi.
+template <int HD, int RB>
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+                                                              const bf16_t* __restrict__ vc, int m, int pos0, int H, int KH, int max_ctx,
+                                                              float scale, float* __restrict__ out) {
+    constexpr int TP = 64, KC = HD / 32, NT = HD / 16, VPR = HD / 8;
+    constexpr int RSV = HD + 16;                       // V row stride (elements): 8 consecutive rows fall into different banks
+    constexpr int IT = TP * VPR / 256;                 // 16-byte pieces of a tile per thread
+    __shared__ __align__(16) bf16_t ks[TP * HD];       // piece p of row r in position p ^ (r & 7)
+    __shared__ __align__(16) bf16_t vs[TP * RSV];
+    const int nblk = (m + 64 * RB - 1) / (64 * RB);
+    int h, blk;
+    if ((H & 7) == 0) {
+        const int idx = blockIdx.x >> 3;
+        h = (blockIdx.x & 7) + 8 * (idx / nblk);
+        blk = nblk - 1 - idx % nblk;
+    } else {
+        h = blockIdx.x / nblk;
+        blk = nblk - 1 - blockIdx.x % nblk;
+    }
+    const int kh = h / (H / KH);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = lane & 15, g = lane >> 4;
+    const int r0 = blk * 64 * RB + wave * 16 * RB;     // this wavefront's first row
+    const size_t q_lo = (size_t)m * H * HD;
+    uint4 qh[RB][KC], ql[RB][KC];
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            const bf16_t* src = q + (size_t)min(r0 + 16 * b + row, m - 1) * H * HD + (size_t)h * HD + k * 32 + g * 8;
+            qh[b][k] = *reinterpret_cast<const uint4*>(src);
+            ql[b][k] = *reinterpret_cast<const uint4*>(src + q_lo);
+        }
+    f32x4 o[RB][NT];
+    float mx[RB], ls[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        mx[b] = -INFINITY; ls[b] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) o[b][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int L = pos0 + min(m, (blk + 1) * 64 * RB);  // positions this workgroup's rows can see
+    const int last_pos = pos0 + min(r0 + 16 * RB, m) - 1;   // .. and this wavefront's
+    const bf16_t* kb = kc + (size_t)kh * max_ctx * HD;
+    const bf16_t* vb = vc + (size_t)kh * max_ctx * HD;
+    u32x4 kr[IT], vr[IT];
+    auto request = [&](int p0) {                       // rows past the end re-read the last row: their weight is zero
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int idx = tid + it * 256, p = idx / VPR, v = idx - p * VPR;
+            const size_t at = (size_t)min(p0 + p, L - 1) * HD + v * 8;
+            kr[it] = *reinterpret_cast<const u32x4*>(kb + at);
+            vr[it] = *reinterpret_cast<const u32x4*>(vb + at);
+        }
+    };
+    request(0);
+    const float sc = scale * 1.44269504088896341f;     // scores in units of log2
+    for (int p0 = 0; p0 < L; p0 += TP) {
+        __syncthreads();                               // the readers of the previous tile are done
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int idx = tid + it * 256, p = idx / VPR, v = idx - p * VPR;
+            *reinterpret_cast<u32x4*>(ks + p * HD + ((v ^ (p & 7)) * 8)) = kr[it];
+            *reinterpret_cast<u32x4*>(vs + p * RSV + v * 8) = vr[it];
+        }
+        if (p0 + TP < L) request(p0 + TP);
+        __syncthreads();
+        if (p0 > last_pos) continue;                   // wavefront-uniform: nothing of this tile is visible to its rows
+        f32x4 s[RB][4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) s[b][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int p = t * 16 + row;
+#pragma unroll
+            for (int k = 0; k < KC; ++k) {
+                const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(ks + p * HD + (((k * 4 + g) ^ (p & 7)) * 8)));
+#pragma unroll
+                for (int b = 0; b < RB; ++b) {
+                    s[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, __builtin_bit_cast(bf16x8, qh[b][k]), s[b][t], 0, 0, 0);
+                    s[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, __builtin_bit_cast(bf16x8, ql[b][k]), s[b][t], 0, 0, 0);
+                }
+            }
+        }
+        const bool edge = p0 + TP - 1 > pos0 + r0;     // some row of the wavefront does not see the whole tile
+        uint4 ph[RB][2], pl[RB][2];
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            const int lim = pos0 + r0 + 16 * b + row - p0 - 4 * g;      // this lane's row sees element (t, v) iff 16 t + v <= lim
+            float tm = -INFINITY;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float x = (edge && 16 * t + v > lim) ? -INFINITY : s[b][t][v] * sc;
+                    s[b][t][v] = x;
+                    tm = fmaxf(tm, x);
+                }
+            tm = fmaxf(tm, __shfl_xor(tm, 16, 64));
+            tm = fmaxf(tm, __shfl_xor(tm, 32, 64));
+            const float nm = fmaxf(mx[b], tm);         // finite: every row sees position 0, in the first tile
+            const float alpha = __builtin_amdgcn_exp2f(mx[b] - nm);
+            mx[b] = nm;
+            float sum = 0.f;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float e = __builtin_amdgcn_exp2f(s[b][t][v] - nm);
+                    s[b][t][v] = e;
+                    sum += e;
+                }
+            ls[b] = ls[b] * alpha + sum;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) o[b][t] *= alpha;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                split_pair(s[b][2 * c][0], s[b][2 * c][1], ph[b][c].x, pl[b][c].x);
+                split_pair(s[b][2 * c][2], s[b][2 * c][3], ph[b][c].y, pl[b][c].y);
+                split_pair(s[b][2 * c + 1][0], s[b][2 * c + 1][1], ph[b][c].z, pl[b][c].z);
+                split_pair(s[b][2 * c + 1][2], s[b][2 * c + 1][3], ph[b][c].w, pl[b][c].w);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const bf16_t* src = vs + (c * 32 + 4 * g + (row >> 2)) * RSV + t * 16 + (row & 3) * 4;
+                const s16x4 a0 = lds_read_tr(src), a1 = lds_read_tr(src + 16 * RSV);
+                const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                for (int b = 0; b < RB; ++b) {
+                    o[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, ph[b][c]), o[b][t], 0, 0, 0);
+                    o[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pl[b][c]), o[b][t], 0, 0, 0);
+                }
+            }
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        float sum = ls[b];
+        sum += __shfl_xor(sum, 16, 64);
+        sum += __shfl_xor(sum, 32, 64);
+        const float inv = 1.0f / sum;
+        const int r = r0 + 16 * b + row;
+        if (r < m) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                store_split4(out, q_lo, (size_t)r * H * HD + (size_t)h * HD + t * 16 + 4 * g,
+                             make_float4(o[b][t][0] * inv, o[b][t][1] * inv, o[b][t][2] * inv, o[b][t][3] * inv));
+        }
+    }
+}
+
+}  // namespace msd

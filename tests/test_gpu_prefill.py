@@ -1,0 +1,112 @@
+"""Prefill of long prompts in large row blocks: every K/V entry the target's cache holds afterwards against a plain PyTorch
+fp32 forward of the same model, at the edges of the row tiles and of the blocks, and the rounds that follow against the oracle."""
+import math
+
+import pytest
+import torch
+
+import paper_2604_05417_amd as M
+import workloads as W
+from test_gpu_batch import batch_pair, make_lockstep
+from test_gpu_bf16 import run_lockstep
+
+pytestmark = pytest.mark.gpu
+TOL = 3e-2
+
+
+def kv_reference(desc, w, tokens):
+    """K and V of every position and layer, [layer, 2, kv_head, n, hd] fp32 (rounded to bf16 where the cache rounds)."""
+    d, H, KH, L = desc["d_model"], desc["n_heads"], desc["n_kv_heads"], desc["n_layers"]
+    hd, n, dev = d // H, len(tokens), w[0].device
+    f = [None if t is None else t.float() for t in w]
+    norm = lambda x, g: x * torch.rsqrt(x.square().mean(-1, keepdim=True) + desc["rms_eps"]) * g
+    ang = (torch.arange(n, device=dev, dtype=torch.float64)[:, None] *
+           desc["rope_theta"] ** (-2.0 * torch.arange(hd // 2, device=dev, dtype=torch.float64) / hd))
+    cs, sn = ang.cos().float()[None], ang.sin().float()[None]
+
+    def rot(x):
+        a, b = x[..., : hd // 2], x[..., hd // 2:]
+        return torch.cat([a * cs - b * sn, a * sn + b * cs], -1)
+
+    h = f[0][torch.as_tensor(tokens, device=dev, dtype=torch.int64)]
+    mask = torch.ones((n, n), dtype=torch.bool, device=dev).tril()
+    out = []
+    for i in range(L):
+        g1, wq, wk, wv, wo, g2, wg, wu, wd = f[1 + 9 * i: 10 + 9 * i]
+        x = norm(h, g1)
+        heads = lambda y, nh: y.view(n, nh, hd).transpose(0, 1)
+        q = rot(heads(x @ wq.T, H))
+        k = rot(heads(x @ wk.T, KH)).bfloat16().float()
+        v = heads(x @ wv.T, KH).bfloat16().float()
+        out.append(torch.stack([k, v]))
+        kk, vv = (t.repeat_interleave(H // KH, 0).contiguous() for t in (k, v))
+        s = torch.matmul(q, kk.transpose(1, 2).contiguous()) / math.sqrt(hd)
+        o = torch.matmul(torch.softmax(s.masked_fill(~mask, -math.inf), -1), vv)
+        h = h + o.transpose(0, 1).reshape(n, H * hd) @ wo.T
+        x = norm(h, g2)
+        h = h + (torch.nn.functional.silu(x @ wg.T) * (x @ wu.T)) @ wd.T
+    return torch.stack(out)
+
+
+def check_prefill(desc, n, batch=1, seed=5):
+    tw = W.gen_weights(desc, seed, device="cuda")
+    drafters = [W.early_exit_drafter(desc, tw, 1, 0.01, 9)]
+    g = M.MetaSD((desc, tw), drafters, gamma_max=3, max_ctx=n + 8, temperature=1.0, seed=1, batch=batch, share_target_kv=True)
+    for b in range(batch):
+        tok = W.prompt_tokens(n - b, desc["vocab"], 3 + b)
+        g.set_context(tok, seq=b)
+        torch.cuda.synchronize()
+        kv = (g.kv_target[b] if batch > 1 else g.kv_target).float()
+        ref = kv_reference(desc, tw, tok[:-1])
+        m = n - b - 1
+        # both sides round to bf16 (half an ulp each, 2^-8 of the value) what they hold to about 1e-3 of the rows' rms
+        bound = ref.abs() * 2.0 ** -7 + 2e-3 * ref.square().mean().sqrt()
+        bad = ((kv[:, :, :, :m] - ref).abs() > bound)
+        assert not bad.any(), (b, bad.nonzero()[:4].tolist(), int(bad.sum()))
+        assert (kv[:, :, :, m:] == 0).all()                       # nothing past the prompt
+    g.close()
+
+
+HD64 = W.model_desc(3, 512, 8, 2, 736, 528, W.SWIGLU, W.BF16)
+HD128 = W.model_desc(2, 512, 4, 4, 1056, 528, W.SWIGLU, W.BF16)
+
+
+@pytest.mark.parametrize("n", [18, 33, 65, 66, 130, 257, 258, 600])
+@pytest.mark.parametrize("desc", [HD64, HD128], ids=["hd64_gqa", "hd128"])
+def test_prefill_leaves_the_models_kv(desc, n):
+    check_prefill(desc, n)
+
+
+def test_prefill_of_more_than_one_block():
+    check_prefill(HD64, 2048 + 21)                                # a block of 2048 rows and one of 20
+
+
+@pytest.mark.parametrize("desc", [W.model_desc(2, 1024, 16, 4, 352, 528, W.SWIGLU, W.BF16), W.model_desc(2, 2048, 16, 16, 352, 528, W.SWIGLU, W.BF16)],
+                         ids=["hd64", "hd128"])
+def test_prefill_with_32_rows_per_wavefront(desc):
+    check_prefill(desc, 2048 + 1)                                 # 16 row blocks of 128 x 16 heads fill the chip
+
+
+def test_prefill_of_a_sequence_in_a_batch():
+    check_prefill(HD64, 140, batch=3)
+
+
+@pytest.mark.parametrize("n", [37, 300])
+def test_rounds_after_a_long_prefill_and_drafter_catch_up(n):
+    cfg = W.config4(n_layers=2, ctx=n, n_new=64, K=2, d_model=256, n_heads=4, d_ffn=512, vocab=1024, dd_model=128, dn_heads=2, dd_ffn=160)
+    cfg["gamma"], cfg["max_ctx"] = 4, n + 60
+    st = run_lockstep(cfg, 1.0, rounds=4, kv_prefilled=False)
+    assert st["max_dp"] <= TOL and st["max_dq"] <= TOL and st["ties_shared"] <= 1, st
+
+
+def test_ragged_batch_with_long_drafter_backlogs():
+    cfg = W.config4(n_layers=2, ctx=40, n_new=64, K=2, d_model=256, n_heads=4, d_ffn=512, vocab=1024, dd_model=128, dn_heads=2, dd_ffn=160)
+    cfg["gamma"], cfg["max_ctx"] = 3, 420
+    prompts = [W.prompt_tokens(n, 1024, 70 + i) for i, n in enumerate((350, 12, 120))]
+    g, seqs = batch_pair(cfg, 1.0, prompts, TOL)
+    bl = make_lockstep(g, cfg, seqs, prompts, 1.0, TOL)
+    for _ in range(4):
+        bl.round()
+    g.close()
+    for ls in bl.seqs:
+        assert ls.stats["max_dp"] <= TOL and ls.stats["max_dq"] <= TOL and ls.stats["ties_shared"] <= 1, ls.stats
