@@ -1,0 +1,186 @@
+// Many-row GEMM on MFMA: prefill blocks and the verification of a batch.  Included after kernels.h and batch.h.
+#pragma once
+
+namespace msd {
+
+// ------------------------------------------------------------------------------------------
+//   out[ks][r][n] = sum over K-slice ks of x[r][k] W[n][k],  W in streaming-tile order (1 KiB: 16 features x 32 inputs),
+//   x interleaved (store_il4): per row and 32-wide chunk one 128-byte line, 32 hi terms, then 32 lo terms.
+// A workgroup of 8 wavefronts, four along the rows and two along the features, owns 64 RB rows x 2 TB tiles of one K-slice;
+// a wavefront multiplies 16 RB rows with TB tiles, both terms.  The slice advances one 32-wide chunk per stage: a stage - the
+// rows' lines and the tiles' KiBs - goes from memory straight into LDS (global_load_lds_dwordx4, no staging registers), NS - 1
+// stages ahead, and a wavefront waits only for the requests of the stage it needs (vmcnt counts), so the stream runs on
+// through the barriers.  Both operands are read from LDS: per stage and wavefront 2 RB + TB KiB for 2 RB TB MFMAs.
+//   LDS layout of a stage: row r: its 8 pieces of 16 bytes, piece q in position q ^ ((r >> 1) & 7) (conflict-free fragment
+// reads); then the tiles as they are.
+//   The wavefronts of a SIMD (w and w + 4) take turns: while 0-3 multiply a stage from registers, 4-7 read theirs from LDS, and
+// the other way round, one barrier between two turns; neither the fragment reads nor the waits for them stand between MFMAs.
+//   What bounds it: from about 500 rows on the power limit - 1.15 to 1.28 PFLOP/s (both terms counted) on the 7B projections
+// with random values, where this machine's library GEMM reaches 0.7 to 1.2 on the same shapes and 1.33 to 1.5 on 8192 .. 16384
+// cubes (all-zero operands: 1.5 and 2.1).  Measured against the kernel it replaces (256 rows per launch, weights in registers): 1499
+// rows, one 7B layer 1586 -> 990 us; 256 rows QKV 54 -> 47, output 29 -> 20, gate|up 90 -> 80, down 52 -> 44 us; 20 rows of the 1B
+// shape gate|up 21.4 -> 15.
+//   Workgroup ids are dealt out so that the row blocks of one feature group run on one XCD one after the other (its L2 then
+// serves the weights to all of them).
+//   grid nrb * ngroups * ksplit, block 512, dynamic LDS NS * (8192 RB + 2048 TB) bytes;
+//   nrb = ceil(R / (64 RB)), ngroups = ceil(ntiles / (2 TB)).
+template <int RB, int TB, int NS>
+__device__ __forceinline__ void gemm_tiles_body(const bf16_t* __restrict__ x, int R, int kchunks, const bf16_t* __restrict__ W0,
+                                                const bf16_t* __restrict__ W1, const bf16_t* __restrict__ W2, int t0, int t1, int ntiles,
+                                                float* __restrict__ out, size_t out_sstride, int N, int cps, int nrb) {
+    extern __shared__ uint4 lds[];
+    constexpr int BM = 64 * RB, NT = 2 * TB;
+    constexpr int STAGE = BM * 8 + NT * 64;            // 16-byte pieces per stage
+    constexpr int NREQ = 8 * RB + NT;                  // requests of 1 KiB per stage: 8 rows each, then one tile each
+    constexpr int PER = NREQ / 8, REM = NREQ % 8;      // wavefront w issues PER (w < REM: one more)
+    const int n8 = gridDim.x >> 3, r8 = gridDim.x & 7, xcd = blockIdx.x & 7;
+    int id = xcd * n8 + min(xcd, r8) + (blockIdx.x >> 3);
+    const int rb = id % nrb;
+    id /= nrb;
+    const int ngroups = (ntiles + NT - 1) / NT, tg = id % ngroups, ks = id / ngroups;
+    if (rb * BM >= R) return;                          // a smaller row group (workgroup-uniform, before any barrier)
+    const int c0 = ks * cps, nst = min(cps, kchunks - c0);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wc = wave & 1, row16 = lane & 15, g = lane >> 4;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds;
+
+    // this wavefront's requests: id w, w + 8, ..: source (uniform base, advancing with the stage; per-lane offset) and place
+    unsigned voff[PER + 1];
+    const char* base[PER + 1];
+    unsigned step[PER + 1];
+#pragma unroll
+    for (int j = 0; j <= PER; ++j) {
+        const int q = wave + 8 * j;
+        if (j < RB) {                                  // (8 RB row requests: j < RB for every wavefront)
+            const int row = 8 * q + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+            base[j] = reinterpret_cast<const char*>(x) + ((size_t)rb * BM * kchunks + c0) * 128;
+            voff[j] = (unsigned)min(row, R - 1 - rb * BM) * (unsigned)kchunks * 128u + (unsigned)piece * 16u;
+            step[j] = 128;
+        } else {
+            const int t = min(tg * NT + min(q - 8 * RB, NT - 1), ntiles - 1);
+            const bf16_t* W;
+            int tt;
+            if (t < t0) { W = W0; tt = t; }
+            else if (t < t1) { W = W1; tt = t - t0; }
+            else { W = W2; tt = t - t1; }
+            base[j] = reinterpret_cast<const char*>(W) + ((size_t)tt * kchunks + c0) * 1024;
+            voff[j] = lane * 16;
+            step[j] = 1024;
+        }
+    }
+    auto request = [&](int buf) {                      // the next stage's requests into buffer buf
+#pragma unroll
+        for (int j = 0; j <= PER; ++j)
+            if (j < PER || wave < REM) {
+                const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)(buf * STAGE * 16 + (wave + 8 * j) * 1024));
+                const unsigned long long b = (unsigned long long)base[j];
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff[j]), "s"(b) : "memory", "m0");
+                base[j] += step[j];
+            }
+    };
+    // all but the youngest NS - 2 stages of this wavefront's requests have landed
+    auto wait_stage = [&]() {
+        if (REM && wave < REM) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((PER + (REM ? 1 : 0)) * (NS - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 2)) : "memory");
+    };
+    static_assert((PER + 1) * (NS - 2) < 64, "vmcnt counts to 63");
+    f32x4 acc[RB][TB];
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int i = 0; i < TB; ++i) acc[a][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int xrow = wr * 16 * RB + row16, sw = (xrow >> 1) & 7;     // the same for all row blocks of the wavefront (16 rows apart)
+    const int xat_h = xrow * 8 + (g ^ sw), xat_l = xrow * 8 + ((g ^ sw) ^ 4), wat = BM * 8 + wc * TB * 64 + lane;
+#pragma unroll
+    for (int u = 0; u < NS - 1; ++u)
+        if (u < nst) request(u);
+    u32x4 w[TB], fh[RB], fl[RB];
+    auto fetch = [&](int buf) {
+        const u32x4* sb = reinterpret_cast<const u32x4*>(lds) + (size_t)buf * STAGE;
+#pragma unroll
+        for (int a = 0; a < RB; ++a) { fh[a] = sb[xat_h + 128 * a]; fl[a] = sb[xat_l + 128 * a]; }
+#pragma unroll
+        for (int i = 0; i < TB; ++i) w[i] = sb[wat + 64 * i];
+    };
+    auto mult = [&]() {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int a = 0; a < RB; ++a) {
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+                acc[a][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[i]), __builtin_bit_cast(bf16x8, fh[a]), acc[a][i], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+                acc[a][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[i]), __builtin_bit_cast(bf16x8, fl[a]), acc[a][i], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_setprio(0);
+    };
+    auto barrier = [&]() { __builtin_amdgcn_sched_barrier(0); lds_barrier(); __builtin_amdgcn_sched_barrier(0); };
+    // waits until stage st + 1 has landed, when the youngest stage requested is st + NS - 1 (or the last)
+    auto wait_next = [&](int st) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + NS <= nst) wait_stage();
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    wait_next(-1);
+    barrier();
+    int buf = 0;
+    if (wave < 4) {
+        for (int st = 0; st < nst; ++st) {
+            if (st + NS - 1 < nst) request(buf == 0 ? NS - 1 : buf - 1);
+            fetch(buf);
+            barrier();
+            mult();
+            wait_next(st);
+            barrier();
+            if (++buf == NS) buf = 0;
+        }
+        barrier();
+    } else {
+        if (NS - 1 < nst) request(NS - 1);
+        barrier();
+        for (int st = 0; st < nst; ++st) {
+            fetch(buf);
+            wait_next(st);
+            barrier();
+            if (st + NS < nst) request(buf);
+            __builtin_amdgcn_sched_barrier(0);
+            mult();
+            barrier();
+            if (++buf == NS) buf = 0;
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < RB; ++a) {
+        const int row = rb * BM + (wr * RB + a) * 16 + row16;
+        if (row < R) {
+#pragma unroll
+            for (int i = 0; i < TB; ++i) {
+                const int t = tg * NT + wc * TB + i;
+                if (t < ntiles)
+                    *reinterpret_cast<float4*>(out + (size_t)ks * out_sstride + (size_t)row * N + (size_t)t * 16 + g * 4) =
+                        make_float4(acc[a][i][0], acc[a][i][1], acc[a][i][2], acc[a][i][3]);
+            }
+        }
+    }
+}
+
+template <int RB, int TB, int NS>
+__global__ __launch_bounds__(512) void gemm_tiles_kernel(const bf16_t* __restrict__ x, int R, int kchunks, const bf16_t* __restrict__ W0,
+                                                         const bf16_t* __restrict__ W1, const bf16_t* __restrict__ W2, int t0, int t1,
+                                                         int ntiles, float* __restrict__ out, size_t out_sstride, int N, int cps, int nrb) {
+    gemm_tiles_body<RB, TB, NS>(x, R, kchunks, W0, W1, W2, t0, t1, ntiles, out, out_sstride, N, cps, nrb);
+}
+
+// One launch for several row groups with weights of their own (same shapes): blockIdx.y is the group; its rows [r0, r0 + m) of
+// x are multiplied with its matrices into the same rows of out.   grid (as above with the largest m, groups)
+template <int RB, int TB, int NS>
+__global__ __launch_bounds__(512) void gemm_tiles_grouped_kernel(const bf16_t* __restrict__ x, int kchunks, int t0, int t1, int ntiles,
+                                                                 float* __restrict__ out, size_t out_sstride, int N, int cps, int nrb,
+                                                                 RowGroups gg) {
+    const int g = blockIdx.y;
+    gemm_tiles_body<RB, TB, NS>(x + (size_t)gg.r0[g] * kchunks * 64, gg.m[g], kchunks, gg.W[g][0], gg.W[g][1], gg.W[g][2], t0, t1, ntiles,
+                                out + (size_t)gg.r0[g] * N, out_sstride, N, cps, nrb);
+}
+
+}  // namespace msd

@@ -142,6 +142,14 @@ __device__ __forceinline__ void store_split4(float* base, size_t n, size_t at, c
     const bf16_t l0 = f2bf(v.x - bf2f(h0)), l1 = f2bf(v.y - bf2f(h1)), l2 = f2bf(v.z - bf2f(h2)), l3 = f2bf(v.w - bf2f(h3));
     *reinterpret_cast<uint2*>(lo) = make_uint2((uint32_t)l0 | ((uint32_t)l1 << 16), (uint32_t)l2 | ((uint32_t)l3 << 16));
 }
+// The interleaved form of the same two terms, read by the many-row GEMM (gemm_tiles.h): per row and 32-wide chunk one 128-byte
+// line, the 32 hi terms, then the 32 lo terms.  at: element index in a row-major block whose rows are a multiple of 32 long.
+__device__ __forceinline__ size_t il_index(size_t at) { return 2 * at - (at & 31); }
+// split = 1: two arrays, n = elements of the whole block; split = 2: interleaved
+__device__ __forceinline__ void store_terms4(float* base, int split, size_t n, size_t at, const float4& v) {
+    if (split == 2) store_split4(base, 32, il_index(at), v);
+    else store_split4(base, n, at, v);
+}
 __device__ __forceinline__ void store_split1(float* base, size_t n, size_t at, float v) {
     bf16_t* hi = reinterpret_cast<bf16_t*>(base) + at;
     const bf16_t h = f2bf(v);
@@ -154,7 +162,7 @@ __device__ __forceinline__ void store_split1(float* base, size_t n, size_t at, f
 // projection, x[r] = [embedding row h[r] ; feature of the position before row r], 2 d values per row.  The feature comes
 // from the table of the target's features (feat[p] = residual stream after the target's last layer at position p; row r at
 // position pos0 + r takes feat[pos0 + r - 1], zeros for position 0) or, est != nullptr, from the head's own estimate of
-// it (est[src.idx[r]]: one row for the draft steps of a chain after the first, the rows of a tree level take their parents').  split != 0: written as two bf16 arrays.     grid (m), block 256
+// it (est[src.idx[r]]: one row for the draft steps of a chain after the first, the rows of a tree level take their parents').  split != 0: written as two bf16 terms (store_terms4).     grid (m), block 256
 struct FeatSrc { uint8_t idx[16]; };   // estimates: the row of `est` that row r takes (chain steps: 0; tree levels: the parent node)
 __global__ void feat_cat_kernel(const float* __restrict__ h, const float* __restrict__ feat, const float* __restrict__ est, FeatSrc src,
                                 int pos0, int d, float* __restrict__ out, int split) {
@@ -166,7 +174,7 @@ __global__ void feat_cat_kernel(const float* __restrict__ h, const float* __rest
         if (i < d) v = *reinterpret_cast<const float4*>(h + (size_t)r * d + i);
         else if (!est && p < 0) v = make_float4(0.f, 0.f, 0.f, 0.f);
         else v = *reinterpret_cast<const float4*>(f + (i - d));
-        if (split) store_split4(out, (size_t)gridDim.x * 2 * d, (size_t)r * 2 * d + i, v);
+        if (split) store_terms4(out, split, (size_t)gridDim.x * 2 * d, (size_t)r * 2 * d + i, v);
         else *reinterpret_cast<float4*>(out + (size_t)r * 2 * d + i) = v;
     }
 }
@@ -181,7 +189,7 @@ __global__ void copy_f4_kernel(const float4* __restrict__ src, float4* __restric
 // residual add of split-K partial sums + RMSNorm:      grid (m), block 1024, d % 4 == 0
 //   h[r] += sum_s part[s][r]   (skipped when nsplit == 0)
 //   xn[r] = h[r] / sqrt(mean(h[r]^2) + eps) * gain          (fp32; T is the type of the gain)
-// split != 0: xn is written as two bf16 arrays (see store_split4), the form the bf16 GEMM stages.
+// split != 0: xn is written as two bf16 terms (store_terms4), the form the bf16 GEMMs stage.
 
 template <typename T>
 __device__ __forceinline__ void addnorm_body(float* __restrict__ h, const float* __restrict__ part, int nsplit, size_t sstride, int d,
@@ -238,7 +246,7 @@ __device__ __forceinline__ void addnorm_body(float* __restrict__ h, const float*
             o.y = v.y * inv * gn.y;
             o.z = v.z * inv * gn.z;
             o.w = v.w * inv * gn.w;
-            if (split) store_split4(xn, (size_t)gridDim.x * d, (size_t)r * d + i, o);
+            if (split) store_terms4(xn, split, (size_t)gridDim.x * d, (size_t)r * d + i, o);
             else *reinterpret_cast<float4*>(xn + (size_t)r * d + i) = o;
         }
     }
@@ -1680,7 +1688,7 @@ __global__ __launch_bounds__(256) void attn_partial_mfma_tree_kernel(const float
 }
 
 // Merge of the chunk records of (head h, block row r): nchunks records are merged, records of one head are
-// nch_stride chunks apart; the result goes to row r_out of out (split: as two bf16 arrays lo_off elements apart).
+// nch_stride chunks apart; the result goes to row r_out of out (split: as two bf16 terms, 1: arrays lo_off elements apart, 2: interleaved).
 template <int HD>
 __device__ __forceinline__ void attn_combine_body(const float* __restrict__ part, int nchunks, int nch_stride, int H,
                                                   float* __restrict__ out, int split, int h, int r, int r_out, size_t lo_off) {
@@ -1707,7 +1715,8 @@ __device__ __forceinline__ void attn_combine_body(const float* __restrict__ part
             Lsum += lc[u] * w;
             o += oc[u] * w;
         }
-        if (split) store_split1(out, lo_off, (size_t)r_out * H * HD + (size_t)h * HD + col, o / Lsum);
+        if (split == 2) store_split1(out, 32, il_index((size_t)r_out * H * HD + (size_t)h * HD + col), o / Lsum);
+        else if (split) store_split1(out, lo_off, (size_t)r_out * H * HD + (size_t)h * HD + col, o / Lsum);
         else out[(size_t)r_out * H * HD + (size_t)h * HD + col] = o / Lsum;
     };
     if (nchunks <= 8) { merge_all(std::integral_constant<int, 8>{}); return; }
@@ -1737,7 +1746,8 @@ __device__ __forceinline__ void attn_combine_body(const float* __restrict__ part
             o += oc[u] * w;
         }
     }
-    if (split) store_split1(out, lo_off, (size_t)r_out * H * HD + (size_t)h * HD + col, o / Lsum);
+    if (split == 2) store_split1(out, 32, il_index((size_t)r_out * H * HD + (size_t)h * HD + col), o / Lsum);
+    else if (split) store_split1(out, lo_off, (size_t)r_out * H * HD + (size_t)h * HD + col, o / Lsum);
     else out[(size_t)r_out * H * HD + (size_t)h * HD + col] = o / Lsum;
 }
 
@@ -1778,7 +1788,7 @@ __global__ void ffn_act4_kernel(const float* __restrict__ part, int nsplit, size
     if (inv) { g.x *= sc; g.y *= sc; g.z *= sc; g.w *= sc; u.x *= sc; u.y *= sc; u.z *= sc; u.w *= sc; }
     auto f1 = [&](float gg, float uu) { return act == 1 ? gg / (1.0f + expf(-gg)) * uu : 0.5f * gg * (1.0f + erff(gg * 0.70710678118654752f)); };
     const float4 y = make_float4(f1(g.x, u.x), f1(g.y, u.y), f1(g.z, u.z), f1(g.w, u.w));
-    if (split) store_split4(out, (size_t)m * f, idx, y);
+    if (split) store_terms4(out, split, (size_t)m * f, idx, y);
     else *reinterpret_cast<float4*>(out + idx) = y;
 }
 

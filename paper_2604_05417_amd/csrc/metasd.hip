@@ -20,6 +20,7 @@
 #include "kernels.h"
 #include "batch.h"
 #include "prefill.h"
+#include "gemm_tiles.h"
 
 using namespace msd;
 
@@ -47,7 +48,6 @@ constexpr int MAX_ROWS = 16;
 constexpr int BIG_ROWS = 2048;                // most rows of one sequence that go through a model in one pass (forward_big)
 constexpr size_t ALIGN = 256;
 constexpr int LDS_BUDGET = 60 * 1024;
-constexpr int ROWS_PD = 2;                    // gemm_bf16_rows_kernel: stages (of two chunks) in flight
 constexpr size_t FULLK_LDS_MAX = 150 * 1024;   // gemm_fullk_residual_kernel: the whole activation block in LDS
 
 size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
@@ -108,32 +108,37 @@ Split choose_split(int m, int ntiles, int kchunks) {
     return s;
 }
 
-// Many-row GEMM (more than 16 rows): tiles per workgroup (8; for more than 128 rows also 6, 4, or 12 - the form that
-// loads its activations straight into LDS) and K split.
-// A workgroup holds a CU (its LDS), so the launch runs in ceil(workgroups / 256) rounds; measured on the 7B
-// shapes at 256 rows a round costs about 0.9 / 0.75 / 0.6 / 1.28 us per 32-wide K chunk with 8 / 6 / 4 / 12 tiles (a
-// fixed part for staging the activations plus the multiplies), and the split-K partials are written and read once.
-Split choose_split_rows(int ntiles, int kchunks, int R, int forced_tpb) {
-    int best = 1, best_tpb = 8;
+// Many-row GEMM (gemm_tiles.h; more than 16 rows): workgroup tile (64 rb rows x 2 tb feature tiles, ns stages of LDS) and K
+// split.  The launch runs in rounds of 256 workgroups.  Measured on the 7B and 1B projections at 20 .. 1499 rows: a stage of
+// 32 inputs takes 0.115 + 0.044 rb tb us (within 5 % from 4 to 24 products: 0.29 us for 1 x 4, 0.64 for 2 x 6, 1.19 for 3 x 8),
+// a launch 5 us more; few rows are bound by the weight stream, 5.6 TB/s; the partials are written and read once at 5 TB/s.
+// A split whose partials exceed PARTIALS_MAX never pays (50 us of traffic).
+struct RowsPlan { int rb, tb, ksplit, cps, nrb, ngroups; };
+constexpr size_t PARTIALS_MAX = (size_t)128 << 20;
+constexpr int ROWS_TILES[][2] = {{4, 6}, {3, 8}, {3, 6}, {3, 4}, {2, 8}, {2, 6}, {2, 4}, {2, 3}, {1, 8}, {1, 6}, {1, 4}, {1, 2}};
+// Stages of LDS of a tile: three to seven within 160 KiB, and four for the smallest so that several workgroups share a CU.
+constexpr int rows_stages(int rb, int tb) {
+    return rb * 8 + tb * 2 >= 40 ? 3 : rb * 8 + tb * 2 >= 28 || (rb == 2 && tb == 4) || (rb == 1 && tb <= 4) ? 4 : 6;
+}
+
+RowsPlan plan_rows(int ntiles, int kchunks, int R, int groups, int forced_tpb, int forced_rb) {
+    RowsPlan best{};
     double best_cost = 1e30;
-    for (int tpb : {8, 6, 4, 12}) {
-        if (tpb != 8 && (R <= 128 || (forced_tpb && tpb != forced_tpb))) continue;
-        if (tpb == 8 && forced_tpb && forced_tpb != 8 && R > 128) continue;
-        const int groups = (ntiles + tpb - 1) / tpb;
-        for (int ks = 1; ks <= 8 && kchunks / ks >= 8; ++ks) {
-            const int cps = ((kchunks + ks - 1) / ks + 3) / 4 * 4;
-            const int rounds = (groups * ks + 255) / 256;
-            const double per_chunk = tpb == 12 ? 1.28 : 0.3 + 0.075 * tpb;
-            const double cost = (double)rounds * cps * per_chunk + (ks > 1 ? (double)ks * R * ntiles * 16 * 8 / 8e6 : 0.0);   // us
-            if (cost < best_cost) { best_cost = cost; best = ks; best_tpb = tpb; }
+    const double stream = (double)groups * ntiles * kchunks * 1024 / 5.6e6;
+    for (const auto& t : ROWS_TILES) {
+        const int rb = t[0], tb = t[1];
+        if ((forced_tpb && 2 * tb != forced_tpb) || (forced_rb && rb != forced_rb)) continue;
+        if (!forced_rb && rb > 1 && 64 * (rb - 1) >= R) continue;
+        const int nrb = (R + 64 * rb - 1) / (64 * rb), ng = (ntiles + 2 * tb - 1) / (2 * tb);
+        for (int ks = 1; ks <= 8 && (ks == 1 || (kchunks / ks >= 8 && (size_t)ks * R * groups * ntiles * 64 <= PARTIALS_MAX)); ++ks) {
+            const int cps = (kchunks + ks - 1) / ks, k2 = (kchunks + cps - 1) / cps;
+            const double rounds = (nrb * ng * k2 * groups + 255) / 256;
+            const double mult = rounds * cps * (0.115 + 0.044 * rb * tb);
+            const double cost = std::max(mult, stream) + 0.15 * std::min(mult, stream) + (double)k2 * R * groups * ntiles * 64 * 1.2 / 5e6;
+            if (cost < best_cost) { best_cost = cost; best = RowsPlan{rb, tb, k2, cps, nrb, ng}; }
         }
     }
-    int ks = best;
-    int cps = ((kchunks + ks - 1) / ks + 3) / 4 * 4;
-    ks = (kchunks + cps - 1) / cps;
-    Split s;
-    s.ksplit = ks; s.cps = cps; s.tpb = best_tpb; s.lds = 0;
-    return s;
+    return best.rb ? best : plan_rows(ntiles, kchunks, R, groups, 0, 0);   // a forced pair that is no tile
 }
 
 const char* check_model(const metasd_model_desc& d, const char* who, char* buf, size_t n) {
@@ -170,7 +175,7 @@ struct Layout {
 
 Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const metasd_model_desc* dr) {
     int dmax = t.d_model, fmax = t.d_ffn, vmax = t.vocab, hmax = t.n_heads, hdmax = t.d_model / t.n_heads;
-    size_t partmax = 0, gxmax = ALIGN;
+    size_t partmax = 0, partfew = 0, gxmax = ALIGN;   // split-K partials of the largest block, of a block of at most 16 rows
     auto acc = [&](const metasd_model_desc& d) {
         // sibling exchange of the residual GEMMs (N = d_model; K = attention width or d_ffn): ksplit - 1 published
         // partial tiles of m rows, for the split choose_split really takes at every block height (LDS capacity
@@ -187,22 +192,20 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
         if (c.feature_heads && d.dtype == METASD_BF16)   // a drafter head's input projection: N = d, K = 2 d
             partmax = std::max(partmax, (size_t)std::max(choose_split(MAX_ROWS, d.d_model / 16, 2 * d.d_model / 32).ksplit, ks_cap()) *
                                             MAX_ROWS * d.d_model * sizeof(float));
-        if (c.feature_heads && big_ok(d))
-            for (int r = MAX_ROWS + 1; r <= big_rows(c); ++r)
-                partmax = std::max(partmax, (size_t)choose_split_rows(d.d_model / 16, 2 * d.d_model / 32, r, 0).ksplit * r * d.d_model * sizeof(float));
+        // the many-row GEMM: one set of partials of the largest block, or any split of it within PARTIALS_MAX
+        auto rows_part = [&](int n, size_t rows) {
+            return std::max(rows * n * sizeof(float), std::min(PARTIALS_MAX, 8 * rows * n * sizeof(float)));
+        };
+        if (c.feature_heads && big_ok(d)) partmax = std::max(partmax, rows_part(d.d_model, big_rows(c)));
         for (int i = 0; i < 5; ++i) {
             int ksplit = 1;
             if (d.dtype == METASD_BF16) ksplit = choose_split(MAX_ROWS, ns[i] / 16, ks[i] / 32).ksplit;
             // a smaller m never needs more splits for LDS, but may use up to 8 for parallelism
             ksplit = std::max(ksplit, ks_cap());
             partmax = std::max(partmax, (size_t)ksplit * MAX_ROWS * ns[i] * sizeof(float));
-            if (big_ok(d) && i < 4)
-                for (int r = MAX_ROWS + 1; r <= big_rows(c); ++r)
-                    partmax = std::max(partmax, (size_t)choose_split_rows(ns[i] / 16, ks[i] / 32, r, 0).ksplit * r * ns[i] * sizeof(float));
-            if (c.batch > 1) {
-                const int kr = d.dtype == METASD_BF16 ? std::min(8, std::max(1, ks[i] / 32 / 8)) : 1;   // any split choose_split_rows may take
-                partmax = std::max(partmax, (size_t)std::max(kr, ksplit) * MAX_ROWS * c.batch * ns[i] * sizeof(float));
-            }
+            partfew = std::max(partfew, (size_t)ksplit * MAX_ROWS * ns[i] * sizeof(float));
+            if (big_ok(d) && i < 4) partmax = std::max(partmax, rows_part(ns[i], big_rows(c)));
+            if (c.batch > 1) partmax = std::max(partmax, rows_part(ns[i], (size_t)MAX_ROWS * c.batch));
         }
     };
     acc(t);
@@ -219,7 +222,7 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
     L.h2 = take((size_t)MAX_ROWS * dmax * 4);
     L.xn = take(RM * dmax * 4);
     L.part = take(partmax);
-    L.part2 = take(partmax);
+    L.part2 = take(partfew);                                        // ping-pong partner of part, blocks of few rows only (forward_rows_fused)
     L.gx = take(gxmax);                                            // tagged partial sums of the residual GEMMs
     L.ssq = take((size_t)(dmax / 16 + 1) * 16 * 4);              // per tile group (or per tile) and row
     L.inv = take(64);
@@ -433,7 +436,9 @@ struct metasd_ctx {
     bool fullk = true;               // residual GEMMs whose input fits in LDS run without split-K (METASD_GEMM_FULLK=0: off)
     bool grouped_on = true;          // batched drafting: one forward per step for all arms (METASD_DRAFT_GROUPED=0: one per arm)
     int att_cpw = 0;                 // batched attention: chunks per workgroup, 0 = by the rule in attention_seg_hd (METASD_ATT_CPW=1..64 forces one)
-    int rows_tpb = 0;                // many-row GEMM: tiles per workgroup, 0 = by the cost model (METASD_ROWS_TPB=4|6|8|12 forces one)
+    int rows_tpb = 0;                // many-row GEMM: feature tiles per workgroup, 0 = by the cost model (METASD_ROWS_TPB=4|6|8|12|16 forces one)
+    int rows_rb = 0;                 // .. and its rows in units of 64 (METASD_ROWS_RB=1..4)
+    struct { int ntiles, kchunks, R, groups; RowsPlan plan; } plans[64] = {};   // rows_plan
     bool fullk_roll = true;          // .. and larger inputs with rolling private staging (METASD_GEMM_ROLL=0: sibling reduction instead)
     bool gemm_reduce = true;         // bf16 models: residual GEMMs reduce their split-K partials themselves (METASD_GEMM_REDUCE=0: off)
     float cur_eps = 1e-5f;           // rms_eps of the model whose forward is being launched
@@ -1039,54 +1044,62 @@ int gemm_rows<float>(metasd_ctx* c, const void* x, int ldx, int R, int K, const 
     return 0;
 }
 
-// more than 64 KiB of dynamic LDS needs the function attribute (set once per variant; harmless below the limit)
-template <int RBW, bool LO, int TPQ = 4, int PD = ROWS_PD, int NRG = 4, int CST = 2, bool DMA = false>
-int launch_gemm_rows(metasd_ctx* c, const bf16_t* xh, size_t x_lo_off, int ldx, int R, int r0, int nr, int K, const void* W0,
-                     const void* W1, const void* W2, int t0, int t1, int ntiles, int N, const Split& s, metasd_ctx::ProfRec* pr) {
-    const size_t lds = (size_t)2 * (LO ? 8 : 4) * CST * (16 * NRG * RBW) * 16;
-    static bool attr_set = false;
-    if (!attr_set) {
-        if (hipFuncSetAttribute((const void*)gemm_bf16_rows_kernel<RBW, PD, LO, TPQ, NRG, CST, DMA>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return c->fail(METASD_E_HIP, "gemm_bf16_rows_kernel: cannot reserve %zu bytes of LDS", lds);
-        attr_set = true;
+// The plan of a many-row launch, kept per shape (a forward repeats a handful of them; the search takes a microsecond or two).
+const RowsPlan& rows_plan(metasd_ctx* c, int ntiles, int kchunks, int R, int groups) {
+    auto& e = c->plans[(unsigned)(ntiles * 31 + kchunks * 17 + R * 5 + groups) % (sizeof c->plans / sizeof c->plans[0])];
+    if (e.ntiles != ntiles || e.kchunks != kchunks || e.R != R || e.groups != groups) {
+        e.ntiles = ntiles; e.kchunks = kchunks; e.R = R; e.groups = groups;
+        e.plan = plan_rows(ntiles, kchunks, R, groups, c->rows_tpb, c->rows_rb);
     }
-    constexpr int TPW = (8 / NRG) * TPQ;           // tiles per workgroup
-    const int groups = (ntiles + TPW - 1) / TPW;
-    hipExtLaunchKernelGGL((gemm_bf16_rows_kernel<RBW, PD, LO, TPQ, NRG, CST, DMA>), dim3(groups * s.ksplit), dim3(512), (uint32_t)lds, c->stream,
-                          pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, xh + (size_t)r0 * ldx, x_lo_off, ldx, nr, K, (const bf16_t*)W0,
-                          (const bf16_t*)W1, (const bf16_t*)W2, t0, t1, ntiles, c->d_part() + (size_t)r0 * N, (size_t)R * N, N, s.ksplit, s.cps);
-    LAUNCH_CHECK(c, "gemm_bf16_rows");
+    return e.plan;
+}
+
+// more than 64 KiB of dynamic LDS needs the function attribute (set once per variant)
+template <int RB, int TB>
+int launch_gemm_tiles(metasd_ctx* c, const bf16_t* x, int R, int K, const void* W0, const void* W1, const void* W2, int t0, int t1,
+                      int ntiles, const RowsPlan& s, const RowGroups* gg, metasd_ctx::ProfRec* pr) {
+    constexpr int NS = rows_stages(RB, TB);
+    constexpr int lds = NS * (8192 * RB + 2048 * TB);
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    const hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
+    const dim3 grid(s.nrb * s.ngroups * s.ksplit, gg ? gg->n : 1);
+    const int N = ntiles * 16;
+    if (gg) {
+        static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tiles_grouped_kernel<RB, TB, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (attr != hipSuccess) return c->fail(METASD_E_HIP, "gemm_tiles_grouped_kernel: cannot reserve %d bytes of LDS", lds);
+        hipExtLaunchKernelGGL((gemm_tiles_grouped_kernel<RB, TB, NS>), grid, dim3(512), (uint32_t)lds, c->stream, ea, eb, 0u, x, K / 32, t0, t1,
+                              ntiles, c->d_part(), (size_t)R * N, N, s.cps, s.nrb, *gg);
+    } else {
+        static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tiles_kernel<RB, TB, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (attr != hipSuccess) return c->fail(METASD_E_HIP, "gemm_tiles_kernel: cannot reserve %d bytes of LDS", lds);
+        hipExtLaunchKernelGGL((gemm_tiles_kernel<RB, TB, NS>), grid, dim3(512), (uint32_t)lds, c->stream, ea, eb, 0u, x, R, K / 32, (const bf16_t*)W0,
+                              (const bf16_t*)W1, (const bf16_t*)W2, t0, t1, ntiles, c->d_part(), (size_t)R * N, N, s.cps, s.nrb);
+    }
+    LAUNCH_CHECK(c, "gemm_tiles");
     return 0;
 }
+
+int launch_gemm_tiles_any(metasd_ctx* c, const void* x, int R, int K, const void* W0, const void* W1, const void* W2, int t0, int t1,
+                          int ntiles, const RowsPlan& s, const RowGroups* gg, metasd_ctx::ProfRec* pr) {
+#define TILES_GO(RB, TB) if (s.rb == RB && s.tb == TB) return launch_gemm_tiles<RB, TB>(c, (const bf16_t*)x, R, K, W0, W1, W2, t0, t1, ntiles, s, gg, pr)
+    TILES_GO(4, 6); TILES_GO(3, 8); TILES_GO(3, 6); TILES_GO(3, 4); TILES_GO(2, 8); TILES_GO(2, 6);
+    TILES_GO(2, 4); TILES_GO(2, 3); TILES_GO(1, 8); TILES_GO(1, 6); TILES_GO(1, 4); TILES_GO(1, 2);
+#undef TILES_GO
+    return c->fail(METASD_E_INVALID, "many-row GEMM: no tile of %d x %d", s.rb, s.tb);
+}
+
+// R > MAX_ROWS: x interleaved (store_terms4, split = 2); R <= MAX_ROWS: two arrays (split = 1)
+int rows_split(int R) { return R > MAX_ROWS ? 2 : 1; }
 
 template <>
 int gemm_rows<bf16_t>(metasd_ctx* c, const void* x, int ldx, int R, int K, const void* W0, int n0, const void* W1, int n1,
                       const void* W2, int n2, int* nsplit_out) {
-    const size_t x_lo_off = (size_t)R * ldx;      // producers write hi [R][ldx], then lo [R][ldx]
-    if (R <= MAX_ROWS) return gemm<bf16_t>(c, x, ldx, R, K, W0, n0, W1, n1, W2, n2, nullptr, nsplit_out, x_lo_off);
-    const int N = n0 + n1 + n2, ntiles = N / 16, kchunks = K / 32;
-    const Split s = choose_split_rows(ntiles, kchunks, R, c->rows_tpb);
+    if (R <= MAX_ROWS) return gemm<bf16_t>(c, x, ldx, R, K, W0, n0, W1, n1, W2, n2, nullptr, nsplit_out, (size_t)R * ldx);
+    const int N = n0 + n1 + n2;
+    const RowsPlan& s = rows_plan(c, N / 16, K / 32, R, 1);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)N * K * 2 + (double)R * K * 4 + (double)R * N * 4 * s.ksplit, N, K, R);
-    const bf16_t* xh = (const bf16_t*)x;
-    const int t0 = n0 / 16, t1 = (n0 + n1) / 16;
-    int rc = 0;
-    // more than 256 rows: two passes over the weights, 256 rows each (a 512-row variant would spill registers)
-    for (int r0 = 0; r0 < R && !rc; r0 += 256) {
-        const int nr = std::min(256, R - r0);
-        metasd_ctx::ProfRec* p = r0 ? nullptr : pr;
-#define ROWS_ARGS (c, xh, x_lo_off, ldx, R, r0, nr, K, W0, W1, W2, t0, t1, ntiles, N, s, p)
-#define ROWS_GO(RBW, TPQ) launch_gemm_rows<RBW, true, TPQ> ROWS_ARGS
-        if (nr <= 64) rc = ROWS_GO(1, 4);
-        else if (nr <= 128) rc = ROWS_GO(2, 4);
-        else if (s.tpb == 12) rc = launch_gemm_rows<8, true, 3, ROWS_PD, 2, 2, true> ROWS_ARGS;     // activations straight into LDS
-        else if (s.tpb == 4) rc = ROWS_GO(4, 2);
-        else if (s.tpb == 6) rc = ROWS_GO(4, 3);
-        else rc = ROWS_GO(4, 4);
-#undef ROWS_GO
-#undef ROWS_ARGS
-    }
     *nsplit_out = s.ksplit;
-    return rc;
+    return launch_gemm_tiles_any(c, x, R, K, W0, W1, W2, n0 / 16, (n0 + n1) / 16, N / 16, s, nullptr, pr);
 }
 
 template <typename T, int HD>
@@ -1130,7 +1143,7 @@ int attention_seg_hd(metasd_ctx* c, const Model& M, int L, const Segs& sg) {
     }
     LAUNCH_CHECK(c, "attn_partial (segments)");
     hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(d.n_heads, R), dim3(HD), 0, c->stream, c->d_apart(), nch_max, d.n_heads,
-                       (float*)c->d_ao(), sizeof(T) == 2 ? 1 : 0, sg, cpw);
+                       (float*)c->d_ao(), sizeof(T) == 2 ? rows_split(R) : 0, sg, cpw);
     LAUNCH_CHECK(c, "attn_combine (segments)");
     return 0;
 }
@@ -1155,7 +1168,7 @@ int attention_big(metasd_ctx* c, const metasd_model_desc& d, int hd, const bf16_
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * (double)(pos0 + m) * hd * 2 + (double)m * d.n_heads * hd * 4);
     hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
 #define BIG_GO(HD, RB) hipExtLaunchKernelGGL((attn_prefill_kernel<HD, RB>), dim3(nblk * d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u, \
-                                             (const bf16_t*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, (float*)c->d_ao())
+                                             (const bf16_t*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, (float*)c->d_ao(), rows_split(m))
     if (hd == 128) { if (two) BIG_GO(128, 2); else BIG_GO(128, 1); }
     else { if (two) BIG_GO(64, 2); else BIG_GO(64, 1); }
 #undef BIG_GO
@@ -1189,7 +1202,7 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
     float* xn = (float*)c->d_xn();
     float* part = c->d_part();
     int ns = 0, rc;
-    constexpr int split = sizeof(T) == 2 ? 1 : 0;
+    const int split = sizeof(T) == 2 ? rows_split(R) : 0;
     const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
     const size_t seq_stride = (size_t)M.kv_layers * 2 * plane;
     hipLaunchKernelGGL(embed_seg_kernel<T>, dim3(R), dim3(256), 0, st, (const int32_t*)c->d_hist(), c->cfg.max_ctx, (const T*)M.w[0], D, h, sg);
@@ -1202,7 +1215,7 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
         if ((rc = gemm_rows<T>(c, xn, D, R, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV, &ns))) return rc;
         T* kc = (T*)M.kv + (size_t)L * 2 * plane;
         hipLaunchKernelGGL(rope_kv_seg_kernel<T>, dim3(H + 2 * KH, R), dim3(64), 0, st, part, ns, (size_t)R * NQKV, NQKV, sg, H, KH, hd,
-                           (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, seq_stride, c->cfg.max_ctx, split,
+                           (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, seq_stride, c->cfg.max_ctx, sizeof(T) == 2 ? 1 : 0,
                            (split && hd >= 64) ? 1 : 0);
         LAUNCH_CHECK(c, "rope_kv (segments)");
         if ((rc = attention_seg<T>(c, M, L, sg))) return rc;
@@ -1235,8 +1248,8 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
 
 // n consecutive tokens of one sequence, hist[seq][pos0 .. pos0 + n), through model M in blocks of up to BIG_ROWS rows: what
 // they leave is their K/V (and, with drafter heads, the target's features).  bf16 models with head_dim >= 64; no tree or
-// streaming mask.  Every weight is read once per pass of 256 rows (gemm_rows) instead of once per 16 rows: a 1500-token query
-// start on the 7B shape took 362 ms in 16-row blocks and takes 63 ms, 512 tokens on the 1B shape 40.7 and 5.6 ms.  The last layer ends with its K/V: nothing
+// streaming mask.  Every weight is read once per pass instead of once per 16 rows: a 1500-token query start on the 7B shape
+// took 362 ms in 16-row blocks and takes 41 ms, 512 tokens on the 1B shape 40.7 and 4.3 ms.  The last layer ends with its K/V: nothing
 // reads what follows, unless the features are wanted.
 int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
     typedef bf16_t T;
@@ -1253,7 +1266,7 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
     if (pos0 + n > c->cfg.max_ctx) return c->fail(METASD_E_OVERFLOW, "positions %d..%d exceed max_ctx %d", pos0, pos0 + n, c->cfg.max_ctx);
     c->cur_model = model_index(c, M);
     for (int done = 0; done < n;) {
-        const int m = std::min(big_rows(c->cfg), n - done), p0 = pos0 + done;
+        const int m = std::min(big_rows(c->cfg), n - done), p0 = pos0 + done, split = rows_split(m);
         int ns = 0, rc;
         hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, st, c->d_hist() + (size_t)seq * c->cfg.max_ctx + p0, (const T*)M.w[0], D,
                            h, p0, hd, d.rope_theta, c->d_rope(), TreeBlk{});
@@ -1261,7 +1274,7 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
         if (M.head) {   // W_fc . [embedding ; the target's feature of the position before]
             float* cat = (float*)c->d_act();
             hipLaunchKernelGGL(feat_cat_kernel, dim3(m), dim3(256), 0, st, (const float*)h, (const float*)c->d_feat(), (const float*)nullptr,
-                               FeatSrc{}, p0, D, cat, 1);
+                               FeatSrc{}, p0, D, cat, split);
             LAUNCH_CHECK(c, "feat_cat");
             if ((rc = gemm_rows<T>(c, cat, 2 * D, m, 2 * D, M.fc, D, nullptr, 0, nullptr, 0, &ns))) return rc;
             const size_t nh = (size_t)m * D;
@@ -1271,7 +1284,7 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
             ns = 0;
         }
         for (int L = 0; L < d.n_layers; ++L) {
-            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 0), d.rms_eps, xn, 1);
+            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 0), d.rms_eps, xn, split);
             LAUNCH_CHECK(c, "addnorm");
             if ((rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV, &ns))) return rc;
             T* kc = kv + (size_t)L * 2 * plane;
@@ -1281,19 +1294,19 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
             if (L + 1 == d.n_layers && !features) break;
             if ((rc = attention_big(c, d, hd, kc, kc + plane, p0, m))) return rc;
             if ((rc = gemm_rows<T>(c, c->d_ao(), DQ, m, DQ, M.layer_w(L, 4), D, nullptr, 0, nullptr, 0, &ns))) return rc;
-            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 5), d.rms_eps, xn, 1);
+            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 5), d.rms_eps, xn, split);
             LAUNCH_CHECK(c, "addnorm");
             if (d.act == METASD_SWIGLU) rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0, &ns);
             else rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0, &ns);
             if (rc) return rc;
             const size_t nact = (size_t)m * F;
             hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, st, part, ns, (size_t)m * NF, m, F, d.act,
-                               (float*)c->d_act(), 1, (const float*)nullptr);
+                               (float*)c->d_act(), split, (const float*)nullptr);
             LAUNCH_CHECK(c, "ffn_act");
             if ((rc = gemm_rows<T>(c, c->d_act(), F, m, F, M.layer_w(L, 8), D, nullptr, 0, nullptr, 0, &ns))) return rc;
         }
         if (features) {
-            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.final_norm(), d.rms_eps, xn, 1);   // finishes the residual rows
+            launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.final_norm(), d.rms_eps, xn, split);   // finishes the residual rows
             LAUNCH_CHECK(c, "addnorm");
             const unsigned n4 = (unsigned)((size_t)m * D / 4);
             hipLaunchKernelGGL(copy_f4_kernel, dim3((n4 + 255) / 256), dim3(256), 0, st, (const float4*)h, (float4*)(c->d_feat() + (size_t)p0 * D), n4);
@@ -1334,35 +1347,15 @@ bool grouped_step_supported(const metasd_ctx* c) {
     return true;
 }
 
-template <int RBW>
-int launch_gemm_rows_grouped(metasd_ctx* c, const void* x, int ldx, int R, int K, const RowGroups& gg, int n0, int n1, int N, const Split& s,
-                             metasd_ctx::ProfRec* pr) {
-    const size_t lds = (size_t)2 * 16 * (64 * RBW) * 16;
-    static bool attr_set = false;
-    if (!attr_set) {
-        if (hipFuncSetAttribute((const void*)gemm_bf16_rows_grouped_kernel<RBW, ROWS_PD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return c->fail(METASD_E_HIP, "gemm_bf16_rows_grouped_kernel: cannot reserve %zu bytes of LDS", lds);
-        attr_set = true;
-    }
-    const int ntiles = N / 16, groups = (ntiles + 7) / 8;
-    hipExtLaunchKernelGGL((gemm_bf16_rows_grouped_kernel<RBW, ROWS_PD>), dim3(groups * s.ksplit, gg.n), dim3(512), (uint32_t)lds, c->stream,
-                          pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, (const bf16_t*)x, (size_t)R * ldx, ldx, K, n0 / 16, (n0 + n1) / 16,
-                          ntiles, c->d_part(), (size_t)R * N, N, s.ksplit, s.cps, gg);
-    LAUNCH_CHECK(c, "gemm_bf16_rows (grouped)");
-    return 0;
-}
-
-// x: R rows in the two-bf16 form (hi, then lo R * ldx elements further); gg: the row groups and their matrices.
-int gemm_rows_grouped(metasd_ctx* c, const void* x, int ldx, int R, int K, const RowGroups& gg, int n0, int n1, int n2, int* nsplit_out) {
-    const int N = n0 + n1 + n2, ntiles = N / 16, kchunks = K / 32;
+// x: R rows, interleaved (store_terms4, split = 2); gg: the row groups and their matrices.
+int gemm_rows_grouped(metasd_ctx* c, const void* x, int R, int K, const RowGroups& gg, int n0, int n1, int n2, int* nsplit_out) {
+    const int N = n0 + n1 + n2;
     int mmax = 1;
     for (int g = 0; g < gg.n; ++g) mmax = std::max(mmax, gg.m[g]);
-    const Split s = choose_split_rows(ntiles, kchunks, 64, 8);
+    const RowsPlan& s = rows_plan(c, N / 16, K / 32, mmax, gg.n);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)gg.n * N * K * 2 + (double)R * K * 4 + (double)R * N * 4 * s.ksplit, N, K, R);
     *nsplit_out = s.ksplit;
-    if (mmax <= 64) return launch_gemm_rows_grouped<1>(c, x, ldx, R, K, gg, n0, n1, N, s, pr);
-    if (mmax <= 128) return launch_gemm_rows_grouped<2>(c, x, ldx, R, K, gg, n0, n1, N, s, pr);
-    return launch_gemm_rows_grouped<4>(c, x, ldx, R, K, gg, n0, n1, N, s, pr);
+    return launch_gemm_tiles_any(c, x, R, K, nullptr, nullptr, nullptr, n0 / 16, (n0 + n1) / 16, N / 16, s, &gg, pr);
 }
 
 // sg: the segments ordered by arm (ms <= 16 rows each, at most 256 rows per arm); arm[s]: the drafter of segment s.
@@ -1418,9 +1411,9 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
     const float scale = 1.0f / sqrtf((float)HD);
     for (int L = 0; L < d.n_layers; ++L) {
         hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
-                           seg_ptrs([&](const Model& M, int) { return (const void*)M.layer_w(L, 0); }), sg.ms, d.rms_eps, xn, 1);
+                           seg_ptrs([&](const Model& M, int) { return (const void*)M.layer_w(L, 0); }), sg.ms, d.rms_eps, xn, 2);
         LAUNCH_CHECK(c, "addnorm (grouped)");
-        if ((rc = gemm_rows_grouped(c, xn, D, R, D, weights(L, 1, 2, 3), DQ, DKV, DKV, &ns))) return rc;
+        if ((rc = gemm_rows_grouped(c, xn, R, D, weights(L, 1, 2, 3), DQ, DKV, DKV, &ns))) return rc;
         const SegPtrs kcs = seg_ptrs([&](const Model& M, int s) { return (const void*)((const T*)M.kv + (size_t)L * 2 * plane + (size_t)sg.seq[s] * M.kv_layers * 2 * plane); });
         const SegPtrs vcs = seg_ptrs([&](const Model& M, int s) { return (const void*)((const T*)M.kv + (size_t)L * 2 * plane + plane + (size_t)sg.seq[s] * M.kv_layers * 2 * plane); });
         hipLaunchKernelGGL(rope_kv_segp_kernel<T>, dim3(H + 2 * KH, R), dim3(64), 0, st, part, ns, (size_t)R * NQKV, NQKV, sg, H, KH, hd,
@@ -1432,29 +1425,29 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
                                   pr ? pr->b : nullptr, 0u, (const float*)c->d_q(), kcs, vcs, sg, H, KH, c->cfg.max_ctx, scale, c->d_apart(),
                                   nch_max, (size_t)R * H * HD);
             LAUNCH_CHECK(c, "attn_partial (grouped)");
-            hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(H, R), dim3(HD), 0, st, c->d_apart(), nch_max, H, (float*)c->d_ao(), 1, sg, 1);
+            hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(H, R), dim3(HD), 0, st, c->d_apart(), nch_max, H, (float*)c->d_ao(), 2, sg, 1);
             LAUNCH_CHECK(c, "attn_combine (segments)");
         }
-        if ((rc = gemm_rows_grouped(c, c->d_ao(), DQ, R, DQ, weights(L, 4, -1, -1), D, 0, 0, &ns))) return rc;
+        if ((rc = gemm_rows_grouped(c, c->d_ao(), R, DQ, weights(L, 4, -1, -1), D, 0, 0, &ns))) return rc;
         hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
-                           seg_ptrs([&](const Model& M, int) { return (const void*)M.layer_w(L, 5); }), sg.ms, d.rms_eps, xn, 1);
+                           seg_ptrs([&](const Model& M, int) { return (const void*)M.layer_w(L, 5); }), sg.ms, d.rms_eps, xn, 2);
         LAUNCH_CHECK(c, "addnorm (grouped)");
         if (d.act == METASD_SWIGLU) {
-            if ((rc = gemm_rows_grouped(c, xn, D, R, D, weights(L, 6, 7, -1), F, F, 0, &ns))) return rc;
+            if ((rc = gemm_rows_grouped(c, xn, R, D, weights(L, 6, 7, -1), F, F, 0, &ns))) return rc;
         } else {
-            if ((rc = gemm_rows_grouped(c, xn, D, R, D, weights(L, 7, -1, -1), F, 0, 0, &ns))) return rc;
+            if ((rc = gemm_rows_grouped(c, xn, R, D, weights(L, 7, -1, -1), F, 0, 0, &ns))) return rc;
         }
         const size_t nact = (size_t)R * F;
         const int NF = (d.act == METASD_SWIGLU ? 2 : 1) * F;
         hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, st, part, ns, (size_t)R * NF, R, F, d.act,
-                           (float*)c->d_act(), 1, (const float*)nullptr);
+                           (float*)c->d_act(), 2, (const float*)nullptr);
         LAUNCH_CHECK(c, "ffn_act");
-        if ((rc = gemm_rows_grouped(c, c->d_act(), F, R, F, weights(L, 8, -1, -1), D, 0, 0, &ns))) return rc;
+        if ((rc = gemm_rows_grouped(c, c->d_act(), R, F, weights(L, 8, -1, -1), D, 0, 0, &ns))) return rc;
     }
     hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
-                       seg_ptrs([](const Model& M, int) { return (const void*)M.final_norm(); }), sg.ms, d.rms_eps, xn, 1);
+                       seg_ptrs([](const Model& M, int) { return (const void*)M.final_norm(); }), sg.ms, d.rms_eps, xn, 2);
     LAUNCH_CHECK(c, "addnorm (grouped)");
-    if ((rc = gemm_rows_grouped(c, xn, D, R, D, weights(-1, 0, -1, -1), V, 0, 0, &ns))) return rc;
+    if ((rc = gemm_rows_grouped(c, xn, R, D, weights(-1, 0, -1, -1), V, 0, 0, &ns))) return rc;
     hipLaunchKernelGGL(sum_partials_seg_kernel, dim3((V + 255) / 256, R), dim3(256), 0, st, (const float*)part, ns, (size_t)R * V, V,
                        logits, sg, out_seq_rows, out_row0, 1);
     LAUNCH_CHECK(c, "sum_partials (segments)");
@@ -1859,7 +1852,8 @@ int32_t metasd_create(metasd_ctx** out, const metasd_config* cfg, const metasd_m
         if (const char* ev = getenv("METASD_GEMM_ROLL")) c->fullk_roll = ev[0] != '0';
         if (const char* ev = getenv("METASD_DRAFT_GROUPED")) c->grouped_on = ev[0] != '0';
         if (const char* ev = getenv("METASD_ATT_CPW")) { const int v = atoi(ev); c->att_cpw = (v >= 1 && v <= 64) ? v : 0; }
-        if (const char* ev = getenv("METASD_ROWS_TPB")) { const int v = atoi(ev); c->rows_tpb = (v == 4 || v == 6 || v == 8 || v == 12) ? v : 0; }
+        if (const char* ev = getenv("METASD_ROWS_TPB")) { const int v = atoi(ev); c->rows_tpb = (v == 4 || v == 6 || v == 8 || v == 12 || v == 16) ? v : 0; }
+        if (const char* ev = getenv("METASD_ROWS_RB")) { const int v = atoi(ev); c->rows_rb = v >= 1 && v <= 4 ? v : 0; }
         {
             const int roll_lds = (int)FULLK_LDS_MAX;
             if (hipFuncSetAttribute((const void*)gemm_fullk_roll_residual_kernel<3, true>, hipFuncAttributeMaxDynamicSharedMemorySize, roll_lds) != hipSuccess ||

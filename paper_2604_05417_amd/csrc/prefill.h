@@ -38,11 +38,11 @@ __device__ __forceinline__ s16x4 lds_read_tr(const bf16_t* p) {
 // that XCD's L2, the longest row blocks first.  Measured: 1499 rows x 32 heads of 128: 124 us per layer (18.4 GFLOP causal, twice
 // that with the second terms: 0.3 PFLOP/s), where 94 passes of the 16-row kernels took 94 x (7 + 5) us; 511 rows x 32 heads of
 // 64 on 8 KV heads: 12.8 us.
-//   grid (ceil(m / (64 RB)) * H), block 256.   out: two bf16 arrays [m][H HD], lo m H HD elements behind hi.
+//   grid (ceil(m / (64 RB)) * H), block 256.   out: [m][H HD] as two bf16 terms (split: see store_terms4).
 template <int HD, int RB>
 __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
                                                               const bf16_t* __restrict__ vc, int m, int pos0, int H, int KH, int max_ctx,
-                                                              float scale, float* __restrict__ out) {
+                                                              float scale, float* __restrict__ out, int split) {
     constexpr int TP = 64, KC = HD / 32, NT = HD / 16, VPR = HD / 8;
     constexpr int RSV = HD + 16;                       // V row stride (elements): 8 consecutive rows fall into different banks
     constexpr int IT = TP * VPR / 256;                 // 16-byte pieces of a tile per thread
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const bf16_t* __re
         if (r < m) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                store_split4(out, q_lo, (size_t)r * H * HD + (size_t)h * HD + t * 16 + 4 * g,
+                store_terms4(out, split, q_lo, (size_t)r * H * HD + (size_t)h * HD + t * 16 + 4 * g,
                              make_float4(o[b][t][0] * inv, o[b][t][1] * inv, o[b][t][2] * inv, o[b][t][3] * inv));
         }
     }

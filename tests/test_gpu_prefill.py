@@ -77,6 +77,19 @@ def test_prefill_leaves_the_models_kv(desc, n):
     check_prefill(desc, n)
 
 
+TILES = [(4, 12), (3, 16), (3, 12), (3, 8), (2, 16), (2, 12), (2, 8), (2, 6), (1, 16), (1, 12), (1, 8), (1, 4)]
+
+
+@pytest.mark.parametrize("rb,tpb", TILES)
+def test_every_tile_of_the_many_row_gemm(rb, tpb, monkeypatch):
+    """Each workgroup tile (64 rb rows x tpb feature tiles), forced: one row less than a row block, a full one, one row more, and
+    a second block with a ragged end; 48 / 92 / 32 tiles and 16 / 23 chunks of K, with and without a K split."""
+    monkeypatch.setenv("METASD_ROWS_RB", str(rb))
+    monkeypatch.setenv("METASD_ROWS_TPB", str(tpb))
+    for rows in (64 * rb - 1, 64 * rb, 64 * rb + 1, 128 * rb + 17):
+        check_prefill(HD64, rows + 1)
+
+
 def test_prefill_of_more_than_one_block():
     check_prefill(HD64, 2048 + 21)                                # a block of 2048 rows and one of 20
 
