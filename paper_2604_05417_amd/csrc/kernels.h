@@ -20,12 +20,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-// round-to-nearest-even float -> bf16 (inf / nan pass through by truncation)
-__device__ __forceinline__ bf16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) != 0x7f800000u) u += 0x7fffu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
-}
+// round-to-nearest-even float -> bf16, the hardware's conversion (one instruction for two values; the same bits as adding the rounding
+// term by hand for every finite value and infinity, six instructions each)
+typedef __bf16 hbf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f2bf2(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, hbf16x2)); }
+__device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
 template <typename T> struct El;
 template <> struct El<float> {
@@ -137,10 +137,11 @@ __global__ void philox_words_kernel(uint64_t seed, uint32_t c0_start, int n, uin
 __device__ __forceinline__ void store_split4(float* base, size_t n, size_t at, const float4& v) {
     bf16_t* hi = reinterpret_cast<bf16_t*>(base) + at;
     bf16_t* lo = hi + n;
-    const bf16_t h0 = f2bf(v.x), h1 = f2bf(v.y), h2 = f2bf(v.z), h3 = f2bf(v.w);
-    *reinterpret_cast<uint2*>(hi) = make_uint2((uint32_t)h0 | ((uint32_t)h1 << 16), (uint32_t)h2 | ((uint32_t)h3 << 16));
-    const bf16_t l0 = f2bf(v.x - bf2f(h0)), l1 = f2bf(v.y - bf2f(h1)), l2 = f2bf(v.z - bf2f(h2)), l3 = f2bf(v.w - bf2f(h3));
-    *reinterpret_cast<uint2*>(lo) = make_uint2((uint32_t)l0 | ((uint32_t)l1 << 16), (uint32_t)l2 | ((uint32_t)l3 << 16));
+    const uint32_t h01 = f2bf2(v.x, v.y), h23 = f2bf2(v.z, v.w);
+    *reinterpret_cast<uint2*>(hi) = make_uint2(h01, h23);
+    *reinterpret_cast<uint2*>(lo) = make_uint2(
+        f2bf2(v.x - __uint_as_float(h01 << 16), v.y - __uint_as_float(h01 & 0xffff0000u)),
+        f2bf2(v.z - __uint_as_float(h23 << 16), v.w - __uint_as_float(h23 & 0xffff0000u)));
 }
 // The interleaved form of the same two terms, read by the many-row GEMM (gemm_tiles.h): per row and 32-wide chunk one 128-byte
 // line, the 32 hi terms, then the 32 lo terms.  at: element index in a row-major block whose rows are a multiple of 32 long.
@@ -330,16 +331,10 @@ constexpr int GEMM_U = 8;  // tiles in flight per wavefront (8 KiB)
 
 __device__ __forceinline__ uint32_t pack_bf16x2(bf16_t lo, bf16_t hi) { return (uint32_t)lo | ((uint32_t)hi << 16); }
 
-// Optional prologues for short, narrow blocks (drafter steps: m <= 4 rows, d_model <= 1024), where the
-// split-K partials of the previous GEMM are few enough that every workgroup can afford to consume them
-// itself; each one removes a kernel from the dependent chain of a layer:
-//   PRO_NORM     x = RMSNorm(h_in + sum of the previous GEMM's partials) * gain.  Every workgroup forms
-//                the full rows (it needs their sum of squares), keeps them in LDS, and stages its
-//                slice; workgroup 0 also writes the rows to h_out (a second buffer: the others still
-//                read h_in).  Replaces addnorm_kernel.
-//   PRO_ACT      x = SiLU(gate) * up or GELU(up) from the partials of the gate | up GEMM.  Replaces ffn_act_kernel.
+// Optional prologue for short, narrow blocks (drafter steps):
 //   PRO_COMBINE  x = attention output merged from the per-chunk partials.  Replaces attn_combine_kernel.
-enum { PRO_PLAIN = 0, PRO_NORM = 1, PRO_ACT = 2, PRO_COMBINE = 3 };
+// (The add+norm and activation prologues those blocks also need are in gemm_step_kernel, step.h.)
+enum { PRO_PLAIN = 0, PRO_COMBINE = 1 };
 
 // Plain streaming read (measurement aid: the read rate of the machine the benchmark runs on, next to the 8 TB/s
 // nominal peak).  The access pattern of the weight-streaming GEMMs without their arithmetic: every wavefront owns a
@@ -379,16 +374,11 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* __restric
 }
 
 struct GemmPro {
-    const float* src;      // NORM: h_in [m][K];  ACT: partials [s][m][(1|2) K];  COMBINE: attention partials
-                           // (PLAIN: sstride = offset in elements from the hi array x to the lo array; optional:
-                           //  src = sums of squares [ns tile groups][16], h_out = 1/rms per row [m], eps)
-    const float* part;     // NORM: partials [s][m][K] of the previous GEMM (ns may be 0)
-    float* h_out;          // NORM: updated residual stream [m][K]
-    const bf16_t* gain;    // NORM
-    size_t sstride;        // NORM / ACT: split stride of the partials (floats)
-    int ns;                // NORM / ACT: number of partials
-    float eps;             // NORM
-    int act;               // ACT: 1 SwiGLU, 0 GELU
+    const float* src;      // COMBINE: attention partials.  PLAIN, optional: sums of squares [ns tile groups][16] -> 1/rms per row
+    float* h_out;          // PLAIN with src: 1/rms per row [m]
+    size_t sstride;        // PLAIN: offset in elements from the hi array x to the lo array
+    int ns;                // PLAIN with src: tile groups
+    float eps;             // PLAIN with src
     int nchunks, hd;       // COMBINE: attention chunks, head dim
     int row0;              // PLAIN with src: first row of the sums-of-squares table that belongs to this block
 };
@@ -421,7 +411,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const float* __restrict_
                                                         const bf16_t* __restrict__ W2, int t0, int t1, int ntiles,
                                                         float* __restrict__ out, int N, int ksplit, int cps, int tpb,
                                                         GemmPro pro, GemmEpi epi) {
-    extern __shared__ uint4 xs[];   // [2 (hi, lo)][m][rs]  (+ [m][K] floats for PRO_NORM)
+    extern __shared__ uint4 xs[];   // [2 (hi, lo)][m][rs]
     const int kchunks = K >> 5;
     const int ks = blockIdx.x % ksplit, tg = blockIdx.x / ksplit;
     const int c0 = ks * cps;
@@ -452,14 +442,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const float* __restrict_
     const int total = m * nc * 4, per = nc * 4;
     auto convert_store = [&](const float (&v)[8], int idx) {
         const int r = idx / per, c = idx - r * per;
-        bf16_t hi[8], lo[8];
+        uint32_t hi[4], lo[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            hi[e] = f2bf(v[e]);
-            lo[e] = f2bf(v[e] - bf2f(hi[e]));
+        for (int e = 0; e < 4; ++e) {
+            hi[e] = f2bf2(v[2 * e], v[2 * e + 1]);
+            lo[e] = f2bf2(v[2 * e] - __uint_as_float(hi[e] << 16), v[2 * e + 1] - __uint_as_float(hi[e] & 0xffff0000u));
         }
-        xs[r * rs + c] = make_uint4(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]), pack_bf16x2(hi[4], hi[5]), pack_bf16x2(hi[6], hi[7]));
-        xlo[r * rs + c] = make_uint4(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(lo[4], lo[5]), pack_bf16x2(lo[6], lo[7]));
+        xs[r * rs + c] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        xlo[r * rs + c] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     };
     if constexpr (PRO == PRO_PLAIN) {
         // When the input is h * gain of a residual epilogue (not yet normalised), workgroup 0 also turns the
@@ -527,82 +517,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const float* __restrict_
                 const int idx = base + (int)threadIdx.x + u * 256;
                 if (idx < total) { const int r = idx / per, c = idx - r * per; xs[r * rs + c] = __builtin_bit_cast(uint4, a[u]); xlo[r * rs + c] = __builtin_bit_cast(uint4, b[u]); }
             }
-        }
-    } else if constexpr (PRO == PRO_NORM) {
-        float* vrow = reinterpret_cast<float*>(xs + 2 * m * rs);     // [m][K] updated residual rows
-        float* red = vrow + (size_t)m * K;                           // [m][4] per-wavefront sums of squares
-        for (int r = 0; r < m; ++r) {
-            float ss = 0.f;
-            for (int i = (int)threadIdx.x * 4; i < K; i += 1024) {
-                float4 v = *reinterpret_cast<const float4*>(pro.src + (size_t)r * K + i);
-                if (pro.ns > 0) {
-                    float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
-                    for (int s0 = 0; s0 < pro.ns; s0 += 8) {      // eight partials in flight, added in the order s = 0, 1, ..
-                        float4 pp[8];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u)
-                            pp[u] = (s0 + u < pro.ns) ? *reinterpret_cast<const float4*>(pro.part + (size_t)(s0 + u) * pro.sstride + (size_t)r * K + i)
-                                                      : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                        for (int u = 0; u < 8; ++u)
-                            if (s0 + u < pro.ns) { y.x += pp[u].x; y.y += pp[u].y; y.z += pp[u].z; y.w += pp[u].w; }
-                    }
-                    v.x += y.x; v.y += y.y; v.z += y.z; v.w += y.w;
-                }
-                *reinterpret_cast<float4*>(vrow + (size_t)r * K + i) = v;
-                ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-            }
-            ss = wave_sum(ss);
-            if (lane == 0) red[r * 4 + wave] = ss;
-        }
-        issue(wa, wp, 0);
-        __syncthreads();
-        if (blockIdx.x == 0)
-            for (int i = (int)threadIdx.x * 4; i < m * K; i += 1024)
-                *reinterpret_cast<float4*>(pro.h_out + i) = *reinterpret_cast<const float4*>(vrow + i);
-        for (int idx = (int)threadIdx.x; idx < total; idx += 256) {
-            const int r = idx / per, c = idx - r * per, k0 = c0 * 32 + c * 8;
-            const float tot = (red[r * 4] + red[r * 4 + 1]) + (red[r * 4 + 2] + red[r * 4 + 3]);
-            const float inv = 1.0f / sqrtf(tot / (float)K + pro.eps);
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = vrow[(size_t)r * K + k0 + e] * inv * bf2f(pro.gain[k0 + e]);
-            convert_store(v, idx);
-        }
-    } else if constexpr (PRO == PRO_ACT) {
-        issue(wa, wp, 0);
-        const int ldp = (pro.act == 1 ? 2 : 1) * K;
-        for (int idx = (int)threadIdx.x; idx < total; idx += 256) {
-            const int r = idx / per, c = idx - r * per, k0 = c0 * 32 + c * 8;
-            const float* pg = pro.src + (size_t)r * ldp + k0;
-            float gsum[8], usum[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) gsum[e] = usum[e] = 0.f;
-            for (int s0 = 0; s0 < pro.ns; s0 += 2) {              // two partials in flight, added in order
-                float4 ga[2], gb[2], ua[2], ub[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const bool ok = s0 + u < pro.ns;
-                    const float* q = pg + (size_t)(ok ? s0 + u : 0) * pro.sstride;
-                    ga[u] = *reinterpret_cast<const float4*>(q);
-                    gb[u] = *reinterpret_cast<const float4*>(q + 4);
-                    if (pro.act == 1) { ua[u] = *reinterpret_cast<const float4*>(q + K); ub[u] = *reinterpret_cast<const float4*>(q + K + 4); }
-                    else { ua[u] = make_float4(0.f, 0.f, 0.f, 0.f); ub[u] = ua[u]; }
-                }
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if (s0 + u < pro.ns) {
-                        gsum[0] += ga[u].x; gsum[1] += ga[u].y; gsum[2] += ga[u].z; gsum[3] += ga[u].w;
-                        gsum[4] += gb[u].x; gsum[5] += gb[u].y; gsum[6] += gb[u].z; gsum[7] += gb[u].w;
-                        usum[0] += ua[u].x; usum[1] += ua[u].y; usum[2] += ua[u].z; usum[3] += ua[u].w;
-                        usum[4] += ub[u].x; usum[5] += ub[u].y; usum[6] += ub[u].z; usum[7] += ub[u].w;
-                    }
-            }
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                v[e] = pro.act == 1 ? gsum[e] / (1.0f + expf(-gsum[e])) * usum[e] : 0.5f * gsum[e] * (1.0f + erff(gsum[e] * 0.70710678118654752f));
-            convert_store(v, idx);
         }
     } else {   // PRO_COMBINE: eight threads per 8-element piece, each merging every eighth chunk
         issue(wa, wp, 0);

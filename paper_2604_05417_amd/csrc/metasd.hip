@@ -21,6 +21,7 @@
 #include "batch.h"
 #include "prefill.h"
 #include "gemm_tiles.h"
+#include "step.h"
 
 using namespace msd;
 
@@ -170,12 +171,12 @@ struct GridBar { int abort; int pad[3]; };
 
 // Workspace layout shared by metasd_workspace_bytes and metasd_create.
 struct Layout {
-    size_t hist, h, h2, xn, part, part2, gx, ssq, inv, q, ao, act, apart, rope, P, Q, cand, bd, res, draft, tstep, feat, fest, bar, xchg, tables, table_stride, total;
+    size_t hist, h, h2, xn, part, gx, ssq, inv, q, ao, act, apart, rope, P, Q, cand, bd, res, draft, tstep, feat, fest, bar, xchg, tables, table_stride, total;
 };
 
 Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const metasd_model_desc* dr) {
     int dmax = t.d_model, fmax = t.d_ffn, vmax = t.vocab, hmax = t.n_heads, hdmax = t.d_model / t.n_heads;
-    size_t partmax = 0, partfew = 0, gxmax = ALIGN;   // split-K partials of the largest block, of a block of at most 16 rows
+    size_t partmax = 0, gxmax = ALIGN;   // split-K partials of the largest block
     auto acc = [&](const metasd_model_desc& d) {
         // sibling exchange of the residual GEMMs (N = d_model; K = attention width or d_ffn): ksplit - 1 published
         // partial tiles of m rows, for the split choose_split really takes at every block height (LDS capacity
@@ -203,7 +204,6 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
             // a smaller m never needs more splits for LDS, but may use up to 8 for parallelism
             ksplit = std::max(ksplit, ks_cap());
             partmax = std::max(partmax, (size_t)ksplit * MAX_ROWS * ns[i] * sizeof(float));
-            partfew = std::max(partfew, (size_t)ksplit * MAX_ROWS * ns[i] * sizeof(float));
             if (big_ok(d) && i < 4) partmax = std::max(partmax, rows_part(ns[i], big_rows(c)));
             if (c.batch > 1) partmax = std::max(partmax, rows_part(ns[i], (size_t)MAX_ROWS * c.batch));
         }
@@ -222,7 +222,6 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
     L.h2 = take((size_t)MAX_ROWS * dmax * 4);
     L.xn = take(RM * dmax * 4);
     L.part = take(partmax);
-    L.part2 = take(partfew);                                        // ping-pong partner of part, blocks of few rows only (forward_rows_fused)
     L.gx = take(gxmax);                                            // tagged partial sums of the residual GEMMs
     L.ssq = take((size_t)(dmax / 16 + 1) * 16 * 4);              // per tile group (or per tile) and row
     L.inv = take(64);
@@ -484,7 +483,6 @@ struct metasd_ctx {
     float* d_ssq() const { return reinterpret_cast<float*>(ws + lay.ssq); }
     float* d_inv() const { return reinterpret_cast<float*>(ws + lay.inv); }
     unsigned long long* d_xchg() const { return reinterpret_cast<unsigned long long*>(ws + lay.xchg); }
-    float* d_part_pp(int i) const { return reinterpret_cast<float*>(ws + (i ? lay.part2 : lay.part)); }
     float* d_h_pp(int i) const { return reinterpret_cast<float*>(ws + (i ? lay.h2 : lay.h)); }
     void* d_q() const { return ws + lay.q; }
     void* d_ao() const { return ws + lay.ao; }
@@ -644,30 +642,106 @@ int gemm_residual(metasd_ctx* c, const void* x, int ldx, int m, int K, const voi
     return 0;
 }
 
-// bf16 GEMM whose prologue forms the activations itself (PRO_NORM / PRO_ACT / PRO_COMBINE, see kernels.h).
-// Partials go to part_out (split stride m*N), or, when direct_out is given and no split is needed, there.
-template <int PRO>
-int gemm_pro(metasd_ctx* c, const GemmPro& pro, int m, int K, const void* W0, int n0, const void* W1, int n1, const void* W2,
-             int n2, float* part_out, float* direct_out, int* nsplit_out) {
-    const int N = n0 + n1 + n2;
-    const int ntiles = N / 16, kchunks = K / 32;
-    const Split s = choose_split(m, ntiles, kchunks);
-    float* out = (direct_out && s.ksplit == 1) ? direct_out : part_out;
+// bf16 GEMM of the merged attention output, merged from the per-chunk records in its prologue (PRO_COMBINE, see kernels.h): partials
+// to part_out (split stride m*N).
+int gemm_combine(metasd_ctx* c, const GemmPro& pro, int m, int K, const void* W, int N, float* part_out, int* nsplit_out) {
+    const int ntiles = N / 16;
+    const Split s = choose_split(m, ntiles, K / 32);
     const int groups = (ntiles + s.tpb - 1) / s.tpb;
-    const size_t lds = s.lds + (PRO == PRO_NORM ? (size_t)m * K * 4 + (size_t)m * 16 : 0);
+    if (s.ksplit > 8) return c->fail(METASD_E_INVALID, "output projection: %d partials for a consumer of at most 8", s.ksplit);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)N * K * 2 + (double)m * K * 4 + (double)m * N * 4, N, K, m);
-    hipExtLaunchKernelGGL(gemm_bf16_kernel<PRO>, dim3(groups * s.ksplit), dim3(256), (uint32_t)lds, c->stream, pr ? pr->a : nullptr,
-                          pr ? pr->b : nullptr, 0u, (const float*)nullptr, K, m, K, (const bf16_t*)W0, (const bf16_t*)W1,
-                          (const bf16_t*)W2, n0 / 16, (n0 + n1) / 16, ntiles, out, N, s.ksplit, s.cps, s.tpb, pro, GemmEpi{});
-    LAUNCH_CHECK(c, "gemm_bf16 (fused prologue)");
-    if (direct_out && s.ksplit > 1) {
-        const size_t n = (size_t)m * N;
-        hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, part_out, s.ksplit, n, n,
-                           direct_out, (const float*)nullptr, N);
-        LAUNCH_CHECK(c, "sum_partials");
-    }
-    *nsplit_out = direct_out ? 0 : s.ksplit;
+    hipExtLaunchKernelGGL(gemm_bf16_kernel<PRO_COMBINE>, dim3(groups * s.ksplit), dim3(256), (uint32_t)s.lds, c->stream, pr ? pr->a : nullptr,
+                          pr ? pr->b : nullptr, 0u, (const float*)nullptr, K, m, K, (const bf16_t*)W, (const bf16_t*)W, (const bf16_t*)W,
+                          ntiles, ntiles, ntiles, part_out, N, s.ksplit, s.cps, s.tpb, pro, GemmEpi{});
+    LAUNCH_CHECK(c, "gemm_bf16 (attention combine)");
+    *nsplit_out = s.ksplit;
     return 0;
+}
+
+// Launch of gemm_step_kernel: units (feature tiles, gate and up tiles of a pair, or half tiles) to workgroups.
+// A CU runs one workgroup of 16 wavefronts and pulls about 25 GB/s whatever the wavefronts do, so the time is the largest number of
+// tiles a CU has to stream; among the plans with the least of that the one with the fewest passes (each ends in a reduction).
+struct StepPlan { int T, S, passes, grid, loads; bool half; };
+
+StepPlan plan_step(int ntiles, int kchunks, bool pairs, bool add, int n_cu) {
+    StepPlan best{};
+    long best_cost = 1L << 60;
+    for (int half = 0; half <= (add && kchunks % 2 == 0 ? 1 : 0); ++half) {
+        const int units = half ? 2 * ntiles : ntiles;
+        for (int T = pairs ? 2 : 1; T <= 16; T += pairs ? 2 : 1) {
+            const int passes = add ? 1 : (units + T * n_cu - 1) / (T * n_cu), grid = (units + T * passes - 1) / (T * passes);
+            const int rounds = (grid + n_cu - 1) / n_cu, S = 16 / T;
+            const long cost = (long)rounds * passes * T * (half ? 1 : 2) * 64 + passes;
+            const int cps = (kchunks + S - 1) / S;
+            if (cost < best_cost) { best_cost = cost; best = StepPlan{T, S, passes, grid, half ? (cps + 1) / 2 : cps, half != 0}; }
+        }
+    }
+    return best;
+}
+
+template <int PRO, int EPI, bool PART, int J, int U, bool HALF>
+hipError_t step_allow_lds() {
+    return hipFuncSetAttribute((const void*)gemm_step_kernel<PRO, EPI, PART, J, U, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FULLK_LDS_MAX);
+}
+template <int PRO, int EPI, bool PART, int J, bool HALF>
+int launch_step(metasd_ctx* c, const StepArgs& a, const StepPlan& pl) {
+    const int N = a.ntiles * 16;
+    metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)N * a.K * 2 + (double)a.m * a.K * 4 + (double)a.m * N * 4, N, a.K, a.m);
+    const uint32_t lds = (uint32_t)step_lds(PRO == STEP_NORM, a.m, a.K);
+    constexpr int BIG = PRO == STEP_NORM ? 8 : HALF ? 3 : 4, FEW = std::min(BIG, 4);   // TERMS: the operands share the registers
+    if (pl.loads <= FEW) hipExtLaunchKernelGGL((gemm_step_kernel<PRO, EPI, PART, J, FEW, HALF>), dim3(pl.grid), dim3(1024), lds, c->stream, pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, a);
+    else hipExtLaunchKernelGGL((gemm_step_kernel<PRO, EPI, PART, J, BIG, HALF>), dim3(pl.grid), dim3(1024), lds, c->stream, pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, a);
+    LAUNCH_CHECK(c, "gemm_step");
+    return 0;
+}
+// the forms that stage their input may use more than 64 KiB of LDS
+template <int EPI, bool PART, int J>
+bool step_init_one() {
+    return step_allow_lds<STEP_NORM, EPI, PART, J, 4, false>() == hipSuccess && step_allow_lds<STEP_NORM, EPI, PART, J, 8, false>() == hipSuccess;
+}
+template <int J>
+bool step_init_j() { return step_init_one<STEP_OUT, false, J>() && step_init_one<STEP_ACT, false, J>() && (J > 2 || step_init_one<STEP_ACT, true, (J > 2 ? 1 : J)>()); }
+bool step_init() {
+    const bool ok = step_init_j<1>() && step_init_j<2>() && step_init_j<4>() && step_init_j<8>();
+    if (!ok) (void)hipGetLastError();
+    return ok;
+}
+
+int step_cols(int m, int K) {           // float4 columns of a row per lane
+    const int wpr = m <= 1 ? 16 : m <= 2 ? 8 : m <= 4 ? 4 : 2;
+    return (K + 256 * wpr - 1) / (256 * wpr);
+}
+bool step_ok(int m, int K) { return m <= STEP_ROWS && step_cols(m, K) <= 8 && step_lds(true, m, K) <= FULLK_LDS_MAX; }
+
+// The projections of normalised rows; a: everything but the weights and the split.
+template <int EPI, bool PART>
+int gemm_step_norm(metasd_ctx* c, StepArgs a, const void* W0, int n0, const void* W1, int n1, const void* W2, int n2) {
+    a.W0 = (const bf16_t*)W0; a.W1 = (const bf16_t*)W1; a.W2 = (const bf16_t*)W2;
+    a.t0 = n0 / 16; a.t1 = (n0 + n1) / 16; a.ntiles = (n0 + n1 + n2) / 16;
+    const StepPlan pl = plan_step(a.ntiles, a.K / 32, EPI == STEP_ACT && a.swiglu, false, c->n_cu);
+    a.T = pl.T; a.S = pl.S; a.passes = pl.passes;
+    const int J = step_cols(a.m, a.K);
+    if (!step_ok(a.m, a.K) || (PART && (J > 2 || a.ns < 1 || a.ns > 8)))
+        return c->fail(METASD_E_INVALID, "step GEMM: %d rows of %d, %d partials do not fit", a.m, a.K, a.ns);
+    if (J == 1) return launch_step<STEP_NORM, EPI, PART, 1, false>(c, a, pl);
+    if (PART || J == 2) return launch_step<STEP_NORM, EPI, PART, 2, false>(c, a, pl);
+    if constexpr (!PART) {
+        if (J <= 4) return launch_step<STEP_NORM, EPI, PART, 4, false>(c, a, pl);
+        return launch_step<STEP_NORM, EPI, PART, 8, false>(c, a, pl);
+    }
+    return 0;
+}
+// h += x W^T, x as two bf16 arrays
+int gemm_step_add(metasd_ctx* c, const void* x, int m, int K, const void* W, int N, float* h) {
+    StepArgs a{};
+    a.x = (const bf16_t*)x; a.x_lo = (size_t)m * K;
+    a.W0 = a.W1 = a.W2 = (const bf16_t*)W;
+    a.t0 = a.t1 = a.ntiles = N / 16;
+    a.out = h; a.N = N; a.m = m; a.K = K;
+    const StepPlan pl = plan_step(a.ntiles, K / 32, false, true, c->n_cu);
+    a.T = pl.T; a.S = pl.S; a.passes = 1;
+    if (m > STEP_ROWS) return c->fail(METASD_E_INVALID, "step GEMM: %d rows", m);
+    return pl.half ? launch_step<STEP_TERMS, STEP_ADD, false, 1, true>(c, a, pl) : launch_step<STEP_TERMS, STEP_ADD, false, 1, false>(c, a, pl);
 }
 
 // combine == false: only the per-chunk records (the consumer merges them itself)
@@ -728,6 +802,24 @@ int attention(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool combin
     }
 }
 
+// Residual rows of a block from its tokens, and its table of rotations.  A drafter head starts from
+// W_fc . [embedding ; feature of the position before] instead of the embedding.
+template <typename T>
+int embed_rows(metasd_ctx* c, Model& M, int pos0, int m, float* h) {
+    const metasd_model_desc& d = M.d;
+    const int D = d.d_model;
+    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, c->stream, c->d_hist() + pos0, (const T*)M.w[0], D, h, pos0, M.hd, d.rope_theta,
+                       c->d_rope(), c->tree ? *c->tree : TreeBlk{});
+    LAUNCH_CHECK(c, "embed + rope table");
+    if (!M.head) return 0;
+    float* cat = (float*)c->d_act();
+    hipLaunchKernelGGL(feat_cat_kernel, dim3(m), dim3(256), 0, c->stream, (const float*)h, (const float*)c->d_feat(),
+                       c->head_est ? (const float*)c->d_fest() : (const float*)nullptr, c->fsrc, pos0, D, cat, sizeof(T) == 2 ? 1 : 0);
+    LAUNCH_CHECK(c, "feat_cat");
+    int dummy;
+    return gemm<T>(c, cat, 2 * D, m, 2 * D, M.fc, D, nullptr, 0, nullptr, 0, h, &dummy, (size_t)m * 2 * D);
+}
+
 // Forward of m <= 16 rows whose tokens are hist[pos0 .. pos0+m) at positions pos0..; appends K/V.
 // logits: nullptr = none; otherwise rows [first_row, m) of the block get logits, written
 // consecutively to `logits` (row stride V).
@@ -742,18 +834,7 @@ int forward_rows(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int fi
     float* part = c->d_part();
     int ns = 0, rc;
     constexpr int split = sizeof(T) == 2 ? 1 : 0;   // bf16 models: activations for the GEMM are stored as two bf16 arrays
-    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, st, c->d_hist() + pos0, (const T*)M.w[0], D, h, pos0, hd, d.rope_theta,
-                       c->d_rope(), c->tree ? *c->tree : TreeBlk{});
-    LAUNCH_CHECK(c, "embed + rope table");
-    if (M.head) {
-        // a drafter head starts from W_fc . [embedding ; feature of the position before] instead of the embedding
-        float* cat = (float*)c->d_act();
-        hipLaunchKernelGGL(feat_cat_kernel, dim3(m), dim3(256), 0, st, (const float*)h, (const float*)c->d_feat(),
-                           c->head_est ? (const float*)c->d_fest() : (const float*)nullptr, c->fsrc, pos0, D, cat, split);
-        LAUNCH_CHECK(c, "feat_cat");
-        int dummy;
-        if ((rc = gemm<T>(c, cat, 2 * D, m, 2 * D, M.fc, D, nullptr, 0, nullptr, 0, h, &dummy, (size_t)m * 2 * D))) return rc;
-    }
+    if ((rc = embed_rows<T>(c, M, pos0, m, h))) return rc;
     for (int L = 0; L < d.n_layers; ++L) {
         // h += previous FFN output (split partials); xn = norm(h)
         hipLaunchKernelGGL(addnorm_kernel<T>, dim3(m), dim3(1024), 0, st, h, part, ns, (size_t)m * D, D, (const T*)M.layer_w(L, 0),
@@ -814,18 +895,7 @@ int forward_rows_residual(metasd_ctx* c, Model& M, int pos0, int m, float* logit
     float* inv = c->d_inv();
     int ns = 0, rc, ntg = 0;
     c->cur_eps = d.rms_eps;
-    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, st, c->d_hist() + pos0, (const T*)M.w[0], D, h, pos0, hd, d.rope_theta,
-                       c->d_rope(), c->tree ? *c->tree : TreeBlk{});
-    LAUNCH_CHECK(c, "embed + rope table");
-    if (M.head) {
-        // a drafter head starts from W_fc . [embedding ; feature of the position before] instead of the embedding (as in forward_rows)
-        float* cat = (float*)c->d_act();
-        hipLaunchKernelGGL(feat_cat_kernel, dim3(m), dim3(256), 0, st, (const float*)h, (const float*)c->d_feat(),
-                           c->head_est ? (const float*)c->d_fest() : (const float*)nullptr, c->fsrc, pos0, D, cat, 1);
-        LAUNCH_CHECK(c, "feat_cat");
-        int dummy;
-        if ((rc = gemm<T>(c, cat, 2 * D, m, 2 * D, M.fc, D, nullptr, 0, nullptr, 0, h, &dummy, (size_t)m * 2 * D))) return rc;
-    }
+    if ((rc = embed_rows<T>(c, M, pos0, m, h))) return rc;
     // first norm: a plain RMSNorm of the embedding rows (normalised x, no scaling downstream)
     hipLaunchKernelGGL(addnorm_kernel<T>, dim3(m), dim3(1024), 0, st, h, part, 0, (size_t)m * D, D, (const T*)M.layer_w(0, 0), d.rms_eps,
                        xn, 1);
@@ -867,18 +937,17 @@ int forward_rows_residual(metasd_ctx* c, Model& M, int pos0, int m, float* logit
     return 0;
 }
 
-// Short blocks of narrow bf16 models (drafter steps; d_model <= 2048, METASD_FUSE_DMAX): the same forward with the add+norm, the FFN
-// activation and the attention combine folded into the prologue of the GEMM that consumes them -
-// 5 launches per layer instead of 10 (q / k / v are formed inside the attention kernel).  The residual stream and the partials ping-pong between two
-// buffers, because a GEMM's workgroups read the old ones while others already write the new ones.
+// Short blocks of narrow bf16 models (drafter steps; d_model <= 2048): the same forward with the add+norm, the FFN activation, the
+// residual add and the attention combine folded into the GEMMs before or behind them (step.h) - 5 launches per layer instead of 10
+// (q / k / v are formed inside the attention kernel).  The residual stream ping-pongs between two buffers where the gate | up
+// projection adds the output projection's partials to it, because its workgroups read the old rows while one writes the new ones.
+// Each launch reads finished sums instead of up to eight split-K partials.  One row of the 1B
+// shape, per layer: QKV 7.6 -> 5.5, attention 7.4 -> 6.7, gate | up with the activation 16.2 -> 15.3, down 9.4 -> 9.0 us; head 25.2 -> 24.3.
 constexpr int fused_max_rows() { return 4; }
 bool fused_small_ok(const Model& M, int m) {
     const metasd_model_desc& d = M.d;
-    constexpr int dmax = 2048;
-    // the add+norm prologue keeps the block's residual rows in LDS (m * d_model floats) beside the staged activations:
-    // within the 64 KiB a kernel gets without asking for more
-    return d.dtype == METASD_BF16 && m <= fused_max_rows() && d.d_model <= dmax && d.d_ffn <= 4 * dmax && M.hd >= 64 &&
-           (size_t)m * d.d_model * 4 <= 40 * 1024;
+    constexpr int dmax = 2048;      // four rows of d_ffn <= 8192 inputs are 128 KiB of LDS, eight float4 per thread of d_model
+    return d.dtype == METASD_BF16 && m <= fused_max_rows() && d.d_model <= dmax && d.d_ffn <= 4 * dmax && M.hd >= 64;
 }
 
 int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int first_row) {
@@ -887,62 +956,98 @@ int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, 
     const int D = d.d_model, H = d.n_heads, KH = d.n_kv_heads, hd = M.hd, F = d.d_ffn, V = d.vocab;
     const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV;
     hipStream_t st = c->stream;
-    int hp = 0, pp = 0, ns = 0, rc;     // current residual buffer, current partials buffer, partials in it
+    int hp = 0, rc;                     // current residual buffer
     hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, st, c->d_hist() + pos0, (const T*)M.w[0], D, c->d_h_pp(0), pos0, hd,
                        d.rope_theta, c->d_rope(), c->tree ? *c->tree : TreeBlk{});
     LAUNCH_CHECK(c, "embed + rope table");
-    auto norm_pro = [&](const void* gain, int row0) {
-        GemmPro p{};
-        p.src = c->d_h_pp(hp) + (size_t)row0 * D;
-        p.part = c->d_part_pp(pp) + (size_t)row0 * D;
-        p.h_out = c->d_h_pp(hp ^ 1) + (size_t)row0 * D;
-        p.gain = (const bf16_t*)gain;
-        p.sstride = (size_t)m * D;
-        p.ns = ns;
-        p.eps = d.rms_eps;
-        return p;
+    auto norm_in = [&](const void* gain, int row0) {
+        StepArgs a{};
+        a.h = c->d_h_pp(hp) + (size_t)row0 * D;
+        a.gain = (const bf16_t*)gain;
+        a.eps = d.rms_eps;
+        a.m = m - row0; a.K = D;
+        return a;
     };
     const int nchunks = (pos0 + m + ATT_CH - 1) / ATT_CH;
     for (int L = 0; L < d.n_layers; ++L) {
-        // QKV projection of norm(h + previous FFN output)
-        if ((rc = gemm_pro<PRO_NORM>(c, norm_pro(M.layer_w(L, 0), 0), m, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV,
-                                     c->d_part_pp(pp ^ 1), nullptr, &ns))) return rc;
-        hp ^= 1; pp ^= 1;
+        // QKV projection of norm(h)
+        StepArgs a = norm_in(M.layer_w(L, 0), 0);
+        a.out = c->d_part(); a.N = NQKV;
+        if ((rc = gemm_step_norm<STEP_OUT, false>(c, a, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV))) return rc;
         const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
         T* kc = (T*)M.kv + (size_t)L * 2 * plane;
-        // q, and the new K / V rows, are summed and rotated inside the attention kernel (no rope launch)
-        {
-            const QkvIn qi{c->d_part_pp(pp), ns, (size_t)m * NQKV, NQKV, (const double2*)c->d_rope(), nullptr, kc, kc + plane};
-            if ((rc = attention<T>(c, M, L, pos0, m, false, &qi))) return rc;
-        }
+        // q, and the new K / V rows, are rotated inside the attention kernel (no rope launch)
+        const QkvIn qi{c->d_part(), 1, (size_t)m * NQKV, NQKV, (const double2*)c->d_rope(), nullptr, kc, kc + plane};
+        if ((rc = attention<T>(c, M, L, pos0, m, false, &qi))) return rc;
         // output projection of the merged attention output
-        {
-            GemmPro p{};
-            p.src = c->d_apart(); p.nchunks = nchunks; p.hd = hd;
-            if ((rc = gemm_pro<PRO_COMBINE>(c, p, m, DQ, M.layer_w(L, 4), D, nullptr, 0, nullptr, 0, c->d_part_pp(pp ^ 1), nullptr, &ns))) return rc;
-            pp ^= 1;
-        }
-        // gate | up projection of norm(h + attention output)
-        if (d.act == METASD_SWIGLU)
-            rc = gemm_pro<PRO_NORM>(c, norm_pro(M.layer_w(L, 5), 0), m, D, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0,
-                                    c->d_part_pp(pp ^ 1), nullptr, &ns);
-        else
-            rc = gemm_pro<PRO_NORM>(c, norm_pro(M.layer_w(L, 5), 0), m, D, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0, c->d_part_pp(pp ^ 1),
-                                    nullptr, &ns);
+        int ns = 0;
+        GemmPro pro{};
+        pro.src = c->d_apart(); pro.nchunks = nchunks; pro.hd = hd;
+        if ((rc = gemm_combine(c, pro, m, DQ, M.layer_w(L, 4), D, c->d_part(), &ns))) return rc;
+        // activation of the gate | up projection of norm(h + attention output)
+        a = norm_in(M.layer_w(L, 5), 0);
+        a.part = c->d_part(); a.sstride = (size_t)m * D; a.ns = ns; a.h_out = c->d_h_pp(hp ^ 1);
+        a.out = (float*)c->d_act(); a.N = F; a.swiglu = d.act == METASD_SWIGLU;
+        if (a.swiglu) rc = gemm_step_norm<STEP_ACT, true>(c, a, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0);
+        else rc = gemm_step_norm<STEP_ACT, true>(c, a, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0);
         if (rc) return rc;
-        hp ^= 1; pp ^= 1;
-        // down projection of the activation
-        {
-            GemmPro p{};
-            p.src = c->d_part_pp(pp); p.ns = ns; p.sstride = (size_t)m * (d.act == METASD_SWIGLU ? 2 : 1) * F; p.act = d.act == METASD_SWIGLU ? 1 : 0;
-            if ((rc = gemm_pro<PRO_ACT>(c, p, m, F, M.layer_w(L, 8), D, nullptr, 0, nullptr, 0, c->d_part_pp(pp ^ 1), nullptr, &ns))) return rc;
-            pp ^= 1;
-        }
+        hp ^= 1;
+        // h += down projection
+        if ((rc = gemm_step_add(c, c->d_act(), m, F, M.layer_w(L, 8), D, c->d_h_pp(hp)))) return rc;
     }
     if (logits) {
-        int dummy;
-        if ((rc = gemm_pro<PRO_NORM>(c, norm_pro(M.final_norm(), first_row), m - first_row, D, M.lm_head(), V, nullptr, 0, nullptr, 0,
-                                     c->d_part_pp(pp ^ 1), logits, &dummy))) return rc;
+        StepArgs a = norm_in(M.final_norm(), first_row);
+        a.out = logits; a.N = V;
+        if ((rc = gemm_step_norm<STEP_OUT, false>(c, a, M.lm_head(), V, nullptr, 0, nullptr, 0))) return rc;
+    }
+    return 0;
+}
+
+// Short blocks (at most 8 rows) whose normalised rows fit in LDS, in general (verification, drafter heads, models wider than the path
+// above takes): 7 launches per layer, none of which leaves partial sums.  Verification of
+// 6 rows, per layer: 1B shape 59 -> 51 us, 7B shape 104 -> 101 us (gate | up and activation 36.1 -> 33.7, QKV 18.6 -> 20.0).
+constexpr int STEP_DMIN = 512;      // from here on each of the 16 wavefronts has a chunk of the input
+int forward_rows_step(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int first_row) {
+    typedef bf16_t T;
+    const metasd_model_desc& d = M.d;
+    const int D = d.d_model, H = d.n_heads, KH = d.n_kv_heads, hd = M.hd, F = d.d_ffn, V = d.vocab;
+    const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV;
+    hipStream_t st = c->stream;
+    float* h = c->d_h();
+    int rc;
+    if ((rc = embed_rows<T>(c, M, pos0, m, h))) return rc;
+    auto norm_in = [&](const void* gain, int row0) {
+        StepArgs a{};
+        a.h = h + (size_t)row0 * D;
+        a.gain = (const bf16_t*)gain;
+        a.eps = d.rms_eps;
+        a.m = m - row0; a.K = D;
+        return a;
+    };
+    for (int L = 0; L < d.n_layers; ++L) {
+        StepArgs a = norm_in(M.layer_w(L, 0), 0);
+        a.out = c->d_part(); a.N = NQKV;
+        if ((rc = gemm_step_norm<STEP_OUT, false>(c, a, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV))) return rc;
+        const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
+        T* kc = (T*)M.kv + (size_t)L * 2 * plane;
+        // (forming q / k / v inside the attention kernel, as the path above does, was measured here and is slower at the 7B shape:
+        // 3.32 against 3.29 ms per pass - the wider kernel loses what the launch saves)
+        hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, c->d_part(), 1, (size_t)m * NQKV, NQKV, pos0, H, KH, hd,
+                           (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, hd >= 64 ? 1 : 0, (const float*)nullptr);
+        LAUNCH_CHECK(c, "rope_kv");
+        if ((rc = attention<T>(c, M, L, pos0, m))) return rc;
+        if ((rc = gemm_step_add(c, c->d_ao(), m, DQ, M.layer_w(L, 4), D, h))) return rc;
+        a = norm_in(M.layer_w(L, 5), 0);
+        a.out = (float*)c->d_act(); a.N = F; a.swiglu = d.act == METASD_SWIGLU;
+        if (a.swiglu) rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0);
+        else rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0);
+        if (rc) return rc;
+        if ((rc = gemm_step_add(c, c->d_act(), m, F, M.layer_w(L, 8), D, h))) return rc;
+    }
+    if (logits) {
+        StepArgs a = norm_in(M.final_norm(), first_row);
+        a.out = logits; a.N = V;
+        if ((rc = gemm_step_norm<STEP_OUT, false>(c, a, M.lm_head(), V, nullptr, 0, nullptr, 0))) return rc;
     }
     return 0;
 }
@@ -990,9 +1095,8 @@ int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool
         // the short-block path never writes the finished residual rows: not for the target when its features are wanted
         const bool fused = c->fuse_small && fused_small_ok(M, m) && !(is_target && c->cfg.feature_heads);
         if (M.d.dtype != METASD_BF16) rc = forward_rows<float>(c, M, pos0 + done, m, lg, first_row);
-        else if (M.head) rc = c->gemm_reduce ? forward_rows_residual(c, M, pos0 + done, m, lg, first_row)     // these two paths carry the head's
-                                             : forward_rows<bf16_t>(c, M, pos0 + done, m, lg, first_row);      // input projection
-        else if (fused) rc = forward_rows_fused(c, M, pos0 + done, m, lg, first_row);
+        else if (fused && !M.head) rc = forward_rows_fused(c, M, pos0 + done, m, lg, first_row);       // (the others carry the head's input projection)
+        else if (c->fuse_small && M.d.d_model >= STEP_DMIN && step_ok(m, M.d.d_model)) rc = forward_rows_step(c, M, pos0 + done, m, lg, first_row);
         else if (c->gemm_reduce) rc = forward_rows_residual(c, M, pos0 + done, m, lg, first_row);
         else rc = forward_rows<bf16_t>(c, M, pos0 + done, m, lg, first_row);
         if (rc) return rc;
@@ -1867,6 +1971,7 @@ int32_t metasd_create(metasd_ctx** out, const metasd_config* cfg, const metasd_m
             }
         }
         if (hipFuncSetAttribute((const void*)gemm_fullk_residual_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FULLK_LDS_MAX) != hipSuccess) { c->fullk = false; (void)hipGetLastError(); }
+        if (!step_init()) c->fuse_small = false;
         c->n_cu = ncu;
     }
     c->target.d_table = (const void**)(c->ws + lay.tables);
