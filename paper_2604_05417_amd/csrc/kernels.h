@@ -55,14 +55,41 @@ __device__ __forceinline__ float wave_max(float v) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
     return v;
 }
-// inclusive prefix sum over the lanes of a wavefront
-__device__ __forceinline__ double wave_scan_incl(double v, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        double t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
+
+// Reductions in the vector unit's own lane moves (DPP): four shifts inside rows of 16 lanes, then the row totals handed on.  A step is
+// one dependent move and one operation, about a tenth of the LDS permute that __shfl_xor is; used where such chains are on the
+// critical path (accept and sampling kernels).  Every lane gets the inclusive scan; the total is lane 63's.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_move(float old, float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v) {          // lanes without a source get 0
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ float dpp_max(float v) {
+    v = fmaxf(v, dpp_move<0x111, 0xf>(-INFINITY, v));           // row_shr:1, 2, 4, 8
+    v = fmaxf(v, dpp_move<0x112, 0xf>(-INFINITY, v));
+    v = fmaxf(v, dpp_move<0x114, 0xf>(-INFINITY, v));
+    v = fmaxf(v, dpp_move<0x118, 0xf>(-INFINITY, v));
+    v = fmaxf(v, dpp_move<0x142, 0xa>(-INFINITY, v));           // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+    v = fmaxf(v, dpp_move<0x143, 0xc>(-INFINITY, v));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ double dpp_scan(double v) {
+    v += dpp_move<0x111, 0xf>(v);
+    v += dpp_move<0x112, 0xf>(v);
+    v += dpp_move<0x114, 0xf>(v);
+    v += dpp_move<0x118, 0xf>(v);
+    v += dpp_move<0x142, 0xa>(v);
+    v += dpp_move<0x143, 0xc>(v);
     return v;
+}
+__device__ __forceinline__ double dpp_sum(double v) {
+    v = dpp_scan(v);
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1764,24 +1791,29 @@ __device__ __forceinline__ float ak_exp(float a) {
     return __builtin_amdgcn_exp2f(a * 1.44269502162933349609375f);   // a = -inf gives 0
 }
 
-// exp((x - mx) / T): for T = 1 the fp32 difference is the correctly rounded argument; otherwise
-// the argument is scaled in fp64 before it is rounded.
+// exp((x - mx) / T).  T = 1: the fp32 difference is the correctly rounded argument.  Otherwise the difference is multiplied by
+// log2(e) / T held as two floats, one rounding more than the difference's own.  (Largest and rms error against 64 bits, T = 0.7:
+// 5.4e-6 and 1.39e-6; with the argument scaled in 64 bits and rounded twice, as before, 7.2e-6 and 1.46e-6 and four more instructions.)
+struct ExpScale { float hi, lo; };
+__device__ __forceinline__ ExpScale exp_scale(double invT) {
+    const double c = invT * 1.4426950408889634074;
+    const float hi = (float)c;
+    return ExpScale{hi, (float)(c - (double)hi)};
+}
 template <bool UNIT_T>
-__device__ __forceinline__ float ak_expx(float x, float mx, double invT) {
-    if constexpr (UNIT_T) return ak_exp(x - mx);
-    else return ak_exp((float)(((double)x - (double)mx) * invT));
+__device__ __forceinline__ float ak_expx(float x, float mx, const ExpScale& k) {
+    const float t = x - mx;
+    if constexpr (UNIT_T) return ak_exp(t);
+    else return __builtin_amdgcn_exp2f(fmaf(t, k.hi, fmaxf(t, -1e30f) * k.lo));   // masked logits give 0: the low term stays finite
 }
 
 __device__ __forceinline__ void ak_load(const float* __restrict__ row, int V, int wave, int lane, float (&x)[AK_CH][4]) {
 #pragma unroll
-    for (int c = 0; c < AK_CH; ++c) {
+    for (int c = 0; c < AK_CH; ++c) {           // unconditional (clamped) requests: each wait counts exactly what it needs
         const int idx = wave * AK_SEG + c * 256 + lane * 4;
-        if (idx < V) {
-            const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + idx));
-            x[c][0] = v[0]; x[c][1] = v[1]; x[c][2] = v[2]; x[c][3] = v[3];
-        } else {
-            x[c][0] = x[c][1] = x[c][2] = x[c][3] = -INFINITY;
-        }
+        const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + min(idx, V - 4)));
+        const bool in = idx < V;
+        x[c][0] = in ? v[0] : -INFINITY; x[c][1] = in ? v[1] : -INFINITY; x[c][2] = in ? v[2] : -INFINITY; x[c][3] = in ? v[3] : -INFINITY;
     }
 }
 
@@ -1798,7 +1830,7 @@ __device__ __forceinline__ float ak_thread_max(const float (&x)[AK_CH][4]) {
 // added in fp32 (rounding errors are random and average out over the 512 threads: about 1e-8 of
 // the total); across threads every sum is fp64.
 template <bool UNIT_T>
-__device__ __forceinline__ double ak_exp_inplace(float (&x)[AK_CH][4], float mx, double invT) {
+__device__ __forceinline__ double ak_exp_inplace(float (&x)[AK_CH][4], float mx, const ExpScale& invT) {
     float s = 0.f;
 #pragma unroll
     for (int c = 0; c < AK_CH; ++c) {
@@ -1843,7 +1875,7 @@ __device__ __forceinline__ void ak_search(const float (&w)[AK_CH][4], const doub
     double cb = base;
 #pragma unroll
     for (int c = 0; c < AK_CH; ++c) {
-        const double ct = wave_sum((double)ak_chunk_sum(w, c));
+        const double ct = dpp_sum((double)ak_chunk_sum(w, c));
         if (ct > 0.0) clast = c;
         if (cstar < 0 && !take_last) {
             if (cb + ct > target) cstar = c;
@@ -1856,7 +1888,7 @@ __device__ __forceinline__ void ak_search(const float (&w)[AK_CH][4], const doub
     for (int c = 0; c < AK_CH; ++c)
         if (c == cstar) { w4[0] = w[c][0]; w4[1] = w[c][1]; w4[2] = w[c][2]; w4[3] = w[c][3]; }
     const double sc = (double)((w4[0] + w4[1]) + (w4[2] + w4[3]));
-    const double incl = wave_scan_incl(sc, lane);
+    const double incl = dpp_scan(sc);
     unsigned long long bal = __ballot(take_last ? (sc > 0.0) : (cb + incl > target));
     if (bal == 0ull) { take_last = true; bal = __ballot(sc > 0.0); }
     int lstar;
@@ -1934,7 +1966,7 @@ __device__ __forceinline__ void accept_rows_body(const float* __restrict__ P, co
         }
         return;
     }
-    const double invT = 1.0 / (double)T;
+    const ExpScale invT = exp_scale(1.0 / (double)T);
     if (has_q) ak_load(Qrow, V, wave, lane, xq);
     // the two logits of the draft token (tiny second read, issued with the stream)
     float pdl = 0.f, qdl = 0.f;
@@ -1942,8 +1974,8 @@ __device__ __forceinline__ void accept_rows_body(const float* __restrict__ P, co
     if (threadIdx.x == 0) sm.token = -1;
     // ---- maxima
     {
-        const float a = wave_max(ak_thread_max(xp));
-        const float c = has_q ? wave_max(ak_thread_max(xq)) : -INFINITY;
+        const float a = dpp_max(ak_thread_max(xp));
+        const float c = has_q ? dpp_max(ak_thread_max(xq)) : -INFINITY;
         if (lane == 0) { sm.fmx[0][wave] = a; sm.fmx[1][wave] = c; }
     }
     __syncthreads();
@@ -1952,8 +1984,8 @@ __device__ __forceinline__ void accept_rows_body(const float* __restrict__ P, co
     for (int k = 1; k < AK_WAVES; ++k) { mp = fmaxf(mp, sm.fmx[0][k]); mq = fmaxf(mq, sm.fmx[1][k]); }
     // ---- exp and the two normalisers
     {
-        const double a = wave_sum(ak_exp_inplace<UNIT_T>(xp, mp, invT));
-        const double c = has_q ? wave_sum(ak_exp_inplace<UNIT_T>(xq, mq, invT)) : 0.0;
+        const double a = dpp_sum(ak_exp_inplace<UNIT_T>(xp, mp, invT));
+        const double c = has_q ? dpp_sum(ak_exp_inplace<UNIT_T>(xq, mq, invT)) : 0.0;
         if (lane == 0) { sm.dz[0][wave] = a; sm.dz[1][wave] = c; }
     }
     __syncthreads();
@@ -1996,8 +2028,8 @@ __device__ __forceinline__ void accept_rows_body(const float* __restrict__ P, co
             fm += mn4;
         }
         double tw = (double)fw, tm = (double)fm;
-        tw = wave_sum(tw);
-        tm = wave_sum(tm);
+        tw = dpp_sum(tw);
+        tm = dpp_sum(tm);
         if (lane == 0) { sm.dw[0][wave] = tw; sm.dw[1][wave] = tm; }
     }
     __syncthreads();
@@ -2065,14 +2097,19 @@ __device__ __forceinline__ bool as_get(const unsigned long long* slot, uint32_t 
     return tw_get(slot, epoch, spin_limit, payload);
 }
 
-// Publish NW floats of this quarter (words first .. first + NW) and collect the same words of all four.
+// Publish NW floats of this quarter (words first .. first + NW) and collect the same words of all nq.
 // `mine` must hold the same values in every thread.  Returns false after a timeout (sm.fail is set).
 template <int NW>
 __device__ __forceinline__ bool as_exchange(unsigned long long* slots, int q, uint32_t epoch, const float (&mine)[NW], int first,
-                                            AsShared& sm, int spin_limit) {
+                                            AsShared& sm, int nq, int spin_limit) {
     const int t = (int)threadIdx.x;
+    if (nq == 1) {                                 // the only one: nobody to meet
+        if (t < NW) sm.xw[0][first + t] = mine[t];
+        __syncthreads();
+        return true;
+    }
     if (t < NW) as_put(slots + q * AS_WORDS + first + t, epoch, __float_as_uint(mine[t]));
-    if (t < AS_Q * NW) {
+    if (t < nq * NW) {
         const int qq = t / NW, ww = t - qq * NW;
         uint32_t bits = 0;
         if (as_get(slots + qq * AS_WORDS + first + ww, epoch, spin_limit, &bits)) sm.xw[qq][first + ww] = __uint_as_float(bits);
@@ -2084,14 +2121,11 @@ __device__ __forceinline__ bool as_exchange(unsigned long long* slots, int q, ui
 
 __device__ __forceinline__ void as_load(const float* __restrict__ row, int V, int seg0, int lane, float (&x)[AS_CH][4]) {
 #pragma unroll
-    for (int c = 0; c < AS_CH; ++c) {
+    for (int c = 0; c < AS_CH; ++c) {           // unconditional (clamped) requests: each wait counts exactly what it needs
         const int idx = seg0 + c * 256 + lane * 4;
-        if (idx < V) {
-            const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + idx));
-            x[c][0] = v[0]; x[c][1] = v[1]; x[c][2] = v[2]; x[c][3] = v[3];
-        } else {
-            x[c][0] = x[c][1] = x[c][2] = x[c][3] = -INFINITY;
-        }
+        const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + min(idx, V - 4)));
+        const bool in = idx < V;
+        x[c][0] = in ? v[0] : -INFINITY; x[c][1] = in ? v[1] : -INFINITY; x[c][2] = in ? v[2] : -INFINITY; x[c][3] = in ? v[3] : -INFINITY;
     }
 }
 
@@ -2106,7 +2140,7 @@ __device__ __forceinline__ float as_thread_max(const float (&x)[AS_CH][4]) {
 
 // x <- exp((x - mx)/T) in place (mx finite); returns this thread's sum (fp32 inside the thread).
 template <bool UNIT_T>
-__device__ __forceinline__ double as_exp_inplace(float (&x)[AS_CH][4], float mx, double invT) {
+__device__ __forceinline__ double as_exp_inplace(float (&x)[AS_CH][4], float mx, const ExpScale& invT) {
     float s = 0.f;
 #pragma unroll
     for (int c = 0; c < AS_CH; ++c) {
@@ -2160,7 +2194,7 @@ __device__ __forceinline__ bool as_search(const float (&w)[AS_CH][4], const doub
         double cb = wbase;
 #pragma unroll
         for (int c = 0; c < AS_CH; ++c) {
-            const double ct = wave_sum((double)((w[c][0] + w[c][1]) + (w[c][2] + w[c][3]))) * scale;
+            const double ct = dpp_sum((double)((w[c][0] + w[c][1]) + (w[c][2] + w[c][3]))) * scale;
             if (ct > 0.0) clast = c;
             if (cstar < 0 && !take_last) {
                 if (cb + ct > target) cstar = c;
@@ -2173,7 +2207,7 @@ __device__ __forceinline__ bool as_search(const float (&w)[AS_CH][4], const doub
         for (int c = 0; c < AS_CH; ++c)
             if (c == cstar) { w4[0] = w[c][0]; w4[1] = w[c][1]; w4[2] = w[c][2]; w4[3] = w[c][3]; }
         const double sc = (double)((w4[0] + w4[1]) + (w4[2] + w4[3])) * scale;
-        const double incl = wave_scan_incl(sc, lane);
+        const double incl = dpp_scan(sc);
         unsigned long long bal = __ballot(take_last ? (sc > 0.0) : (cb + incl > target));
         if (bal == 0ull) { take_last = true; bal = __ballot(sc > 0.0); }
         int lstar;
@@ -2203,7 +2237,7 @@ __device__ __forceinline__ void accept_split_item(const float* __restrict__ P, c
                                                   const RoundTab& rt, uint32_t seq0, unsigned long long* __restrict__ cand,
                                                   double* __restrict__ bd, unsigned long long* __restrict__ xchg, uint32_t epoch,
                                                   int spin_limit, AsShared& sm) {
-    const int q = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+    const int q = blockIdx.x, nq = gridDim.x, j = blockIdx.y, b = blockIdx.z;
     const uint32_t round = round_of(rt, b);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t item = (size_t)b * (gamma + 1) + j;
@@ -2240,11 +2274,11 @@ __device__ __forceinline__ void accept_split_item(const float* __restrict__ P, c
         for (int k = 1; k < AS_WAVES; ++k)
             if (sm.fmx[0][k] > rv || (sm.fmx[0][k] == rv && sm.ival[k] < ri)) { rv = sm.fmx[0][k]; ri = sm.ival[k]; }
         const float mine[2] = {rv, __int_as_float(ri)};
-        if (!as_exchange<2>(slots, q, epoch, mine, 0, sm, spin_limit)) { fail_out(); return; }
+        if (!as_exchange<2>(slots, q, epoch, mine, 0, sm, nq, spin_limit)) { fail_out(); return; }
         if (q == 0 && threadIdx.x == 0) {
             float gv = sm.xw[0][0];
             int gi = __float_as_int(sm.xw[0][1]);
-            for (int k = 1; k < AS_Q; ++k) {
+            for (int k = 1; k < nq; ++k) {
                 const float ov = sm.xw[k][0];
                 const int oi = __float_as_int(sm.xw[k][1]);
                 if (ov > gv || (ov == gv && oi < gi)) { gv = ov; gi = oi; }
@@ -2255,14 +2289,14 @@ __device__ __forceinline__ void accept_split_item(const float* __restrict__ P, c
         }
         return;
     }
-    const double invT = 1.0 / (double)T;
+    const ExpScale invT = exp_scale(1.0 / (double)T);
     if (has_q) as_load(Qrow, V, seg0, lane, xq);
     float pdl = 0.f, qdl = 0.f;
     if (has_q) { pdl = Prow[dtok]; qdl = Qrow[dtok]; }
     // ---- local maxima
     {
-        const float a = wave_max(as_thread_max(xp));
-        const float c = has_q ? wave_max(as_thread_max(xq)) : -INFINITY;
+        const float a = dpp_max(as_thread_max(xp));
+        const float c = has_q ? dpp_max(as_thread_max(xq)) : -INFINITY;
         if (lane == 0) { sm.fmx[0][wave] = a; sm.fmx[1][wave] = c; }
     }
     __syncthreads();
@@ -2273,8 +2307,8 @@ __device__ __forceinline__ void accept_split_item(const float* __restrict__ P, c
     const float emp = lmp > -INFINITY ? lmp : 0.f, emq = lmq > -INFINITY ? lmq : 0.f;
     // ---- local exp and sums
     {
-        const double a = wave_sum(as_exp_inplace<UNIT_T>(xp, emp, invT));
-        const double c = has_q ? wave_sum(as_exp_inplace<UNIT_T>(xq, emq, invT)) : 0.0;
+        const double a = dpp_sum(as_exp_inplace<UNIT_T>(xp, emp, invT));
+        const double c = has_q ? dpp_sum(as_exp_inplace<UNIT_T>(xq, emq, invT)) : 0.0;
         if (lane == 0) { sm.dz[0][wave] = a; sm.dz[1][wave] = c; }
     }
     __syncthreads();
@@ -2287,7 +2321,7 @@ __device__ __forceinline__ void accept_split_item(const float* __restrict__ P, c
         for (int k = 0; k < AS_WAVES; ++k) { lp += sm.dz[0][k]; lq += sm.dz[1][k]; }
         const float ph = (float)lp, qh = (float)lq;
         const float mine[6] = {lmp, lmq, ph, (float)(lp - (double)ph), qh, (float)(lq - (double)qh)};
-        if (!as_exchange<6>(slots, q, epoch, mine, 0, sm, spin_limit)) { fail_out(); return; }
+        if (!as_exchange<6>(slots, q, epoch, mine, 0, sm, nq, spin_limit)) { fail_out(); return; }
         mp = fmaxf(fmaxf(sm.xw[0][0], sm.xw[1][0]), fmaxf(sm.xw[2][0], sm.xw[3][0]));
         mq = fmaxf(fmaxf(sm.xw[0][1], sm.xw[1][1]), fmaxf(sm.xw[2][1], sm.xw[3][1]));
         sp_mine = 0.0; sq_mine = 0.0;
@@ -2335,7 +2369,7 @@ __device__ __forceinline__ void accept_split_item(const float* __restrict__ P, c
             fw += (xq[c][0] + xq[c][1]) + (xq[c][2] + xq[c][3]);
             fm += mn4;
         }
-        const double tw = wave_sum((double)fw), tm = wave_sum((double)fm);
+        const double tw = dpp_sum((double)fw), tm = dpp_sum((double)fm);
         if (lane == 0) { sm.dw[0][wave] = tw; sm.dw[1][wave] = tm; }
     }
     __syncthreads();
@@ -2347,7 +2381,7 @@ __device__ __forceinline__ void accept_split_item(const float* __restrict__ P, c
         for (int k = 0; k < AS_WAVES; ++k) { lr += sm.dw[0][k]; lm += sm.dw[1][k]; }
         const float rh = (float)lr, mh = (float)lm;
         const float mine[4] = {rh, (float)(lr - (double)rh), mh, (float)(lm - (double)mh)};
-        if (!as_exchange<4>(slots, q, epoch, mine, 6, sm, spin_limit)) { fail_out(); return; }
+        if (!as_exchange<4>(slots, q, epoch, mine, 6, sm, nq, spin_limit)) { fail_out(); return; }
 #pragma unroll
         for (int k = 0; k < AS_Q; ++k) {
             zrq[k] = (double)sm.xw[k][6] + (double)sm.xw[k][7];
@@ -2375,28 +2409,31 @@ __global__ __launch_bounds__(AS_NT) void accept_split_kernel(const float* __rest
                                                              uint32_t* __restrict__ mask, int32_t* __restrict__ hist, int l) {
     __shared__ AsShared sm;
     if (threadIdx.x == 0) { sm.token = -1; sm.fail = 0; }
+    if (threadIdx.x < AS_Q * AS_WORDS) {           // a quarter without a workgroup: no maximum, no mass
+        const int w = (int)threadIdx.x % AS_WORDS;
+        (&sm.xw[0][0])[threadIdx.x] = w < 2 ? -INFINITY : 0.f;
+    }
+    __syncthreads();
     if (T == 1.0f) accept_split_item<true>(P, Q, d, gamma, V, T, seed, rt, seq0, cand, bd, xchg, epoch, spin_limit, sm);
     else accept_split_item<false>(P, Q, d, gamma, V, T, seed, rt, seq0, cand, bd, xchg, epoch, spin_limit, sm);
-    // ---- per row: first failed test, emitted token, mask (one thread of the bonus position's first quarter)
-    if (blockIdx.x == 0 && (int)blockIdx.y == gamma && threadIdx.x == 0) {
-        const int b = blockIdx.z;
-        int n = gamma, tok = -2;
-        uint32_t mk = 0, cn = 0;
-        bool ok = true;
-        for (int j = gamma; j >= 0 && ok; --j) {
-            uint32_t w = 0;
-            ok = as_get(cand + (size_t)b * (gamma + 1) + j, epoch, spin_limit, &w) && !(w & AS_CAND_FAIL);
-            if (!ok) break;
-            if (j == gamma) { cn = w; continue; }
-            if (w & AS_CAND_ACCEPT) mk |= 1u << j;
-            else { n = j; cn = w; }
+    // ---- per row: first failed test, emitted token, mask.  The first wavefront of the bonus position's first quarter asks for all
+    // gamma + 1 candidates at once, one per lane (one after the other each costs a trip to memory:
+    // one row, gamma 5 11.7 -> 9.9 us)
+    if (blockIdx.x == 0 && (int)blockIdx.y == gamma && threadIdx.x < 64) {
+        const int b = blockIdx.z, j = (int)threadIdx.x;
+        uint32_t w = 0;
+        const bool got = j > gamma || (as_get(cand + (size_t)b * (gamma + 1) + j, epoch, spin_limit, &w) && !(w & AS_CAND_FAIL));
+        const bool ok = __ballot(!got) == 0ull;
+        const uint32_t mk = (uint32_t)__ballot(j < gamma && (w & AS_CAND_ACCEPT));
+        const uint32_t failed = ~mk & ((1u << gamma) - 1u);
+        const int n = failed ? __ffs((int)failed) - 1 : gamma;
+        const int tok = ok ? (int)((uint32_t)__builtin_amdgcn_readlane((int)w, n) & 0x1fffffffu) : -2;
+        if (j == 0) {
+            n_acc[b] = ok ? n : 0;
+            token[b] = tok;
+            if (mask) mask[b] = ok ? mk : 0u;
+            if (hist && tok >= 0) hist[l + n] = tok;
         }
-        if (ok) tok = (int)(cn & 0x1fffffffu);
-        else { n = 0; mk = 0; }
-        n_acc[b] = n;
-        token[b] = tok;
-        if (mask) mask[b] = mk;
-        if (hist && tok >= 0) hist[l + n] = tok;
     }
 }
 
@@ -2427,13 +2464,13 @@ __global__ void accept_finalize_kernel(const int2* __restrict__ cand, int rows, 
 template <bool UNIT_T>
 __device__ __forceinline__ int sample_rows_body(float (&xp)[AK_CH][4], int V, float T, float u, AkShared& sm, int wave, int lane) {
     if (threadIdx.x == 0) sm.token = -1;
-    const float a = wave_max(ak_thread_max(xp));
+    const float a = dpp_max(ak_thread_max(xp));
     if (lane == 0) sm.fmx[0][wave] = a;
     __syncthreads();
     float mp = sm.fmx[0][0];
 #pragma unroll
     for (int k = 1; k < AK_WAVES; ++k) mp = fmaxf(mp, sm.fmx[0][k]);
-    const double s = wave_sum(ak_exp_inplace<UNIT_T>(xp, mp, 1.0 / (double)T));
+    const double s = dpp_sum(ak_exp_inplace<UNIT_T>(xp, mp, exp_scale(1.0 / (double)T)));
     if (lane == 0) sm.dz[0][wave] = s;
     __syncthreads();
     double Zp = 0.0;
@@ -2562,7 +2599,7 @@ __device__ __forceinline__ float ak_thread_sum(const float (&x)[AK_CH][4]) {
 
 // sm.dz[which][wave] <- the wavefront totals of x; returns their sum (every thread).  Two barriers.
 __device__ __forceinline__ double ak_totals(const float (&x)[AK_CH][4], AkShared& sm, int which, int wave, int lane) {
-    const double a = wave_sum((double)ak_thread_sum(x));
+    const double a = dpp_sum((double)ak_thread_sum(x));
     __syncthreads();                                   // earlier readers of sm.dz are done
     if (lane == 0) sm.dz[which][wave] = a;
     __syncthreads();
@@ -2600,13 +2637,13 @@ __device__ __forceinline__ void tree_children_sample_body(const float* __restric
     if (nch == 0) return;                              // workgroup-uniform
     float x[AK_CH][4];
     ak_load(logits + (size_t)blockIdx.x * V, V, wave, lane, x);
-    const float a = wave_max(ak_thread_max(x));
+    const float a = dpp_max(ak_thread_max(x));
     if (lane == 0) sm.fmx[0][wave] = a;
     __syncthreads();
     float mx = sm.fmx[0][0];
 #pragma unroll
     for (int k = 1; k < AK_WAVES; ++k) mx = fmaxf(mx, sm.fmx[0][k]);
-    ak_exp_inplace<UNIT_T>(x, mx, 1.0 / (double)T);
+    ak_exp_inplace<UNIT_T>(x, mx, exp_scale(1.0 / (double)T));
     for (int c = 0; c < nch; ++c) {
         const double Z = ak_totals(x, sm, 0, wave, lane);
         const float u = philox_uniform(seed, seq, round, (uint32_t)(ch[c] - 1), 2u);
@@ -2638,10 +2675,10 @@ __device__ __forceinline__ void ak_scale(float (&x)[AK_CH][4], double Z) {
 
 // x <- softmax(row / T) as fp32 probabilities
 template <bool UNIT_T>
-__device__ __forceinline__ void ak_normalised(const float* __restrict__ row, int V, double invT, float (&x)[AK_CH][4], AkShared& sm, int wave,
+__device__ __forceinline__ void ak_normalised(const float* __restrict__ row, int V, const ExpScale& invT, float (&x)[AK_CH][4], AkShared& sm, int wave,
                                               int lane) {
     ak_load(row, V, wave, lane, x);
-    const float a = wave_max(ak_thread_max(x));
+    const float a = dpp_max(ak_thread_max(x));
     __syncthreads();
     if (lane == 0) sm.fmx[0][wave] = a;
     __syncthreads();
@@ -2664,7 +2701,7 @@ __device__ __forceinline__ void accept_tree_node_body(const float* __restrict__ 
                                                       uint32_t round, const TreeShape& ts, int2* __restrict__ step, AkShared& sm,
                                                       float* pick) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const double invT = 1.0 / (double)T;
+    const ExpScale invT = exp_scale(1.0 / (double)T);
     const int cur = blockIdx.x;
     float xp[AK_CH][4], xq[AK_CH][4];
     int ch[TREE_RANKS];

@@ -77,6 +77,20 @@ def test_accept_shapes_and_temperatures(V, rows, gamma, T):
     assert r["ties"] <= 2
 
 
+@pytest.mark.parametrize("V", [8192, 8196, 16384, 16388, 24580])
+@pytest.mark.parametrize("T", [0.0, 0.7, 1.0])
+def test_accept_at_the_edges_of_the_vocabulary_quarters(V, T):
+    """One to four workgroups per position, the last with as little as four values; 31 positions (every bit of the mask)."""
+    g = torch.Generator(device="cuda").manual_seed(V)
+    gamma = 31 if V == 8196 else 3
+    P = torch.randn((2, gamma + 1, V), generator=g, device="cuda") * 2
+    Q = (P[:, :gamma] + 0.3 * torch.randn((2, gamma, V), generator=g, device="cuda")).contiguous()
+    Q[:, 1] = P[:, 1]                                       # p == q: always accepted
+    P[0, 0, : V - 4] = torch.finfo(torch.float32).min      # all mass in the last four values, the rest masked with the lowest value
+    r = check_accept(P, Q, T, seed=3, rnd=2)
+    assert r["ties"] <= 2
+
+
 def test_accept_greedy_and_degenerate_rows():
     V, gamma, rows = 1000, 4, 16
     g = torch.Generator(device="cuda").manual_seed(5)
