@@ -1090,20 +1090,24 @@ __device__ __forceinline__ void rope_kv_body(const float* __restrict__ part, int
 }
 
 // Token embedding and rotation table of a block in one launch: h[r][:] = E[tok[r]][:], and (first hd/2
-// threads of row r's workgroup) tab[r][i] = (cos, sin)((pos0 + r) * theta^(-2i/hd)).   grid (m), block 256
+// threads of the last wavefront of row r's workgroup) tab[r][i] = (cos, sin)((pos0 + r) * theta^(-2i/hd)).   grid (m), block 320
 template <typename T>
 __global__ void embed_rope_kernel(const int32_t* __restrict__ tok, const T* __restrict__ E, int d, float* __restrict__ h, int pos0,
                                   int hd, float theta, double2* __restrict__ tab, TreeBlk tb) {
-    const int r = blockIdx.x, i = threadIdx.x, half = hd >> 1;
-    const size_t t = (size_t)tok[r];
-    for (int k = i; k < d; k += blockDim.x) h[(size_t)r * d + k] = El<T>::ld(E[t * d + k]);
-    if (i < half) {
+    const int r = blockIdx.x, half = hd >> 1;
+    if (threadIdx.x >= 256) {                      // the 64-bit power, sine and cosine run beside the trips for token and row
+        const int i = (int)threadIdx.x - 256;
+        if (i >= half) return;
         const double freq = pow((double)theta, -2.0 * (double)i / (double)hd);
         const int pos = tb.on == 1 ? tb.base + (int)tb.depth[tb.i0 + r] : pos0 + r;     // a tree node is rotated for its depth, not its slot
         double sn, cs;
         sincos((double)pos * freq, &sn, &cs);
         tab[r * half + i] = make_double2(cs, sn);
+        return;
     }
+    const size_t t = (size_t)tok[r];
+#pragma unroll 4
+    for (int k = (int)threadIdx.x; k < d; k += 256) h[(size_t)r * d + k] = El<T>::ld(E[t * d + k]);
 }
 
 template <typename T>
@@ -1127,7 +1131,7 @@ template <typename T, int HD>
 __device__ __forceinline__ void attn_partial_body(const float* __restrict__ q, const T* __restrict__ kc,
                                                   const T* __restrict__ vc, int m, int pos0, int H, int KH, int max_ctx,
                                                   float scale, float* __restrict__ part, int nchunks, int c, int h,
-                                                  const TreeBlk* tb = nullptr) {
+                                                  const TreeBlk* tb = nullptr, float* direct = nullptr) {
     constexpr int EPV = 16 / (int)sizeof(T);     // elements per 16-byte piece
     constexpr int RS = HD + EPV;                 // padded LDS row stride (elements)
     constexpr int VPR = HD / EPV;                // 16-byte pieces per row
@@ -1145,15 +1149,27 @@ __device__ __forceinline__ void attn_partial_body(const float* __restrict__ q, c
     const int np = min(ATT_CH, L - p0);
     const int tid = threadIdx.x;
 
+    // the chunk's K and V rows are requested together, ahead of everything (rows past the end re-read the last one)
+    constexpr int PCS = ATT_CH * VPR / 256;
+    uint4 kreg[PCS], vreg[PCS];
+    const T* kbase = kc + ((size_t)kh * max_ctx + p0) * HD;
+    const T* vbase = vc + ((size_t)kh * max_ctx + p0) * HD;
+#pragma unroll
+    for (int u = 0; u < PCS; ++u) kreg[u] = *reinterpret_cast<const uint4*>(kbase + (size_t)min(tid + u * 256, np * VPR - 1) * EPV);
     for (int idx = tid; idx < m * HD; idx += 256) {
         const int r = idx / HD, i = idx - r * HD;
         qs[idx] = q[(size_t)r * H * HD + (size_t)h * HD + i];
     }
-    const T* kbase = kc + ((size_t)kh * max_ctx + p0) * HD;
-    for (int idx = tid; idx < np * VPR; idx += 256) {
-        const int p = idx / VPR, v = idx - p * VPR;
-        *reinterpret_cast<uint4*>(kv + p * RS + v * EPV) = *reinterpret_cast<const uint4*>(kbase + (size_t)p * HD + v * EPV);
-    }
+#pragma unroll
+    for (int u = 0; u < PCS; ++u) vreg[u] = *reinterpret_cast<const uint4*>(vbase + (size_t)min(tid + u * 256, np * VPR - 1) * EPV);
+    auto stage = [&](const uint4 (&x)[PCS]) {
+#pragma unroll
+        for (int u = 0; u < PCS; ++u) {
+            const int idx = tid + u * 256, p = idx / VPR, v = idx - p * VPR;
+            if (p < np) *reinterpret_cast<uint4*>(kv + p * RS + v * EPV) = x[u];
+        }
+    };
+    stage(kreg);
     __syncthreads();
 
     {   // scores: thread = (position p, row half rh); 8 rows per thread
@@ -1205,11 +1221,7 @@ __device__ __forceinline__ void attn_partial_body(const float* __restrict__ q, c
     }
     __syncthreads();   // all reads of the K tile are done
 
-    const T* vbase = vc + ((size_t)kh * max_ctx + p0) * HD;
-    for (int idx = tid; idx < np * VPR; idx += 256) {
-        const int p = idx / VPR, v = idx - p * VPR;
-        *reinterpret_cast<uint4*>(kv + p * RS + v * EPV) = *reinterpret_cast<const uint4*>(vbase + (size_t)p * HD + v * EPV);
-    }
+    stage(vreg);
     __syncthreads();
 
     constexpr int G = 256 / HD;   // position groups
@@ -1235,9 +1247,10 @@ __device__ __forceinline__ void attn_partial_body(const float* __restrict__ q, c
         float s = 0.f;
 #pragma unroll
         for (int gg = 0; gg < G; ++gg) s += red[(gg * 16 + r) * HD + cc];
-        dst[r * (HD + 2) + cc] = s;
+        if (direct) direct[(size_t)r * H * HD + (size_t)h * HD + cc] = s / lrow[r];     // the only chunk: what the merge would leave
+        else dst[r * (HD + 2) + cc] = s;
     }
-    if (tid < m) {
+    if (!direct && tid < m) {
         dst[tid * (HD + 2) + HD] = mrow[tid];
         dst[tid * (HD + 2) + HD + 1] = lrow[tid];
     }
@@ -1246,15 +1259,17 @@ __device__ __forceinline__ void attn_partial_body(const float* __restrict__ q, c
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restrict__ q, const T* __restrict__ kc,
                                                            const T* __restrict__ vc, int m, int pos0, int H, int KH,
-                                                           int max_ctx, float scale, float* __restrict__ part, int nchunks) {
-    attn_partial_body<T, HD>(q, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x, (int)blockIdx.y);
+                                                           int max_ctx, float scale, float* __restrict__ part, int nchunks,
+                                                           float* __restrict__ direct) {
+    attn_partial_body<T, HD>(q, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x, (int)blockIdx.y, nullptr, direct);
 }
 // the same for a tree block (row r = node tb.i0 + r in slot pos0 + r)
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void attn_partial_tree_kernel(const float* __restrict__ q, const T* __restrict__ kc,
                                                                 const T* __restrict__ vc, int m, int pos0, int H, int KH,
-                                                                int max_ctx, float scale, float* __restrict__ part, int nchunks, TreeBlk tb) {
-    attn_partial_body<T, HD>(q, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x, (int)blockIdx.y, &tb);
+                                                                int max_ctx, float scale, float* __restrict__ part, int nchunks, TreeBlk tb,
+                                                                float* __restrict__ direct) {
+    attn_partial_body<T, HD>(q, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x, (int)blockIdx.y, &tb, direct);
 }
 
 // Source of a block's fresh q / k / v when the attention kernel forms them itself (no rope_kv_kernel launch): the split-K
@@ -1875,6 +1890,7 @@ __device__ __forceinline__ void ak_search(const float (&w)[AK_CH][4], const doub
     double cb = base;
 #pragma unroll
     for (int c = 0; c < AK_CH; ++c) {
+        if (wave * AK_SEG + c * 256 >= V) break;             // wave-uniform
         const double ct = dpp_sum((double)ak_chunk_sum(w, c));
         if (ct > 0.0) clast = c;
         if (cstar < 0 && !take_last) {
@@ -2194,6 +2210,7 @@ __device__ __forceinline__ bool as_search(const float (&w)[AS_CH][4], const doub
         double cb = wbase;
 #pragma unroll
         for (int c = 0; c < AS_CH; ++c) {
+            if (q * AS_QSEG + wave * AS_WSEG + c * 256 >= V) break;             // wave-uniform
             const double ct = dpp_sum((double)((w[c][0] + w[c][1]) + (w[c][2] + w[c][3]))) * scale;
             if (ct > 0.0) clast = c;
             if (cstar < 0 && !take_last) {

@@ -22,6 +22,7 @@
 #include "prefill.h"
 #include "gemm_tiles.h"
 #include "step.h"
+#include "step_f32.h"
 
 using namespace msd;
 
@@ -773,14 +774,17 @@ int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool com
                                   (const float*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale,
                                   c->d_apart(), nchunks);
     } else {
+        // a context of one chunk needs no merge (fp32: nothing but the division is left of it)
+        float* direct = sizeof(T) == 4 && combine && nchunks == 1 ? (float*)c->d_ao() : nullptr;
+        if (direct) combine = false;
         if (c->tree)
             hipExtLaunchKernelGGL((attn_partial_tree_kernel<T, HD>), dim3(nchunks, d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u,
                                   (const float*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale,
-                                  c->d_apart(), nchunks, *c->tree);
+                                  c->d_apart(), nchunks, *c->tree, direct);
         else
             hipExtLaunchKernelGGL((attn_partial_kernel<T, HD>), dim3(nchunks, d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u,
                                   (const float*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale,
-                                  c->d_apart(), nchunks);
+                                  c->d_apart(), nchunks, direct);
     }
     LAUNCH_CHECK(c, "attn_partial");
     if (!combine) return 0;
@@ -808,7 +812,7 @@ template <typename T>
 int embed_rows(metasd_ctx* c, Model& M, int pos0, int m, float* h) {
     const metasd_model_desc& d = M.d;
     const int D = d.d_model;
-    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, c->stream, c->d_hist() + pos0, (const T*)M.w[0], D, h, pos0, M.hd, d.rope_theta,
+    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, c->stream, c->d_hist() + pos0, (const T*)M.w[0], D, h, pos0, M.hd, d.rope_theta,
                        c->d_rope(), c->tree ? *c->tree : TreeBlk{});
     LAUNCH_CHECK(c, "embed + rope table");
     if (!M.head) return 0;
@@ -877,6 +881,59 @@ int forward_rows(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int fi
             return rc;
     }
     return 0;
+}
+
+// fp32 models of narrow rows (step_f32.h): five launches per layer instead of ten, six when the context has more than one chunk.
+bool f32_step_ok(const Model& M) { return M.d.dtype == METASD_F32 && M.d.d_model <= STEP_F32_K; }
+
+template <int NF, bool NORM, int EPI>
+int launch_f32_step(metasd_ctx* c, const F32Args& a, const char* what) {
+    const dim3 grid((a.units + 3) / 4);
+    const uint32_t lds = NORM ? (uint32_t)(a.m * a.K * 4) : 0u;
+    if (a.m <= 1) hipLaunchKernelGGL((gemm_f32_step_kernel<1, NF, NORM, EPI>), grid, dim3(256), lds, c->stream, a);
+    else if (a.m <= 4) hipLaunchKernelGGL((gemm_f32_step_kernel<4, NF, NORM, EPI>), grid, dim3(256), lds, c->stream, a);
+    else if (a.m <= 8) hipLaunchKernelGGL((gemm_f32_step_kernel<8, NF, NORM, EPI>), grid, dim3(256), lds, c->stream, a);
+    else hipLaunchKernelGGL((gemm_f32_step_kernel<16, NF, NORM, EPI>), grid, dim3(256), lds, c->stream, a);
+    LAUNCH_CHECK(c, what);
+    return 0;
+}
+
+int forward_rows_f32(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int first_row) {
+    typedef float T;
+    const metasd_model_desc& d = M.d;
+    const int D = d.d_model, H = d.n_heads, KH = d.n_kv_heads, hd = M.hd, F = d.d_ffn;
+    float* h = c->d_h();
+    int rc;
+    if ((rc = embed_rows<T>(c, M, pos0, m, h))) return rc;
+    F32Args base{};
+    base.eps = d.rms_eps; base.m = m;
+    base.tab = (const double2*)c->d_rope(); base.pos0 = pos0; base.H = H; base.KH = KH; base.hd = hd; base.max_ctx = c->cfg.max_ctx;
+    for (int L = 0; L < d.n_layers; ++L) {
+        const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
+        auto W = [&](int i) { return (const float*)M.layer_w(L, i); };
+        F32Args a = base;                           // q, and k and v in the cache
+        a.x = h; a.gain = W(0); a.W0 = W(1); a.W1 = W(2); a.W2 = W(3); a.K = D;
+        a.out = (float*)c->d_q(); a.ldo = H * hd; a.units = (H + 2 * KH) * (hd / 2);
+        a.kc = (float*)M.kv + (size_t)L * 2 * plane; a.vc = a.kc + plane;
+        if ((rc = launch_f32_step<2, true, F32_ROPE>(c, a, "gemm_f32 (q, k, v)"))) return rc;
+        if ((rc = attention<T>(c, M, L, pos0, m))) return rc;
+        a = base;                                   // h += output projection
+        a.x = (const float*)c->d_ao(); a.W0 = W(4); a.K = H * hd; a.out = h; a.ldo = D; a.units = D;
+        if ((rc = launch_f32_step<1, false, F32_ADD>(c, a, "gemm_f32 (output)"))) return rc;
+        a = base;                                   // activation of the FFN
+        a.x = h; a.gain = W(5); a.K = D; a.out = (float*)c->d_act(); a.ldo = F; a.units = F;
+        if (d.act == METASD_SWIGLU) { a.W0 = W(6); a.W1 = W(7); rc = launch_f32_step<2, true, F32_ACT>(c, a, "gemm_f32 (gate, up)"); }
+        else { a.W0 = W(7); rc = launch_f32_step<1, true, F32_ACT>(c, a, "gemm_f32 (up)"); }
+        if (rc) return rc;
+        a = base;                                   // h += down projection
+        a.x = (const float*)c->d_act(); a.W0 = W(8); a.K = F; a.out = h; a.ldo = D; a.units = D;
+        if ((rc = launch_f32_step<1, false, F32_ADD>(c, a, "gemm_f32 (down)"))) return rc;
+    }
+    if (!logits) return 0;
+    F32Args a = base;
+    a.x = h + (size_t)first_row * D; a.m = m - first_row; a.gain = (const float*)M.final_norm(); a.W0 = (const float*)M.lm_head();
+    a.K = D; a.out = logits; a.ldo = d.vocab; a.units = d.vocab;
+    return launch_f32_step<1, true, F32_OUT>(c, a, "gemm_f32 (head)");
 }
 
 // bf16 models, general case: the two projections into the residual stream reduce their split-K partials
@@ -957,7 +1014,7 @@ int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, 
     const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV;
     hipStream_t st = c->stream;
     int hp = 0, rc;                     // current residual buffer
-    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, st, c->d_hist() + pos0, (const T*)M.w[0], D, c->d_h_pp(0), pos0, hd,
+    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, st, c->d_hist() + pos0, (const T*)M.w[0], D, c->d_h_pp(0), pos0, hd,
                        d.rope_theta, c->d_rope(), c->tree ? *c->tree : TreeBlk{});
     LAUNCH_CHECK(c, "embed + rope table");
     auto norm_in = [&](const void* gain, int row0) {
@@ -1094,7 +1151,8 @@ int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool
         const bool is_target = &M == &c->target;
         // the short-block path never writes the finished residual rows: not for the target when its features are wanted
         const bool fused = c->fuse_small && fused_small_ok(M, m) && !(is_target && c->cfg.feature_heads);
-        if (M.d.dtype != METASD_BF16) rc = forward_rows<float>(c, M, pos0 + done, m, lg, first_row);
+        if (c->fuse_small && f32_step_ok(M)) rc = forward_rows_f32(c, M, pos0 + done, m, lg, first_row);
+        else if (M.d.dtype != METASD_BF16) rc = forward_rows<float>(c, M, pos0 + done, m, lg, first_row);
         else if (fused && !M.head) rc = forward_rows_fused(c, M, pos0 + done, m, lg, first_row);       // (the others carry the head's input projection)
         else if (c->fuse_small && M.d.d_model >= STEP_DMIN && step_ok(m, M.d.d_model)) rc = forward_rows_step(c, M, pos0 + done, m, lg, first_row);
         else if (c->gemm_reduce) rc = forward_rows_residual(c, M, pos0 + done, m, lg, first_row);
@@ -1372,7 +1430,7 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
     for (int done = 0; done < n;) {
         const int m = std::min(big_rows(c->cfg), n - done), p0 = pos0 + done, split = rows_split(m);
         int ns = 0, rc;
-        hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(256), 0, st, c->d_hist() + (size_t)seq * c->cfg.max_ctx + p0, (const T*)M.w[0], D,
+        hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, st, c->d_hist() + (size_t)seq * c->cfg.max_ctx + p0, (const T*)M.w[0], D,
                            h, p0, hd, d.rope_theta, c->d_rope(), TreeBlk{});
         LAUNCH_CHECK(c, "embed + rope table");
         if (M.head) {   // W_fc . [embedding ; the target's feature of the position before]
