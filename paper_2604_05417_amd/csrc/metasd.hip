@@ -1154,7 +1154,9 @@ int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool
         if (c->fuse_small && f32_step_ok(M)) rc = forward_rows_f32(c, M, pos0 + done, m, lg, first_row);
         else if (M.d.dtype != METASD_BF16) rc = forward_rows<float>(c, M, pos0 + done, m, lg, first_row);
         else if (fused && !M.head) rc = forward_rows_fused(c, M, pos0 + done, m, lg, first_row);       // (the others carry the head's input projection)
-        else if (c->fuse_small && M.d.d_model >= STEP_DMIN && step_ok(m, M.d.d_model)) rc = forward_rows_step(c, M, pos0 + done, m, lg, first_row);
+        // (a switch that names one of the split-K forms of the residual projections asks for the path that has them)
+        else if (c->fuse_small && c->gemm_reduce && c->fullk_roll && M.d.d_model >= STEP_DMIN && step_ok(m, M.d.d_model))
+            rc = forward_rows_step(c, M, pos0 + done, m, lg, first_row);
         else if (c->gemm_reduce) rc = forward_rows_residual(c, M, pos0 + done, m, lg, first_row);
         else rc = forward_rows<bf16_t>(c, M, pos0 + done, m, lg, first_row);
         if (rc) return rc;
