@@ -183,7 +183,7 @@ def main():
 
     rg, ra, rc = roof(pg), roof(pa), roof(pc)
     # dominant kernels: the bf16 weight-streaming GEMMs
-    dom, dom_name = rg, "gemm_bf16_kernel<*> + gemm_fullk_residual_kernel + gemm_fullk_roll_residual_kernel (weight-streaming GEMMs)"
+    dom, dom_name = rg, "gemm_step_kernel<*> + gemm_bf16_kernel<*> + gemm_fullk_*_residual_kernel (weight-streaming GEMMs)"
     roofline = {"bound": "hbm", "kernel": dom_name, "achieved": dom["GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": dom["GBs"] / HBM_PEAK_GBS, "traffic": read_traffic(),
                 "avg_launch_us": dom["avg_us"], "algorithmic_bytes_per_launch": dom["bytes_per_launch"],
