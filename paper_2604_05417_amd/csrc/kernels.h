@@ -1809,17 +1809,22 @@ __device__ __forceinline__ float ak_exp(float a) {
 // exp((x - mx) / T).  T = 1: the fp32 difference is the correctly rounded argument.  Otherwise the difference is multiplied by
 // log2(e) / T held as two floats, one rounding more than the difference's own.  (Largest and rms error against 64 bits, T = 0.7:
 // 5.4e-6 and 1.39e-6; with the argument scaled in 64 bits and rounded twice, as before, 7.2e-6 and 1.46e-6 and four more instructions.)
-struct ExpScale { float hi, lo; };
+// Any T > 0: where the argument is below -200 the result is 0 whatever the low term adds, so the difference is held at `floor` there
+// and the low term stays finite - masked entries (-inf, the lowest float) and the lanes past the vocabulary would else give -inf + inf
+// from T of about 1e-16 down.  The scale is held at the largest float (T of 4e-39 and less, where any difference of more than 1e-36
+// gives 0), or the largest entry would be 0 * inf.
+struct ExpScale { float hi, lo, floor; };
 __device__ __forceinline__ ExpScale exp_scale(double invT) {
-    const double c = invT * 1.4426950408889634074;
+    constexpr double FMAX = 3.4028234663852886e38;
+    const double c = fmin(invT * 1.4426950408889634074, FMAX);
     const float hi = (float)c;
-    return ExpScale{hi, (float)(c - (double)hi)};
+    return ExpScale{hi, (float)(c - (double)hi), (float)fmax(-200.0 / c, -FMAX)};
 }
 template <bool UNIT_T>
 __device__ __forceinline__ float ak_expx(float x, float mx, const ExpScale& k) {
     const float t = x - mx;
     if constexpr (UNIT_T) return ak_exp(t);
-    else return __builtin_amdgcn_exp2f(fmaf(t, k.hi, fmaxf(t, -1e30f) * k.lo));   // masked logits give 0: the low term stays finite
+    else return __builtin_amdgcn_exp2f(fmaf(t, k.hi, fmaxf(t, k.floor) * k.lo));
 }
 
 __device__ __forceinline__ void ak_load(const float* __restrict__ row, int V, int wave, int lane, float (&x)[AK_CH][4]) {

@@ -91,6 +91,25 @@ def test_accept_at_the_edges_of_the_vocabulary_quarters(V, T):
     assert r["ties"] <= 2
 
 
+@pytest.mark.parametrize("split", ["1", "0"])
+@pytest.mark.parametrize("T", [1e-3, 1e-15, 3e-17, 1.3e-20, 1e-30, 1e-39, 1.4e-45, 1e30])
+def test_accept_and_sampling_at_temperatures_far_from_one(T, split, monkeypatch):
+    """Down to the smallest float the law is the one of the 64-bit oracle: entries masked with -inf or the lowest float, and the lanes
+    past a vocabulary that ends inside a wavefront's piece, carry no mass; two equal largest logits share it; upwards (1e30) only
+    -inf masks.  Between them T = 3e-17, 1.3e-20 and 1e-30 are ones where log2(e) / T rounds up to its float (a negative low term)."""
+    monkeypatch.setenv("METASD_ACCEPT_SPLIT", split)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    V, gamma, rows = 32000, 4, 3
+    P = torch.randn((rows, gamma + 1, V), generator=g, device="cuda") * 2
+    Q = (P[:, :gamma] + 0.5 * torch.randn((rows, gamma, V), generator=g, device="cuda")).contiguous()
+    Q[:, 1] = P[:, 1]                                       # p == q: always accepted
+    P[0, :, 100:], Q[0, :, 50: V - 8] = -float("inf"), -float("inf")
+    P[1, :, : V - 4], Q[1, 2:, 8:] = torch.finfo(torch.float32).min, torch.finfo(torch.float32).min
+    P[2, 0, 5] = P[2, 0, 31000] = 50.0                      # two largest: half of the mass each
+    r = check_accept(P, Q, T, seed=3, rnd=2)
+    assert r["ties"] <= 2
+
+
 def test_accept_greedy_and_degenerate_rows():
     V, gamma, rows = 1000, 4, 16
     g = torch.Generator(device="cuda").manual_seed(5)

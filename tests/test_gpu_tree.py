@@ -317,6 +317,20 @@ def test_fp32_sampled_tree_rounds(kind, temp):
     g.close()
 
 
+def test_fp32_sampled_tree_rounds_at_a_temperature_near_zero():
+    """T = 3e-17 (a negative low term of log2(e) / T; the vocabulary of 512 leaves most lanes of the workgroup past its end): the
+    sampled rounds are the greedy ones, and the output is the target's own greedy continuation."""
+    cfg = W.config1_tree()
+    g, ls = make(cfg, Tree(**W.draft_tree("chain5")), 1e-4, temp=3e-17)
+    n = len(cfg["prompt"])
+    while ls.st.l < n + 24:
+        ls.round(ls.st.t % 3)
+    assert ls.stats["ties"] == 0, ls.stats
+    ref = oracle.ar_decode(oracle.Model(cfg["target"][0], W.to_numpy(cfg["target"][1]), cfg["max_ctx"]), cfg["prompt"], 24, T=0.0)
+    assert np.array_equal(ls.st.hist[n: n + 24], ref)
+    g.close()
+
+
 def test_bf16_sampled_tree_rounds():
     """Sampled tree rounds on a small bf16 target (head_dim 128: the MFMA attention kernel with the tree mask): the GPU's
     draws and walk are the oracle's on the GPU's own logits, logits within the bf16 tolerance, arms forced so that a
