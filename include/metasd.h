@@ -126,7 +126,11 @@ typedef struct {
  * sequence b's cache starting b * bytes into the buffer). */
 int32_t metasd_kv_bytes(const metasd_model_desc* m, int32_t max_ctx, size_t* bytes_out);
 
-/* Bytes of device workspace metasd_create needs for this configuration. */
+/* Bytes of device workspace metasd_create needs for this configuration.  Models in bf16 with head_dim 64 or 128 take long
+ * prompts and backlogs in blocks of up to min(2048, max_ctx) rows, and most of the workspace is the rows of such a block (per
+ * row about 4 * (4 d_model + d_ffn + widest projection) bytes, the widest being 2 d_ffn with SwiGLU): 0.42 GB for the 7B shape
+ * (d_model 4096, d_ffn 11008) and 0.28 GB for the 1B shape (2048, 8192) from max_ctx 2048 on, whether caches are prefilled
+ * by the caller or not. */
 int32_t metasd_workspace_bytes(const metasd_config* cfg, const metasd_model_desc* target,
                                const metasd_model_desc* drafters /*[K]*/, size_t* bytes_out);
 

@@ -228,7 +228,7 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
     L.inv = take(64);
     L.q = take(RM * dmax * 4);
     L.ao = take(RM * dmax * 4);
-    L.act = take(RM * fmax * 4 * 2);          // also the fused gate | up result
+    L.act = take(RM * std::max(fmax, c.feature_heads ? 2 * dmax : 0) * 4);   // a drafter head's input rows, 2 d wide, are staged here too
     L.apart = take(B * hmax * nchunks * 16 * (hdmax + 2) * 4);
     L.rope = take(RM * (hdmax / 2) * sizeof(double2));
     L.P = take(B * (c.gamma_max + 1) * vmax * 4);

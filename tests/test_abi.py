@@ -63,7 +63,17 @@ def test_sizes_and_validation(lib):
     assert lib.metasd_workspace_bytes(C.byref(heads), C.byref(desc()), dr, C.byref(n)) == 0
     d_model = desc().d_model
     assert (96 + 16) * d_model * 4 <= n.value - one <= (96 + 16) * d_model * 4 + 2 * 256
-    heads.batch = 2
+    # .. and, only then, what a head's input rows [rows][2 d_model] need beyond the activations [rows][d_ffn] (prompts of up to 300 rows go
+    # through in one block)
+    square = dict(dtype=1, d_model=512, n_heads=8, n_kv_heads=8, d_ffn=544, act=1)
+    drs = (B._Desc * 3)(*[desc(n_layers=1, **square) for _ in range(3)])
+    heads.max_ctx, heads.feature_heads = 300, 0
+    assert lib.metasd_workspace_bytes(C.byref(heads), C.byref(desc(**square)), drs, C.byref(n)) == 0
+    plain, heads.feature_heads = n.value, 1
+    assert lib.metasd_workspace_bytes(C.byref(heads), C.byref(desc(**square)), drs, C.byref(n)) == 0
+    extra = (300 + 16) * 512 * 4 + 300 * (2 * 512 - 544) * 4
+    assert extra <= n.value - plain <= extra + 3 * 256
+    heads.max_ctx, heads.batch = 96, 2
     assert lib.metasd_workspace_bytes(C.byref(heads), C.byref(desc()), dr, C.byref(n)) == -1
     heads.batch, heads.feature_heads = 1, 2
     assert lib.metasd_workspace_bytes(C.byref(heads), C.byref(desc()), dr, C.byref(n)) == -1
