@@ -166,6 +166,19 @@ const char* check_model(const metasd_model_desc& d, const char* who, char* buf, 
 bool big_ok(const metasd_model_desc& d) { return d.dtype == METASD_BF16 && d.d_model / d.n_heads >= 64; }
 int big_rows(const metasd_config& c) { return std::min(BIG_ROWS, c.max_ctx); }
 
+// Whether n rows (more than MAX_ROWS) from position pos0 on are faster through forward_big than in blocks of 16, which nseq sequences
+// share.  Few rows leave attn_prefill_kernel one workgroup per head, which walks all positions before it: 1.2 (head_dim 64) or 2.4 us
+// per 64 positions and layer but the last, where the 16-row kernels deal the positions out over the chip (0.16 us).  Otherwise a layer
+// takes its weights' time (7 TB/s) and 26 us against 55 us per 16-row block.  Draft step after 17 rows at context 8000, big / small:
+// 768 x 12 heads of 64 288 / 264 us, 2048 x 16 heads of 128 490 / 357, 4096 x 32 703 / 607; 36 rows 293 / 414, 497 / 539, 717 / 910;
+// 17 rows at context 2000 177 / 217, 267 / 292, 455 / 501.  From position 0 the big block always wins.
+bool big_pays(const metasd_model_desc& d, int pos0, int n, int nseq) {
+    const double hd = d.d_model / d.n_heads, D = d.d_model, walk = (pos0 + n) / 64.0;
+    const double w = (2 * D * D + 2 * D * d.n_kv_heads * hd + (d.act == METASD_SWIGLU ? 3 : 2) * D * d.d_ffn) * 2 / 7e6;
+    const double small = (double)n / (MAX_ROWS * nseq) * (55 + w + 0.16 * walk);
+    return small >= 26 + w + 1.2 * hd / 64 * walk * (d.n_layers - 1) / d.n_layers;
+}
+
 // Word the split-K siblings of a residual GEMM set when their bounded wait for each other runs out (read back with
 // the results of every accept).
 struct GridBar { int abort; int pad[3]; };
@@ -1137,9 +1150,10 @@ int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool
     c->cur_model = model_index(c, M);
     if (pos0 + n > c->cfg.max_ctx) return c->fail(METASD_E_OVERFLOW, "positions %d..%d exceed max_ctx %d", pos0, pos0 + n, c->cfg.max_ctx);
     int done = 0;
-    // long blocks: everything but the row that carries logits (and a last handful of rows) goes through in big blocks
-    if (big_ok(M.d) && !c->tree && n - (logits ? 1 : 0) > MAX_ROWS) {
-        done = n - (logits ? 1 : 0);
+    // long blocks: everything but the row that carries logits goes through in big blocks
+    const int rows = n - (logits ? 1 : 0);
+    if (big_ok(M.d) && !c->tree && rows > MAX_ROWS && big_pays(M.d, pos0, rows, 1)) {
+        done = rows;
         if (int rc = forward_big(c, M, 0, pos0, done)) return rc;
     }
     while (done < n) {
@@ -1721,7 +1735,7 @@ int draft_batch(metasd_ctx* c, const int32_t* k, int gamma) {
     for (int b = 0; b < B; ++b) {
         Model& D = c->drafters[k[b]];
         const int pend = c->sq[b].l - D.kvl[b], nseq = (int)std::count(k, k + B, k[b]);
-        if (big_ok(D.d) && pend > MAX_ROWS && pend > MAX_ROWS * nseq)
+        if (big_ok(D.d) && pend > MAX_ROWS && pend > MAX_ROWS * nseq && big_pays(D.d, D.kvl[b], pend - 1, nseq))
             if (int rc = forward_big(c, D, b, D.kvl[b], pend - 1)) return rc;
     }
     for (int j = 0; j < gamma; ++j) {

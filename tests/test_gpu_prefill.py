@@ -8,7 +8,8 @@ import torch
 import paper_2604_05417_amd as M
 import workloads as W
 from test_gpu_batch import batch_pair, make_lockstep
-from test_gpu_bf16 import run_lockstep
+from lockstep import LockStep
+from test_gpu_bf16 import oracle_models, run_lockstep
 
 pytestmark = pytest.mark.gpu
 TOL = 3e-2
@@ -110,6 +111,34 @@ def test_rounds_after_a_long_prefill_and_drafter_catch_up(n):
     cfg["gamma"], cfg["max_ctx"] = 4, n + 60
     st = run_lockstep(cfg, 1.0, rounds=4, kv_prefilled=False)
     assert st["max_dp"] <= TOL and st["max_dq"] <= TOL and st["ties_shared"] <= 1, st
+
+
+@pytest.mark.parametrize("ctx,idle,big", [(600, 2, True), (3000, 2, False), (3000, 3, True)])
+def test_short_backlog_at_a_long_context(ctx, idle, big):
+    """A drafter that was idle for `idle` rounds of nine tokens returns: its 18 or 27 unseen rows go through in one block, or, where the
+    context is long against them, in blocks of 16 (one block walks 3000 positions with two workgroups).  Drafters are copies of the
+    target with the same K/V, so that every draft token is accepted."""
+    desc = W.model_desc(2, 256, 2, 2, 512, 528, W.SWIGLU, W.BF16)
+    w = W.gen_weights(desc, 0)
+    cfg = dict(target=(desc, w), drafters=[(desc, w), (desc, w)], max_ctx=ctx + 64)
+    g = M.MetaSD((desc, w), cfg["drafters"], gamma_max=8, max_ctx=cfg["max_ctx"], temperature=0.0, seed=1)
+    ot, od = oracle_models(cfg)
+    kv = W.kv_fill(desc, ctx - 1, 7, device="cuda")
+    for i, t in enumerate(kv):
+        for gpu, om in zip([g.kv_target] + g.kv_drafters, [ot] + od):
+            gpu[:, i, :, : ctx - 1] = t
+            om.kv(i)[:, :, : ctx - 1] = t.float().cpu().numpy()
+    prompt = W.prompt_tokens(ctx, desc["vocab"], 3)
+    g.set_context(prompt, kv_prefilled=True)
+    ls = LockStep(g, ot, od, prompt, 8, 0.0, 1, 1.0, logit_tol=TOL, kv_prefilled=True)
+    for _ in range(idle):
+        ls.round(0)
+    assert ls.l == ctx + 9 * idle
+    g.profile(512)
+    ls.round(1)
+    rows = max(x["m"] for x in g.profile_shapes(target_only=False))      # of the GEMM launches of this round
+    assert rows == (9 * idle if big else 16), rows
+    g.close()
 
 
 def test_ragged_batch_with_long_drafter_backlogs():
