@@ -16,6 +16,8 @@ SHAPES = [
     ((2048, 32, 8, 1024, W.SWIGLU, 1040), (2048, 16, 8192, W.SWIGLU), 2),  # widest rows and d_ffn the short path takes
     ((512, 4, 4, 33024, W.SWIGLU, 512), (256, 4, 288, W.SWIGLU), 5),      # more pairs of tiles than one pass of 256 workgroups
     ((3072, 24, 24, 4096, W.SWIGLU, 1024), (128, 2, 160, W.SWIGLU), 7),   # 8 rows of 3072: four float4 columns and more per lane
+    ((4096, 32, 8, 1024, W.SWIGLU, 512), (128, 2, 160, W.SWIGLU), 7),     # 8 rows of 4096: all eight columns, the most LDS it takes
+    ((4224, 33, 11, 1024, W.SWIGLU, 512), (128, 2, 160, W.SWIGLU), 7),    # 8 rows of 4224 do not fit: verified on the split-K path
 ]
 
 
