@@ -113,12 +113,14 @@ Split choose_split(int m, int ntiles, int kchunks) {
 // Many-row GEMM (gemm_tiles.h; more than 16 rows): workgroup tile (64 rb rows x 2 tb feature tiles, ns stages of LDS) and K
 // split.  The launch runs in rounds of 256 workgroups.  Measured on the 7B and 1B projections at 20 .. 1499 rows: a stage of
 // 32 inputs takes 0.115 + 0.044 rb tb us (within 5 % from 4 to 24 products: 0.29 us for 1 x 4, 0.64 for 2 x 6, 1.19 for 3 x 8),
-// a launch 5 us more; few rows are bound by the weight stream, 5.6 TB/s; the partials are written and read once at 5 TB/s.
+// a launch 5 us more whatever
+// the plan (left out of the cost); few rows are bound by the weight stream, 5.6 TB/s; the partials are written and read once at 5 TB/s.
 // A split whose partials exceed PARTIALS_MAX never pays (50 us of traffic).
 struct RowsPlan { int rb, tb, ksplit, cps, nrb, ngroups; };
 constexpr size_t PARTIALS_MAX = (size_t)128 << 20;
 constexpr int ROWS_TILES[][2] = {{4, 6}, {3, 8}, {3, 6}, {3, 4}, {2, 8}, {2, 6}, {2, 4}, {2, 3}, {1, 8}, {1, 6}, {1, 4}, {1, 2}};
-// Stages of LDS of a tile: three to seven within 160 KiB, and four for the smallest so that several workgroups share a CU.
+// Stages of LDS of a tile: three of 40 KiB and more, else four or six (144 KiB at most); four for the two smallest, so that several
+// workgroups share a CU.
 constexpr int rows_stages(int rb, int tb) {
     return rb * 8 + tb * 2 >= 40 ? 3 : rb * 8 + tb * 2 >= 28 || (rb == 2 && tb == 4) || (rb == 1 && tb <= 4) ? 4 : 6;
 }
@@ -1016,7 +1018,9 @@ int forward_rows_residual(metasd_ctx* c, Model& M, int pos0, int m, float* logit
 constexpr int fused_max_rows() { return 4; }
 bool fused_small_ok(const Model& M, int m) {
     const metasd_model_desc& d = M.d;
-    constexpr int dmax = 2048;      // four rows of d_ffn <= 8192 inputs are 128 KiB of LDS, eight float4 per thread of d_model
+    // d_model: the gate | up form that adds the output projection's partials exists for two float4 columns per lane, which at four rows
+    // is 2048.  d_ffn: no launch needs the limit; it is the widest FFN these blocks were measured with, wider ones take forward_rows_step.
+    constexpr int dmax = 2048;
     return d.dtype == METASD_BF16 && m <= fused_max_rows() && d.d_model <= dmax && d.d_ffn <= 4 * dmax && M.hd >= 64;
 }
 
@@ -1163,7 +1167,8 @@ int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool
         const int first_row = want_all ? 0 : m - 1;
         int rc;
         const bool is_target = &M == &c->target;
-        // the short-block path never writes the finished residual rows: not for the target when its features are wanted
+        // the short-block path may leave the finished rows in the second residual buffer, which the feature copy below does not read: not
+        // for the target when its features are wanted
         const bool fused = c->fuse_small && fused_small_ok(M, m) && !(is_target && c->cfg.feature_heads);
         if (c->fuse_small && f32_step_ok(M)) rc = forward_rows_f32(c, M, pos0 + done, m, lg, first_row);
         else if (M.d.dtype != METASD_BF16) rc = forward_rows<float>(c, M, pos0 + done, m, lg, first_row);

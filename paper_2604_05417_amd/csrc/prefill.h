@@ -4,18 +4,12 @@
 
 namespace msd {
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-// two floats -> two bf16 (round to nearest even) in one word, element 0 in the low half: one hardware instruction
-__device__ __forceinline__ uint32_t cvt_bf16x2(float a, float b) {
-    const bf16x2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, v);
-}
 // the two-term form of a pair: hi = bf16(x), lo = bf16(x - hi)
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& hi, uint32_t& lo) {
-    hi = cvt_bf16x2(a, b);
-    lo = cvt_bf16x2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
+    hi = f2bf2(a, b);
+    lo = f2bf2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
 }
 // Transposing LDS read: the 16 lanes of a group give the addresses of a 4 x 16 block of 16-bit elements (lane i: row i / 4,
 // columns 4 (i % 4) .. + 3); lane i receives column i (rows 0 .. 3).

@@ -13,7 +13,8 @@ namespace msd {
 //   STEP_ACT    out = SiLU(gate) * up or GELU(up) as two bf16 arrays; with SwiGLU units 2 j and 2 j + 1 are gate and up of 16 features
 // What bounds it: bytes of weights per CU at about 25 GB/s, and the chain launch - input - multiply - LDS - store in front of and behind
 // them (2.9 us for a kernel that does nothing else with one wide workgroup per CU, 4.5 us with 256 threads).  So the input is requested
-// first and the first 4 or 8 KiB of weights per wavefront (64 - 128 KiB per CU) before it is waited for.  The hi and lo term of a row
+// first and the first group of weights before it is waited for: per wavefront 4 or 8 KiB with STEP_NORM, 4 with STEP_TERMS, 3 with half
+// tiles (48 - 128 KiB per CU).  The hi and lo term of a row
 // are columns r and 8 + r of one MFMA operand: one multiply per KiB instead of two.
 // HALF: a unit is half a feature tile (8 features), so that a projection of d_model features has enough units for all CUs: one load
 // brings the 8 features of two neighbouring chunks, multiplied with the inputs of either one (two MFMAs, each good for 8 of its rows).

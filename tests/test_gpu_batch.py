@@ -157,8 +157,8 @@ def test_bf16_batches_span_the_gemm_variants(B, i):
 
 @pytest.mark.parametrize("rows", [(11, 6), (20, 7), (32, 8)])
 def test_bf16_wide_blocks(rows):
-    """More rows than one 64-row workgroup tile holds: 11 x 7 = 77 rows (128-row variant), 20 x 8 = 160 rows
-    (256-row variant) and the largest batch, 32 x 9 = 288 rows (two passes of the 256-row variant); real prefill."""
+    """More rows than one 64-row block: 11 x 7 = 77 rows, 20 x 8 = 160 rows and the largest batch, 32 x 9 = 288 rows (more than one
+    block of the tallest tile); real prefill."""
     B, gamma = rows
     s = SMALL[0]
     cfg = W.config4(n_layers=2, ctx=140, n_new=64, K=2, d_model=s["d_model"], n_heads=s["n_heads"], d_ffn=s["d_ffn"], vocab=s["vocab"],
@@ -176,10 +176,10 @@ def test_bf16_wide_blocks(rows):
     g.close()
 
 
-@pytest.mark.parametrize("tpb", [4, 6, 12])
+@pytest.mark.parametrize("tpb", [4, 6, 12, 16])
 def test_bf16_wide_blocks_other_tile_counts(tpb, monkeypatch):
-    """The 256-row GEMM variant with 4, 6 and 12 feature tiles per workgroup (12: the form whose activations go straight from memory into LDS) (the cost model picks them for the 7B shapes;
-    here forced at context creation): 20 x 8 = 160 rows, tile counts that are no multiple of 4 or 6 (ragged last group)."""
+    """The many-row GEMM with 4, 6, 12 and 16 feature tiles per workgroup, forced at context creation (the cost model decides otherwise; its
+    rows per workgroup stay free): 20 x 8 = 160 rows, tile counts that are no multiple of any of them (ragged last group)."""
     monkeypatch.setenv("METASD_ROWS_TPB", str(tpb))
     s = SMALL[0]
     cfg = W.config4(n_layers=2, ctx=140, n_new=64, K=2, d_model=s["d_model"], n_heads=s["n_heads"], d_ffn=s["d_ffn"], vocab=s["vocab"],
