@@ -1815,10 +1815,11 @@ __device__ __forceinline__ float ak_exp(float a) {
 // gives 0), or the largest entry would be 0 * inf.
 struct ExpScale { float hi, lo, floor; };
 __device__ __forceinline__ ExpScale exp_scale(double invT) {
-    constexpr double FMAX = 3.4028234663852886e38;
-    const double c = fmin(invT * 1.4426950408889634074, FMAX);
+    constexpr float FMAX = 3.4028234663852886e38f;
+    const double c = fmin(invT * 1.4426950408889634074, (double)FMAX);
     const float hi = (float)c;
-    return ExpScale{hi, (float)(c - (double)hi), (float)fmax(-200.0 / c, -FMAX)};
+    // (the reciprocal is 0 for the largest scales, whose low term is then left out: only differences that give 0 would see it)
+    return ExpScale{hi, (float)(c - (double)hi), fmaxf(-200.f * __builtin_amdgcn_rcpf(hi), -FMAX)};
 }
 template <bool UNIT_T>
 __device__ __forceinline__ float ak_expx(float x, float mx, const ExpScale& k) {
