@@ -15,9 +15,10 @@ namespace msd {
 // reads); then the tiles as they are.
 //   The wavefronts of a SIMD (w and w + 4) take turns: while 0-3 multiply a stage from registers, 4-7 read theirs from LDS, and
 // the other way round, one barrier between two turns; neither the fragment reads nor the waits for them stand between MFMAs.
-//   What bounds it: from about 500 rows on the power limit - 1.15 to 1.28 PFLOP/s (both terms counted) on the 7B projections
-// with random values, where this machine's library GEMM reaches 0.7 to 1.2 on the same shapes and 1.33 to 1.5 on 8192 .. 16384
-// cubes (all-zero operands: 1.5 and 2.1).  Measured against the kernel it replaces (256 rows per launch, weights in registers): 1499
+//   What bounds it: from about 500 rows on its own turns and, behind them, power.  1.14 to 1.27 PFLOP/s (both terms counted) on the 7B
+// projections with random values, the MFMAs busy 53 - 58 % of the cycles (1499 rows; 44 % at 256, 15 - 46 % on the 1B shapes at 511,
+// whose grids fill the chip once); with zero weights 1.34 to 1.51, the clock 2.40 instead of 2.24 GHz.  This machine's library GEMM
+// reaches 0.7 to 1.2 on the same shapes and 1.33 to 1.5 on 8192 .. 16384 cubes.  Measured against the kernel it replaces (256 rows per launch, weights in registers): 1499
 // rows, one 7B layer 1586 -> 990 us; 256 rows QKV 54 -> 47, output 29 -> 20, gate|up 90 -> 80, down 52 -> 44 us; 20 rows of the 1B
 // shape gate|up 21.4 -> 15.
 //   Workgroup ids are dealt out so that the row blocks of one feature group run on one XCD one after the other (its L2 then

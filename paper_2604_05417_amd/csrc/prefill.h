@@ -26,11 +26,12 @@ __device__ __forceinline__ s16x4 lds_read_tr(const bf16_t* p) {
 //                             that held S^T: an MFMA sums over k in whatever order its two operands agree on, so slot 8 g + j
 //                             of a 32-position chunk stands for position 4 g + j (j < 4) or 16 + 4 g + j - 4, which is where
 //                             the lanes of group g already hold the scores.
-// What bounds it: the MFMAs (two terms for q and for P, 4 per 16 x 16 x 32 block) and the LDS reads of K and V, which RB = 2
-// halves per row (one tile of K and V feeds 32 rows of a wavefront).  The next tile is requested into registers while the
+// What bounds it: the chain of a tile - barrier, scores, maximum, exponentials, products - with two workgroups of a CU to cover it:
+// MFMAs busy 13 % of the cycles (5 % at 511 rows), wavefronts waiting half of them.  RB = 2 halves the LDS reads of K and V per row
+// (one tile feeds 32 rows of a wavefront).  The next tile is requested into registers while the
 // current one is multiplied.  Heads are dealt out over the 8 XCDs (workgroup id mod 8) so that the row blocks of one head share
-// that XCD's L2, the longest row blocks first.  Measured: 1499 rows x 32 heads of 128: 124 us per layer (18.4 GFLOP causal, twice
-// that with the second terms: 0.3 PFLOP/s), where 94 passes of the 16-row kernels took 94 x (7 + 5) us; 511 rows x 32 heads of
+// that XCD's L2, the longest row blocks first.  Measured: 1499 rows x 32 heads of 128: 113 us per layer (18.4 GFLOP causal, twice
+// that with the second terms: 0.33 PFLOP/s), where 94 passes of the 16-row kernels took 94 x (7 + 5) us; 511 rows x 32 heads of
 // 64 on 8 KV heads: 12.8 us.
 //   grid (ceil(m / (64 RB)) * H), block 256.   out: [m][H HD] as two bf16 terms (split: see store_terms4).
 template <int HD, int RB>
