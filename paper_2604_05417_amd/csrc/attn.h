@@ -1,0 +1,268 @@
+// Attention of short blocks (at most 16 rows of a sequence) over a bf16 cache with head_dim 64 or 128; included after kernels.h,
+// batch.h and prefill.h.
+#pragma once
+
+namespace msd {
+
+// One workgroup of 4 wavefronts per (span of positions, query heads, sequence).  The rows of hp query heads that share a K/V head
+// (hp m <= 16) are the columns of one MFMA operand, so K and V are read once for all of them.  A wavefront walks its sub-blocks of 32
+// positions (every fourth of the span) on its own, with a running (maximum, sum, O) per row and no barrier:
+//   S^T[pos][row] = K . q^T    A = K rows straight from the cache, B = q as two bf16 terms
+//   O^T[hd][row] += V^T . P^T  A = V rows staged in a private piece of LDS and read transposed, B = P as two bf16 terms straight from the
+//                              registers that held S^T (slot 8 g + j of the 32 positions stands for 4 g + j or 16 + 4 g + j - 4)
+// K and V of the next sub-block are requested as soon as the registers of the current one are free (16 KiB per wavefront at head_dim
+// 128, up to 192 KiB per CU); at the end the wavefronts merge through LDS.  One record per workgroup, merged by attn_combine_kernel; a
+// span that is the whole context needs no merge and the workgroup writes the rows itself.
+// What bounds it: HBM (6.6 TB/s with 1024 workgroups or more), for short contexts the chain request - scores - products - merge.
+// Measured beside the kernel it replaced (one chunk of 128 positions per workgroup, V staged behind two workgroup barriers and gathered
+// element by element), with the merge: 32 heads of 128, 6 rows, 2054 positions 15.5 -> 11.8 us; 12 rows, 8012 positions 42.0 -> 26.1 us
+// (8 records per head instead of 63); 32 sequences of 2056 positions (1.05 GB) 211 -> 160 us.
+constexpr int ATT_NW = 4;
+template <int HD>
+struct AttnShared {
+    static constexpr int RSV = HD + 16;                // V row stride (elements)
+    __align__(16) bf16_t v[ATT_NW][32 * RSV];          // .. and at the end the O tile of each wavefront
+    float mx[ATT_NW][16], sum[ATT_NW][16];
+};
+
+struct AttnOut {
+    float* part;       // records [head][nrec][16][HD + 2] (O, maximum, sum per row) of the sequence
+    int nrec, rec;
+    float* out;        // nrec == 1: the rows [.][H HD] as two bf16 terms instead (split: see store_terms4)
+    int split;
+    size_t lo_off;     // elements of the whole block
+    int row0, rows;    // first row of the sequence in out and rows to write (past m: padding, copies of the last one)
+};
+
+// q: rows of this sequence (lo terms q_lo elements behind the hi terms); h0: first of hp query heads; kb / vb: K and V rows of their K/V
+// head; sub-blocks s0 .. s1 - 1.  SHARED: other workgroups read the same K and V rows.
+template <int HD, bool SHARED>
+__device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __restrict__ q, size_t q_lo, int H, int h0, int hp,
+                                          const bf16_t* __restrict__ kb, const bf16_t* __restrict__ vb, int m, int pos0, float scale, int s0, int s1,
+                                          const AttnOut& ao, const TreeBlk* tb) {
+    constexpr int KC = HD / 32, NT = HD / 16, VPR = HD / 8, VIT = 32 * VPR / 64, RSV = AttnShared<HD>::RSV;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, g = lane >> 4, L = pos0 + m;
+    const bool colok = col < hp * m;
+    const int hh = colok ? col / m : hp - 1, row = colok ? col - hh * m : m - 1;      // columns past the last one repeat it
+    u32x4 qh[KC], ql[KC];
+    {
+        const bf16_t* src = q + ((size_t)row * H + h0 + hh) * HD + g * 8;
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            qh[k] = *reinterpret_cast<const u32x4*>(src + k * 32);
+            ql[k] = *reinterpret_cast<const u32x4*>(src + q_lo + k * 32);
+        }
+    }
+    auto next = [&](int s) {                           // streaming caches: sub-blocks no row attends to are passed over
+        if (tb && tb->on == 2)
+            while (s < s1 && stream_skips(*tb, s * 32, 32, pos0)) s += ATT_NW;
+        return s;
+    };
+    u32x4 kf[2][KC], vr[VIT];
+    // byte offsets of 32 bits against uniform bases; positions past the end re-read the last one: their weight is zero
+    auto request_k = [&](int s) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t at = (uint32_t)min(s * 32 + t * 16 + col, L - 1) * (HD * 2) + g * 16;
+#pragma unroll
+            for (int k = 0; k < KC; ++k) kf[t][k] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(kb) + at + k * 64);
+        }
+    };
+    auto request_v = [&](int s) {
+#pragma unroll
+        for (int it = 0; it < VIT; ++it) {
+            const uint32_t at = (uint32_t)min(s * 32 + it * (64 / VPR) + lane / VPR, L - 1) * (HD * 2) + (lane % VPR) * 16;
+            const u32x4* vp = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(vb) + at);
+            vr[it] = SHARED ? *vp : __builtin_nontemporal_load(vp);
+        }
+    };
+    f32x4 o[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mx = -INFINITY, sum = 0.f;
+    constexpr float L2E = 1.44269504088896341f;
+    bf16_t* vs = sm.v[wave];
+    int s = next(s0 + wave);
+    if (s < s1) { request_k(s); request_v(s); }
+    while (s < s1) {
+        const int p0 = s * 32, sn = next(s + ATT_NW), sq = min(sn, s1 - 1);    // past the end the last sub-block is requested: no branch around requests
+        f32x4 sc[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll
+            for (int k = 0; k < KC; ++k) {
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t][k]), __builtin_bit_cast(bf16x8, qh[k]), a, 0, 0, 0);
+                b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t][k]), __builtin_bit_cast(bf16x8, ql[k]), b, 0, 0, 0);
+            }
+            sc[t] = a + b;
+        }
+        request_k(sq);
+        float tm = -INFINITY;
+        const bool edge = tb || p0 + 32 > pos0;        // some row may not see all 32 positions
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float x = sc[t][v] * scale;
+                if (edge) {
+                    const int p = p0 + t * 16 + g * 4 + v;
+                    const bool see = tb ? tree_allowed(*tb, p, row, pos0) : p <= pos0 + row;
+                    x = see && p < L ? x : -INFINITY;
+                }
+                sc[t][v] = x;
+                tm = fmaxf(tm, x);
+            }
+        tm = fmaxf(tm, __shfl_xor(tm, 16, 64));
+        tm = fmaxf(tm, __shfl_xor(tm, 32, 64));
+        const float nm = fmaxf(mx, tm), base = nm == -INFINITY ? 0.f : nm;
+        const float alpha = __builtin_amdgcn_exp2f((mx - base) * L2E);
+        mx = nm;
+        float part = 0.f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float e = __builtin_amdgcn_exp2f((sc[t][v] - base) * L2E);
+                sc[t][v] = e;
+                part += e;
+            }
+        sum = sum * alpha + part;
+        uint4 ph, pl;
+        split_pair(sc[0][0], sc[0][1], ph.x, pl.x);
+        split_pair(sc[0][2], sc[0][3], ph.y, pl.y);
+        split_pair(sc[1][0], sc[1][1], ph.z, pl.z);
+        split_pair(sc[1][2], sc[1][3], ph.w, pl.w);
+#pragma unroll
+        for (int it = 0; it < VIT; ++it)
+            *reinterpret_cast<u32x4*>(vs + (lane / VPR) * RSV + (lane % VPR) * 8 + it * (64 / VPR) * RSV) = vr[it];
+        request_v(sq);
+        asm volatile("" ::: "memory");                 // a wavefront's own LDS accesses are carried out in program order
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const bf16_t* src = vs + (4 * g + (col >> 2)) * RSV + t * 16 + (col & 3) * 4;
+            const s16x4 a0 = lds_read_tr(src), a1 = lds_read_tr(src + 16 * RSV);
+            const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+            o[t] *= alpha;
+            o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, ph), o[t], 0, 0, 0);
+            o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, pl), o[t], 0, 0, 0);
+        }
+        asm volatile("" ::: "memory");
+        s = sn;
+    }
+    // ---- merge the wavefronts
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    if (g == 0) { sm.mx[wave][col] = mx; sm.sum[wave][col] = sum; }
+    constexpr int OS = HD + 4;
+    float* ow = reinterpret_cast<float*>(vs);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4*>(ow + col * OS + t * 16 + 4 * g) = o[t];
+    __syncthreads();
+    const int rows = ao.nrec == 1 ? ao.rows : m;
+    for (int i = tid; i < hp * rows * (HD / 4); i += ATT_NW * 64) {
+        const int hr = i / (HD / 4), c4 = (i - hr * (HD / 4)) * 4, hi = hr / rows, r = hr - hi * rows, c = hi * m + min(r, m - 1), h = h0 + hi;
+        float M = sm.mx[0][c];
+#pragma unroll
+        for (int w = 1; w < ATT_NW; ++w) M = fmaxf(M, sm.mx[w][c]);
+        f32x4 y = {0.f, 0.f, 0.f, 0.f};
+        float tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < ATT_NW; ++w) {
+            const float f = sm.mx[w][c] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((sm.mx[w][c] - M) * L2E);
+            y += *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(sm.v[w]) + c * OS + c4) * f;
+            tot += sm.sum[w][c] * f;
+        }
+        if (ao.nrec == 1) {
+            store_terms4(ao.out, ao.split, ao.lo_off, ((size_t)(ao.row0 + r) * H + h) * HD + c4, make_float4(y[0] / tot, y[1] / tot, y[2] / tot, y[3] / tot));
+        } else {
+            float* dst = ao.part + (((size_t)h * ao.nrec + ao.rec) * 16 + r) * (HD + 2);
+            *reinterpret_cast<float2*>(dst + c4) = make_float2(y[0], y[1]);
+            *reinterpret_cast<float2*>(dst + c4 + 2) = make_float2(y[2], y[3]);
+            if (c4 == 0) *reinterpret_cast<float2*>(dst + HD) = make_float2(M, tot);
+        }
+    }
+}
+
+// The workgroups of a launch: item = (sequence, record, group of query heads).  Groups that share a K/V head and a span are 8 workgroup
+// ids apart and so on one XCD, whose L2 they share.
+struct AttnItem { int s, rec, h0, kh; };
+__device__ __forceinline__ bool attn_item(int id, int nseg, int nrec, int H, int KH, int hp, AttnItem& it) {
+    const int gph = H / (KH * hp), x = id & 7, j = id >> 3, u = (j / gph) * 8 + x, gi = j % gph;     // u: (sequence, K/V head, record)
+    if (u >= nseg * KH * nrec) return false;
+    it.rec = u % nrec;
+    it.kh = u / nrec % KH;
+    it.s = u / (nrec * KH);
+    it.h0 = it.kh * (H / KH) + gi * hp;
+    return true;
+}
+
+// A block of one sequence; spw sub-blocks per workgroup.   grid: attn_grid, block 256
+template <int HD, bool TREE, bool SHARED>
+__global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc,
+                                                                            const bf16_t* __restrict__ vc, int m, int pos0, int H, int KH, int hp,
+                                                                            int max_ctx, float scale, int spw, AttnOut ao, TreeBlk tb) {
+    __shared__ AttnShared<HD> sm;
+    AttnItem it;
+    if (!attn_item(blockIdx.x, 1, ao.nrec, H, KH, hp, it)) return;     // workgroup-uniform
+    const size_t at = (size_t)it.kh * max_ctx * HD;
+    ao.rec = it.rec;
+    attn_body<HD, SHARED>(sm, q, (size_t)m * H * HD, H, it.h0, hp, kc + at, vc + at, m, pos0, scale, it.rec * spw,
+                          min((pos0 + m + 31) >> 5, (it.rec + 1) * spw), ao, TREE ? &tb : nullptr);
+}
+
+// Blocks of several sequences: K and V planes of segment s at kc.p[s], vc.p[s] (PTRS) or kv_seq_stride elements per sequence behind
+// kc0, vc0; q_lo: elements of the whole block's q.  The records of a segment follow those of the one before.
+template <int HD, bool SHARED, bool PTRS>
+__global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_seg_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc0,
+                                                                                const bf16_t* __restrict__ vc0, size_t kv_seq_stride, SegPtrs kc,
+                                                                                SegPtrs vc, Segs sg, int H, int KH, int hp, int max_ctx, float scale,
+                                                                                size_t q_lo, int spw, AttnOut ao) {
+    __shared__ AttnShared<HD> sm;
+    AttnItem it;
+    if (!attn_item(blockIdx.x, sg.n, ao.nrec, H, KH, hp, it)) return;  // workgroup-uniform
+    const int s = it.s, m = sg.m[s], pos0 = sg.pos0[s], nsub = (pos0 + m + 31) >> 5;
+    if (it.rec * spw >= nsub) return;
+    const size_t at = (size_t)it.kh * max_ctx * HD, so = (size_t)sg.seq[s] * kv_seq_stride;
+    ao.rec = it.rec;
+    ao.part += (size_t)s * H * ao.nrec * 16 * (HD + 2);
+    ao.row0 = s * sg.ms;
+    ao.rows = sg.ms;
+    attn_body<HD, SHARED>(sm, q + (size_t)s * sg.ms * H * HD, q_lo, H, it.h0, hp, (PTRS ? static_cast<const bf16_t*>(kc.p[s]) : kc0 + so) + at,
+                          (PTRS ? static_cast<const bf16_t*>(vc.p[s]) : vc0 + so) + at, m, pos0, scale, it.rec * spw, min(nsub, (it.rec + 1) * spw),
+                          ao, nullptr);
+}
+
+// How a block is split.  hp: as many query heads of a K/V head as fit into 16 rows.  Records per head: none to merge (one workgroup sees
+// the whole context) where that fills the CUs - 32 sequences x 32 heads 160 us against 180 + 10 with three records, 8 x 32 heads 43
+// against 47 + 4 - or where the context is short (up to 128 KiB of K and V per workgroup: 5 sequences of 333 positions, 32 heads of 64,
+// 6.0 us against 5.4 + 2.8); otherwise up to 8, the most the merge takes in its shortest form, each a whole number of passes of its
+// wavefronts (65 sub-blocks x 32 heads: 6 records of 3 passes 11.8 us, 8 of 2.25 12.4), and two passes where that still gives half the
+// CUs a workgroup (3 sequences of 500 positions: 11.5 against 13.7 us).  Up to 16 where few heads walk a long context (12 heads x 8012
+// positions: 11.6 against 13.1 us).
+struct AttnPlan { int hp, spw, nrec, grid; };
+inline AttnPlan plan_attn(int nseg, int H, int KH, int hd, int m, int max_len, int n_cu, int force_passes) {
+    AttnPlan p{};
+    const int G = H / KH;
+    p.hp = 1;
+    for (int t = 2; t <= G && t * m <= 16; ++t)
+        if (G % t == 0) p.hp = t;
+    const int nsub = (max_len + 31) / 32, wgs = nseg * (H / p.hp);
+    auto passes_of = [&](int records) { return (nsub + ATT_NW * records - 1) / (ATT_NW * records); };
+    int passes = force_passes;
+    if (passes <= 0) {
+        if (wgs >= n_cu || (size_t)max_len * hd * 4 <= 128 * 1024) passes = passes_of(1);
+        else {
+            passes = passes_of(std::min(8, (3 * n_cu / 2 + wgs - 1) / wgs));
+            if (passes == 1 && wgs * ((nsub + 2 * ATT_NW - 1) / (2 * ATT_NW)) >= n_cu / 2) passes = 2;
+            if (passes > 4 && wgs * 8 <= n_cu / 2) passes = passes_of(16);
+        }
+    }
+    p.spw = ATT_NW * passes;
+    p.nrec = (nsub + p.spw - 1) / p.spw;
+    p.grid = 8 * ((nseg * KH * p.nrec + 7) / 8) * (G / p.hp);
+    return p;
+}
+
+}  // namespace msd

@@ -1619,13 +1619,6 @@ __device__ __forceinline__ void attn_partial_mfma_body(const float* __restrict__
     }
 }
 
-template <int HD>
-__global__ __launch_bounds__(256) void attn_partial_mfma_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kc,
-                                                                const bf16_t* __restrict__ vc, int m, int pos0, int H, int KH,
-                                                                int max_ctx, float scale, float* __restrict__ part, int nchunks) {
-    attn_partial_mfma_body<HD>(q, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x, (int)blockIdx.y,
-                               (size_t)m * H * HD);
-}
 // The same with q and the block's own K / V rows formed from the QKV projection's partial sums (tb.on selects the tree mask).
 template <int HD>
 __global__ __launch_bounds__(256, 3) void attn_partial_mfma_qkv_kernel(QkvIn qi, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
@@ -1634,15 +1627,6 @@ __global__ __launch_bounds__(256, 3) void attn_partial_mfma_qkv_kernel(QkvIn qi,
     attn_partial_mfma_body<HD, false, true>(nullptr, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x,
                                             (int)blockIdx.y, 0, 1, 0, tb.on ? &tb : nullptr, &qi);
 }
-template <int HD>
-__global__ __launch_bounds__(256) void attn_partial_mfma_tree_kernel(const float* __restrict__ q, const bf16_t* __restrict__ kc,
-                                                                     const bf16_t* __restrict__ vc, int m, int pos0, int H, int KH,
-                                                                     int max_ctx, float scale, float* __restrict__ part, int nchunks,
-                                                                     TreeBlk tb) {
-    attn_partial_mfma_body<HD>(q, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x, (int)blockIdx.y,
-                               (size_t)m * H * HD, 1, 0, &tb);
-}
-
 // Merge of the chunk records of (head h, block row r): nchunks records are merged, records of one head are
 // nch_stride chunks apart; the result goes to row r_out of out (split: as two bf16 terms, 1: arrays lo_off elements apart, 2: interleaved).
 template <int HD>

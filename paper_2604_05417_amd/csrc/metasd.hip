@@ -20,6 +20,7 @@
 #include "kernels.h"
 #include "batch.h"
 #include "prefill.h"
+#include "attn.h"
 #include "gemm_tiles.h"
 #include "step.h"
 #include "step_f32.h"
@@ -450,7 +451,7 @@ struct metasd_ctx {
     bool prof_on = false;
     bool fullk = true;               // residual GEMMs whose input fits in LDS run without split-K (METASD_GEMM_FULLK=0: off)
     bool grouped_on = true;          // batched drafting: one forward per step for all arms (METASD_DRAFT_GROUPED=0: one per arm)
-    int att_cpw = 0;                 // batched attention: chunks per workgroup, 0 = by the rule in attention_seg_hd (METASD_ATT_CPW=1..64 forces one)
+    int att_cpw = 0;                 // attention of short blocks: passes of 128 positions per workgroup, 0 = plan_attn (METASD_ATT_CPW=1..64 forces them)
     int rows_tpb = 0;                // many-row GEMM: feature tiles per workgroup, 0 = by the cost model (METASD_ROWS_TPB=4|6|8|12|16 forces one)
     int rows_rb = 0;                 // .. and its rows in units of 64 (METASD_ROWS_RB=1..4)
     struct { int ntiles, kchunks, R, groups; RowsPlan plan; } plans[64] = {};   // rows_plan
@@ -775,19 +776,24 @@ int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool com
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * (double)(pos0 + m) * HD * sizeof(T) +
                                                                  (double)m * d.n_heads * HD * 4);
     hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
+    int nrec = nchunks;
     if constexpr (sizeof(T) == 2 && HD >= 64) {
-        if (qi)
+        if (qi) {
             hipExtLaunchKernelGGL((attn_partial_mfma_qkv_kernel<HD>), dim3(nchunks, d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u, *qi,
                                   kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, c->d_apart(), nchunks,
                                   c->tree ? *c->tree : TreeBlk{});
-        else if (c->tree)
-            hipExtLaunchKernelGGL((attn_partial_mfma_tree_kernel<HD>), dim3(nchunks, d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u,
-                                  (const float*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale,
-                                  c->d_apart(), nchunks, *c->tree);
-        else
-            hipExtLaunchKernelGGL((attn_partial_mfma_kernel<HD>), dim3(nchunks, d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u,
-                                  (const float*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale,
-                                  c->d_apart(), nchunks);
+        } else {
+            const AttnPlan pl = plan_attn(1, d.n_heads, d.n_kv_heads, HD, m, pos0 + m, c->n_cu, c->att_cpw);
+            const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), 1, (size_t)m * d.n_heads * HD, 0, m};
+            nrec = pl.nrec;
+            if (nrec == 1) combine = false;
+#define ATTN_GO(TREE, SHARED) hipExtLaunchKernelGGL((attn_kernel<HD, TREE, SHARED>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, (const bf16_t*)c->d_q(), \
+                                                    kc, vc, m, pos0, d.n_heads, d.n_kv_heads, pl.hp, c->cfg.max_ctx, scale, pl.spw, ao, c->tree ? *c->tree : TreeBlk{})
+            const bool shared = d.n_heads > d.n_kv_heads * pl.hp;
+            if (c->tree) { if (shared) ATTN_GO(true, true); else ATTN_GO(true, false); }
+            else { if (shared) ATTN_GO(false, true); else ATTN_GO(false, false); }
+#undef ATTN_GO
+        }
     } else {
         // a context of one chunk needs no merge (fp32: nothing but the division is left of it)
         float* direct = sizeof(T) == 4 && combine && nchunks == 1 ? (float*)c->d_ao() : nullptr;
@@ -803,7 +809,7 @@ int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool com
     }
     LAUNCH_CHECK(c, "attn_partial");
     if (!combine) return 0;
-    hipLaunchKernelGGL((attn_combine_kernel<T, HD>), dim3(d.n_heads, m), dim3(HD), 0, c->stream, c->d_apart(), nchunks,
+    hipLaunchKernelGGL((attn_combine_kernel<T, HD>), dim3(d.n_heads, m), dim3(HD), 0, c->stream, c->d_apart(), nrec,
                        d.n_heads, (float*)c->d_ao(), sizeof(T) == 2 ? 1 : 0);
     LAUNCH_CHECK(c, "attn_combine");
     return 0;
@@ -1293,40 +1299,37 @@ int attention_seg_hd(metasd_ctx* c, const Model& M, int L, const Segs& sg) {
     const size_t seq_stride = (size_t)M.kv_layers * 2 * plane;
     const T* kc = (const T*)M.kv + (size_t)L * 2 * plane;
     const T* vc = kc + plane;
-    int nch_max = 1;
+    int max_len = 1;
     double kvpos = 0.0;
     for (int s = 0; s < sg.n; ++s) {
-        nch_max = std::max(nch_max, (sg.pos0[s] + sg.m[s] + ATT_CH - 1) / ATT_CH);
+        max_len = std::max(max_len, sg.pos0[s] + sg.m[s]);
         kvpos += (double)(sg.pos0[s] + sg.m[s]);
     }
+    const int nch_max = (max_len + ATT_CH - 1) / ATT_CH;
     const float scale = 1.0f / sqrtf((float)HD);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * kvpos * HD * sizeof(T) + (double)R * d.n_heads * HD * 4);
     hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
-    int cpw = 1;                       // chunks per workgroup (bf16 MFMA kernel): fewer, larger records while the grid still fills the chip
+    int nrec = nch_max, passes = 1;
     if constexpr (sizeof(T) == 2 && HD >= 64) {
-        // Measured at 32 sequences x 4096 positions (7B shape, head_dim 128): 391 + 53 us (partial + merge) with one chunk per
-        // workgroup, 380 + 10 us with eight; with head_dim 64 the chunks are too small for the loop to pay (37 -> 51 us).
-        if (HD >= 128)
-            for (int t = 8; t >= 2 && cpw == 1; t /= 2)
-                if ((size_t)d.n_heads * sg.n * ((nch_max + t - 1) / t) >= (size_t)c->n_cu * 4) cpw = t;
-        if (c->att_cpw > 0) cpw = c->att_cpw;
-        const dim3 grid((nch_max + cpw - 1) / cpw, d.n_heads, sg.n);
-        if (cpw > 1)
-            hipExtLaunchKernelGGL((attn_partial_mfma_seg_kernel<HD, true>), grid, dim3(256), 0u, c->stream, ea, eb, 0u, (const float*)c->d_q(), kc,
-                                  vc, seq_stride, sg, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, c->d_apart(), nch_max,
-                                  (size_t)R * d.n_heads * HD, cpw);
-        else
-            hipExtLaunchKernelGGL((attn_partial_mfma_seg_kernel<HD, false>), grid, dim3(256), 0u, c->stream, ea, eb, 0u, (const float*)c->d_q(), kc,
-                                  vc, seq_stride, sg, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, c->d_apart(), nch_max,
-                                  (size_t)R * d.n_heads * HD, cpw);
+        const AttnPlan pl = plan_attn(sg.n, d.n_heads, d.n_kv_heads, HD, sg.ms, max_len, c->n_cu, c->att_cpw);
+        const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), rows_split(R), (size_t)R * d.n_heads * HD, 0, 0};
+        nrec = pl.nrec;
+        passes = pl.spw / ATT_NW;
+#define ATTN_GO(SHARED) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, false>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, (const bf16_t*)c->d_q(), \
+                                              kc, vc, seq_stride, SegPtrs{}, SegPtrs{}, sg, d.n_heads, d.n_kv_heads, pl.hp, c->cfg.max_ctx, scale, \
+                                              (size_t)R * d.n_heads * HD, pl.spw, ao)
+        if (d.n_heads > d.n_kv_heads * pl.hp) ATTN_GO(true);
+        else ATTN_GO(false);
+#undef ATTN_GO
+        if (nrec == 1) { LAUNCH_CHECK(c, "attn (segments)"); return 0; }
     } else {
         hipExtLaunchKernelGGL((attn_partial_seg_kernel<T, HD>), dim3(nch_max, d.n_heads, sg.n), dim3(256), 0u, c->stream, ea, eb, 0u,
                               (const float*)c->d_q(), kc, vc, seq_stride, sg, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale,
                               c->d_apart(), nch_max);
     }
     LAUNCH_CHECK(c, "attn_partial (segments)");
-    hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(d.n_heads, R), dim3(HD), 0, c->stream, c->d_apart(), nch_max, d.n_heads,
-                       (float*)c->d_ao(), sizeof(T) == 2 ? rows_split(R) : 0, sg, cpw);
+    hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(d.n_heads, R), dim3(HD), 0, c->stream, c->d_apart(), nrec, d.n_heads,
+                       (float*)c->d_ao(), sizeof(T) == 2 ? rows_split(R) : 0, sg, passes);
     LAUNCH_CHECK(c, "attn_combine (segments)");
     return 0;
 }
@@ -1585,12 +1588,14 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
     LAUNCH_CHECK(c, "embed (grouped)");
     hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope());
     LAUNCH_CHECK(c, "rope_table (segments)");
-    int nch_max = 1;
+    int max_len = 1;
     double kvpos = 0.0;
     for (int s = 0; s < sg.n; ++s) {
-        nch_max = std::max(nch_max, (sg.pos0[s] + sg.m[s] + ATT_CH - 1) / ATT_CH);
+        max_len = std::max(max_len, sg.pos0[s] + sg.m[s]);
         kvpos += (double)(sg.pos0[s] + sg.m[s]);
     }
+    const AttnPlan pl = plan_attn(sg.n, H, KH, HD, sg.ms, max_len, c->n_cu, c->att_cpw);
+    const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), 2, (size_t)R * H * HD, 0, 0};
     const float scale = 1.0f / sqrtf((float)HD);
     for (int L = 0; L < d.n_layers; ++L) {
         hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
@@ -1604,12 +1609,17 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
         LAUNCH_CHECK(c, "rope_kv (grouped)");
         {
             metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * KH * kvpos * HD * sizeof(T) + (double)R * H * HD * 4);
-            hipExtLaunchKernelGGL((attn_partial_mfma_segp_kernel<HD>), dim3(nch_max, H, sg.n), dim3(256), 0u, st, pr ? pr->a : nullptr,
-                                  pr ? pr->b : nullptr, 0u, (const float*)c->d_q(), kcs, vcs, sg, H, KH, c->cfg.max_ctx, scale, c->d_apart(),
-                                  nch_max, (size_t)R * H * HD);
-            LAUNCH_CHECK(c, "attn_partial (grouped)");
-            hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(H, R), dim3(HD), 0, st, c->d_apart(), nch_max, H, (float*)c->d_ao(), 2, sg, 1);
-            LAUNCH_CHECK(c, "attn_combine (segments)");
+#define ATTN_GO(SHARED) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, true>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, st, pr ? pr->a : nullptr, pr ? pr->b : nullptr, \
+                                              0u, (const bf16_t*)c->d_q(), (const bf16_t*)nullptr, (const bf16_t*)nullptr, (size_t)0, kcs, vcs, sg, H, KH, pl.hp, \
+                                              c->cfg.max_ctx, scale, (size_t)R * H * HD, pl.spw, ao)
+            if (H > KH * pl.hp) ATTN_GO(true);
+            else ATTN_GO(false);
+#undef ATTN_GO
+            LAUNCH_CHECK(c, "attn (grouped)");
+            if (pl.nrec > 1) {
+                hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(H, R), dim3(HD), 0, st, c->d_apart(), pl.nrec, H, (float*)c->d_ao(), 2, sg, pl.spw / ATT_NW);
+                LAUNCH_CHECK(c, "attn_combine (segments)");
+            }
         }
         if ((rc = gemm_rows_grouped(c, c->d_ao(), R, DQ, weights(L, 4, -1, -1), D, 0, 0, &ns))) return rc;
         hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
