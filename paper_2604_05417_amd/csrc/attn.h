@@ -54,8 +54,13 @@ __device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __re
             ql[k] = *reinterpret_cast<const u32x4*>(src + q_lo + k * 32);
         }
     }
+    // what this lane's row sees of a tree block (tree_allowed): everything below v0, and from there on the nodes of a mask (mode 1) or the
+    // positions from v1 on (mode 2), up to its own
+    const bool stream = tb && tb->on == 2;
+    const int v0 = tb ? (stream ? tb->sink : tb->base) : 0, v1 = stream ? max(tb->base, pos0 + row - tb->i0 + 1) : v0;
+    const uint32_t nodes = tb && !stream ? tb->anc[tb->i0 + row] : 0;
     auto next = [&](int s) {                           // streaming caches: sub-blocks no row attends to are passed over
-        if (tb && tb->on == 2)
+        if (stream)
             while (s < s1 && stream_skips(*tb, s * 32, 32, pos0)) s += ATT_NW;
         return s;
     };
@@ -100,7 +105,7 @@ __device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __re
         }
         request_k(sq);
         float tm = -INFINITY;
-        const bool edge = tb || p0 + 32 > pos0;        // some row may not see all 32 positions
+        const bool edge = tb ? stream || p0 + 32 > v0 : p0 + 32 > pos0;    // some row may not see all 32 positions
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -108,7 +113,8 @@ __device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __re
                 float x = sc[t][v] * scale;
                 if (edge) {
                     const int p = p0 + t * 16 + g * 4 + v;
-                    const bool see = tb ? tree_allowed(*tb, p, row, pos0) : p <= pos0 + row;
+                    bool see = p <= pos0 + row;
+                    if (tb) see = stream ? see && (p < v0 || p >= v1) : p < v0 || (p - v0 < TREE_MAX && (nodes >> (p - v0)) & 1);
                     x = see && p < L ? x : -INFINITY;
                 }
                 sc[t][v] = x;

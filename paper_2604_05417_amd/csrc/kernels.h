@@ -1272,361 +1272,6 @@ __global__ __launch_bounds__(256) void attn_partial_tree_kernel(const float* __r
     attn_partial_body<T, HD>(q, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x, (int)blockIdx.y, &tb, direct);
 }
 
-// Source of a block's fresh q / k / v when the attention kernel forms them itself (no rope_kv_kernel launch): the split-K
-// partial sums of the QKV projection (rope-ordered q and k columns: pair (i, i + hd/2) of a head at columns 16(i/8) + 2(i%8), +1),
-// the rotation table of the block, the optional 1/rms per row, and where the new K / V rows go.  The arithmetic per element is
-// rope_kv_body's: partials added in order from zero, scaled, rotated in fp64, rounded once.
-struct QkvIn {
-    const float* part;     // [nsplit][m][N]
-    int nsplit;
-    size_t sstride;        // m * N
-    int N;                 // (H + 2 KH) * hd
-    const double2* tab;    // [m][hd/2] (cos, sin)
-    const float* inv;      // [m] or nullptr
-    bf16_t* kc;            // cache planes of this layer, written for positions pos0 .. pos0+m-1
-    bf16_t* vc;
-};
-
-// bf16-cache variant on MFMA.  One workgroup (4 wavefronts) per (chunk of 128 positions, query head):
-//   S^T[pos][row] = K[pos][:] . q[row][:]   A = K rows straight from global (16 B per lane, no LDS),
-//                                           B = q as two bf16 terms (hi + lo); wavefront w owns
-//                                           positions 32w .. 32w+31 of the chunk;
-//   softmax numerators p = exp(s - max) per row over the chunk (shuffles across the 4 lane groups,
-//   LDS across the 4 wavefronts), written to LDS as P[row][pos] in two bf16 terms;
-//   O^T[hd][row] = V^T[hd][pos] . P^T[pos][row]   A = V gathered from the LDS-staged V chunk,
-//                                           wavefront w owns head-dim tiles {w, w+4, ..}.
-// Output layout and the combine kernel are shared with the generic kernel above.
-
-// q_lo_off: distance (elements) from the hi array of q to its lo array (rows of the whole block x H x HD).
-// MULTI: the workgroup walks cpw consecutive chunks starting at chunk c and keeps a running (max, sum, O) per row
-// (each new chunk rescales what is there by exp(old max - new max)); it writes one record, number rec of head h,
-// so the records written and merged later shrink by the factor cpw.  Without MULTI: one chunk, record c.
-// QKV (one chunk per workgroup only): q, and the K / V rows of the block's own positions, are formed here from the QKV
-// projection's partial sums instead of being read (see QkvIn).  The pieces (four consecutive columns of one row: all of q of
-// this head, and the new K and V rows that fall into this chunk) are dealt out over the 256 threads and requested before the
-// cache loads, so they arrive in the same trip to memory; q and the new K rows pass through LDS into the MFMA fragment layout,
-// the new V rows go straight into the staged V chunk.  The first query head of each KV head also writes the new rows to the
-// cache.  Every workgroup forms the new rows it needs itself: nothing in this launch reads what another workgroup writes.
-template <int HD, bool MULTI = false, bool QKV = false>
-__device__ __forceinline__ void attn_partial_mfma_body(const float* __restrict__ q, const bf16_t* __restrict__ kc,
-                                                       const bf16_t* __restrict__ vc, int m, int pos0, int H, int KH,
-                                                       int max_ctx, float scale, float* __restrict__ part, int nchunks, int c,
-                                                       int h, size_t q_lo_off, int cpw = 1, int rec = 0, const TreeBlk* tb = nullptr,
-                                                       const QkvIn* qi = nullptr) {
-    static_assert(!(MULTI && QKV), "fresh q/k/v are formed for a single chunk per workgroup");
-    constexpr int RS = HD + 8;                 // padded LDS row stride of the V chunk (elements)
-    constexpr int VPR = HD / 8;                // 16-byte pieces per row
-    constexpr int PS = ATT_CH + 8;             // padded row stride of P (elements)
-    constexpr int KC = HD / 32;                // 32-wide head-dim chunks
-    constexpr int NT = HD / 16;                // 16-wide head-dim tiles
-    __shared__ __align__(16) bf16_t vs[ATT_CH * RS];
-    __shared__ __align__(16) bf16_t phi[16 * PS];
-    __shared__ __align__(16) bf16_t plo[16 * PS];
-    __shared__ float wmax[4][16], wsum[4][16];
-
-    const int kh = h / (H / KH);
-    const int L = pos0 + m;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int row = lane & 15, g = lane >> 4;
-    const bool rowok = row < m;
-    constexpr int VIT = ATT_CH * VPR / 256;    // 16-byte pieces of a V chunk per thread
-    constexpr int NTW = (NT + 3) / 4;          // head-dim tiles per wavefront
-
-    // ---- q fragments (B operand): q[row][32 kc + 8 g .. +8], already split into two bf16 terms by rope_kv_kernel
-    uint4 qh[KC], ql[KC];
-#pragma unroll
-    for (int k = 0; k < KC; ++k) {
-        qh[k] = make_uint4(0, 0, 0, 0);
-        ql[k] = make_uint4(0, 0, 0, 0);
-        if (!QKV && rowok) {
-            const bf16_t* src = reinterpret_cast<const bf16_t*>(q) + (size_t)row * H * HD + (size_t)h * HD + k * 32 + g * 8;
-            qh[k] = *reinterpret_cast<const uint4*>(src);
-            ql[k] = *reinterpret_cast<const uint4*>(src + q_lo_off);
-        }
-    }
-    const bf16_t* kbase = kc + (size_t)kh * max_ctx * HD;
-    constexpr int QS = HD + 8;                 // padded row stride (elements) of q and of the new K rows in LDS
-    constexpr int C4 = HD / 4;                 // four-column pieces per row
-    constexpr int half = HD / 2;
-    // running state of this lane's query row (MULTI): maximum, sum, and this wavefront's O^T tiles
-    float run_max = -INFINITY, run_sum = 0.f;
-    f32x4 orun[NTW];
-#pragma unroll
-    for (int i = 0; i < NTW; ++i) orun[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int nloop = MULTI ? cpw : 1;
-    for (int ci = 0; ci < nloop; ++ci) {
-        const int p0 = (c + ci) * ATT_CH;
-        if (MULTI && p0 >= L) break;               // workgroup-uniform
-        const int np = min(ATT_CH, L - p0);
-        if (!MULTI && tb && stream_skips(*tb, p0, ATT_CH, pos0)) {
-            // a streaming cache holds nothing any row attends to in this chunk: an empty record (weight zero in the merge)
-            float* dst = part + ((size_t)h * nchunks + c) * 16 * (HD + 2);
-            for (int i = tid; i < m * (HD + 2); i += 256) dst[i] = (i % (HD + 2)) == HD ? -INFINITY : 0.f;
-            return;
-        }
-        // the block's own rows that fall into this chunk: rows r_lo .. r_lo + nnew - 1
-        const int r_lo = max(0, p0 - pos0), nnew = QKV ? max(0, min(m, p0 + ATT_CH - pos0) - r_lo) : 0;
-        // ---- fresh q / k / v: the pieces of this thread (piece number tid + 256 j), two per trip.  Requests are unconditional
-        // (clamped to valid addresses, unused values dropped later) so that the code up to the first use is one straight line
-        // and the wait for the pieces does not have to wait for the cache rows requested after them.
-        constexpr int GRP = 2;
-        const int n_q = m * C4, n_kv = nnew * C4, n_items = QKV ? n_q + 2 * n_kv : 0;
-        float4 raw[GRP][4];
-        double2 rot[GRP][2];
-        float rsc[GRP];
-        auto item_at = [&](int idx, int& kind, int& r, int& cc) {      // idx < n_items; kinds: 0 q, 1 K, 2 V
-            const int k1 = idx - n_q, k2 = k1 - n_kv;
-            kind = idx < n_q ? 0 : (k2 < 0 ? 1 : 2);
-            const int loc = kind == 0 ? idx : (kind == 1 ? k1 : k2);
-            const int rr = loc / C4;
-            cc = loc - rr * C4;
-            r = kind == 0 ? rr : r_lo + rr;
-        };
-        auto item_src = [&](int kind, int r, int cc) {
-            const size_t col = kind == 0 ? (size_t)h * HD : kind == 1 ? (size_t)(H + kh) * HD : (size_t)(H + KH + kh) * HD;
-            return qi->part + (size_t)r * qi->N + col + 4 * cc;
-        };
-        auto item_request = [&](int j0) {
-            const int ns1 = qi->nsplit - 1;
-#pragma unroll
-            for (int j = 0; j < GRP; ++j) {
-                const int idx = min(tid + 256 * (j0 + j), n_items - 1);
-                int kind, r, cc;
-                item_at(idx, kind, r, cc);
-                const float* src = item_src(kind, r, cc);
-#pragma unroll
-                for (int s = 0; s < 4; ++s) raw[j][s] = *reinterpret_cast<const float4*>(src + (size_t)min(s, ns1) * qi->sstride);
-                const double2* t = qi->tab + (size_t)r * half + 8 * (cc >> 2) + 2 * (cc & 3);   // pairs i, i + 1 of columns 4 cc ..
-                rot[j][0] = t[0]; rot[j][1] = t[1];
-                rsc[j] = *(qi->inv ? qi->inv + r : reinterpret_cast<const float*>(qi->tab));
-            }
-        };
-        if constexpr (QKV) {
-            item_request(0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // ---- issue the V chunk loads (consumed last); rows beyond the ragged end re-read the last row and are zeroed when staged
-        const bf16_t* vbase = vc + ((size_t)kh * max_ctx + p0) * HD;
-        uint4 vreg[VIT];
-#pragma unroll
-        for (int it = 0; it < VIT; ++it) {
-            const int idx = tid + it * 256;
-            const int p = idx / VPR, v = idx - p * VPR;
-            vreg[it] = *reinterpret_cast<const uint4*>(vbase + (size_t)min(p, np - 1) * HD + v * 8);
-        }
-        // ---- K rows of this wavefront's 32 positions: two 16-position tiles (A operand straight from the cache)
-        u32x4 kf[2][KC];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int pl = wave * 32 + t * 16 + row;                       // this lane's K row within the chunk
-            const int pg = min(p0 + pl, L - 1);                            // clamp: stays inside the cache
-            const u32x4* kp = reinterpret_cast<const u32x4*>(kbase + (size_t)pg * HD + g * 8);
-#pragma unroll
-            for (int k = 0; k < KC; ++k) kf[t][k] = kp[k * 4];             // +32 elements = 4 x 16 bytes
-        }
-        if constexpr (QKV) {
-            __builtin_amdgcn_sched_barrier(0);
-            __shared__ __align__(16) bf16_t kn[16 * QS];                   // the new K rows of this chunk, rotated
-            bf16_t* qs_hi = phi;                                            // q as two bf16 terms: phi / plo are free until the scores exist
-            bf16_t* qs_lo = plo;
-            const bool kv_writer = h % (H / KH) == 0;
-            auto item_finish = [&](int j0) {
-#pragma unroll
-                for (int j = 0; j < GRP; ++j) {
-                    const int idx = tid + 256 * (j0 + j);
-                    float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        const float w = s < qi->nsplit ? 1.f : 0.f;      // a repeated request counts as + 0 (the sums stay the ordered ones)
-                        f.x += w * raw[j][s].x; f.y += w * raw[j][s].y; f.z += w * raw[j][s].z; f.w += w * raw[j][s].w;
-                    }
-                    if (idx < n_items) {
-                        int kind, r, cc;
-                        item_at(idx, kind, r, cc);
-                        if (qi->nsplit > 4) {                               // more than four partials: the rest one by one
-                            const float* src = item_src(kind, r, cc);
-                            for (int s = 4; s < qi->nsplit; ++s) {
-                                const float4 x = *reinterpret_cast<const float4*>(src + (size_t)s * qi->sstride);
-                                f.x += x.x; f.y += x.y; f.z += x.z; f.w += x.w;
-                            }
-                        }
-                        if (qi->inv) { const float sc = rsc[j]; f.x *= sc; f.y *= sc; f.z *= sc; f.w *= sc; }
-                        if (kind == 2) {
-                            const uint2 pk = make_uint2(pack_bf16x2(f2bf(f.x), f2bf(f.y)), pack_bf16x2(f2bf(f.z), f2bf(f.w)));
-                            *reinterpret_cast<uint2*>(vs + (pos0 + r - p0) * RS + 4 * cc) = pk;
-                            if (kv_writer) *reinterpret_cast<uint2*>(qi->vc + ((size_t)kh * max_ctx + pos0 + r) * HD + 4 * cc) = pk;
-                        } else {
-                            // columns 4 cc .. + 3 hold (a_i, b_i, a_{i+1}, b_{i+1}): elements i, i + 1 and their partners hd/2 further on
-                            const int i = 8 * (cc >> 2) + 2 * (cc & 3);
-                            const float a0 = (float)((double)f.x * rot[j][0].x - (double)f.y * rot[j][0].y);
-                            const float b0 = (float)((double)f.x * rot[j][0].y + (double)f.y * rot[j][0].x);
-                            const float a1 = (float)((double)f.z * rot[j][1].x - (double)f.w * rot[j][1].y);
-                            const float b1 = (float)((double)f.z * rot[j][1].y + (double)f.w * rot[j][1].x);
-                            const bf16_t a0h = f2bf(a0), a1h = f2bf(a1), b0h = f2bf(b0), b1h = f2bf(b1);
-                            if (kind == 0) {
-                                *reinterpret_cast<uint32_t*>(qs_hi + r * QS + i) = pack_bf16x2(a0h, a1h);
-                                *reinterpret_cast<uint32_t*>(qs_hi + r * QS + i + half) = pack_bf16x2(b0h, b1h);
-                                *reinterpret_cast<uint32_t*>(qs_lo + r * QS + i) = pack_bf16x2(f2bf(a0 - bf2f(a0h)), f2bf(a1 - bf2f(a1h)));
-                                *reinterpret_cast<uint32_t*>(qs_lo + r * QS + i + half) = pack_bf16x2(f2bf(b0 - bf2f(b0h)), f2bf(b1 - bf2f(b1h)));
-                            } else {
-                                *reinterpret_cast<uint32_t*>(kn + (r - r_lo) * QS + i) = pack_bf16x2(a0h, a1h);
-                                *reinterpret_cast<uint32_t*>(kn + (r - r_lo) * QS + i + half) = pack_bf16x2(b0h, b1h);
-                            }
-                        }
-                    }
-                }
-            };
-            item_finish(0);
-            for (int j0 = GRP; j0 * 256 < n_items; j0 += GRP) {           // more than two pieces per thread: further trips
-                item_request(j0);
-                item_finish(j0);
-            }
-            __syncthreads();
-            if (rowok) {
-#pragma unroll
-                for (int k = 0; k < KC; ++k) {
-                    qh[k] = *reinterpret_cast<const uint4*>(qs_hi + row * QS + k * 32 + g * 8);
-                    ql[k] = *reinterpret_cast<const uint4*>(qs_lo + row * QS + k * 32 + g * 8);
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int pg = min(p0 + wave * 32 + t * 16 + row, L - 1);
-                if (pg >= pos0) {                                          // what was read from the cache there is not written yet
-#pragma unroll
-                    for (int k = 0; k < KC; ++k)
-                        kf[t][k] = __builtin_bit_cast(u32x4, *reinterpret_cast<const uint4*>(kn + (pg - pos0 - r_lo) * QS + k * 32 + g * 8));
-                }
-            }
-            if (kv_writer && tid < nnew * VPR) {                           // the new K rows to the cache, 16 bytes per thread
-                const int rr = tid / VPR, v = tid - rr * VPR;
-                *reinterpret_cast<uint4*>(qi->kc + ((size_t)kh * max_ctx + pos0 + r_lo + rr) * HD + v * 8) =
-                    *reinterpret_cast<const uint4*>(kn + rr * QS + v * 8);
-            }
-        }
-        // ---- scores
-        f32x4 sacc[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acl = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int k = 0; k < KC; ++k) {
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t][k]), __builtin_bit_cast(bf16x8, qh[k]), acc, 0, 0, 0);
-                acl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t][k]), __builtin_bit_cast(bf16x8, ql[k]), acl, 0, 0, 0);
-            }
-            sacc[t] = acc + acl;
-        }
-        // lane (g, row) holds positions wave*32 + t*16 + 4g + v of query row `row`
-        float sv[8];
-        float lmax = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int pl = wave * 32 + t * 16 + g * 4 + v;
-                const bool see = tb ? tree_allowed(*tb, p0 + pl, rowok ? row : 0, pos0) : (p0 + pl) <= pos0 + row;
-                const bool ok = rowok && pl < np && see;
-                const float x = ok ? sacc[t][v] * scale : -INFINITY;
-                sv[t * 4 + v] = x;
-                lmax = fmaxf(lmax, x);
-            }
-        lmax = fmaxf(lmax, __shfl_xor(lmax, 16, 64));
-        lmax = fmaxf(lmax, __shfl_xor(lmax, 32, 64));
-        if (g == 0) wmax[wave][row] = lmax;
-        // ---- stage V into LDS while the maxima settle
-#pragma unroll
-        for (int it = 0; it < VIT; ++it) {
-            const int idx = tid + it * 256;
-            const int p = idx / VPR, v = idx - p * VPR;
-            if (!(QKV && p < np && p0 + p >= pos0))                       // the block's own rows are in place already
-                *reinterpret_cast<uint4*>(vs + p * RS + v * 8) = p < np ? vreg[it] : make_uint4(0, 0, 0, 0);
-        }
-        __syncthreads();
-        const float cmx = fmaxf(fmaxf(wmax[0][row], wmax[1][row]), fmaxf(wmax[2][row], wmax[3][row]));
-        const float mx = MULTI ? fmaxf(run_max, cmx) : cmx;
-        float lsum = 0.f;
-        bf16_t ph[8], pl8[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float e = (mx == -INFINITY) ? 0.f : expf(sv[i] - mx);   // expf(-inf) = 0 for masked positions
-            lsum += e;
-            ph[i] = f2bf(e);
-            pl8[i] = f2bf(e - bf2f(ph[i]));
-        }
-        lsum += __shfl_xor(lsum, 16, 64);
-        lsum += __shfl_xor(lsum, 32, 64);
-        if (g == 0) wsum[wave][row] = lsum;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int pl = wave * 32 + t * 16 + g * 4;
-            *reinterpret_cast<uint2*>(phi + row * PS + pl) = make_uint2(pack_bf16x2(ph[t * 4], ph[t * 4 + 1]), pack_bf16x2(ph[t * 4 + 2], ph[t * 4 + 3]));
-            *reinterpret_cast<uint2*>(plo + row * PS + pl) = make_uint2(pack_bf16x2(pl8[t * 4], pl8[t * 4 + 1]), pack_bf16x2(pl8[t * 4 + 2], pl8[t * 4 + 3]));
-        }
-        __syncthreads();
-        // what the earlier chunks left is rescaled to the new maximum
-        const float alpha = (MULTI && run_max != -INFINITY) ? expf(run_max - mx) : 0.f;
-        // ---- O^T tiles: wavefront w takes head-dim tiles w, w+4, ..
-        float* dst = part + ((size_t)h * nchunks + (MULTI ? rec : c)) * 16 * (HD + 2);
-#pragma unroll
-        for (int ti = 0; ti < NTW; ++ti) {
-            const int nt = wave + 4 * ti;
-            if (nt < NT) {                                                  // wavefront-uniform
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acl = {0.f, 0.f, 0.f, 0.f};
-                const int col = nt * 16 + row;                              // A operand row index i = lane % 16 -> head-dim column
-#pragma unroll
-                for (int k = 0; k < ATT_CH / 32; ++k) {
-                    const bf16_t* vp = vs + (k * 32 + g * 8) * RS + col;
-                    const uint4 a = make_uint4(pack_bf16x2(vp[0], vp[RS]), pack_bf16x2(vp[2 * RS], vp[3 * RS]),
-                                               pack_bf16x2(vp[4 * RS], vp[5 * RS]), pack_bf16x2(vp[6 * RS], vp[7 * RS]));
-                    const uint4 bh = *reinterpret_cast<const uint4*>(phi + row * PS + k * 32 + g * 8);
-                    const uint4 bl = *reinterpret_cast<const uint4*>(plo + row * PS + k * 32 + g * 8);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, bh), acc, 0, 0, 0);
-                    acl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, bl), acl, 0, 0, 0);
-                }
-                if constexpr (MULTI) {
-                    orun[ti] = orun[ti] * alpha + (acc + acl);
-                } else if (rowok) {
-                    float* o = dst + row * (HD + 2) + nt * 16 + g * 4;       // D[i = 4g + v][j = row]
-                    o[0] = acc[0] + acl[0]; o[1] = acc[1] + acl[1]; o[2] = acc[2] + acl[2]; o[3] = acc[3] + acl[3];
-                }
-            }
-        }
-        if constexpr (MULTI) {
-            run_sum = run_sum * alpha + ((wsum[0][row] + wsum[1][row]) + (wsum[2][row] + wsum[3][row]));
-            run_max = mx;
-            const bool last = ci + 1 == nloop || p0 + ATT_CH >= L;
-            if (!last) {
-                __syncthreads();                   // the next chunk overwrites vs, phi, plo, wmax and wsum
-            } else {
-#pragma unroll
-                for (int ti = 0; ti < NTW; ++ti) {
-                    const int nt = wave + 4 * ti;
-                    if (nt < NT && rowok) {
-                        float* o = dst + row * (HD + 2) + nt * 16 + g * 4;
-                        o[0] = orun[ti][0]; o[1] = orun[ti][1]; o[2] = orun[ti][2]; o[3] = orun[ti][3];
-                    }
-                }
-                if (tid < m) {                     // wavefront 0, g = 0: this lane's row is tid
-                    dst[tid * (HD + 2) + HD] = run_max;
-                    dst[tid * (HD + 2) + HD + 1] = run_sum;
-                }
-            }
-        } else if (tid < m) {
-            dst[tid * (HD + 2) + HD] = fmaxf(fmaxf(wmax[0][tid], wmax[1][tid]), fmaxf(wmax[2][tid], wmax[3][tid]));
-            dst[tid * (HD + 2) + HD + 1] = (wsum[0][tid] + wsum[1][tid]) + (wsum[2][tid] + wsum[3][tid]);
-        }
-    }
-}
-
-// The same with q and the block's own K / V rows formed from the QKV projection's partial sums (tb.on selects the tree mask).
-template <int HD>
-__global__ __launch_bounds__(256, 3) void attn_partial_mfma_qkv_kernel(QkvIn qi, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
-                                                                    int m, int pos0, int H, int KH, int max_ctx, float scale,
-                                                                    float* __restrict__ part, int nchunks, TreeBlk tb) {
-    attn_partial_mfma_body<HD, false, true>(nullptr, kc, vc, m, pos0, H, KH, max_ctx, scale, part, nchunks, (int)blockIdx.x,
-                                            (int)blockIdx.y, 0, 1, 0, tb.on ? &tb : nullptr, &qi);
-}
 // Merge of the chunk records of (head h, block row r): nchunks records are merged, records of one head are
 // nch_stride chunks apart; the result goes to row r_out of out (split: as two bf16 terms, 1: arrays lo_off elements apart, 2: interleaved).
 template <int HD>

@@ -717,7 +717,7 @@ bool step_init_one() {
     return step_allow_lds<STEP_NORM, EPI, PART, J, 4, false>() == hipSuccess && step_allow_lds<STEP_NORM, EPI, PART, J, 8, false>() == hipSuccess;
 }
 template <int J>
-bool step_init_j() { return step_init_one<STEP_OUT, false, J>() && step_init_one<STEP_ACT, false, J>() && (J > 2 || step_init_one<STEP_ACT, true, (J > 2 ? 1 : J)>()); }
+bool step_init_j() { return step_init_one<STEP_OUT, false, J>() && step_init_one<STEP_ROPE, false, J>() && step_init_one<STEP_ACT, false, J>() && (J > 2 || step_init_one<STEP_ACT, true, (J > 2 ? 1 : J)>()); }
 bool step_init() {
     const bool ok = step_init_j<1>() && step_init_j<2>() && step_init_j<4>() && step_init_j<8>();
     if (!ok) (void)hipGetLastError();
@@ -761,11 +761,21 @@ int gemm_step_add(metasd_ctx* c, const void* x, int m, int K, const void* W, int
     return pl.half ? launch_step<STEP_TERMS, STEP_ADD, false, 1, true>(c, a, pl) : launch_step<STEP_TERMS, STEP_ADD, false, 1, false>(c, a, pl);
 }
 
-// combine == false: only the per-chunk records (the consumer merges them itself)
-// qi (bf16 caches, head_dim >= 64 only): q and the block's own K / V rows come from the QKV projection's partial sums inside
-// the attention kernel (no separate rope launch)
+// q, k and v of layer L: q rotated in d_q, the block's K / V rows (positions pos0 ..) rotated and rounded in the cache
+int gemm_step_qkv(metasd_ctx* c, const Model& M, int L, int pos0, StepArgs a) {
+    const metasd_model_desc& d = M.d;
+    const int DQ = d.n_heads * M.hd, DKV = d.n_kv_heads * M.hd;
+    const size_t plane = (size_t)d.n_kv_heads * c->cfg.max_ctx * M.hd;
+    a.out = (float*)c->d_q(); a.N = DQ;
+    a.tab = (const double2*)c->d_rope();
+    a.kc = (bf16_t*)M.kv + (size_t)L * 2 * plane; a.vc = a.kc + plane;
+    a.H = d.n_heads; a.KH = d.n_kv_heads; a.hd = M.hd; a.pos0 = pos0; a.max_ctx = c->cfg.max_ctx;
+    return gemm_step_norm<STEP_ROPE, false>(c, a, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV);
+}
+
+// nrec_out != nullptr: the records are left to the consumer, which merges them itself (*nrec_out of them; 1: the rows are in d_ao)
 template <typename T, int HD>
-int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool combine, const QkvIn* qi) {
+int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, int* nrec_out) {
     const metasd_model_desc& d = M.d;
     const size_t plane = (size_t)d.n_kv_heads * c->cfg.max_ctx * HD;
     const T* kc = (const T*)M.kv + (size_t)L * 2 * plane;
@@ -777,23 +787,18 @@ int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool com
                                                                  (double)m * d.n_heads * HD * 4);
     hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
     int nrec = nchunks;
+    bool combine = true;
     if constexpr (sizeof(T) == 2 && HD >= 64) {
-        if (qi) {
-            hipExtLaunchKernelGGL((attn_partial_mfma_qkv_kernel<HD>), dim3(nchunks, d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u, *qi,
-                                  kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, c->d_apart(), nchunks,
-                                  c->tree ? *c->tree : TreeBlk{});
-        } else {
-            const AttnPlan pl = plan_attn(1, d.n_heads, d.n_kv_heads, HD, m, pos0 + m, c->n_cu, c->att_cpw);
-            const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), 1, (size_t)m * d.n_heads * HD, 0, m};
-            nrec = pl.nrec;
-            if (nrec == 1) combine = false;
+        const AttnPlan pl = plan_attn(1, d.n_heads, d.n_kv_heads, HD, m, pos0 + m, c->n_cu, c->att_cpw);
+        const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), 1, (size_t)m * d.n_heads * HD, 0, m};
+        nrec = pl.nrec;
+        if (nrec == 1) combine = false;
 #define ATTN_GO(TREE, SHARED) hipExtLaunchKernelGGL((attn_kernel<HD, TREE, SHARED>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, (const bf16_t*)c->d_q(), \
-                                                    kc, vc, m, pos0, d.n_heads, d.n_kv_heads, pl.hp, c->cfg.max_ctx, scale, pl.spw, ao, c->tree ? *c->tree : TreeBlk{})
-            const bool shared = d.n_heads > d.n_kv_heads * pl.hp;
-            if (c->tree) { if (shared) ATTN_GO(true, true); else ATTN_GO(true, false); }
-            else { if (shared) ATTN_GO(false, true); else ATTN_GO(false, false); }
+                                                kc, vc, m, pos0, d.n_heads, d.n_kv_heads, pl.hp, c->cfg.max_ctx, scale, pl.spw, ao, c->tree ? *c->tree : TreeBlk{})
+        const bool shared = d.n_heads > d.n_kv_heads * pl.hp;
+        if (c->tree) { if (shared) ATTN_GO(true, true); else ATTN_GO(true, false); }
+        else { if (shared) ATTN_GO(false, true); else ATTN_GO(false, false); }
 #undef ATTN_GO
-        }
     } else {
         // a context of one chunk needs no merge (fp32: nothing but the division is left of it)
         float* direct = sizeof(T) == 4 && combine && nchunks == 1 ? (float*)c->d_ao() : nullptr;
@@ -808,7 +813,8 @@ int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool com
                                   c->d_apart(), nchunks, direct);
     }
     LAUNCH_CHECK(c, "attn_partial");
-    if (!combine) return 0;
+    if (nrec_out) *nrec_out = combine ? nrec : 1;
+    if (!combine || nrec_out) return 0;
     hipLaunchKernelGGL((attn_combine_kernel<T, HD>), dim3(d.n_heads, m), dim3(HD), 0, c->stream, c->d_apart(), nrec,
                        d.n_heads, (float*)c->d_ao(), sizeof(T) == 2 ? 1 : 0);
     LAUNCH_CHECK(c, "attn_combine");
@@ -816,13 +822,12 @@ int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool com
 }
 
 template <typename T>
-int attention(metasd_ctx* c, const Model& M, int L, int pos0, int m, bool combine = true, const QkvIn* qi = nullptr) {
-    if (qi && (sizeof(T) != 2 || M.hd < 64)) return c->fail(METASD_E_INVALID, "attention: fused q/k/v needs a bf16 cache and head_dim >= 64");
+int attention(metasd_ctx* c, const Model& M, int L, int pos0, int m, int* nrec_out = nullptr) {
     switch (M.hd) {
-        case 32: return attention_hd<T, 32>(c, M, L, pos0, m, combine, nullptr);
-        case 64: return attention_hd<T, 64>(c, M, L, pos0, m, combine, qi);
+        case 32: return attention_hd<T, 32>(c, M, L, pos0, m, nrec_out);
+        case 64: return attention_hd<T, 64>(c, M, L, pos0, m, nrec_out);
         default:
-            if constexpr (sizeof(T) == 2) return attention_hd<T, 128>(c, M, L, pos0, m, combine, qi);
+            if constexpr (sizeof(T) == 2) return attention_hd<T, 128>(c, M, L, pos0, m, nrec_out);
             return c->fail(METASD_E_INVALID, "fp32 head_dim 128 unsupported");
     }
 }
@@ -984,8 +989,6 @@ int forward_rows_residual(metasd_ctx* c, Model& M, int pos0, int m, float* logit
                           scaled ? ssq : nullptr, ntg, inv, 0))) return rc;
         const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
         T* kc = (T*)M.kv + (size_t)L * 2 * plane;
-        // (forming q / k / v inside the attention kernel, as the short-block path below does, was measured here and is slower
-        // at the 7B shape: 3.32 against 3.29 ms per pass - the wider kernel loses what the launch saves)
         hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, part, ns, (size_t)m * NQKV, NQKV, pos0, H, KH, hd,
                            (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, hd >= 64 ? 1 : 0,
                            scaled ? (const float*)inv : nullptr);
@@ -1015,12 +1018,11 @@ int forward_rows_residual(metasd_ctx* c, Model& M, int pos0, int m, float* logit
     return 0;
 }
 
-// Short blocks of narrow bf16 models (drafter steps; d_model <= 2048): the same forward with the add+norm, the FFN activation, the
-// residual add and the attention combine folded into the GEMMs before or behind them (step.h) - 5 launches per layer instead of 10
-// (q / k / v are formed inside the attention kernel).  The residual stream ping-pongs between two buffers where the gate | up
-// projection adds the output projection's partials to it, because its workgroups read the old rows while one writes the new ones.
-// Each launch reads finished sums instead of up to eight split-K partials.  One row of the 1B
-// shape, per layer: QKV 7.6 -> 5.5, attention 7.4 -> 6.7, gate | up with the activation 16.2 -> 15.3, down 9.4 -> 9.0 us; head 25.2 -> 24.3.
+// Short blocks of narrow bf16 models (drafter steps; d_model <= 2048): the same forward with the add+norm, the rotation and cache append,
+// the FFN activation, the residual add and the attention merge folded into the GEMMs before or behind them (step.h) - 5 launches per
+// layer instead of 10.  The residual stream ping-pongs between two buffers where the gate | up projection adds the output projection's
+// partials to it, because its workgroups read the old rows while one writes the new ones; attention that leaves finished rows (one
+// record) needs neither the merge nor the partials: the output projection adds to the stream itself.
 constexpr int fused_max_rows() { return 4; }
 bool fused_small_ok(const Model& M, int m) {
     const metasd_model_desc& d = M.d;
@@ -1033,11 +1035,10 @@ bool fused_small_ok(const Model& M, int m) {
 int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int first_row) {
     typedef bf16_t T;
     const metasd_model_desc& d = M.d;
-    const int D = d.d_model, H = d.n_heads, KH = d.n_kv_heads, hd = M.hd, F = d.d_ffn, V = d.vocab;
-    const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV;
-    hipStream_t st = c->stream;
+    const int D = d.d_model, H = d.n_heads, hd = M.hd, F = d.d_ffn, V = d.vocab;
+    const int DQ = H * hd;
     int hp = 0, rc;                     // current residual buffer
-    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, st, c->d_hist() + pos0, (const T*)M.w[0], D, c->d_h_pp(0), pos0, hd,
+    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, c->stream, c->d_hist() + pos0, (const T*)M.w[0], D, c->d_h_pp(0), pos0, hd,
                        d.rope_theta, c->d_rope(), c->tree ? *c->tree : TreeBlk{});
     LAUNCH_CHECK(c, "embed + rope table");
     auto norm_in = [&](const void* gain, int row0) {
@@ -1048,30 +1049,31 @@ int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, 
         a.m = m - row0; a.K = D;
         return a;
     };
-    const int nchunks = (pos0 + m + ATT_CH - 1) / ATT_CH;
     for (int L = 0; L < d.n_layers; ++L) {
-        // QKV projection of norm(h)
+        // q, and the new K / V rows in the cache, from the QKV projection of norm(h)
         StepArgs a = norm_in(M.layer_w(L, 0), 0);
-        a.out = c->d_part(); a.N = NQKV;
-        if ((rc = gemm_step_norm<STEP_OUT, false>(c, a, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV))) return rc;
-        const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
-        T* kc = (T*)M.kv + (size_t)L * 2 * plane;
-        // q, and the new K / V rows, are rotated inside the attention kernel (no rope launch)
-        const QkvIn qi{c->d_part(), 1, (size_t)m * NQKV, NQKV, (const double2*)c->d_rope(), nullptr, kc, kc + plane};
-        if ((rc = attention<T>(c, M, L, pos0, m, false, &qi))) return rc;
-        // output projection of the merged attention output
-        int ns = 0;
-        GemmPro pro{};
-        pro.src = c->d_apart(); pro.nchunks = nchunks; pro.hd = hd;
-        if ((rc = gemm_combine(c, pro, m, DQ, M.layer_w(L, 4), D, c->d_part(), &ns))) return rc;
+        if ((rc = gemm_step_qkv(c, M, L, pos0, a))) return rc;
+        int nrec = 0;
+        if ((rc = attention<T>(c, M, L, pos0, m, &nrec))) return rc;
+        if (nrec > 1) {
+            // output projection of the attention output, merged in its prologue; the gate | up projection adds its partials to h
+            int ns = 0;
+            GemmPro pro{};
+            pro.src = c->d_apart(); pro.nchunks = nrec; pro.hd = hd;
+            if ((rc = gemm_combine(c, pro, m, DQ, M.layer_w(L, 4), D, c->d_part(), &ns))) return rc;
+            a = norm_in(M.layer_w(L, 5), 0);
+            a.part = c->d_part(); a.sstride = (size_t)m * D; a.ns = ns; a.h_out = c->d_h_pp(hp ^ 1);
+            hp ^= 1;
+        } else {
+            if ((rc = gemm_step_add(c, c->d_ao(), m, DQ, M.layer_w(L, 4), D, c->d_h_pp(hp)))) return rc;
+            a = norm_in(M.layer_w(L, 5), 0);
+        }
         // activation of the gate | up projection of norm(h + attention output)
-        a = norm_in(M.layer_w(L, 5), 0);
-        a.part = c->d_part(); a.sstride = (size_t)m * D; a.ns = ns; a.h_out = c->d_h_pp(hp ^ 1);
         a.out = (float*)c->d_act(); a.N = F; a.swiglu = d.act == METASD_SWIGLU;
-        if (a.swiglu) rc = gemm_step_norm<STEP_ACT, true>(c, a, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0);
-        else rc = gemm_step_norm<STEP_ACT, true>(c, a, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0);
+        const void *w0 = M.layer_w(L, a.swiglu ? 6 : 7), *w1 = a.swiglu ? M.layer_w(L, 7) : nullptr;
+        rc = nrec > 1 ? gemm_step_norm<STEP_ACT, true>(c, a, w0, F, w1, w1 ? F : 0, nullptr, 0)
+                      : gemm_step_norm<STEP_ACT, false>(c, a, w0, F, w1, w1 ? F : 0, nullptr, 0);
         if (rc) return rc;
-        hp ^= 1;
         // h += down projection
         if ((rc = gemm_step_add(c, c->d_act(), m, F, M.layer_w(L, 8), D, c->d_h_pp(hp)))) return rc;
     }
@@ -1084,15 +1086,12 @@ int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, 
 }
 
 // Short blocks (at most 8 rows) whose normalised rows fit in LDS, in general (verification, drafter heads, models wider than the path
-// above takes): 7 launches per layer, none of which leaves partial sums.  Verification of
-// 6 rows, per layer: 1B shape 59 -> 51 us, 7B shape 104 -> 101 us (gate | up and activation 36.1 -> 33.7, QKV 18.6 -> 20.0).
+// above takes): 6 launches per layer (5 where attention needs no merge), none of which leaves partial sums.
 constexpr int STEP_DMIN = 512;      // from here on each of the 16 wavefronts has a chunk of the input
 int forward_rows_step(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int first_row) {
     typedef bf16_t T;
     const metasd_model_desc& d = M.d;
-    const int D = d.d_model, H = d.n_heads, KH = d.n_kv_heads, hd = M.hd, F = d.d_ffn, V = d.vocab;
-    const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV;
-    hipStream_t st = c->stream;
+    const int D = d.d_model, F = d.d_ffn, V = d.vocab, DQ = d.n_heads * M.hd;
     float* h = c->d_h();
     int rc;
     if ((rc = embed_rows<T>(c, M, pos0, m, h))) return rc;
@@ -1106,15 +1105,7 @@ int forward_rows_step(metasd_ctx* c, Model& M, int pos0, int m, float* logits, i
     };
     for (int L = 0; L < d.n_layers; ++L) {
         StepArgs a = norm_in(M.layer_w(L, 0), 0);
-        a.out = c->d_part(); a.N = NQKV;
-        if ((rc = gemm_step_norm<STEP_OUT, false>(c, a, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV))) return rc;
-        const size_t plane = (size_t)KH * c->cfg.max_ctx * hd;
-        T* kc = (T*)M.kv + (size_t)L * 2 * plane;
-        // (forming q / k / v inside the attention kernel, as the path above does, was measured here and is slower at the 7B shape:
-        // 3.32 against 3.29 ms per pass - the wider kernel loses what the launch saves)
-        hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, c->d_part(), 1, (size_t)m * NQKV, NQKV, pos0, H, KH, hd,
-                           (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, hd >= 64 ? 1 : 0, (const float*)nullptr);
-        LAUNCH_CHECK(c, "rope_kv");
+        if ((rc = gemm_step_qkv(c, M, L, pos0, a))) return rc;
         if ((rc = attention<T>(c, M, L, pos0, m))) return rc;
         if ((rc = gemm_step_add(c, c->d_ao(), m, DQ, M.layer_w(L, 4), D, h))) return rc;
         a = norm_in(M.layer_w(L, 5), 0);

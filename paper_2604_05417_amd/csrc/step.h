@@ -11,6 +11,9 @@ namespace msd {
 //   STEP_TERMS  the input is given as two bf16 arrays (store_split4); each wavefront loads the operands of its slice straight into registers
 //   STEP_OUT    out[r][n] = sum          STEP_ADD  out[r][n] += sum (the residual stream)
 //   STEP_ACT    out = SiLU(gate) * up or GELU(up) as two bf16 arrays; with SwiGLU units 2 j and 2 j + 1 are gate and up of 16 features
+//   STEP_ROPE   q | k | v projection: q rotated into out (two bf16 arrays; one of floats when head_dim < 64), the rotated k and the v
+//               rows rounded into the cache.  The packed tiles keep both members of a rotary pair in one lane.  What was a launch of
+//               its own behind the projection (4.3 us of a 7B layer at 6 rows, 3.1 of a 1B one).
 // What bounds it: bytes of weights per CU at about 25 GB/s, and the chain launch - input - multiply - LDS - store in front of and behind
 // them (2.9 us for a kernel that does nothing else with one wide workgroup per CU, 4.5 us with 256 threads).  So the input is requested
 // first and the first group of weights before it is waited for: per wavefront 4 or 8 KiB with STEP_NORM, 4 with STEP_TERMS, 3 with half
@@ -19,7 +22,7 @@ namespace msd {
 // HALF: a unit is half a feature tile (8 features), so that a projection of d_model features has enough units for all CUs: one load
 // brings the 8 features of two neighbouring chunks, multiplied with the inputs of either one (two MFMAs, each good for 8 of its rows).
 enum { STEP_NORM = 0, STEP_TERMS = 1 };
-enum { STEP_OUT = 0, STEP_ADD = 1, STEP_ACT = 2 };
+enum { STEP_OUT = 0, STEP_ADD = 1, STEP_ACT = 2, STEP_ROPE = 3 };
 constexpr int STEP_ROWS = 8;
 
 struct StepArgs {
@@ -38,6 +41,9 @@ struct StepArgs {
     int N;                           // row length of out (ACT: d_ffn)
     int swiglu;                      // ACT
     int m, K, T, S, passes;          // T * S <= 16; a workgroup works through passes * T units (ADD: one pass)
+    const double2* tab;              // ROPE: rotations [m][hd / 2]
+    bf16_t *kc, *vc;                 // ROPE: cache planes of the layer, row r goes to position pos0 + r
+    int H, KH, hd, pos0, max_ctx;    // ROPE
 };
 
 // LDS of a launch: NORM [2 (hi, lo)][m][rs] 16-byte pieces and 16 sums of squares, then [16][64] partial tiles.
@@ -155,6 +161,7 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
                 if (gi * U + u < nl) mul1(b, u, gi * U + u);
         }
     };
+    double2 rot0 = make_double2(1.0, 0.0), rot1 = rot0;        // ROPE: rotations of this lane's two pairs
     for (int p = 0; p < a.passes; ++p) {
         acc0 = f32x4{0.f, 0.f, 0.f, 0.f};
         acc1 = acc0;
@@ -175,6 +182,11 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
             }
         }
         if (p + 1 < a.passes) { wp = unit_base(p + 1); issue(ba, wp, 0); }
+        if constexpr (EPI == STEP_ROPE) {          // arrives while the partial tiles are gathered
+            const int n = min(unit_of(p, min(wave, T - 1)), nunits - 1) * 16, half = a.hd >> 1;
+            const double2* t = a.tab + min(col, m - 1) * half + min(((n % a.hd) >> 1) + 2 * g, half - 2);
+            rot0 = t[0]; rot1 = t[1];
+        }
         if (p > 0) __syncthreads();                // the partial tiles of the pass before are read
         if constexpr (HALF) red[wave * 64 + lane] = g < 2 ? acc0 : acc1;
         else red[wave * 64 + lane] = acc0 + acc1;
@@ -208,6 +220,36 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
                 }
                 if (col < m && ft * 16 < a.N)
                     store_split4(a.out, (size_t)m * a.N, (size_t)col * a.N + ft * 16 + g * 4, make_float4(y[0], y[1], y[2], y[3]));
+            } else if constexpr (EPI == STEP_ROPE) {
+                const f32x4 y = unit_sum(wave);
+                const int n = unit_of(p, wave) * 16, hd = a.hd, half = hd >> 1, head = n / hd, c = n - head * hd;
+                if (col < m && unit_of(p, wave) < nunits) {
+                    const float v[4] = {y[0] * inv, y[1] * inv, y[2] * inv, y[3] * inv};
+                    // packed columns c + 4 g .. are the pairs i, i + 1 (first and second member, hd / 2 apart)
+                    const int i = (c >> 1) + 2 * g;
+                    const float a0 = (float)((double)v[0] * rot0.x - (double)v[1] * rot0.y), b0 = (float)((double)v[0] * rot0.y + (double)v[1] * rot0.x);
+                    const float a1 = (float)((double)v[2] * rot1.x - (double)v[3] * rot1.y), b1 = (float)((double)v[2] * rot1.y + (double)v[3] * rot1.x);
+                    const uint32_t ah = f2bf2(a0, a1), bh = f2bf2(b0, b1);
+                    const size_t pos = (size_t)a.pos0 + col;
+                    if (head >= a.H + a.KH) {
+                        *reinterpret_cast<uint2*>(a.vc + ((size_t)(head - a.H - a.KH) * a.max_ctx + pos) * hd + c + 4 * g) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+                    } else if (head >= a.H) {
+                        bf16_t* k = a.kc + ((size_t)(head - a.H) * a.max_ctx + pos) * hd + i;
+                        *reinterpret_cast<uint32_t*>(k) = ah;
+                        *reinterpret_cast<uint32_t*>(k + half) = bh;
+                    } else if (hd >= 64) {
+                        bf16_t* qh = reinterpret_cast<bf16_t*>(a.out) + ((size_t)col * a.H + head) * hd + i;
+                        bf16_t* ql = qh + (size_t)m * a.H * hd;
+                        *reinterpret_cast<uint32_t*>(qh) = ah;
+                        *reinterpret_cast<uint32_t*>(qh + half) = bh;
+                        *reinterpret_cast<uint32_t*>(ql) = f2bf2(a0 - __uint_as_float(ah << 16), a1 - __uint_as_float(ah & 0xffff0000u));
+                        *reinterpret_cast<uint32_t*>(ql + half) = f2bf2(b0 - __uint_as_float(bh << 16), b1 - __uint_as_float(bh & 0xffff0000u));
+                    } else {
+                        float* q = a.out + ((size_t)col * a.H + head) * hd + i;
+                        *reinterpret_cast<float2*>(q) = make_float2(a0, a1);
+                        *reinterpret_cast<float2*>(q + half) = make_float2(b0, b1);
+                    }
+                }
             } else {
                 const f32x4 y = unit_sum(wave);
                 const int u = unit_of(p, wave);
