@@ -1234,34 +1234,47 @@ const RowsPlan& rows_plan(metasd_ctx* c, int ntiles, int kchunks, int R, int gro
     return e.plan;
 }
 
+// One launch of the many-row GEMM.  out, N: partials [ks][R][N] or what the epilogue writes.
+struct TilesLaunch {
+    const bf16_t* x;
+    int R, K;
+    const void *W0, *W1, *W2;
+    int t0, t1, ntiles;
+    const RowGroups* gg;
+    float* out;
+    int N;
+    TilesEpi ep;
+};
+
 // more than 64 KiB of dynamic LDS needs the function attribute (set once per variant)
-template <int RB, int TB>
-int launch_gemm_tiles(metasd_ctx* c, const bf16_t* x, int R, int K, const void* W0, const void* W1, const void* W2, int t0, int t1,
-                      int ntiles, const RowsPlan& s, const RowGroups* gg, metasd_ctx::ProfRec* pr) {
+template <int RB, int TB, int EPI>
+int launch_gemm_tiles(metasd_ctx* c, const TilesLaunch& a, const RowsPlan& s, metasd_ctx::ProfRec* pr) {
     constexpr int NS = rows_stages(RB, TB);
     constexpr int lds = NS * (8192 * RB + 2048 * TB);
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     const hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
-    const dim3 grid(s.nrb * s.ngroups * s.ksplit, gg ? gg->n : 1);
-    const int N = ntiles * 16;
-    if (gg) {
-        static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tiles_grouped_kernel<RB, TB, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (attr != hipSuccess) return c->fail(METASD_E_HIP, "gemm_tiles_grouped_kernel: cannot reserve %d bytes of LDS", lds);
-        hipExtLaunchKernelGGL((gemm_tiles_grouped_kernel<RB, TB, NS>), grid, dim3(512), (uint32_t)lds, c->stream, ea, eb, 0u, x, K / 32, t0, t1,
-                              ntiles, c->d_part(), (size_t)R * N, N, s.cps, s.nrb, *gg);
+    const dim3 grid(s.nrb * s.ngroups * s.ksplit, a.gg ? a.gg->n : 1);
+    if (a.gg) {
+        if constexpr (EPI == TILES_PART || EPI == TILES_ACT) {
+            static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tiles_grouped_kernel<RB, TB, NS, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (attr != hipSuccess) return c->fail(METASD_E_HIP, "gemm_tiles_grouped_kernel: cannot reserve %d bytes of LDS", lds);
+            hipExtLaunchKernelGGL((gemm_tiles_grouped_kernel<RB, TB, NS, EPI>), grid, dim3(512), (uint32_t)lds, c->stream, ea, eb, 0u, a.x, a.K / 32, a.t0,
+                                  a.t1, a.ntiles, a.out, (size_t)a.R * a.N, a.N, s.cps, s.nrb, *a.gg, a.ep);
+        }
     } else {
-        static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tiles_kernel<RB, TB, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tiles_kernel<RB, TB, NS, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (attr != hipSuccess) return c->fail(METASD_E_HIP, "gemm_tiles_kernel: cannot reserve %d bytes of LDS", lds);
-        hipExtLaunchKernelGGL((gemm_tiles_kernel<RB, TB, NS>), grid, dim3(512), (uint32_t)lds, c->stream, ea, eb, 0u, x, R, K / 32, (const bf16_t*)W0,
-                              (const bf16_t*)W1, (const bf16_t*)W2, t0, t1, ntiles, c->d_part(), (size_t)R * N, N, s.cps, s.nrb);
+        hipExtLaunchKernelGGL((gemm_tiles_kernel<RB, TB, NS, EPI>), grid, dim3(512), (uint32_t)lds, c->stream, ea, eb, 0u, a.x, a.R, a.K / 32,
+                              (const bf16_t*)a.W0, (const bf16_t*)a.W1, (const bf16_t*)a.W2, a.t0, a.t1, a.ntiles, a.out, (size_t)a.R * a.N, a.N, s.cps,
+                              s.nrb, a.ep);
     }
     LAUNCH_CHECK(c, "gemm_tiles");
     return 0;
 }
 
-int launch_gemm_tiles_any(metasd_ctx* c, const void* x, int R, int K, const void* W0, const void* W1, const void* W2, int t0, int t1,
-                          int ntiles, const RowsPlan& s, const RowGroups* gg, metasd_ctx::ProfRec* pr) {
-#define TILES_GO(RB, TB) if (s.rb == RB && s.tb == TB) return launch_gemm_tiles<RB, TB>(c, (const bf16_t*)x, R, K, W0, W1, W2, t0, t1, ntiles, s, gg, pr)
+template <int EPI>
+int launch_gemm_tiles_any(metasd_ctx* c, const TilesLaunch& a, const RowsPlan& s, metasd_ctx::ProfRec* pr) {
+#define TILES_GO(RB, TB) if (s.rb == RB && s.tb == TB) return launch_gemm_tiles<RB, TB, EPI>(c, a, s, pr)
     TILES_GO(4, 6); TILES_GO(3, 8); TILES_GO(3, 6); TILES_GO(3, 4); TILES_GO(2, 8); TILES_GO(2, 6);
     TILES_GO(2, 4); TILES_GO(2, 3); TILES_GO(1, 8); TILES_GO(1, 6); TILES_GO(1, 4); TILES_GO(1, 2);
 #undef TILES_GO
@@ -1279,7 +1292,48 @@ int gemm_rows<bf16_t>(metasd_ctx* c, const void* x, int ldx, int R, int K, const
     const RowsPlan& s = rows_plan(c, N / 16, K / 32, R, 1);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)N * K * 2 + (double)R * K * 4 + (double)R * N * 4 * s.ksplit, N, K, R);
     *nsplit_out = s.ksplit;
-    return launch_gemm_tiles_any(c, x, R, K, W0, W1, W2, n0 / 16, (n0 + n1) / 16, N / 16, s, nullptr, pr);
+    return launch_gemm_tiles_any<TILES_PART>(c, TilesLaunch{(const bf16_t*)x, R, K, W0, W1, W2, n0 / 16, (n0 + n1) / 16, N / 16, nullptr, c->d_part(), N, {}}, s, pr);
+}
+
+// h += x W^T where the plan leaves K whole (*nsplit_out = 0: nothing is left to add), else the partials
+template <typename T>
+int gemm_rows_add(metasd_ctx* c, const void* x, int R, int K, const void* W, int N, float* h, int* nsplit_out) {
+    if constexpr (sizeof(T) == 2) {
+        if (R > MAX_ROWS && rows_plan(c, N / 16, K / 32, R, 1).ksplit == 1) {
+            const RowsPlan& s = rows_plan(c, N / 16, K / 32, R, 1);
+            metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)N * K * 2 + (double)R * K * 4 + (double)R * N * 4, N, K, R);
+            *nsplit_out = 0;
+            return launch_gemm_tiles_any<TILES_ADD>(c, TilesLaunch{(const bf16_t*)x, R, K, W, W, W, N / 16, N / 16, N / 16, nullptr, h, N, {}}, s, pr);
+        }
+    }
+    return gemm_rows<T>(c, x, K, R, K, W, N, nullptr, 0, nullptr, 0, nsplit_out);
+}
+
+// The activations of layer L's FFN from the normalised rows x (d_act; split as the rows are): in the projection's own launch where
+// its plan leaves K whole, else from its partials.
+template <typename T>
+int gemm_rows_act(metasd_ctx* c, const Model& M, int L, const void* x, int R, int split) {
+    const metasd_model_desc& d = M.d;
+    const int D = d.d_model, F = d.d_ffn, sw = d.act == METASD_SWIGLU, NF = (sw ? 2 : 1) * F;
+    const void *w0 = M.layer_w(L, sw ? 6 : 7), *w1 = sw ? M.layer_w(L, 7) : nullptr;
+    if constexpr (sizeof(T) == 2) {
+        if (R > MAX_ROWS) {
+            const RowsPlan& s = rows_plan(c, NF / 16, D / 32, R, 1);
+            if (s.ksplit == 1 && (!sw || s.tb % 2 == 0)) {
+                metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)NF * D * 2 + (double)R * D * 4 + (double)R * F * 4, NF, D, R);
+                TilesEpi ep{};
+                ep.swiglu = sw;
+                return launch_gemm_tiles_any<TILES_ACT>(c, TilesLaunch{(const bf16_t*)x, R, D, w0, w1, w1, F / 16, NF / 16, NF / 16, nullptr, (float*)c->d_act(), F, ep}, s, pr);
+            }
+        }
+    }
+    int ns = 0;
+    if (int rc = gemm_rows<T>(c, x, D, R, D, w0, F, w1, sw ? F : 0, nullptr, 0, &ns)) return rc;
+    const size_t nact = (size_t)R * F;
+    hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, c->stream, (const float*)c->d_part(), ns, (size_t)R * NF, R, F, d.act,
+                       (float*)c->d_act(), split, (const float*)nullptr);
+    LAUNCH_CHECK(c, "ffn_act");
+    return 0;
 }
 
 template <typename T, int HD>
@@ -1396,20 +1450,11 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
                            (split && hd >= 64) ? 1 : 0);
         LAUNCH_CHECK(c, "rope_kv (segments)");
         if ((rc = attention_seg<T>(c, M, L, sg))) return rc;
-        if ((rc = gemm_rows<T>(c, c->d_ao(), DQ, R, DQ, M.layer_w(L, 4), D, nullptr, 0, nullptr, 0, &ns))) return rc;
+        if ((rc = gemm_rows_add<T>(c, c->d_ao(), R, DQ, M.layer_w(L, 4), D, h, &ns))) return rc;
         launch_addnorm_many<T>(c, R, h, part, ns, D, (const T*)M.layer_w(L, 5), d.rms_eps, xn, split);
         LAUNCH_CHECK(c, "addnorm");
-        if (d.act == METASD_SWIGLU) {
-            if ((rc = gemm_rows<T>(c, xn, D, R, D, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0, &ns))) return rc;
-        } else {
-            if ((rc = gemm_rows<T>(c, xn, D, R, D, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0, &ns))) return rc;
-        }
-        const size_t nact = (size_t)R * F;
-        const int NF = (d.act == METASD_SWIGLU ? 2 : 1) * F;
-        hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, st, part, ns, (size_t)R * NF, R, F, d.act,
-                           (float*)c->d_act(), split, (const float*)nullptr);
-        LAUNCH_CHECK(c, "ffn_act");
-        if ((rc = gemm_rows<T>(c, c->d_act(), F, R, F, M.layer_w(L, 8), D, nullptr, 0, nullptr, 0, &ns))) return rc;
+        if ((rc = gemm_rows_act<T>(c, M, L, xn, R, split))) return rc;
+        if ((rc = gemm_rows_add<T>(c, c->d_act(), R, F, M.layer_w(L, 8), D, h, &ns))) return rc;
     }
     if (logits) {
         launch_addnorm_many<T>(c, R, h, part, ns, D, (const T*)M.final_norm(), d.rms_eps, xn, split);
@@ -1432,7 +1477,7 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
     typedef bf16_t T;
     const metasd_model_desc& d = M.d;
     const int D = d.d_model, H = d.n_heads, KH = d.n_kv_heads, hd = M.hd, F = d.d_ffn;
-    const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV, NF = (d.act == METASD_SWIGLU ? 2 : 1) * F;
+    const int DQ = H * hd, DKV = KH * hd, NQKV = DQ + 2 * DKV;
     hipStream_t st = c->stream;
     float* h = c->d_h();
     float* xn = (float*)c->d_xn();
@@ -1463,24 +1508,26 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
         for (int L = 0; L < d.n_layers; ++L) {
             launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 0), d.rms_eps, xn, split);
             LAUNCH_CHECK(c, "addnorm");
-            if ((rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV, &ns))) return rc;
             T* kc = kv + (size_t)L * 2 * plane;
-            hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, part, ns, (size_t)m * NQKV, NQKV, p0, H, KH, hd,
-                               (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, 1, (const float*)nullptr);
-            LAUNCH_CHECK(c, "rope_kv");
+            const RowsPlan* pl = m > MAX_ROWS ? &rows_plan(c, NQKV / 16, D / 32, m, 1) : nullptr;
+            if (pl && pl->ksplit == 1) {
+                metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)NQKV * D * 2 + (double)m * D * 4 + (double)m * NQKV * 4, NQKV, D, m);
+                const TilesEpi ep{0, 0, (const double2*)c->d_rope(), kc, kc + plane, H, KH, hd, p0, c->cfg.max_ctx};
+                if ((rc = launch_gemm_tiles_any<TILES_ROPE>(c, TilesLaunch{(const bf16_t*)xn, m, D, M.layer_w(L, 1), M.layer_w(L, 2), M.layer_w(L, 3), DQ / 16,
+                                                                          (DQ + DKV) / 16, NQKV / 16, nullptr, (float*)c->d_q(), DQ, ep}, *pl, pr))) return rc;
+            } else {
+                if ((rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV, &ns))) return rc;
+                hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, part, ns, (size_t)m * NQKV, NQKV, p0, H, KH, hd,
+                                   (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, 1, (const float*)nullptr);
+                LAUNCH_CHECK(c, "rope_kv");
+            }
             if (L + 1 == d.n_layers && !features) break;
             if ((rc = attention_big(c, d, hd, kc, kc + plane, p0, m))) return rc;
-            if ((rc = gemm_rows<T>(c, c->d_ao(), DQ, m, DQ, M.layer_w(L, 4), D, nullptr, 0, nullptr, 0, &ns))) return rc;
+            if ((rc = gemm_rows_add<T>(c, c->d_ao(), m, DQ, M.layer_w(L, 4), D, h, &ns))) return rc;
             launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 5), d.rms_eps, xn, split);
             LAUNCH_CHECK(c, "addnorm");
-            if (d.act == METASD_SWIGLU) rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0, &ns);
-            else rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0, &ns);
-            if (rc) return rc;
-            const size_t nact = (size_t)m * F;
-            hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, st, part, ns, (size_t)m * NF, m, F, d.act,
-                               (float*)c->d_act(), split, (const float*)nullptr);
-            LAUNCH_CHECK(c, "ffn_act");
-            if ((rc = gemm_rows<T>(c, c->d_act(), F, m, F, M.layer_w(L, 8), D, nullptr, 0, nullptr, 0, &ns))) return rc;
+            if ((rc = gemm_rows_act<T>(c, M, L, xn, m, split))) return rc;
+            if ((rc = gemm_rows_add<T>(c, c->d_act(), m, F, M.layer_w(L, 8), D, h, &ns))) return rc;
         }
         if (features) {
             launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.final_norm(), d.rms_eps, xn, split);   // finishes the residual rows
@@ -1525,14 +1572,21 @@ bool grouped_step_supported(const metasd_ctx* c) {
 }
 
 // x: R rows, interleaved (store_terms4, split = 2); gg: the row groups and their matrices.
-int gemm_rows_grouped(metasd_ctx* c, const void* x, int R, int K, const RowGroups& gg, int n0, int n1, int n2, int* nsplit_out) {
+// act >= 0 (METASD_GELU, METASD_SWIGLU): the activations in d_act instead of partials where the plan leaves K whole (*nsplit_out = 0).
+int gemm_rows_grouped(metasd_ctx* c, const void* x, int R, int K, const RowGroups& gg, int n0, int n1, int n2, int* nsplit_out, int act = -1) {
     const int N = n0 + n1 + n2;
     int mmax = 1;
     for (int g = 0; g < gg.n; ++g) mmax = std::max(mmax, gg.m[g]);
     const RowsPlan& s = rows_plan(c, N / 16, K / 32, mmax, gg.n);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)gg.n * N * K * 2 + (double)R * K * 4 + (double)R * N * 4 * s.ksplit, N, K, R);
+    TilesLaunch a{(const bf16_t*)x, R, K, nullptr, nullptr, nullptr, n0 / 16, (n0 + n1) / 16, N / 16, &gg, c->d_part(), N, {}};
+    if (act >= 0 && s.ksplit == 1 && (act != METASD_SWIGLU || s.tb % 2 == 0)) {
+        a.out = (float*)c->d_act(); a.N = n0; a.ep.swiglu = act == METASD_SWIGLU;
+        *nsplit_out = 0;
+        return launch_gemm_tiles_any<TILES_ACT>(c, a, s, pr);
+    }
     *nsplit_out = s.ksplit;
-    return launch_gemm_tiles_any(c, x, R, K, nullptr, nullptr, nullptr, n0 / 16, (n0 + n1) / 16, N / 16, s, &gg, pr);
+    return launch_gemm_tiles_any<TILES_PART>(c, a, s, pr);
 }
 
 // sg: the segments ordered by arm (ms <= 16 rows each, at most 256 rows per arm); arm[s]: the drafter of segment s.
@@ -1616,16 +1670,14 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
         hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
                            seg_ptrs([&](const Model& M, int) { return (const void*)M.layer_w(L, 5); }), sg.ms, d.rms_eps, xn, 2);
         LAUNCH_CHECK(c, "addnorm (grouped)");
-        if (d.act == METASD_SWIGLU) {
-            if ((rc = gemm_rows_grouped(c, xn, R, D, weights(L, 6, 7, -1), F, F, 0, &ns))) return rc;
-        } else {
-            if ((rc = gemm_rows_grouped(c, xn, R, D, weights(L, 7, -1, -1), F, 0, 0, &ns))) return rc;
+        const int sw = d.act == METASD_SWIGLU, NF = (sw ? 2 : 1) * F;
+        if ((rc = gemm_rows_grouped(c, xn, R, D, sw ? weights(L, 6, 7, -1) : weights(L, 7, -1, -1), F, sw ? F : 0, 0, &ns, d.act))) return rc;
+        if (ns) {
+            const size_t nact = (size_t)R * F;
+            hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, st, part, ns, (size_t)R * NF, R, F, d.act,
+                               (float*)c->d_act(), 2, (const float*)nullptr);
+            LAUNCH_CHECK(c, "ffn_act");
         }
-        const size_t nact = (size_t)R * F;
-        const int NF = (d.act == METASD_SWIGLU ? 2 : 1) * F;
-        hipLaunchKernelGGL(ffn_act4_kernel, dim3((unsigned)((nact / 4 + 255) / 256)), dim3(256), 0, st, part, ns, (size_t)R * NF, R, F, d.act,
-                           (float*)c->d_act(), 2, (const float*)nullptr);
-        LAUNCH_CHECK(c, "ffn_act");
         if ((rc = gemm_rows_grouped(c, c->d_act(), R, F, weights(L, 8, -1, -1), D, 0, 0, &ns))) return rc;
     }
     hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
