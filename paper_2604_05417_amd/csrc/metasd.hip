@@ -1394,14 +1394,12 @@ int attention_seg(metasd_ctx* c, const Model& M, int L, const Segs& sg) {
 // workgroup for every CU, else 16.
 int attention_big(metasd_ctx* c, const metasd_model_desc& d, int hd, const bf16_t* kc, const bf16_t* vc, int pos0, int m) {
     const float scale = 1.0f / sqrtf((float)hd);
-    const bool two = (size_t)((m + 127) / 128) * d.n_heads >= (size_t)c->n_cu;
-    const int nblk = two ? (m + 127) / 128 : (m + 63) / 64;
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * (double)(pos0 + m) * hd * 2 + (double)m * d.n_heads * hd * 4);
     hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
-#define BIG_GO(HD, RB) hipExtLaunchKernelGGL((attn_prefill_kernel<HD, RB>), dim3(nblk * d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u, \
-                                             (const bf16_t*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, (float*)c->d_ao(), rows_split(m))
-    if (hd == 128) { if (two) BIG_GO(128, 2); else BIG_GO(128, 1); }
-    else { if (two) BIG_GO(64, 2); else BIG_GO(64, 1); }
+#define BIG_GO(HD) hipExtLaunchKernelGGL((attn_prefill_kernel<HD>), dim3((m + 63) / 64 * d.n_heads), dim3(256), 0u, c->stream, ea, eb, 0u, \
+                                         (const bf16_t*)c->d_q(), kc, vc, m, pos0, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, (float*)c->d_ao(), rows_split(m))
+    if (hd == 128) BIG_GO(128);
+    else BIG_GO(64);
 #undef BIG_GO
     LAUNCH_CHECK(c, "attn_prefill");
     return 0;
