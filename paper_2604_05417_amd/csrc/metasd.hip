@@ -909,7 +909,8 @@ int forward_rows(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int fi
     return 0;
 }
 
-// fp32 models of narrow rows (step_f32.h): five launches per layer instead of ten, six when the context has more than one chunk.
+// fp32 models of narrow rows (step_f32.h): four launches per layer instead of ten while the context is short, then five, six when it has
+// more than one chunk.
 bool f32_step_ok(const Model& M) { return M.d.dtype == METASD_F32 && M.d.d_model <= STEP_F32_K; }
 
 template <int NF, bool NORM, int EPI>
@@ -921,6 +922,32 @@ int launch_f32_step(metasd_ctx* c, const F32Args& a, const char* what) {
     else if (a.m <= 8) hipLaunchKernelGGL((gemm_f32_step_kernel<8, NF, NORM, EPI>), grid, dim3(256), lds, c->stream, a);
     else hipLaunchKernelGGL((gemm_f32_step_kernel<16, NF, NORM, EPI>), grid, dim3(256), lds, c->stream, a);
     LAUNCH_CHECK(c, what);
+    return 0;
+}
+
+// Contexts short enough for attention and output projection in one launch, h += ..: one row over 128 positions (head_dim 64: 64), several
+// rows over 64 (head_dim 32).
+bool f32_attn_out_ok(const Model& M, int m, int len) {
+    return M.d.n_heads * M.hd <= STEP_F32_K && len <= (m == 1 && M.hd == 32 ? 128 : 64) && (m == 1 || M.hd == 32);
+}
+int launch_f32_attn_out(metasd_ctx* c, const Model& M, int L, int pos0, int m, const float* W, float* h) {
+    const metasd_model_desc& d = M.d;
+    const size_t plane = (size_t)d.n_kv_heads * c->cfg.max_ctx * M.hd;
+    const float* kc = (const float*)M.kv + (size_t)L * 2 * plane;
+    const float scale = 1.0f / sqrtf((float)M.hd);
+    const int len = pos0 + m;
+    metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * (double)len * M.hd * 4 + (double)m * d.n_heads * M.hd * 4);
+#define AO_GO(KERNEL, NW, ...) hipExtLaunchKernelGGL(KERNEL, dim3((d.d_model + NW - 1) / NW), dim3(64 * NW), 0u, c->stream, pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, \
+                                                     (const float*)c->d_q(), kc, kc + plane, W, h, __VA_ARGS__, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale, d.d_model, \
+                                                     c->tree ? *c->tree : TreeBlk{})
+    if (m == 1) {
+        if (M.hd == 64) AO_GO((attn_out_f32_kernel<64, 1>), 4, pos0);
+        else if (len <= 64) AO_GO((attn_out_f32_kernel<32, 1>), 4, pos0);
+        else AO_GO((attn_out_f32_kernel<32, 2>), 4, pos0);
+    } else if (m <= 8) AO_GO((attn_out_rows_f32_kernel<8>), 16, m, pos0);
+    else AO_GO((attn_out_rows_f32_kernel<16>), 16, m, pos0);
+#undef AO_GO
+    LAUNCH_CHECK(c, "attention and output projection");
     return 0;
 }
 
@@ -942,10 +969,14 @@ int forward_rows_f32(metasd_ctx* c, Model& M, int pos0, int m, float* logits, in
         a.out = (float*)c->d_q(); a.ldo = H * hd; a.units = (H + 2 * KH) * (hd / 2);
         a.kc = (float*)M.kv + (size_t)L * 2 * plane; a.vc = a.kc + plane;
         if ((rc = launch_f32_step<2, true, F32_ROPE>(c, a, "gemm_f32 (q, k, v)"))) return rc;
-        if ((rc = attention<T>(c, M, L, pos0, m))) return rc;
-        a = base;                                   // h += output projection
-        a.x = (const float*)c->d_ao(); a.W0 = W(4); a.K = H * hd; a.out = h; a.ldo = D; a.units = D;
-        if ((rc = launch_f32_step<1, false, F32_ADD>(c, a, "gemm_f32 (output)"))) return rc;
+        if (f32_attn_out_ok(M, m, pos0 + m)) {
+            if ((rc = launch_f32_attn_out(c, M, L, pos0, m, W(4), h))) return rc;
+        } else {
+            if ((rc = attention<T>(c, M, L, pos0, m))) return rc;
+            a = base;                               // h += output projection
+            a.x = (const float*)c->d_ao(); a.W0 = W(4); a.K = H * hd; a.out = h; a.ldo = D; a.units = D;
+            if ((rc = launch_f32_step<1, false, F32_ADD>(c, a, "gemm_f32 (output)"))) return rc;
+        }
         a = base;                                   // activation of the FFN
         a.x = h; a.gain = W(5); a.K = D; a.out = (float*)c->d_act(); a.ldo = F; a.units = F;
         if (d.act == METASD_SWIGLU) { a.W0 = W(6); a.W1 = W(7); rc = launch_f32_step<2, true, F32_ACT>(c, a, "gemm_f32 (gate, up)"); }

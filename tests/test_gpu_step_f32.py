@@ -35,3 +35,20 @@ def test_f32_layers(i, fuse, monkeypatch):
         ls.round(arm)
     g.close()
     assert ls.stats["max_dp"] <= TOL and ls.stats["max_dq"] <= TOL and ls.stats["ties_shared"] <= 1, ls.stats
+
+
+@pytest.mark.parametrize("d,H,KH,n,gamma", [(96, 3, 1, 30, 1), (256, 8, 8, 55, 7), (512, 16, 4, 117, 5), (256, 4, 2, 46, 15), (128, 2, 2, 60, 3)])
+def test_f32_attention_with_output_projection(d, H, KH, n, gamma):
+    """Attention and output projection in one launch (contexts of up to 128 positions at head_dim 32, 64 at head_dim 64), with rounds that
+    grow past 64 and 128 positions: the two forms of the kernel and the path behind them, every block height, grouped queries."""
+    td, dd = W.model_desc(2, d, H, KH, 132, 260, W.GELU, W.FP32), W.model_desc(1, d, H, KH, 68, 260, W.SWIGLU, W.FP32)
+    tw, dw = W.gen_weights(td, 0), W.gen_weights(dd, 7)
+    max_ctx, prompt = n + 5 * (gamma + 1) + 8, W.prompt_tokens(n, 260, 3)
+    g = M.MetaSD((td, tw), [(dd, dw)], gamma_max=gamma, max_ctx=max_ctx, temperature=1.0, seed=4)
+    ot, od = oracle.Model(td, W.to_numpy(tw), max_ctx), [oracle.Model(dd, W.to_numpy(dw), max_ctx)]
+    g.set_context(prompt)
+    ls = LockStep(g, ot, od, prompt, gamma, 1.0, 4, 1.0, logit_tol=TOL)
+    for _ in range(4):
+        ls.round(0)
+    g.close()
+    assert ls.stats["max_dp"] <= TOL and ls.stats["max_dq"] <= TOL and ls.stats["ties_shared"] <= 1, ls.stats
