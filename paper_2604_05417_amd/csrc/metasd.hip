@@ -126,7 +126,11 @@ constexpr int rows_stages(int rb, int tb) {
     return rb * 8 + tb * 2 >= 40 ? 3 : rb * 8 + tb * 2 >= 28 || (rb == 2 && tb == 4) || (rb == 1 && tb <= 4) ? 4 : 6;
 }
 
-RowsPlan plan_rows(int ntiles, int kchunks, int R, int groups, int forced_tpb, int forced_rb) {
+//   behind: what is done with the sums besides storing them, in the launch itself where K is whole (TILES_ACT: pairs of tiles for SwiGLU;
+// TILES_ROPE), else in a launch of its own, which costs 3 us and their traffic again.  256 rows, gate | up of the 7B shape: two K halves
+// of 256-row tiles 90 + 8 us with the activation, 128-row tiles over the whole K 83 us.
+enum { BEHIND_NONE = 0, BEHIND_ACT = 1, BEHIND_PAIRS = 2, BEHIND_ROPE = 3 };
+RowsPlan plan_rows(int ntiles, int kchunks, int R, int groups, int forced_tpb, int forced_rb, int behind) {
     RowsPlan best{};
     double best_cost = 1e30;
     const double stream = (double)groups * ntiles * kchunks * 1024 / 5.6e6;
@@ -139,11 +143,14 @@ RowsPlan plan_rows(int ntiles, int kchunks, int R, int groups, int forced_tpb, i
             const int cps = (kchunks + ks - 1) / ks, k2 = (kchunks + cps - 1) / cps;
             const double rounds = (nrb * ng * k2 * groups + 255) / 256;
             const double mult = rounds * cps * (0.115 + 0.044 * rb * tb);
-            const double cost = std::max(mult, stream) + 0.15 * std::min(mult, stream) + (double)k2 * R * groups * ntiles * 64 * 1.2 / 5e6;
+            const double sums = (double)R * groups * ntiles * 64 / 5e6;      // R: rows of a group
+            const bool whole = k2 == 1 && (behind != BEHIND_PAIRS || tb % 2 == 0);
+            const double cost = std::max(mult, stream) + 0.15 * std::min(mult, stream) +
+                                (behind == BEHIND_NONE ? 1.2 * k2 * sums : whole ? 0.6 * sums : 1.2 * k2 * sums + 3 + 0.5 * sums);
             if (cost < best_cost) { best_cost = cost; best = RowsPlan{rb, tb, k2, cps, nrb, ng}; }
         }
     }
-    return best.rb ? best : plan_rows(ntiles, kchunks, R, groups, 0, 0);   // a forced pair that is no tile
+    return best.rb ? best : plan_rows(ntiles, kchunks, R, groups, 0, 0, behind);   // a forced pair that is no tile
 }
 
 const char* check_model(const metasd_model_desc& d, const char* who, char* buf, size_t n) {
@@ -454,7 +461,7 @@ struct metasd_ctx {
     int att_cpw = 0;                 // attention of short blocks: passes of 128 positions per workgroup, 0 = plan_attn (METASD_ATT_CPW=1..64 forces them)
     int rows_tpb = 0;                // many-row GEMM: feature tiles per workgroup, 0 = by the cost model (METASD_ROWS_TPB=4|6|8|12|16 forces one)
     int rows_rb = 0;                 // .. and its rows in units of 64 (METASD_ROWS_RB=1..4)
-    struct { int ntiles, kchunks, R, groups; RowsPlan plan; } plans[64] = {};   // rows_plan
+    struct { int ntiles, kchunks, R, groups, behind; RowsPlan plan; } plans[64] = {};   // rows_plan
     bool fullk_roll = true;          // .. and larger inputs with rolling private staging (METASD_GEMM_ROLL=0: sibling reduction instead)
     bool gemm_reduce = true;         // bf16 models: residual GEMMs reduce their split-K partials themselves (METASD_GEMM_REDUCE=0: off)
     float cur_eps = 1e-5f;           // rms_eps of the model whose forward is being launched
@@ -1256,11 +1263,11 @@ int gemm_rows<float>(metasd_ctx* c, const void* x, int ldx, int R, int K, const 
 }
 
 // The plan of a many-row launch, kept per shape (a forward repeats a handful of them; the search takes a microsecond or two).
-const RowsPlan& rows_plan(metasd_ctx* c, int ntiles, int kchunks, int R, int groups) {
-    auto& e = c->plans[(unsigned)(ntiles * 31 + kchunks * 17 + R * 5 + groups) % (sizeof c->plans / sizeof c->plans[0])];
-    if (e.ntiles != ntiles || e.kchunks != kchunks || e.R != R || e.groups != groups) {
-        e.ntiles = ntiles; e.kchunks = kchunks; e.R = R; e.groups = groups;
-        e.plan = plan_rows(ntiles, kchunks, R, groups, c->rows_tpb, c->rows_rb);
+const RowsPlan& rows_plan(metasd_ctx* c, int ntiles, int kchunks, int R, int groups, int behind = BEHIND_NONE) {
+    auto& e = c->plans[(unsigned)(ntiles * 31 + kchunks * 17 + R * 5 + groups + behind) % (sizeof c->plans / sizeof c->plans[0])];
+    if (e.ntiles != ntiles || e.kchunks != kchunks || e.R != R || e.groups != groups || e.behind != behind) {
+        e.ntiles = ntiles; e.kchunks = kchunks; e.R = R; e.groups = groups; e.behind = behind;
+        e.plan = plan_rows(ntiles, kchunks, R, groups, c->rows_tpb, c->rows_rb, behind);
     }
     return e.plan;
 }
@@ -1349,7 +1356,7 @@ int gemm_rows_act(metasd_ctx* c, const Model& M, int L, const void* x, int R, in
     const void *w0 = M.layer_w(L, sw ? 6 : 7), *w1 = sw ? M.layer_w(L, 7) : nullptr;
     if constexpr (sizeof(T) == 2) {
         if (R > MAX_ROWS) {
-            const RowsPlan& s = rows_plan(c, NF / 16, D / 32, R, 1);
+            const RowsPlan& s = rows_plan(c, NF / 16, D / 32, R, 1, sw ? BEHIND_PAIRS : BEHIND_ACT);
             if (s.ksplit == 1 && (!sw || s.tb % 2 == 0)) {
                 metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)NF * D * 2 + (double)R * D * 4 + (double)R * F * 4, NF, D, R);
                 TilesEpi ep{};
@@ -1538,7 +1545,7 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
             launch_addnorm_many<T>(c, m, h, part, ns, D, (const T*)M.layer_w(L, 0), d.rms_eps, xn, split);
             LAUNCH_CHECK(c, "addnorm");
             T* kc = kv + (size_t)L * 2 * plane;
-            const RowsPlan* pl = m > MAX_ROWS ? &rows_plan(c, NQKV / 16, D / 32, m, 1) : nullptr;
+            const RowsPlan* pl = m > MAX_ROWS ? &rows_plan(c, NQKV / 16, D / 32, m, 1, BEHIND_ROPE) : nullptr;
             if (pl && pl->ksplit == 1) {
                 metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)NQKV * D * 2 + (double)m * D * 4 + (double)m * NQKV * 4, NQKV, D, m);
                 const TilesEpi ep{0, 0, (const double2*)c->d_rope(), kc, kc + plane, H, KH, hd, p0, c->cfg.max_ctx};
@@ -1606,7 +1613,7 @@ int gemm_rows_grouped(metasd_ctx* c, const void* x, int R, int K, const RowGroup
     const int N = n0 + n1 + n2;
     int mmax = 1;
     for (int g = 0; g < gg.n; ++g) mmax = std::max(mmax, gg.m[g]);
-    const RowsPlan& s = rows_plan(c, N / 16, K / 32, mmax, gg.n);
+    const RowsPlan& s = rows_plan(c, N / 16, K / 32, mmax, gg.n, act < 0 ? BEHIND_NONE : act == METASD_SWIGLU ? BEHIND_PAIRS : BEHIND_ACT);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)gg.n * N * K * 2 + (double)R * K * 4 + (double)R * N * 4 * s.ksplit, N, K, R);
     TilesLaunch a{(const bf16_t*)x, R, K, nullptr, nullptr, nullptr, n0 / 16, (n0 + n1) / 16, N / 16, &gg, c->d_part(), N, {}};
     if (act >= 0 && s.ksplit == 1 && (act != METASD_SWIGLU || s.tb % 2 == 0)) {
