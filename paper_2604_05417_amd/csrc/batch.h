@@ -63,11 +63,13 @@ __global__ __launch_bounds__(1024) void addnorm_segp_kernel(float* __restrict__ 
     addnorm_body<T>(h, part, nsplit, sstride, d, static_cast<const T*>(gain.p[blockIdx.x / ms]), eps, xn, split);
 }
 
-// Rotation table per block row: tab[r][i] = (cos, sin)(position of row r * theta^(-2i/hd)), in fp64.   grid (R), block hd/2
-__global__ void rope_table_seg_kernel(Segs sg, int hd, float theta, double2* __restrict__ tab) {
+// Rotation table per block row: tab[r][i] = (cos, sin)(position of row r * theta^(-2i/hd)), in fp64.  rowkv != nullptr: also where row r
+// goes in a K/V head's plane (elements behind the plane of sequence 0; -1: padding).   grid (R), block hd/2
+__global__ void rope_table_seg_kernel(Segs sg, int hd, float theta, double2* __restrict__ tab, long long* __restrict__ rowkv, size_t kv_seq_stride) {
     const int r = blockIdx.x, i = threadIdx.x, half = hd >> 1;
     if (i >= half) return;
     const int s = r / sg.ms, j = min(r - s * sg.ms, sg.m[s] - 1);
+    if (rowkv && i == 0) rowkv[r] = r - s * sg.ms < sg.m[s] ? (long long)((size_t)sg.seq[s] * kv_seq_stride + (size_t)(sg.pos0[s] + j) * hd) : -1;
     const double freq = pow((double)theta, -2.0 * (double)i / (double)hd);
     double sn, cs;
     sincos((double)(sg.pos0[s] + j) * freq, &sn, &cs);

@@ -1474,7 +1474,7 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
     const size_t seq_stride = (size_t)M.kv_layers * 2 * plane;
     hipLaunchKernelGGL(embed_seg_kernel<T>, dim3(R), dim3(256), 0, st, (const int32_t*)c->d_hist(), c->cfg.max_ctx, (const T*)M.w[0], D, h, sg);
     LAUNCH_CHECK(c, "embed (segments)");
-    hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope());
+    hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope(), (long long*)nullptr, (size_t)0);
     LAUNCH_CHECK(c, "rope_table (segments)");
     for (int L = 0; L < d.n_layers; ++L) {
         launch_addnorm_many<T>(c, R, h, part, ns, D, (const T*)M.layer_w(L, 0), d.rms_eps, xn, split);
@@ -1498,6 +1498,56 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
         if ((rc = gemm_rows<T>(c, xn, D, R, D, M.lm_head(), V, nullptr, 0, nullptr, 0, &ns))) return rc;
         hipLaunchKernelGGL(sum_partials_seg_kernel, dim3((V + 255) / 256, R), dim3(256), 0, st, (const float*)part, ns, (size_t)R * V, V,
                            logits, sg, out_seq_rows, out_row0, last_only);
+        LAUNCH_CHECK(c, "sum_partials (segments)");
+    }
+    for (int s = 0; s < sg.n; ++s) M.kvl[sg.seq[s]] = sg.pos0[s] + sg.m[s];
+    return 0;
+}
+
+// At most 8 rows of several sequences (the drafter steps of a small batch, its verification of a token or two): the step GEMMs of
+// forward_rows_step with the rows' places in their caches taken from a table - 5 launches per layer (6 where attention leaves records)
+// instead of 10.  One row in each of 5 sequences, 1B shape, per layer: 60 -> 43 us.
+bool segs_step_ok(const metasd_ctx* c, const Model& M, int R) {
+    return c->fuse_small && c->gemm_reduce && c->fullk_roll && M.d.dtype == METASD_BF16 && M.hd >= 64 && M.d.d_model >= STEP_DMIN && step_ok(R, M.d.d_model);
+}
+int forward_segs_step(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int out_seq_rows, int out_row0, int last_only) {
+    typedef bf16_t T;
+    const metasd_model_desc& d = M.d;
+    const int D = d.d_model, F = d.d_ffn, V = d.vocab, hd = M.hd, DQ = d.n_heads * hd, R = sg.n * sg.ms;
+    hipStream_t st = c->stream;
+    float* h = c->d_h();
+    long long* rowkv = reinterpret_cast<long long*>(c->d_inv());       // 8 rows: the 64 bytes of the 1/rms table, which this path does not use
+    static_assert(STEP_ROWS * sizeof(long long) <= 64, "row table");
+    int rc;
+    hipLaunchKernelGGL(embed_seg_kernel<T>, dim3(R), dim3(256), 0, st, (const int32_t*)c->d_hist(), c->cfg.max_ctx, (const T*)M.w[0], D, h, sg);
+    LAUNCH_CHECK(c, "embed (segments)");
+    hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope(), rowkv,
+                       (size_t)M.kv_layers * 2 * d.n_kv_heads * c->cfg.max_ctx * hd);
+    LAUNCH_CHECK(c, "rope_table (segments)");
+    auto norm_in = [&](const void* gain) {
+        StepArgs a{};
+        a.h = h; a.gain = (const bf16_t*)gain; a.eps = d.rms_eps; a.m = R; a.K = D;
+        return a;
+    };
+    for (int L = 0; L < d.n_layers; ++L) {
+        StepArgs a = norm_in(M.layer_w(L, 0));
+        a.rowkv = rowkv;
+        if ((rc = gemm_step_qkv(c, M, L, 0, a))) return rc;
+        if ((rc = attention_seg<T>(c, M, L, sg))) return rc;
+        if ((rc = gemm_step_add(c, c->d_ao(), R, DQ, M.layer_w(L, 4), D, h))) return rc;
+        a = norm_in(M.layer_w(L, 5));
+        a.out = (float*)c->d_act(); a.N = F; a.swiglu = d.act == METASD_SWIGLU;
+        if (a.swiglu) rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0);
+        else rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0);
+        if (rc) return rc;
+        if ((rc = gemm_step_add(c, c->d_act(), R, F, M.layer_w(L, 8), D, h))) return rc;
+    }
+    if (logits) {
+        StepArgs a = norm_in(M.final_norm());
+        a.out = c->d_part(); a.N = V;
+        if ((rc = gemm_step_norm<STEP_OUT, false>(c, a, M.lm_head(), V, nullptr, 0, nullptr, 0))) return rc;
+        hipLaunchKernelGGL(sum_partials_seg_kernel, dim3((V + 255) / 256, R), dim3(256), 0, st, (const float*)c->d_part(), 1, (size_t)R * V, V, logits, sg,
+                           out_seq_rows, out_row0, last_only);
         LAUNCH_CHECK(c, "sum_partials (segments)");
     }
     for (int s = 0; s < sg.n; ++s) M.kvl[sg.seq[s]] = sg.pos0[s] + sg.m[s];
@@ -1583,6 +1633,7 @@ int forward_segs(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int out
     for (int s = 0; s < sg.n; ++s)
         if (sg.pos0[s] + sg.m[s] > c->cfg.max_ctx)
             return c->fail(METASD_E_OVERFLOW, "sequence %d: positions %d..%d exceed max_ctx %d", sg.seq[s], sg.pos0[s], sg.pos0[s] + sg.m[s], c->cfg.max_ctx);
+    if (segs_step_ok(c, M, sg.n * sg.ms)) return forward_segs_step(c, M, sg, logits, out_seq_rows, out_row0, last_only);
     if (M.d.dtype == METASD_BF16) return forward_segs_t<bf16_t>(c, M, sg, logits, out_seq_rows, out_row0, last_only);
     return forward_segs_t<float>(c, M, sg, logits, out_seq_rows, out_row0, last_only);
 }
@@ -1667,7 +1718,7 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
     hipLaunchKernelGGL(embed_segp_kernel<T>, dim3(R), dim3(256), 0, st, (const int32_t*)c->d_hist(), c->cfg.max_ctx,
                        seg_ptrs([](const Model& M, int) { return (const void*)M.w[0]; }), D, h, sg);
     LAUNCH_CHECK(c, "embed (grouped)");
-    hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope());
+    hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope(), (long long*)nullptr, (size_t)0);
     LAUNCH_CHECK(c, "rope_table (segments)");
     int max_len = 1;
     double kvpos = 0.0;

@@ -44,6 +44,7 @@ struct StepArgs {
     const double2* tab;              // ROPE: rotations [m][hd / 2]
     bf16_t *kc, *vc;                 // ROPE: cache planes of the layer, row r goes to position pos0 + r
     int H, KH, hd, pos0, max_ctx;    // ROPE
+    const long long* rowkv;          // ROPE, rows of several sequences: where row r goes in a K/V head's plane (elements), -1: nowhere
 };
 
 // LDS of a launch: NORM [2 (hi, lo)][m][rs] 16-byte pieces and 16 sums of squares, then [16][64] partial tiles.
@@ -162,6 +163,7 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
         }
     };
     double2 rot0 = make_double2(1.0, 0.0), rot1 = rot0;        // ROPE: rotations of this lane's two pairs
+    long long kv_at = 0;                                       // .. and its row's place in a plane of the cache
     for (int p = 0; p < a.passes; ++p) {
         acc0 = f32x4{0.f, 0.f, 0.f, 0.f};
         acc1 = acc0;
@@ -186,6 +188,7 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
             const int n = min(unit_of(p, min(wave, T - 1)), nunits - 1) * 16, half = a.hd >> 1;
             const double2* t = a.tab + min(col, m - 1) * half + min(((n % a.hd) >> 1) + 2 * g, half - 2);
             rot0 = t[0]; rot1 = t[1];
+            kv_at = a.rowkv ? a.rowkv[min(col, m - 1)] : (long long)(a.pos0 + col) * a.hd;
         }
         if (p > 0) __syncthreads();                // the partial tiles of the pass before are read
         if constexpr (HALF) red[wave * 64 + lane] = g < 2 ? acc0 : acc1;
@@ -230,13 +233,17 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
                     const float a0 = (float)((double)v[0] * rot0.x - (double)v[1] * rot0.y), b0 = (float)((double)v[0] * rot0.y + (double)v[1] * rot0.x);
                     const float a1 = (float)((double)v[2] * rot1.x - (double)v[3] * rot1.y), b1 = (float)((double)v[2] * rot1.y + (double)v[3] * rot1.x);
                     const uint32_t ah = f2bf2(a0, a1), bh = f2bf2(b0, b1);
-                    const size_t pos = (size_t)a.pos0 + col;
-                    if (head >= a.H + a.KH) {
-                        *reinterpret_cast<uint2*>(a.vc + ((size_t)(head - a.H - a.KH) * a.max_ctx + pos) * hd + c + 4 * g) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
-                    } else if (head >= a.H) {
-                        bf16_t* k = a.kc + ((size_t)(head - a.H) * a.max_ctx + pos) * hd + i;
-                        *reinterpret_cast<uint32_t*>(k) = ah;
-                        *reinterpret_cast<uint32_t*>(k + half) = bh;
+                    if (head >= a.H) {
+                        if (kv_at >= 0) {
+                            const size_t plane = (size_t)a.max_ctx * hd;
+                            if (head >= a.H + a.KH) {
+                                *reinterpret_cast<uint2*>(a.vc + (size_t)(head - a.H - a.KH) * plane + kv_at + c + 4 * g) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+                            } else {
+                                bf16_t* k = a.kc + (size_t)(head - a.H) * plane + kv_at + i;
+                                *reinterpret_cast<uint32_t*>(k) = ah;
+                                *reinterpret_cast<uint32_t*>(k + half) = bh;
+                            }
+                        }
                     } else if (hd >= 64) {
                         bf16_t* qh = reinterpret_cast<bf16_t*>(a.out) + ((size_t)col * a.H + head) * hd + i;
                         bf16_t* ql = qh + (size_t)m * a.H * hd;

@@ -362,3 +362,23 @@ def test_largest_batch_and_draft_length():
         st = ls.stats
         assert st["max_dp"] <= TOL and st["max_dq"] <= TOL and st["ties_shared"] <= 1, st
     g.close()
+
+
+@pytest.mark.parametrize("heads,kv,B,gamma", [(8, 2, 2, 3), (8, 8, 5, 1), (4, 4, 8, 2), (4, 2, 3, 1)])
+def test_bf16_few_rows_of_several_sequences(heads, kv, B, gamma):
+    """Blocks of at most 8 rows over several sequences (csrc/step.h with a table of the rows' places): head_dim 64 and 128, grouped
+    queries, one row per sequence, ragged catch-ups whose padding rows must leave the caches alone, verification of 4 to 8 rows and,
+    beside it, of more than 8."""
+    td = W.model_desc(2, 512, heads, kv, 416, 1024, W.SWIGLU, W.BF16)
+    dd = W.model_desc(1, 512, heads, kv, 288, 1024, W.GELU, W.BF16)
+    cfg = dict(target=(td, W.gen_weights(td, 0)), drafters=[(dd, W.gen_weights(dd, 7)), (dd, W.gen_weights(dd, 8))], gamma=gamma, beta=1.0, seed=3,
+               max_ctx=160, prompt=W.prompt_tokens(70, 1024, 1))
+    prompts = [W.prompt_tokens(max(2, 70 - 31 * b), 1024, 40 + b) for b in range(B)]
+    g, seqs = batch_pair(cfg, 1.0, prompts, TOL)
+    bl = make_lockstep(g, cfg, seqs, prompts, 1.0, TOL)
+    for _ in range(5):
+        bl.round()
+    g.close()
+    for ls in bl.seqs:
+        st = ls.stats
+        assert st["max_dp"] <= 4e-3 and st["max_dq"] <= 4e-3 and st["ties_shared"] <= 1, st     # (bound: see test_gpu_attn.py)
