@@ -2139,15 +2139,30 @@ __device__ __forceinline__ int sample_rows_body(float (&xp)[AK_CH][4], int V, fl
     return sm.token;
 }
 
+// What the drafter's next step starts from, left by the launch that draws its token (one row): the token's embedding and the rotations of
+// its position, as embed_rope_kernel writes them - that launch (2 - 4 us, on top of the one for the draw) stood between every two steps.
+struct NextRow {
+    const void* E;               // embedding table; nullptr: nothing is left
+    int bf16, d, pos, hd;
+    float theta;
+    float* h;
+    double2* tab;
+};
 __global__ __launch_bounds__(AK_NT) void sample_rows_kernel(const float* __restrict__ logits, int V, float T, uint64_t seed,
                                                             uint32_t round, uint32_t pos, uint32_t seq0,
                                                             int32_t* __restrict__ tok, int tok_stride,
-                                                            int32_t* __restrict__ tok_copy) {
+                                                            int32_t* __restrict__ tok_copy, NextRow next) {
     __shared__ AkShared sm;
     const int b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float xp[AK_CH][4];
     ak_load(logits + (size_t)b * V, V, wave, lane, xp);
+    if (next.E && wave == AK_WAVES - 1 && lane < next.hd >> 1) {       // 64-bit power, sine and cosine while the logits are on their way
+        const double freq = pow((double)next.theta, -2.0 * (double)lane / (double)next.hd);
+        double sn, cs;
+        sincos((double)next.pos * freq, &sn, &cs);
+        next.tab[lane] = make_double2(cs, sn);
+    }
     int token;
     if (T <= 0.f) {
         token = ak_argmax(xp, sm, wave, lane);
@@ -2158,6 +2173,17 @@ __global__ __launch_bounds__(AK_NT) void sample_rows_kernel(const float* __restr
     if (threadIdx.x == 0) {
         tok[(size_t)b * tok_stride] = token;
         if (tok_copy) tok_copy[b] = token;
+    }
+    if (next.E) {
+        const size_t at = (size_t)min(max(token, 0), V - 1) * next.d;
+        for (int k = (int)threadIdx.x * 4; k < next.d; k += AK_NT * 4) {
+            float4 v;
+            if (next.bf16) {
+                const uint2 w = *reinterpret_cast<const uint2*>(static_cast<const bf16_t*>(next.E) + at + k);
+                v = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
+            } else v = *reinterpret_cast<const float4*>(static_cast<const float*>(next.E) + at + k);
+            *reinterpret_cast<float4*>(next.h + k) = v;
+        }
     }
 }
 

@@ -468,6 +468,7 @@ struct metasd_ctx {
     bool fuse_small = true;          // short blocks of narrow bf16 models use the GEMMs with fused prologues (METASD_FUSE_SMALL=0: off)
     int n_cu = 0;
     const TreeBlk* tree = nullptr;   // set while a block of draft-tree nodes is being launched (positions and mask of its rows)
+    bool embedded = false;           // the one row of the forward being launched is in d_h and its rotations in d_rope already (NextRow)
     bool head_est = false;           // a drafter head's forward takes its own estimates (d_fest) as the feature input (draft steps after the first)
     FeatSrc fsrc{};                  // .. row r the estimate fsrc.idx[r] (chain steps: 0; tree levels: the parent node's)
     TreeShape tshape{};              // the tree of the running round (metasd_draft_tree)
@@ -845,9 +846,11 @@ template <typename T>
 int embed_rows(metasd_ctx* c, Model& M, int pos0, int m, float* h) {
     const metasd_model_desc& d = M.d;
     const int D = d.d_model;
-    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, c->stream, c->d_hist() + pos0, (const T*)M.w[0], D, h, pos0, M.hd, d.rope_theta,
-                       c->d_rope(), c->tree ? *c->tree : TreeBlk{});
-    LAUNCH_CHECK(c, "embed + rope table");
+    if (!c->embedded) {
+        hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, c->stream, c->d_hist() + pos0, (const T*)M.w[0], D, h, pos0, M.hd, d.rope_theta,
+                           c->d_rope(), c->tree ? *c->tree : TreeBlk{});
+        LAUNCH_CHECK(c, "embed + rope table");
+    }
     if (!M.head) return 0;
     float* cat = (float*)c->d_act();
     hipLaunchKernelGGL(feat_cat_kernel, dim3(m), dim3(256), 0, c->stream, (const float*)h, (const float*)c->d_feat(),
@@ -1076,9 +1079,7 @@ int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, 
     const int D = d.d_model, H = d.n_heads, hd = M.hd, F = d.d_ffn, V = d.vocab;
     const int DQ = H * hd;
     int hp = 0, rc;                     // current residual buffer
-    hipLaunchKernelGGL(embed_rope_kernel<T>, dim3(m), dim3(320), 0, c->stream, c->d_hist() + pos0, (const T*)M.w[0], D, c->d_h_pp(0), pos0, hd,
-                       d.rope_theta, c->d_rope(), c->tree ? *c->tree : TreeBlk{});
-    LAUNCH_CHECK(c, "embed + rope table");
+    if ((rc = embed_rows<T>(c, M, pos0, m, c->d_h_pp(0)))) return rc;
     auto norm_in = [&](const void* gain, int row0) {
         StepArgs a{};
         a.h = c->d_h_pp(hp) + (size_t)row0 * D;
@@ -1810,9 +1811,9 @@ int catch_up(metasd_ctx* c, Model& M, const std::vector<int>& seqs, const std::v
 }
 
 int launch_sample(hipStream_t st, const float* logits, int rows, int V, float T, uint64_t seed, uint32_t round, uint32_t pos,
-                  uint32_t seq0, int32_t* tok, int stride, int32_t* tok_copy) {
+                  uint32_t seq0, int32_t* tok, int stride, int32_t* tok_copy, const NextRow& next = NextRow{}) {
     hipLaunchKernelGGL(sample_rows_kernel, dim3(rows), dim3(AK_NT), 0, st, logits, V, T, seed, round, pos, seq0, tok, stride,
-                       tok_copy);
+                       tok_copy, next);
     return hipGetLastError() == hipSuccess ? 0 : METASD_E_HIP;
 }
 
@@ -2328,6 +2329,7 @@ int32_t metasd_draft(metasd_ctx* c, const int32_t* k, int32_t gamma) {
     Model& D = c->drafters[k[0]];
     const int V = D.d.vocab, l = c->sq[0].l;
     const float T = c->cfg.temperature;
+    const bool next_row = (uintptr_t)D.w[0] % 16 == 0;     // the draw reads embedding rows in pieces of 8 or 16 bytes
     for (int j = 0; j < gamma; ++j) {
         float* Qj = c->d_Q() + (size_t)j * V;
         int rc;
@@ -2343,12 +2345,16 @@ int32_t metasd_draft(metasd_ctx* c, const int32_t* k, int32_t gamma) {
         } else if (j == 0) rc = forward(c, D, D.kvl[0], l - D.kvl[0], Qj, false);   // catch-up, ends with the last committed token
         else {
             c->head_est = D.head;                      // a drafter head goes on from its own estimate of the last feature
+            c->embedded = next_row;                    // the draw of the token left its row
             rc = forward(c, D, l + j - 1, 1, Qj, false);
+            c->embedded = false;
             c->head_est = false;
         }
         if (rc) return rc;
+        NextRow next{};
+        if (next_row && j + 1 < gamma) next = NextRow{D.w[0], D.d.dtype == METASD_BF16, D.d.d_model, l + j, D.hd, D.d.rope_theta, c->d_h(), c->d_rope()};
         if (launch_sample(c->stream, Qj, 1, V, T, c->cfg.seed, (uint32_t)c->sq[0].round, (uint32_t)j, 0u, c->d_hist() + l + j, 1,
-                          c->d_draft() + j))
+                          c->d_draft() + j, next))
             return c->fail(METASD_E_HIP, "launch sample_rows failed");
     }
     c->sq[0].cur_k = k[0];
