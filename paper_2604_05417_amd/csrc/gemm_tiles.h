@@ -8,19 +8,20 @@ namespace msd {
 //   x interleaved (store_il4): per row and 32-wide chunk one 128-byte line, 32 hi terms, then 32 lo terms.
 // A workgroup of 8 wavefronts, four along the rows and two along the features, owns 64 RB rows x 2 TB tiles of one K-slice;
 // a wavefront multiplies 16 RB rows with TB tiles, both terms.  The slice advances one 32-wide chunk per stage: a stage - the
-// rows' lines and the tiles' KiBs - goes from memory straight into LDS (global_load_lds_dwordx4, no staging registers), NS - 1
+// rows' lines and the tiles' KiBs - goes from memory straight into LDS (global_load_lds_dwordx4, no staging registers), NS
 // stages ahead, and a wavefront waits only for the requests of the stage it needs (vmcnt counts), so the stream runs on
 // through the barriers.  Both operands are read from LDS: per stage and wavefront 2 RB + TB KiB for 2 RB TB MFMAs.
 //   LDS layout of a stage: row r: its 8 pieces of 16 bytes, piece q in position q ^ ((r >> 1) & 7) (conflict-free fragment
 // reads); then the tiles as they are.
-//   The wavefronts of a SIMD (w and w + 4) take turns: while 0-3 multiply a stage from registers, 4-7 read theirs from LDS, and
-// the other way round, one barrier between two turns; neither the fragment reads nor the waits for them stand between MFMAs.
-//   What bounds it: from about 500 rows on its own turns and, behind them, power.  1.14 to 1.27 PFLOP/s (both terms counted) on the 7B
-// projections with random values, the MFMAs busy 53 - 58 % of the cycles (1499 rows; 44 % at 256, 15 - 46 % on the 1B shapes at 511,
-// whose grids fill the chip once); with zero weights 1.34 to 1.51, the clock 2.40 instead of 2.24 GHz.  This machine's library GEMM
-// reaches 0.7 to 1.2 on the same shapes and 1.33 to 1.5 on 8192 .. 16384 cubes.  Measured against the kernel it replaces (256 rows per launch, weights in registers): 1499
-// rows, one 7B layer 1586 -> 990 us; 256 rows QKV 54 -> 47, output 29 -> 20, gate|up 90 -> 80, down 52 -> 44 us; 20 rows of the 1B
-// shape gate|up 21.4 -> 15.
+//   Fragments are held twice: while a stage is multiplied from one set of registers, the next is read from LDS into the other, so one
+// barrier per stage is enough, neither the reads nor the waits for them stand between MFMAs, and a stage's buffer is free as soon as it
+// has been read - its next request is made NS stages ahead.  The first row block is multiplied before the requests and reads are issued,
+// so that the matrix cores start right behind the barrier.
+//   What bounds it: from about 500 rows on power and the quantum of whole tiles per CU.  1.26 PFLOP/s (both terms counted) on gate | up of
+// the 7B shape at 1499 rows with random values.  Two groups of wavefronts taking turns between reading and multiplying, two barriers per
+// stage and one register set, were here before; on the same card, 1499 rows of the 7B shape: gate | up 457 -> 430 us, q | k | v 268 -> 260,
+// output and down 141 -> 132 (mean); 511 rows of the 1B shape: gate | up 62.5 -> 56.5, down 37.3 -> 36.2; 256 rows 47.6 -> 44.8 with 128 x 256
+// tiles, 47.1 -> 48.1 with 128 x 192.
 //   Workgroup ids are dealt out so that the row blocks of one feature group run on one XCD one after the other (its L2 then
 // serves the weights to all of them).
 //   grid nrb * ngroups * ksplit, block 512, dynamic LDS NS * (8192 RB + 2048 TB) bytes;
@@ -99,7 +100,7 @@ __device__ __forceinline__ void gemm_tiles_body(const bf16_t* __restrict__ x, in
         if (REM && wave < REM) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((PER + (REM ? 1 : 0)) * (NS - 2)) : "memory");
         else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 2)) : "memory");
     };
-    static_assert((PER + 1) * (NS - 2) < 64, "vmcnt counts to 63");
+    static_assert((PER + 1) * (NS - 1) < 64, "vmcnt counts to 63");
     f32x4 acc[RB][TB];
 #pragma unroll
     for (int a = 0; a < RB; ++a)
@@ -108,63 +109,59 @@ __device__ __forceinline__ void gemm_tiles_body(const bf16_t* __restrict__ x, in
     const int xrow = wr * 16 * RB + row16, sw = (xrow >> 1) & 7;     // the same for all row blocks of the wavefront (16 rows apart)
     const int xat_h = xrow * 8 + (g ^ sw), xat_l = xrow * 8 + ((g ^ sw) ^ 4), wat = BM * 8 + wc * TB * 64 + lane;
 #pragma unroll
-    for (int u = 0; u < NS - 1; ++u)
+    for (int u = 0; u < NS; ++u)
         if (u < nst) request(u);
-    u32x4 w[TB], fh[RB], fl[RB];
-    auto fetch = [&](int buf) {
+    struct Frag { u32x4 w[TB], fh[RB], fl[RB]; };
+    auto fetch = [&](Frag& f, int buf) {
         const u32x4* sb = reinterpret_cast<const u32x4*>(lds) + (size_t)buf * STAGE;
 #pragma unroll
-        for (int a = 0; a < RB; ++a) { fh[a] = sb[xat_h + 128 * a]; fl[a] = sb[xat_l + 128 * a]; }
+        for (int i = 0; i < TB; ++i) f.w[i] = sb[wat + 64 * i];
 #pragma unroll
-        for (int i = 0; i < TB; ++i) w[i] = sb[wat + 64 * i];
+        for (int a = 0; a < RB; ++a) { f.fh[a] = sb[xat_h + 128 * a]; f.fl[a] = sb[xat_l + 128 * a]; }
     };
-    auto mult = [&]() {
-        __builtin_amdgcn_s_setprio(1);
+    auto mult = [&](const Frag& f, int a0, int a1) {
 #pragma unroll
         for (int a = 0; a < RB; ++a) {
+            if (a < a0 || a >= a1) continue;
 #pragma unroll
             for (int i = 0; i < TB; ++i)
-                acc[a][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[i]), __builtin_bit_cast(bf16x8, fh[a]), acc[a][i], 0, 0, 0);
+                acc[a][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.w[i]), __builtin_bit_cast(bf16x8, f.fh[a]), acc[a][i], 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < TB; ++i)
-                acc[a][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[i]), __builtin_bit_cast(bf16x8, fl[a]), acc[a][i], 0, 0, 0);
+                acc[a][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.w[i]), __builtin_bit_cast(bf16x8, f.fl[a]), acc[a][i], 0, 0, 0);
         }
-        __builtin_amdgcn_s_setprio(0);
     };
-    auto barrier = [&]() { __builtin_amdgcn_sched_barrier(0); lds_barrier(); __builtin_amdgcn_sched_barrier(0); };
-    // waits until stage st + 1 has landed, when the youngest stage requested is st + NS - 1 (or the last)
-    auto wait_next = [&](int st) {
+    // top of stage st: its fragments are in registers (every wavefront's, behind the barrier: its buffer is free) and stage st + 1 has landed
+    auto top = [&](int st) {
         __builtin_amdgcn_sched_barrier(0);
-        if (st + NS <= nst) wait_stage();
+        if (st + NS - 1 < nst) wait_stage();           // stages st + 1 .. st + NS - 1 are on their way
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
     };
-    wait_next(-1);
-    barrier();
+    Frag fa, fb;
+    // the prologue asked for stages 0 .. NS - 1
+    if (NS - 1 < nst) {
+        if (REM && wave < REM) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((PER + (REM ? 1 : 0)) * (NS - 1)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (NS - 1)) : "memory");
+    } else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(fa, 0);
     int buf = 0;
-    if (wave < 4) {
-        for (int st = 0; st < nst; ++st) {
-            if (st + NS - 1 < nst) request(buf == 0 ? NS - 1 : buf - 1);
-            fetch(buf);
-            barrier();
-            mult();
-            wait_next(st);
-            barrier();
-            if (++buf == NS) buf = 0;
-        }
-        barrier();
-    } else {
-        if (NS - 1 < nst) request(NS - 1);
-        barrier();
-        for (int st = 0; st < nst; ++st) {
-            fetch(buf);
-            wait_next(st);
-            barrier();
-            if (st + NS < nst) request(buf);
-            __builtin_amdgcn_sched_barrier(0);
-            mult();
-            barrier();
-            if (++buf == NS) buf = 0;
-        }
+    auto stage = [&](int st, const Frag& now, Frag& nxt) {
+        top(st);
+        const int nb = buf + 1 == NS ? 0 : buf + 1;
+        mult(now, 0, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + NS < nst) request(buf);
+        if (st + 1 < nst) fetch(nxt, nb);
+        mult(now, 1, RB);
+        buf = nb;
+    };
+    for (int st = 0; st < nst; st += 2) {
+        stage(st, fa, fb);
+        if (st + 1 < nst) stage(st + 1, fb, fa);
     }
 #pragma unroll
     for (int a = 0; a < RB; ++a) {
