@@ -2,7 +2,11 @@
 // batch.h and prefill.h.
 #pragma once
 
+#include "attn_plan.h"
+
 namespace msd {
+
+static_assert(ATT_SEGS == MAX_SEGS, "sequences of a launch");
 
 // One workgroup of 4 wavefronts per (span of positions, query heads, sequence).  The rows of hp query heads that share a K/V head
 // (hp m <= 16) are the columns of one MFMA operand, so K and V are read once for all of them.  A wavefront walks its sub-blocks of 32
@@ -12,12 +16,11 @@ namespace msd {
 //                              registers that held S^T (slot 8 g + j of the 32 positions stands for 4 g + j or 16 + 4 g + j - 4)
 // K and V of the next sub-block are requested as soon as the registers of the current one are free (16 KiB per wavefront at head_dim
 // 128, up to 192 KiB per CU); at the end the wavefronts merge through LDS.  One record per workgroup, merged by attn_combine_kernel; a
-// span that is the whole context needs no merge and the workgroup writes the rows itself.
+// span that is the whole context of its sequence needs no merge and the workgroup writes the rows itself.
 // What bounds it: HBM (6.6 TB/s with 1024 workgroups or more), for short contexts the chain request - scores - products - merge.
 // Measured beside the kernel it replaced (one chunk of 128 positions per workgroup, V staged behind two workgroup barriers and gathered
 // element by element), with the merge: 32 heads of 128, 6 rows, 2054 positions 15.5 -> 11.8 us; 12 rows, 8012 positions 42.0 -> 26.1 us
 // (8 records per head instead of 63); 32 sequences of 2056 positions (1.05 GB) 211 -> 160 us.
-constexpr int ATT_NW = 4;
 template <int HD>
 struct AttnShared {
     static constexpr int RSV = HD + 16;                // V row stride (elements)
@@ -28,7 +31,8 @@ struct AttnShared {
 struct AttnOut {
     float* part;       // records [head][nrec][16][HD + 2] (O, maximum, sum per row) of the sequence
     int nrec, rec;
-    float* out;        // nrec == 1: the rows [.][H HD] as two bf16 terms instead (split: see store_terms4)
+    int direct;        // one record holds the whole context: the rows are written instead of it, to
+    float* out;        // [.][H HD] as two bf16 terms (split: see store_terms4)
     int split;
     size_t lo_off;     // elements of the whole block
     int row0, rows;    // first row of the sequence in out and rows to write (past m: padding, copies of the last one)
@@ -166,7 +170,7 @@ __device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __re
 #pragma unroll
     for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4*>(ow + col * OS + t * 16 + 4 * g) = o[t];
     __syncthreads();
-    const int rows = ao.nrec == 1 ? ao.rows : m;
+    const int rows = ao.direct ? ao.rows : m;
     for (int i = tid; i < hp * rows * (HD / 4); i += ATT_NW * 64) {
         const int hr = i / (HD / 4), c4 = (i - hr * (HD / 4)) * 4, hi = hr / rows, r = hr - hi * rows, c = hi * m + min(r, m - 1), h = h0 + hi;
         float M = sm.mx[0][c];
@@ -180,7 +184,7 @@ __device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __re
             y += *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(sm.v[w]) + c * OS + c4) * f;
             tot += sm.sum[w][c] * f;
         }
-        if (ao.nrec == 1) {
+        if (ao.direct) {
             store_terms4(ao.out, ao.split, ao.lo_off, ((size_t)(ao.row0 + r) * H + h) * HD + c4, make_float4(y[0] / tot, y[1] / tot, y[2] / tot, y[3] / tot));
         } else {
             float* dst = ao.part + (((size_t)h * ao.nrec + ao.rec) * 16 + r) * (HD + 2);
@@ -191,17 +195,12 @@ __device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __re
     }
 }
 
-// The workgroups of a launch: item = (sequence, record, group of query heads).  Groups that share a K/V head and a span are 8 workgroup
-// ids apart and so on one XCD, whose L2 they share.
-struct AttnItem { int s, rec, h0, kh; };
-__device__ __forceinline__ bool attn_item(int id, int nseg, int nrec, int H, int KH, int hp, AttnItem& it) {
-    const int gph = H / (KH * hp), x = id & 7, j = id >> 3, u = (j / gph) * 8 + x, gi = j % gph;     // u: (sequence, K/V head, record)
-    if (u >= nseg * KH * nrec) return false;
-    it.rec = u % nrec;
-    it.kh = u / nrec % KH;
-    it.s = u / (nrec * KH);
-    it.h0 = it.kh * (H / KH) + gi * hp;
-    return true;
+// The workgroups of a launch: u = (item, group of query heads).  Groups that share a K/V head and a span are 8 workgroup ids apart and so on
+// one XCD, whose L2 they share; the items of a sequence follow each other over the XCDs.
+__device__ __forceinline__ int attn_unit(int id, int groups, int& group) {
+    const int j = id >> 3;
+    group = j % groups;
+    return (j / groups) * 8 + (id & 7);
 }
 
 // A block of one sequence; spw sub-blocks per workgroup.   grid: attn_grid, block 256
@@ -210,65 +209,53 @@ __global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_kernel(co
                                                                             const bf16_t* __restrict__ vc, int m, int pos0, int H, int KH, int hp,
                                                                             int max_ctx, float scale, int spw, AttnOut ao, TreeBlk tb) {
     __shared__ AttnShared<HD> sm;
-    AttnItem it;
-    if (!attn_item(blockIdx.x, 1, ao.nrec, H, KH, hp, it)) return;     // workgroup-uniform
-    const size_t at = (size_t)it.kh * max_ctx * HD;
-    ao.rec = it.rec;
-    attn_body<HD, SHARED>(sm, q, (size_t)m * H * HD, H, it.h0, hp, kc + at, vc + at, m, pos0, scale, it.rec * spw,
-                          min((pos0 + m + 31) >> 5, (it.rec + 1) * spw), ao, TREE ? &tb : nullptr);
+    int gi;
+    const int u = attn_unit(blockIdx.x, H / (KH * hp), gi), kh = u / ao.nrec;
+    if (kh >= KH) return;                              // workgroup-uniform
+    const size_t at = (size_t)kh * max_ctx * HD;
+    ao.rec = u - kh * ao.nrec;
+    ao.direct = ao.nrec == 1;
+    attn_body<HD, SHARED>(sm, q, (size_t)m * H * HD, H, kh * (H / KH) + gi * hp, hp, kc + at, vc + at, m, pos0, scale, ao.rec * spw,
+                          min((pos0 + m + 31) >> 5, (ao.rec + 1) * spw), ao, TREE ? &tb : nullptr);
 }
 
 // Blocks of several sequences: K and V planes of segment s at kc.p[s], vc.p[s] (PTRS) or kv_seq_stride elements per sequence behind
-// kc0, vc0; q_lo: elements of the whole block's q.  The records of a segment follow those of the one before.
-template <int HD, bool SHARED, bool PTRS>
+// kc0, vc0; q_lo: elements of the whole block's q.  ONE: every sequence has one record.  Otherwise the records of a segment follow those of
+// the one before, and a segment that needs only one gets its rows written here and leaves none.  (Looking an item up takes 0.3 - 0.5 us of
+// a launch, 6.7 us for 5 sequences of 333 positions: ONE does without.)
+template <int HD, bool SHARED, bool PTRS, bool ONE>
 __global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_seg_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc0,
                                                                                 const bf16_t* __restrict__ vc0, size_t kv_seq_stride, SegPtrs kc,
                                                                                 SegPtrs vc, Segs sg, int H, int KH, int hp, int max_ctx, float scale,
-                                                                                size_t q_lo, int spw, AttnOut ao) {
+                                                                                size_t q_lo, int spw, AttnOut ao, AttnItems items) {
     __shared__ AttnShared<HD> sm;
-    AttnItem it;
-    if (!attn_item(blockIdx.x, sg.n, ao.nrec, H, KH, hp, it)) return;  // workgroup-uniform
-    const int s = it.s, m = sg.m[s], pos0 = sg.pos0[s], nsub = (pos0 + m + 31) >> 5;
-    if (it.rec * spw >= nsub) return;
-    const size_t at = (size_t)it.kh * max_ctx * HD, so = (size_t)sg.seq[s] * kv_seq_stride;
-    ao.rec = it.rec;
+    int gi;
+    const int u = attn_unit(blockIdx.x, H / (KH * hp), gi);
+    int s, kh, nrec = 1;                               // sequence and K/V head of the item
+    if constexpr (ONE) {
+        s = u / KH; kh = u - s * KH;
+        if (s >= sg.n) return;                         // workgroup-uniform
+    } else {
+        if (u >= items.n) return;
+        s = 0;
+        int r = u;                                     // .. and its place in the sequence
+#pragma unroll
+        for (int i = 1; i < ATT_SEGS; ++i)
+            if (items.first[i] <= u) { s = i; r = u - items.first[i]; }
+        nrec = (((sg.pos0[s] + sg.m[s] + 31) >> 5) + spw - 1) / spw;
+        kh = r / nrec;
+        ao.rec = r - kh * nrec;
+    }
+    const int m = sg.m[s], pos0 = sg.pos0[s], nsub = (pos0 + m + 31) >> 5;
+    const size_t at = (size_t)kh * max_ctx * HD, so = (size_t)sg.seq[s] * kv_seq_stride;
+    if (ONE) ao.rec = 0;
+    ao.direct = nrec == 1;
     ao.part += (size_t)s * H * ao.nrec * 16 * (HD + 2);
     ao.row0 = s * sg.ms;
     ao.rows = sg.ms;
-    attn_body<HD, SHARED>(sm, q + (size_t)s * sg.ms * H * HD, q_lo, H, it.h0, hp, (PTRS ? static_cast<const bf16_t*>(kc.p[s]) : kc0 + so) + at,
-                          (PTRS ? static_cast<const bf16_t*>(vc.p[s]) : vc0 + so) + at, m, pos0, scale, it.rec * spw, min(nsub, (it.rec + 1) * spw),
+    attn_body<HD, SHARED>(sm, q + (size_t)s * sg.ms * H * HD, q_lo, H, kh * (H / KH) + gi * hp, hp, (PTRS ? static_cast<const bf16_t*>(kc.p[s]) : kc0 + so) + at,
+                          (PTRS ? static_cast<const bf16_t*>(vc.p[s]) : vc0 + so) + at, m, pos0, scale, ao.rec * spw, min(nsub, (ao.rec + 1) * spw),
                           ao, nullptr);
-}
-
-// How a block is split.  hp: as many query heads of a K/V head as fit into 16 rows.  Records per head: none to merge (one workgroup sees
-// the whole context) where that fills the CUs - 32 sequences x 32 heads 160 us against 180 + 10 with three records, 8 x 32 heads 43
-// against 47 + 4 - or where the context is short (up to 128 KiB of K and V per workgroup: 5 sequences of 333 positions, 32 heads of 64,
-// 6.0 us against 5.4 + 2.8); otherwise up to 8, the most the merge takes in its shortest form, each a whole number of passes of its
-// wavefronts (65 sub-blocks x 32 heads: 6 records of 3 passes 11.8 us, 8 of 2.25 12.4), and two passes where that still gives half the
-// CUs a workgroup (3 sequences of 500 positions: 11.5 against 13.7 us).  Up to 16 where few heads walk a long context (12 heads x 8012
-// positions: 11.6 against 13.1 us).
-struct AttnPlan { int hp, spw, nrec, grid; };
-inline AttnPlan plan_attn(int nseg, int H, int KH, int hd, int m, int max_len, int n_cu, int force_passes) {
-    AttnPlan p{};
-    const int G = H / KH;
-    p.hp = 1;
-    for (int t = 2; t <= G && t * m <= 16; ++t)
-        if (G % t == 0) p.hp = t;
-    const int nsub = (max_len + 31) / 32, wgs = nseg * (H / p.hp);
-    auto passes_of = [&](int records) { return (nsub + ATT_NW * records - 1) / (ATT_NW * records); };
-    int passes = force_passes;
-    if (passes <= 0) {
-        if (wgs >= n_cu || (size_t)max_len * hd * 4 <= 128 * 1024) passes = passes_of(1);
-        else {
-            passes = passes_of(std::min(8, (3 * n_cu / 2 + wgs - 1) / wgs));
-            if (passes == 1 && wgs * ((nsub + 2 * ATT_NW - 1) / (2 * ATT_NW)) >= n_cu / 2) passes = 2;
-            if (passes > 4 && wgs * 8 <= n_cu / 2) passes = passes_of(16);
-        }
-    }
-    p.spw = ATT_NW * passes;
-    p.nrec = (nsub + p.spw - 1) / p.spw;
-    p.grid = 8 * ((nseg * KH * p.nrec + 7) / 8) * (G / p.hp);
-    return p;
 }
 
 }  // namespace msd

@@ -116,12 +116,13 @@ __global__ __launch_bounds__(256) void attn_partial_seg_kernel(const float* __re
                              part + (size_t)s * H * nch_max * 16 * (HD + 2), nch_max, c, (int)blockIdx.y);
 }
 
-// grid (H, R), block HD
+// singles: the rows of segments with one record are to be written too (attn_seg_kernel leaves them finished).   grid (H, R), block HD
 template <int HD>
 __global__ void attn_combine_seg_kernel(const float* __restrict__ part, int nch_max, int H, float* __restrict__ out, int split,
-                                        Segs sg, int cpw) {
+                                        Segs sg, int cpw, int singles) {
     const int r = blockIdx.y, s = r / sg.ms, j = min(r - s * sg.ms, sg.m[s] - 1);
     const int nch = ((sg.pos0[s] + sg.m[s] + ATT_CH - 1) / ATT_CH + cpw - 1) / cpw;    // records: one per cpw * ATT_CH positions
+    if (nch == 1 && !singles) return;
     attn_combine_body<HD>(part + (size_t)s * H * nch_max * 16 * (HD + 2), nch, nch_max, H, out, split, (int)blockIdx.x, j, r,
                           (size_t)gridDim.y * H * HD);
 }

@@ -797,8 +797,9 @@ int attention_hd(metasd_ctx* c, const Model& M, int L, int pos0, int m, int* nre
     int nrec = nchunks;
     bool combine = true;
     if constexpr (sizeof(T) == 2 && HD >= 64) {
-        const AttnPlan pl = plan_attn(1, d.n_heads, d.n_kv_heads, HD, m, pos0 + m, c->n_cu, c->att_cpw);
-        const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), 1, (size_t)m * d.n_heads * HD, 0, m};
+        const int len = pos0 + m;
+        const AttnPlan pl = plan_attn(&len, 1, d.n_heads, d.n_kv_heads, HD, m, c->n_cu, c->att_cpw);
+        const AttnOut ao{c->d_apart(), pl.nrec, 0, 0, (float*)c->d_ao(), 1, (size_t)m * d.n_heads * HD, 0, m};
         nrec = pl.nrec;
         if (nrec == 1) combine = false;
 #define ATTN_GO(TREE, SHARED) hipExtLaunchKernelGGL((attn_kernel<HD, TREE, SHARED>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, (const bf16_t*)c->d_q(), \
@@ -1375,56 +1376,68 @@ int gemm_rows_act(metasd_ctx* c, const Model& M, int L, const void* x, int R, in
     return 0;
 }
 
+// What the attention of a block is launched with, the same in every layer.
+struct SegAttn {
+    AttnPlan pl;       // bf16, head_dim 64 and 128
+    int nch_max;       // chunks of ATT_CH positions of the longest context
+    double kvpos;      // positions of all sequences
+};
+SegAttn plan_segs(const metasd_ctx* c, const metasd_model_desc& d, int hd, const Segs& sg) {
+    SegAttn a{};
+    int len[ATT_SEGS], max_len = 1;
+    for (int s = 0; s < sg.n; ++s) {
+        len[s] = sg.pos0[s] + sg.m[s];
+        max_len = std::max(max_len, len[s]);
+        a.kvpos += (double)len[s];
+    }
+    a.nch_max = (max_len + ATT_CH - 1) / ATT_CH;
+    if (d.dtype == METASD_BF16 && hd >= 64) a.pl = plan_attn(len, sg.n, d.n_heads, d.n_kv_heads, hd, sg.ms, c->n_cu, c->att_cpw);
+    return a;
+}
+
 template <typename T, int HD>
-int attention_seg_hd(metasd_ctx* c, const Model& M, int L, const Segs& sg) {
+int attention_seg_hd(metasd_ctx* c, const Model& M, int L, const Segs& sg, const SegAttn& at) {
     const metasd_model_desc& d = M.d;
     const int R = sg.n * sg.ms;
     const size_t plane = (size_t)d.n_kv_heads * c->cfg.max_ctx * HD;
     const size_t seq_stride = (size_t)M.kv_layers * 2 * plane;
     const T* kc = (const T*)M.kv + (size_t)L * 2 * plane;
     const T* vc = kc + plane;
-    int max_len = 1;
-    double kvpos = 0.0;
-    for (int s = 0; s < sg.n; ++s) {
-        max_len = std::max(max_len, sg.pos0[s] + sg.m[s]);
-        kvpos += (double)(sg.pos0[s] + sg.m[s]);
-    }
-    const int nch_max = (max_len + ATT_CH - 1) / ATT_CH;
     const float scale = 1.0f / sqrtf((float)HD);
-    metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * kvpos * HD * sizeof(T) + (double)R * d.n_heads * HD * 4);
+    metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * at.kvpos * HD * sizeof(T) + (double)R * d.n_heads * HD * 4);
     hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
-    int nrec = nch_max, passes = 1;
+    int nrec = at.nch_max, passes = 1;
     if constexpr (sizeof(T) == 2 && HD >= 64) {
-        const AttnPlan pl = plan_attn(sg.n, d.n_heads, d.n_kv_heads, HD, sg.ms, max_len, c->n_cu, c->att_cpw);
-        const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), rows_split(R), (size_t)R * d.n_heads * HD, 0, 0};
+        const AttnPlan& pl = at.pl;
+        const AttnOut ao{c->d_apart(), pl.nrec, 0, 0, (float*)c->d_ao(), rows_split(R), (size_t)R * d.n_heads * HD, 0, 0};
         nrec = pl.nrec;
         passes = pl.spw / ATT_NW;
-#define ATTN_GO(SHARED) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, false>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, (const bf16_t*)c->d_q(), \
-                                              kc, vc, seq_stride, SegPtrs{}, SegPtrs{}, sg, d.n_heads, d.n_kv_heads, pl.hp, c->cfg.max_ctx, scale, \
-                                              (size_t)R * d.n_heads * HD, pl.spw, ao)
-        if (d.n_heads > d.n_kv_heads * pl.hp) ATTN_GO(true);
-        else ATTN_GO(false);
+#define ATTN_GO(SHARED, ONE) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, false, ONE>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, \
+                                                   (const bf16_t*)c->d_q(), kc, vc, seq_stride, SegPtrs{}, SegPtrs{}, sg, d.n_heads, d.n_kv_heads, pl.hp, \
+                                                   c->cfg.max_ctx, scale, (size_t)R * d.n_heads * HD, pl.spw, ao, pl.items)
+        if (d.n_heads > d.n_kv_heads * pl.hp) { if (nrec == 1) ATTN_GO(true, true); else ATTN_GO(true, false); }
+        else { if (nrec == 1) ATTN_GO(false, true); else ATTN_GO(false, false); }
 #undef ATTN_GO
         if (nrec == 1) { LAUNCH_CHECK(c, "attn (segments)"); return 0; }
     } else {
-        hipExtLaunchKernelGGL((attn_partial_seg_kernel<T, HD>), dim3(nch_max, d.n_heads, sg.n), dim3(256), 0u, c->stream, ea, eb, 0u,
+        hipExtLaunchKernelGGL((attn_partial_seg_kernel<T, HD>), dim3(at.nch_max, d.n_heads, sg.n), dim3(256), 0u, c->stream, ea, eb, 0u,
                               (const float*)c->d_q(), kc, vc, seq_stride, sg, d.n_heads, d.n_kv_heads, c->cfg.max_ctx, scale,
-                              c->d_apart(), nch_max);
+                              c->d_apart(), at.nch_max);
     }
     LAUNCH_CHECK(c, "attn_partial (segments)");
     hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(d.n_heads, R), dim3(HD), 0, c->stream, c->d_apart(), nrec, d.n_heads,
-                       (float*)c->d_ao(), sizeof(T) == 2 ? rows_split(R) : 0, sg, passes);
+                       (float*)c->d_ao(), sizeof(T) == 2 ? rows_split(R) : 0, sg, passes, sizeof(T) == 2 && HD >= 64 ? 0 : 1);
     LAUNCH_CHECK(c, "attn_combine (segments)");
     return 0;
 }
 
 template <typename T>
-int attention_seg(metasd_ctx* c, const Model& M, int L, const Segs& sg) {
+int attention_seg(metasd_ctx* c, const Model& M, int L, const Segs& sg, const SegAttn& at) {
     switch (M.hd) {
-        case 32: return attention_seg_hd<T, 32>(c, M, L, sg);
-        case 64: return attention_seg_hd<T, 64>(c, M, L, sg);
+        case 32: return attention_seg_hd<T, 32>(c, M, L, sg, at);
+        case 64: return attention_seg_hd<T, 64>(c, M, L, sg, at);
         default:
-            if constexpr (sizeof(T) == 2) return attention_seg_hd<T, 128>(c, M, L, sg);
+            if constexpr (sizeof(T) == 2) return attention_seg_hd<T, 128>(c, M, L, sg, at);
             return c->fail(METASD_E_INVALID, "fp32 head_dim 128 unsupported");
     }
 }
@@ -1477,6 +1490,7 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
     LAUNCH_CHECK(c, "embed (segments)");
     hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope(), (long long*)nullptr, (size_t)0);
     LAUNCH_CHECK(c, "rope_table (segments)");
+    const SegAttn at = plan_segs(c, d, hd, sg);
     for (int L = 0; L < d.n_layers; ++L) {
         launch_addnorm_many<T>(c, R, h, part, ns, D, (const T*)M.layer_w(L, 0), d.rms_eps, xn, split);
         LAUNCH_CHECK(c, "addnorm");
@@ -1486,7 +1500,7 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
                            (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, seq_stride, c->cfg.max_ctx, sizeof(T) == 2 ? 1 : 0,
                            (split && hd >= 64) ? 1 : 0);
         LAUNCH_CHECK(c, "rope_kv (segments)");
-        if ((rc = attention_seg<T>(c, M, L, sg))) return rc;
+        if ((rc = attention_seg<T>(c, M, L, sg, at))) return rc;
         if ((rc = gemm_rows_add<T>(c, c->d_ao(), R, DQ, M.layer_w(L, 4), D, h, &ns))) return rc;
         launch_addnorm_many<T>(c, R, h, part, ns, D, (const T*)M.layer_w(L, 5), d.rms_eps, xn, split);
         LAUNCH_CHECK(c, "addnorm");
@@ -1530,11 +1544,12 @@ int forward_segs_step(metasd_ctx* c, Model& M, const Segs& sg, float* logits, in
         a.h = h; a.gain = (const bf16_t*)gain; a.eps = d.rms_eps; a.m = R; a.K = D;
         return a;
     };
+    const SegAttn at = plan_segs(c, d, hd, sg);
     for (int L = 0; L < d.n_layers; ++L) {
         StepArgs a = norm_in(M.layer_w(L, 0));
         a.rowkv = rowkv;
         if ((rc = gemm_step_qkv(c, M, L, 0, a))) return rc;
-        if ((rc = attention_seg<T>(c, M, L, sg))) return rc;
+        if ((rc = attention_seg<T>(c, M, L, sg, at))) return rc;
         if ((rc = gemm_step_add(c, c->d_ao(), R, DQ, M.layer_w(L, 4), D, h))) return rc;
         a = norm_in(M.layer_w(L, 5));
         a.out = (float*)c->d_act(); a.N = F; a.swiglu = d.act == METASD_SWIGLU;
@@ -1721,14 +1736,9 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
     LAUNCH_CHECK(c, "embed (grouped)");
     hipLaunchKernelGGL(rope_table_seg_kernel, dim3(R), dim3(hd / 2), 0, st, sg, hd, d.rope_theta, c->d_rope(), (long long*)nullptr, (size_t)0);
     LAUNCH_CHECK(c, "rope_table (segments)");
-    int max_len = 1;
-    double kvpos = 0.0;
-    for (int s = 0; s < sg.n; ++s) {
-        max_len = std::max(max_len, sg.pos0[s] + sg.m[s]);
-        kvpos += (double)(sg.pos0[s] + sg.m[s]);
-    }
-    const AttnPlan pl = plan_attn(sg.n, H, KH, HD, sg.ms, max_len, c->n_cu, c->att_cpw);
-    const AttnOut ao{c->d_apart(), pl.nrec, 0, (float*)c->d_ao(), 2, (size_t)R * H * HD, 0, 0};
+    const SegAttn at = plan_segs(c, d, HD, sg);
+    const AttnPlan& pl = at.pl;
+    const AttnOut ao{c->d_apart(), pl.nrec, 0, 0, (float*)c->d_ao(), 2, (size_t)R * H * HD, 0, 0};
     const float scale = 1.0f / sqrtf((float)HD);
     for (int L = 0; L < d.n_layers; ++L) {
         hipLaunchKernelGGL(addnorm_segp_kernel<T>, dim3(R), dim3(1024), 0, st, h, part, ns, (size_t)R * D, D,
@@ -1741,16 +1751,16 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
                            (const double2*)c->d_rope(), (float*)c->d_q(), kcs, vcs, c->cfg.max_ctx, 1, 1);
         LAUNCH_CHECK(c, "rope_kv (grouped)");
         {
-            metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * KH * kvpos * HD * sizeof(T) + (double)R * H * HD * 4);
-#define ATTN_GO(SHARED) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, true>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, st, pr ? pr->a : nullptr, pr ? pr->b : nullptr, \
-                                              0u, (const bf16_t*)c->d_q(), (const bf16_t*)nullptr, (const bf16_t*)nullptr, (size_t)0, kcs, vcs, sg, H, KH, pl.hp, \
-                                              c->cfg.max_ctx, scale, (size_t)R * H * HD, pl.spw, ao)
-            if (H > KH * pl.hp) ATTN_GO(true);
-            else ATTN_GO(false);
+            metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * KH * at.kvpos * HD * sizeof(T) + (double)R * H * HD * 4);
+#define ATTN_GO(SHARED, ONE) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, true, ONE>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, st, pr ? pr->a : nullptr, \
+                                                   pr ? pr->b : nullptr, 0u, (const bf16_t*)c->d_q(), (const bf16_t*)nullptr, (const bf16_t*)nullptr, (size_t)0, \
+                                                   kcs, vcs, sg, H, KH, pl.hp, c->cfg.max_ctx, scale, (size_t)R * H * HD, pl.spw, ao, pl.items)
+            if (H > KH * pl.hp) { if (pl.nrec == 1) ATTN_GO(true, true); else ATTN_GO(true, false); }
+            else { if (pl.nrec == 1) ATTN_GO(false, true); else ATTN_GO(false, false); }
 #undef ATTN_GO
             LAUNCH_CHECK(c, "attn (grouped)");
             if (pl.nrec > 1) {
-                hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(H, R), dim3(HD), 0, st, c->d_apart(), pl.nrec, H, (float*)c->d_ao(), 2, sg, pl.spw / ATT_NW);
+                hipLaunchKernelGGL((attn_combine_seg_kernel<HD>), dim3(H, R), dim3(HD), 0, st, c->d_apart(), pl.nrec, H, (float*)c->d_ao(), 2, sg, pl.spw / ATT_NW, 0);
                 LAUNCH_CHECK(c, "attn_combine (segments)");
             }
         }

@@ -382,3 +382,26 @@ def test_bf16_few_rows_of_several_sequences(heads, kv, B, gamma):
     for ls in bl.seqs:
         st = ls.stats
         assert st["max_dp"] <= 4e-3 and st["max_dq"] <= 4e-3 and st["ties_shared"] <= 1, st     # (bound: see test_gpu_attn.py)
+
+
+@pytest.mark.parametrize("grouped", ["1", "0"])
+@pytest.mark.parametrize("heads,kv", [(8, 2), (4, 4), (12, 12)])
+def test_bf16_one_long_context_among_short_ones(heads, kv, grouped, monkeypatch):
+    """Contexts of 1200, 300, 40 and 9 positions: the long one is split into several records per head and merged, the next into two, the short
+    ones are finished by one workgroup each, in the same launch (head_dim 64 with grouped queries, 128, and more heads than a power of two);
+    verification of 16 rows and, in the drafters, steps of all arms together and arm by arm.  The contexts grow past a sub-block (32
+    positions) and the shortest ones from one sub-block to two."""
+    monkeypatch.setenv("METASD_DRAFT_GROUPED", grouped)
+    d = 768 if heads == 12 else 512
+    td = W.model_desc(2, d, heads, kv, 416, 1024, W.SWIGLU, W.BF16)
+    dd = W.model_desc(1, d, heads, kv, 288, 1024, W.GELU, W.BF16)
+    cfg = dict(target=(td, W.gen_weights(td, 0)), drafters=[(dd, W.gen_weights(dd, 7)), (dd, W.gen_weights(dd, 8))], gamma=3, beta=1.0, seed=3, max_ctx=1240)
+    prompts = [W.prompt_tokens(n, 1024, 40 + n) for n in (300, 1200, 9, 40)]
+    g, seqs = batch_pair(cfg, 1.0, prompts, TOL)
+    bl = make_lockstep(g, cfg, seqs, prompts, 1.0, TOL)
+    for r in range(6):
+        bl.round([(b + r // 2) % 2 for b in range(4)])
+    g.close()
+    for ls in bl.seqs:
+        st = ls.stats
+        assert st["max_dp"] <= 4e-3 and st["max_dq"] <= 4e-3 and st["ties_shared"] <= 1, st     # (bound: see test_gpu_attn.py)
