@@ -69,20 +69,23 @@ __device__ __forceinline__ void attn_body(AttnShared<HD>& sm, const bf16_t* __re
         return s;
     };
     u32x4 kf[2][KC], vr[VIT];
-    // byte offsets of 32 bits against uniform bases; positions past the end re-read the last one: their weight is zero
+    // byte offsets of 32 bits against the first row of the span (a span is at most 4 GiB long, a plane can be longer); positions past the
+    // end re-read the last one: their weight is zero
+    const char *kspan = reinterpret_cast<const char*>(kb) + (size_t)s0 * (32 * HD * 2), *vspan = reinterpret_cast<const char*>(vb) + (size_t)s0 * (32 * HD * 2);
+    const int last = L - 1 - s0 * 32;
     auto request_k = [&](int s) {
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const uint32_t at = (uint32_t)min(s * 32 + t * 16 + col, L - 1) * (HD * 2) + g * 16;
+            const uint32_t at = (uint32_t)min((s - s0) * 32 + t * 16 + col, last) * (HD * 2) + g * 16;
 #pragma unroll
-            for (int k = 0; k < KC; ++k) kf[t][k] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(kb) + at + k * 64);
+            for (int k = 0; k < KC; ++k) kf[t][k] = *reinterpret_cast<const u32x4*>(kspan + at + k * 64);
         }
     };
     auto request_v = [&](int s) {
 #pragma unroll
         for (int it = 0; it < VIT; ++it) {
-            const uint32_t at = (uint32_t)min(s * 32 + it * (64 / VPR) + lane / VPR, L - 1) * (HD * 2) + (lane % VPR) * 16;
-            const u32x4* vp = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(vb) + at);
+            const uint32_t at = (uint32_t)min((s - s0) * 32 + it * (64 / VPR) + lane / VPR, last) * (HD * 2) + (lane % VPR) * 16;
+            const u32x4* vp = reinterpret_cast<const u32x4*>(vspan + at);
             vr[it] = SHARED ? *vp : __builtin_nontemporal_load(vp);
         }
     };

@@ -21,6 +21,7 @@ constexpr int ATT_NW = 4;      // wavefronts of a workgroup; each takes every fo
 // Per layer, one record per head of every sequence against this rule: 32 sequences, one of 8000 positions and 31 of 64, 256 verification rows of
 // the 7B shape 335 -> 284 us, a drafter step (12 heads of 64) 97 -> 66; 8 sequences with one of 8000 232 -> 175; 64 .. 8000 in even
 // steps, a drafter step 152 -> 138.
+constexpr int ATT_MAX_PASSES = 1 << 16;     // a span's K or V rows of 128: 2 GiB, so that the kernel's byte offsets in it fit into 32 bits
 constexpr int ATT_SEGS = 32;   // most sequences of a launch
 // The workgroup items of a launch - (sequence, K/V head, record) - without gaps: those of sequence s are first[s] .. first[s + 1] - 1, of n in all
 // (past the last sequence: first[s] = n).
@@ -51,7 +52,7 @@ inline AttnPlan plan_attn(const int* len, int nseg, int H, int KH, int hd, int m
             if (passes > 4 && wgs * 8 <= n_cu / 2) passes = passes_of(16);
         }
     }
-    p.spw = ATT_NW * passes;
+    p.spw = ATT_NW * std::min(passes, ATT_MAX_PASSES);
     p.nrec = (nsub + p.spw - 1) / p.spw;
     for (int s = 0; s < ATT_SEGS; ++s) p.items.first[s + 1] = p.items.first[s] + (s < nseg ? KH * (((len[s] + 31) / 32 + p.spw - 1) / p.spw) : 0);
     p.items.n = p.items.first[nseg];

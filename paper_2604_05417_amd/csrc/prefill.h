@@ -73,12 +73,14 @@ __global__ __launch_bounds__(256, HD == 128 ? 2 : 4) void attn_prefill_kernel(co
     const bf16_t* vb = vc + (size_t)kh * max_ctx * HD;
     u32x4 kr[IT], vr[IT];
     auto request = [&](int p0) {                       // rows past the end re-read the last row: their weight is zero
+        // byte offsets of 32 bits (addresses of 64 bits per piece do not fit in the registers) against the base of the tile, which is uniform:
+        // a whole plane can be longer than 4 GiB
+        const char *kt = reinterpret_cast<const char*>(kb) + (size_t)p0 * (HD * 2), *vt = reinterpret_cast<const char*>(vb) + (size_t)p0 * (HD * 2);
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            // byte offsets of 32 bits against uniform bases (addresses of 64 bits per piece do not fit in the registers)
-            const uint32_t at = (uint32_t)min(p0 + it * (256 / VPR) + tid / VPR, L - 1) * (HD * 2) + (tid % VPR) * 16;
-            kr[it] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(kb) + at);
-            vr[it] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(vb) + at);
+            const uint32_t at = (uint32_t)min(it * (256 / VPR) + tid / VPR, L - 1 - p0) * (HD * 2) + (tid % VPR) * 16;
+            kr[it] = *reinterpret_cast<const u32x4*>(kt + at);
+            vr[it] = *reinterpret_cast<const u32x4*>(vt + at);
         }
     };
     auto stage = [&](int b) {
