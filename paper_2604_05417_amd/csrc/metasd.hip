@@ -1294,8 +1294,12 @@ int launch_gemm_tiles(metasd_ctx* c, const TilesLaunch& a, const RowsPlan& s, me
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     const hipEvent_t ea = pr ? pr->a : nullptr, eb = pr ? pr->b : nullptr;
     const dim3 grid(s.nrb * s.ngroups * s.ksplit, a.gg ? a.gg->n : 1);
+    // forms that do not exist (the callers' plans avoid them): a wavefront with an odd number of tiles has no pairs of gate and up, and row
+    // groups have neither rotations nor residual rows
+    if (EPI == TILES_ACT && TB % 2 && a.ep.swiglu) return c->fail(METASD_E_INVALID, "many-row GEMM: SwiGLU behind %d tiles per wavefront", TB);
     if (a.gg) {
-        if constexpr (EPI == TILES_PART || EPI == TILES_ACT) {
+        if constexpr (EPI != TILES_PART && EPI != TILES_ACT) return c->fail(METASD_E_INVALID, "many-row GEMM: row groups with epilogue %d", EPI);
+        else {
             static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_tiles_grouped_kernel<RB, TB, NS, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (attr != hipSuccess) return c->fail(METASD_E_HIP, "gemm_tiles_grouped_kernel: cannot reserve %d bytes of LDS", lds);
             hipExtLaunchKernelGGL((gemm_tiles_grouped_kernel<RB, TB, NS, EPI>), grid, dim3(512), (uint32_t)lds, c->stream, ea, eb, 0u, a.x, a.K / 32, a.t0,
