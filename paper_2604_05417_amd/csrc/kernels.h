@@ -2141,6 +2141,7 @@ __device__ __forceinline__ int sample_rows_body(float (&xp)[AK_CH][4], int V, fl
 
 // What the drafter's next step starts from, left by the launch that draws its token (one row): the token's embedding and the rotations of
 // its position, as embed_rope_kernel writes them - that launch (2 - 4 us, on top of the one for the draw) stood between every two steps.
+// Rows are read in pieces of 8 or 16 bytes: every weight is 16-byte aligned (metasd_create, metasd_swap_weight), d_model a multiple of 4.
 struct NextRow {
     const void* E;               // embedding table; nullptr: nothing is left
     int bf16, d, pos, hd;

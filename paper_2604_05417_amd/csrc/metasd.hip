@@ -2343,7 +2343,6 @@ int32_t metasd_draft(metasd_ctx* c, const int32_t* k, int32_t gamma) {
     Model& D = c->drafters[k[0]];
     const int V = D.d.vocab, l = c->sq[0].l;
     const float T = c->cfg.temperature;
-    const bool next_row = (uintptr_t)D.w[0] % 16 == 0;     // the draw reads embedding rows in pieces of 8 or 16 bytes
     for (int j = 0; j < gamma; ++j) {
         float* Qj = c->d_Q() + (size_t)j * V;
         int rc;
@@ -2359,14 +2358,14 @@ int32_t metasd_draft(metasd_ctx* c, const int32_t* k, int32_t gamma) {
         } else if (j == 0) rc = forward(c, D, D.kvl[0], l - D.kvl[0], Qj, false);   // catch-up, ends with the last committed token
         else {
             c->head_est = D.head;                      // a drafter head goes on from its own estimate of the last feature
-            c->embedded = next_row;                    // the draw of the token left its row
+            c->embedded = true;                        // the draw of the token left its row
             rc = forward(c, D, l + j - 1, 1, Qj, false);
             c->embedded = false;
             c->head_est = false;
         }
         if (rc) return rc;
         NextRow next{};
-        if (next_row && j + 1 < gamma) next = NextRow{D.w[0], D.d.dtype == METASD_BF16, D.d.d_model, l + j, D.hd, D.d.rope_theta, c->d_h(), c->d_rope()};
+        if (j + 1 < gamma) next = NextRow{D.w[0], D.d.dtype == METASD_BF16, D.d.d_model, l + j, D.hd, D.d.rope_theta, c->d_h(), c->d_rope()};
         if (launch_sample(c->stream, Qj, 1, V, T, c->cfg.seed, (uint32_t)c->sq[0].round, (uint32_t)j, 0u, c->d_hist() + l + j, 1,
                           c->d_draft() + j, next))
             return c->fail(METASD_E_HIP, "launch sample_rows failed");

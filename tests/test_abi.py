@@ -95,6 +95,22 @@ def test_sizes_and_validation(lib):
     assert lib.metasd_last_error(None) is not None
 
 
+@pytest.mark.parametrize("model,index", [(-1, 0), (0, 0), (1, 3)])
+def test_weights_off_their_alignment_are_refused(lib, model, index):
+    """Kernels read weights, embedding rows among them, in pieces of 16 bytes: a table entry that is not 16-byte aligned is refused before
+    anything reaches the device."""
+    cfg = B._Config(2, 4, 1, 96, 1.0, 0, 1.0, 1)
+    td, dr = desc(), (B._Desc * 2)(desc(n_layers=1), desc(n_layers=1))
+    n = C.c_size_t(0)
+    assert lib.metasd_workspace_bytes(C.byref(cfg), C.byref(td), dr, C.byref(n)) == 0
+    tables = [(C.c_void_p * (1 + 9 * layers + 2))(*[4096] * (1 + 9 * layers + 2)) for layers in (2, 1, 1)]
+    tables[model + 1][index] = 4096 + 8
+    dtab = (C.POINTER(C.c_void_p) * 2)(*[C.cast(t, C.POINTER(C.c_void_p)) for t in tables[1:]])
+    kv, h = (C.c_void_p * 2)(8192, 12288), C.c_void_p()
+    assert lib.metasd_create(C.byref(h), C.byref(cfg), C.byref(td), dr, tables[0], dtab, 16384, kv, 1 << 20, n.value, None) == -1
+    assert f"weight {index} is not 16-byte aligned".encode() in lib.metasd_last_error(None) and not h.value
+
+
 def test_no_cpu_fallback():
     import torch
     if torch.cuda.is_available():
