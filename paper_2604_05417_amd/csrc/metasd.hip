@@ -1446,8 +1446,7 @@ int attention_seg(metasd_ctx* c, const Model& M, int L, const Segs& sg, const Se
     }
 }
 
-// Causal attention of the m rows of a long block (q in d_q, result in d_ao): 32 rows per wavefront where that still leaves a
-// workgroup for every CU, else 16.
+// Causal attention of the m rows of a long block (q in d_q, result in d_ao), 64 rows of a head per workgroup.
 int attention_big(metasd_ctx* c, const metasd_model_desc& d, int hd, const bf16_t* kc, const bf16_t* vc, int pos0, int m) {
     const float scale = 1.0f / sqrtf((float)hd);
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * d.n_kv_heads * (double)(pos0 + m) * hd * 2 + (double)m * d.n_heads * hd * 4);

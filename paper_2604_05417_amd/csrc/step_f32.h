@@ -5,7 +5,8 @@ namespace msd {
 
 // A layer of a narrow fp32 model moves a few hundred KB, so its time is its launches: 2 - 4 us each, ten of them, of which six (norms,
 // rotation, merge, activation, residual) only hand rows from one GEMM to the next.  Here the GEMM that reads a row normalises it and the
-// GEMM that makes it rotates, activates or adds it: five launches per layer.
+// GEMM that makes it rotates, activates or adds it: five launches per layer, four where the context is short enough for attention and output
+// projection in one (below).
 // One wavefront per unit = NF output features: one, or the pair a rotation or a SwiGLU needs; lanes stride over K.  Everything a wavefront
 // reads is requested before anything is waited for; NORM: every workgroup normalises all m rows into LDS itself (they are few and short).
 // Sums: lane partials in fp32, then over the lanes; the norm is 1/sqrt(mean of squares + eps) of the rows in fp32 as in addnorm_kernel.
