@@ -13,8 +13,10 @@ constexpr int ATT_NW = 4;      // wavefronts of a workgroup; each takes every fo
 // head groups): a long context among short ones is split as if it were alone.  Records per head: none to merge (one workgroup sees the
 // whole context) where that fills the CUs - 32 sequences x 32 heads 160 us against 180 + 10 with three records, 8 x 32 heads 43 against
 // 47 + 4 - also nearly (7/8 of them: 12 sequences, half of 3000 and half of 500 positions, a layer 227 against 236 us with two records) or with
-// contexts a quarter shorter on average than the longest (8 sequences, half of them half as long, 218 against 224); or where the context is short (up to 128 KiB of K and V per workgroup: 5 sequences of 333 positions, 32 heads of 64,
-// 6.0 us against 5.4 + 2.8); otherwise up to 8, the most the merge takes in its shortest form, each a whole number of passes of its
+// contexts a quarter shorter on average than the longest (8 sequences, half of them half as long, 218 against 224); or where several sequences with fewer workgroups than CUs are done sooner so: one workgroup alone on its CU walks 35 GB/s, the full
+// chip does 25 per CU, and a merge and the records cost 5.5 us (7B shape, a layer, without and with records: 2 sequences of 333 positions 91.6
+// / 93.9 us, of 900 100.3 / 96.9; 4 of 500 105.3 / 107.5, of 1600 122.3 / 121.0; 5 of 333 118.6 / 124.9, of 1600 136.5 / 139.7; drafter steps of
+// 20 of 1600 66.8 / 72.0); or where the context is short (128 KiB of K and V); otherwise up to 8, the most the merge takes in its shortest form, each a whole number of passes of its
 // wavefronts (65 sub-blocks x 32 heads: 6 records of 3 passes 11.8 us, 8 of 2.25 12.4), and two passes where that still gives half the
 // CUs a workgroup (3 sequences of 500 positions: 11.5 against 13.7 us).  Up to 16 where few heads walk a long context (12 heads x 8012
 // positions: 11.6 against 13.1 us).
@@ -45,7 +47,9 @@ inline AttnPlan plan_attn(const int* len, int nseg, int H, int KH, int hd, int m
     int passes = force_passes;
     if (passes <= 0) {
         const bool full = all >= n_cu && (wgs * 8 >= n_cu * 7 || wgs * 4 >= all * 3);
-        if (full || (size_t)max_len * hd * 4 <= 128 * 1024) passes = passes_of(1);
+        const double kv = (double)max_len * hd * 4;       // bytes
+        const bool few = nseg > 1 && all < n_cu && kv * (1 / 35e3 - wgs / (25e3 * n_cu)) <= 5.5;
+        if (full || few || kv <= 128 * 1024) passes = passes_of(1);
         else {
             passes = passes_of(std::min(8, (3 * n_cu / 2 + wgs - 1) / wgs));
             if (passes == 1 && wgs * ((nsub + 2 * ATT_NW - 1) / (2 * ATT_NW)) >= n_cu / 2) passes = 2;
