@@ -17,11 +17,13 @@ namespace msd {
 // barrier per stage is enough, neither the reads nor the waits for them stand between MFMAs, and a stage's buffer is free as soon as it
 // has been read - its next request is made NS stages ahead.  The first row block is multiplied before the requests and reads are issued,
 // so that the matrix cores start right behind the barrier.
-//   What bounds it: from about 500 rows on power and the quantum of whole tiles per CU.  1.26 PFLOP/s (both terms counted) on gate | up of
-// the 7B shape at 1499 rows with random values.  Two groups of wavefronts taking turns between reading and multiplying, two barriers per
-// stage and one register set, were here before; on the same card, 1499 rows of the 7B shape: gate | up 457 -> 430 us, q | k | v 268 -> 260,
-// output and down 141 -> 132 (mean); 511 rows of the 1B shape: gate | up 62.5 -> 56.5, down 37.3 -> 36.2; 256 rows 47.6 -> 44.8 with 128 x 256
-// tiles, 47.1 -> 48.1 with 128 x 192.
+//   What bounds it: from about 500 rows on the quantum of whole tiles per CU and power.  Gate | up of the 7B shape at 1499 rows (192 x 256
+// tiles) 391 us with random values, 1.38 PFLOP/s with both terms counted, 331 us with zeros.
+// Two groups of wavefronts taking turns between reading and multiplying, two barriers per stage and one register set, were here before;
+// on the same card and with the same tiles, 7B shape at 1499 rows: gate | up 457 -> 430 us, q | k | v 268 -> 260, output and down 141 -> 132
+// (mean); 511 rows of the 1B shape: gate | up 62.5 -> 56.5, down 37.3 -> 36.2.  Large tiles gained most (192 x 256 9 %, 128 x 256 8,
+// 256 x 192 7 over all shapes and splits), small ones lost some (64 x 256 4 %, 128 x 96 3, 64 x 192 2): q | k | v at 256 rows in two
+// halves of K 54.5 -> 47.8 with 128 x 256 tiles, 44.1 -> 44.5 with 128 x 192.
 //   Workgroup ids are dealt out so that the row blocks of one feature group run on one XCD one after the other (its L2 then
 // serves the weights to all of them).
 //   grid nrb * ngroups * ksplit, block 512, dynamic LDS NS * (8192 RB + 2048 TB) bytes;
