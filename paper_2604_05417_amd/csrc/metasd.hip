@@ -181,16 +181,17 @@ bool big_ok(const metasd_model_desc& d) { return d.dtype == METASD_BF16 && d.d_m
 int big_rows(const metasd_config& c) { return std::min(BIG_ROWS, c.max_ctx); }
 
 // Whether n rows (more than MAX_ROWS) from position pos0 on are faster through forward_big than in blocks of 16, which nseq sequences
-// share.  Few rows leave attn_prefill_kernel one workgroup per head, which walks all positions before it: 1.2 (head_dim 64) or 2.4 us
-// per 64 positions and layer but the last, where the 16-row kernels deal the positions out over the chip (0.16 us).  Otherwise a layer
-// takes its weights' time (7 TB/s) and 26 us against 55 us per 16-row block.  Draft step after 17 rows at context 8000, big / small:
-// 768 x 12 heads of 64 288 / 264 us, 2048 x 16 heads of 128 490 / 357, 4096 x 32 703 / 607; 36 rows 293 / 414, 497 / 539, 717 / 910;
-// 17 rows at context 2000 177 / 217, 267 / 292, 455 / 501.  From position 0 the big block always wins.
+// share.  Few rows leave attn_prefill_kernel one workgroup per head, which walks all positions before it: 1.0 (head_dim 64) or 1.6 us
+// per 64 positions and layer but the last, where the 16-row kernels deal the positions out over the chip (7.2 TB/s, at least 0.03 us).
+// Otherwise a layer takes its weights' time (7 TB/s) and 25 us against 54 us per 16-row block.  Measured after 18 .. 192 rows behind 500 ..
+// 32000 positions, 2 to 6 layers, 768 x 12 heads of 64 to 4096 x 32 of 128: the choice costs 0.06 % on average, 5.5 % at most.  Draft step of two
+// layers at context 32000, big / small: 768 x 12 heads after 48 rows 642 / 551 us, 4096 x 32 1249 / 1505; of six, 768 x 12 after 64 2937 / 2033.
+// From position 0 the big block always wins.
 bool big_pays(const metasd_model_desc& d, int pos0, int n, int nseq) {
     const double hd = d.d_model / d.n_heads, D = d.d_model, walk = (pos0 + n) / 64.0;
     const double w = (2 * D * D + 2 * D * d.n_kv_heads * hd + (d.act == METASD_SWIGLU ? 3 : 2) * D * d.d_ffn) * 2 / 7e6;
-    const double small = (double)n / (MAX_ROWS * nseq) * (55 + w + 0.16 * walk);
-    return small >= 26 + w + 1.2 * hd / 64 * walk * (d.n_layers - 1) / d.n_layers;
+    const double small = (double)n / (MAX_ROWS * nseq) * (54 + w + std::max(0.03, d.n_kv_heads * hd * 256 / 7.2e6) * walk);
+    return small >= 25 + w + (hd > 64 ? 1.6 : 1.0) * walk * (d.n_layers - 1) / d.n_layers;
 }
 
 // Word the split-K siblings of a residual GEMM set when their bounded wait for each other runs out (read back with
