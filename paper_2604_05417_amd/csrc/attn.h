@@ -223,10 +223,10 @@ __global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_kernel(co
 }
 
 // Blocks of several sequences: K and V planes of segment s at kc.p[s], vc.p[s] (PTRS) or kv_seq_stride elements per sequence behind
-// kc0, vc0; q_lo: elements of the whole block's q.  ONE: every sequence has one record.  Otherwise the records of a segment follow those of
-// the one before, and a segment that needs only one gets its rows written here and leaves none.  (Looking an item up takes 0.3 - 0.5 us of
-// a launch, 6.7 us for 5 sequences of 333 positions: ONE does without.)
-template <int HD, bool SHARED, bool PTRS, bool ONE>
+// kc0, vc0; q_lo: elements of the whole block's q.  The records of a segment follow those of the one before; a segment that needs only one
+// gets its rows written here and leaves none.  EVEN: every sequence has ao.nrec records, so that an item needs no look-up (0.3 - 0.5 us of
+// a launch, 6.7 us for 5 sequences of 333 positions).
+template <int HD, bool SHARED, bool PTRS, bool EVEN>
 __global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_seg_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc0,
                                                                                 const bf16_t* __restrict__ vc0, size_t kv_seq_stride, SegPtrs kc,
                                                                                 SegPtrs vc, Segs sg, int H, int KH, int hp, int max_ctx, float scale,
@@ -234,9 +234,13 @@ __global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_seg_kerne
     __shared__ AttnShared<HD> sm;
     int gi;
     const int u = attn_unit(blockIdx.x, H / (KH * hp), gi);
-    int s, kh, nrec = 1;                               // sequence and K/V head of the item
-    if constexpr (ONE) {
-        s = u / KH; kh = u - s * KH;
+    int s, kh, nrec;                                   // sequence and K/V head of the item, records of the sequence
+    if constexpr (EVEN) {
+        nrec = ao.nrec;
+        const int head = u / nrec;
+        ao.rec = u - head * nrec;
+        s = head / KH;
+        kh = head - s * KH;
         if (s >= sg.n) return;                         // workgroup-uniform
     } else {
         if (u >= items.n) return;
@@ -251,7 +255,6 @@ __global__ __launch_bounds__(64 * ATT_NW, HD == 128 ? 3 : 4) void attn_seg_kerne
     }
     const int m = sg.m[s], pos0 = sg.pos0[s], nsub = (pos0 + m + 31) >> 5;
     const size_t at = (size_t)kh * max_ctx * HD, so = (size_t)sg.seq[s] * kv_seq_stride;
-    if (ONE) ao.rec = 0;
     ao.direct = nrec == 1;
     ao.part += (size_t)s * H * ao.nrec * 16 * (HD + 2);
     ao.row0 = s * sg.ms;

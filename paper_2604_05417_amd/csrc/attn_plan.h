@@ -12,11 +12,13 @@ constexpr int ATT_NW = 4;      // wavefronts of a workgroup; each takes every fo
 // so what decides is the work of the whole block in units of its longest context (wgs; for sequences of one length their number times the
 // head groups): a long context among short ones is split as if it were alone.  Records per head: none to merge (one workgroup sees the
 // whole context) where that fills the CUs - 32 sequences x 32 heads 160 us against 180 + 10 with three records, 8 x 32 heads 43 against
-// 47 + 4 - also nearly (7/8 of them: 12 sequences, half of 3000 and half of 500 positions, a layer 227 against 236 us with two records) or with
-// contexts a quarter shorter on average than the longest (8 sequences, half of them half as long, 218 against 224); or where several sequences with fewer workgroups than CUs are done sooner so: one workgroup alone on its CU walks 35 GB/s, the full
-// chip does 25 per CU, and a merge and the records cost 5.5 us (7B shape, a layer, without and with records: 2 sequences of 333 positions 91.6
-// / 93.9 us, of 900 100.3 / 96.9; 4 of 500 105.3 / 107.5, of 1600 122.3 / 121.0; 5 of 333 118.6 / 124.9, of 1600 136.5 / 139.7; drafter steps of
-// 20 of 1600 66.8 / 72.0); or where the context is short (128 KiB of K and V); otherwise up to 8, the most the merge takes in its shortest form, each a whole number of passes of its
+// 47 + 4 - also nearly (7/8 of them: 12 sequences, half of 3000 and half of 500 positions, a layer 227 against 236 us with two records) or
+// with contexts a quarter shorter on average than the longest (8 sequences, half of them half as long, 218 against 224); or where several
+// sequences with fewer workgroups than CUs are done sooner so: one workgroup alone on its CU walks 35 GB/s, the full chip does 25 per CU, and
+// a merge and the records cost 5.5 us (7B shape, a layer, without and with records: 2 sequences of 333 positions 91.6 / 93.9 us, of 900 100.3 /
+// 96.9; 4 of 500 105.3 / 107.5, of 1600 122.3 / 121.0; 5 of 333 118.6 / 124.9, of 1600 136.5 / 139.7; drafter steps of 20 of 1600 66.8 / 72.0);
+// or where the context is short (128 KiB of K and V); otherwise up to 8, the most the merge takes in its shortest form, each a whole number
+// of passes of its
 // wavefronts (65 sub-blocks x 32 heads: 6 records of 3 passes 11.8 us, 8 of 2.25 12.4), and two passes where that still gives half the
 // CUs a workgroup (3 sequences of 500 positions: 11.5 against 13.7 us).  Up to 16 where few heads walk a long context (12 heads x 8012
 // positions: 11.6 against 13.1 us).
@@ -30,6 +32,7 @@ constexpr int ATT_SEGS = 32;   // most sequences of a launch
 struct AttnItems { int n, first[ATT_SEGS + 1]; };
 struct AttnPlan {
     int hp, spw, nrec, grid;     // spw: sub-blocks per record; nrec: records of the longest context
+    bool even;                   // every sequence has nrec records
     AttnItems items;
 };
 // len: positions that the sequences see
@@ -60,6 +63,7 @@ inline AttnPlan plan_attn(const int* len, int nseg, int H, int KH, int hd, int m
     p.nrec = (nsub + p.spw - 1) / p.spw;
     for (int s = 0; s < ATT_SEGS; ++s) p.items.first[s + 1] = p.items.first[s] + (s < nseg ? KH * (((len[s] + 31) / 32 + p.spw - 1) / p.spw) : 0);
     p.items.n = p.items.first[nseg];
+    p.even = p.items.n == nseg * KH * p.nrec;
     p.grid = 8 * ((p.items.n + 7) / 8) * (G / p.hp);
     return p;
 }

@@ -1421,11 +1421,11 @@ int attention_seg_hd(metasd_ctx* c, const Model& M, int L, const Segs& sg, const
         const AttnOut ao{c->d_apart(), pl.nrec, 0, 0, (float*)c->d_ao(), rows_split(R), (size_t)R * d.n_heads * HD, 0, 0};
         nrec = pl.nrec;
         passes = pl.spw / ATT_NW;
-#define ATTN_GO(SHARED, ONE) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, false, ONE>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, \
+#define ATTN_GO(SHARED, EVEN) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, false, EVEN>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, c->stream, ea, eb, 0u, \
                                                    (const bf16_t*)c->d_q(), kc, vc, seq_stride, SegPtrs{}, SegPtrs{}, sg, d.n_heads, d.n_kv_heads, pl.hp, \
                                                    c->cfg.max_ctx, scale, (size_t)R * d.n_heads * HD, pl.spw, ao, pl.items)
-        if (d.n_heads > d.n_kv_heads * pl.hp) { if (nrec == 1) ATTN_GO(true, true); else ATTN_GO(true, false); }
-        else { if (nrec == 1) ATTN_GO(false, true); else ATTN_GO(false, false); }
+        if (d.n_heads > d.n_kv_heads * pl.hp) { if (pl.even) ATTN_GO(true, true); else ATTN_GO(true, false); }
+        else { if (pl.even) ATTN_GO(false, true); else ATTN_GO(false, false); }
 #undef ATTN_GO
         if (nrec == 1) { LAUNCH_CHECK(c, "attn (segments)"); return 0; }
     } else {
@@ -1760,11 +1760,11 @@ int forward_step_grouped(metasd_ctx* c, const Segs& sg, const int* arm, float* l
         LAUNCH_CHECK(c, "rope_kv (grouped)");
         {
             metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_ATTN, 2.0 * KH * at.kvpos * HD * sizeof(T) + (double)R * H * HD * 4);
-#define ATTN_GO(SHARED, ONE) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, true, ONE>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, st, pr ? pr->a : nullptr, \
+#define ATTN_GO(SHARED, EVEN) hipExtLaunchKernelGGL((attn_seg_kernel<HD, SHARED, true, EVEN>), dim3(pl.grid), dim3(64 * ATT_NW), 0u, st, pr ? pr->a : nullptr, \
                                                    pr ? pr->b : nullptr, 0u, (const bf16_t*)c->d_q(), (const bf16_t*)nullptr, (const bf16_t*)nullptr, (size_t)0, \
                                                    kcs, vcs, sg, H, KH, pl.hp, c->cfg.max_ctx, scale, (size_t)R * H * HD, pl.spw, ao, pl.items)
-            if (H > KH * pl.hp) { if (pl.nrec == 1) ATTN_GO(true, true); else ATTN_GO(true, false); }
-            else { if (pl.nrec == 1) ATTN_GO(false, true); else ATTN_GO(false, false); }
+            if (H > KH * pl.hp) { if (pl.even) ATTN_GO(true, true); else ATTN_GO(true, false); }
+            else { if (pl.even) ATTN_GO(false, true); else ATTN_GO(false, false); }
 #undef ATTN_GO
             LAUNCH_CHECK(c, "attn (grouped)");
             if (pl.nrec > 1) {
