@@ -112,13 +112,14 @@ Split choose_split(int m, int ntiles, int kchunks) {
 }
 
 // Many-row GEMM (gemm_tiles.h; more than 16 rows): workgroup tile (64 rb rows x 2 tb feature tiles, ns stages of LDS) and K
-// split.  The launch runs in rounds of 256 workgroups.  A stage of 32 inputs takes 0.13 + 0.034 rb tb us, a round 0.75 us besides, a launch
-// some 4 us whatever the plan (left out of the cost); few rows are bound by the weight stream, 7.2 TB/s; a set of partials costs 1.65 times
+// split.  The launch runs in rounds of 256 workgroups.  A stage of 32 inputs takes 0.158 + 0.0374 rb tb us, a round 1.1 us besides, a launch
+// some 4 us whatever the plan (left out of the cost); few rows are bound by the weight stream, 6.1 TB/s; a set of partials costs 1.93 times
 // its traffic at 5 TB/s (written and read again).  The constants are those whose choice loses least over every tile and split of the 7B
-// and 1B projections at 17 .. 2048 rows, each timed with the launch that reads its partials: 1.4 % to the best plan on average, 12.5 at most
-// (a rotation behind 160 rows of 3072 x 2048, 17.5 against 15.5 us); with those fitted to the kernel before (0.115 + 0.044 rb tb, 5.6 TB/s,
-// 1.2) 2.3 and 27 %: gate | up of the 7B shape at 777 rows 312 us in tiles of 64 x 192 instead of 266, of the 1B shape at 20 rows with whole K
-// 21.0 instead of 18.7, q | k | v of the 7B shape at 256 rows with whole K 60.4 instead of 52.5.
+// and 1B projections at 17 .. 2048 rows, each timed with the launch that reads its partials (which costs 2 us more among a layer's launches
+// than in that loop): 1.2 % to the best plan on average, 12.5 at most (a rotation behind 160 rows of 3072 x 2048, 17.5 against 15.5 us);
+// with those fitted to the kernel before (0.115 + 0.044 rb tb, 5.6 TB/s, 1.2) 2.3 and 27 %: gate | up of the 7B shape at 777 rows 312 us in
+// tiles of 64 x 192 instead of 245, of the 1B shape at 20 rows with whole K 21.0 instead of 18.7, q | k | v of the 7B shape at 256 rows with
+// whole K 60.4 instead of 52.5.
 // A split whose partials exceed PARTIALS_MAX never pays (50 us of traffic).
 struct RowsPlan { int rb, tb, ksplit, cps, nrb, ngroups; };
 constexpr size_t PARTIALS_MAX = (size_t)128 << 20;
@@ -131,13 +132,13 @@ constexpr int rows_stages(int rb, int tb) {
 }
 
 //   behind: what is done with the sums besides storing them, in the launch itself where K is whole (TILES_ACT: pairs of tiles for SwiGLU;
-// TILES_ROPE: 0.93 times the sums' traffic in all), else in a launch of its own, which costs its start and the traffic of its results.  These
+// TILES_ROPE: 1.43 times the sums' traffic in all), else in a launch of its own, 3.2 us and the traffic of its results.  These
 // are the same for every split, so that of the plans with partials the cheapest is the one that BEHIND_NONE would give.
 enum { BEHIND_NONE = 0, BEHIND_ACT = 1, BEHIND_PAIRS = 2, BEHIND_ROPE = 3 };
 RowsPlan plan_rows(int ntiles, int kchunks, int R, int groups, int forced_tpb, int forced_rb, int behind) {
     RowsPlan best{};
     double best_cost = 1e30;
-    const double stream = (double)groups * ntiles * kchunks * 1024 / 7.2e6;
+    const double stream = (double)groups * ntiles * kchunks * 1024 / 6.1e6;
     for (const auto& t : ROWS_TILES) {
         const int rb = t[0], tb = t[1];
         if ((forced_tpb && 2 * tb != forced_tpb) || (forced_rb && rb != forced_rb)) continue;
@@ -146,11 +147,11 @@ RowsPlan plan_rows(int ntiles, int kchunks, int R, int groups, int forced_tpb, i
         for (int ks = 1; ks <= 8 && (ks == 1 || (kchunks / ks >= 8 && (size_t)ks * R * groups * ntiles * 64 <= PARTIALS_MAX)); ++ks) {
             const int cps = (kchunks + ks - 1) / ks, k2 = (kchunks + cps - 1) / cps;
             const double rounds = (nrb * ng * k2 * groups + 255) / 256;
-            const double mult = rounds * (cps * (0.13 + 0.034 * rb * tb) + 0.75);
+            const double mult = rounds * (cps * (0.158 + 0.0374 * rb * tb) + 1.1);
             const double sums = (double)R * groups * ntiles * 64 / 5e6;      // R: rows of a group
             const bool whole = k2 == 1 && (behind != BEHIND_PAIRS || tb % 2 == 0);
-            const double cost = std::max(mult, stream) + 0.26 * std::min(mult, stream) +
-                                (behind == BEHIND_NONE ? 1.65 * k2 * sums : whole ? 0.93 * sums : 1.65 * k2 * sums + 1.4 + 0.34 * sums);
+            const double cost = std::max(mult, stream) + 0.27 * std::min(mult, stream) +
+                                (behind == BEHIND_NONE ? 1.93 * k2 * sums : whole ? 1.43 * sums : 1.93 * k2 * sums + 3.2 + 0.29 * sums);
             if (cost < best_cost) { best_cost = cost; best = RowsPlan{rb, tb, k2, cps, nrb, ng}; }
         }
     }
