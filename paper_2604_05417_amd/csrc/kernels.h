@@ -4,6 +4,7 @@
 // (see check_model / the asserts next to each launcher), kernels themselves only guard ragged tails.
 #pragma once
 
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -65,17 +66,20 @@ __device__ __forceinline__ float dpp_move(float old, float v) {
 }
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_move(double v) {          // lanes without a source get 0
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    constexpr bool ALL = ROWS == 0xf;                           // (rows left out keep the 0 that the destination is filled with first)
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, ALL);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, ALL);
     return __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ float dpp_max(float v) {
-    v = fmaxf(v, dpp_move<0x111, 0xf>(-INFINITY, v));           // row_shr:1, 2, 4, 8
-    v = fmaxf(v, dpp_move<0x112, 0xf>(-INFINITY, v));
-    v = fmaxf(v, dpp_move<0x114, 0xf>(-INFINITY, v));
-    v = fmaxf(v, dpp_move<0x118, 0xf>(-INFINITY, v));
-    v = fmaxf(v, dpp_move<0x142, 0xa>(-INFINITY, v));           // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
-    v = fmaxf(v, dpp_move<0x143, 0xc>(-INFINITY, v));
+    // row_shr:1, 2, 4, 8, row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3; a lane without a source keeps its value.  (A DPP
+    // operand is read two wait states after it was written.)
+    asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf" : "+v"(v));
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 __device__ __forceinline__ double dpp_scan(double v) {
@@ -1437,24 +1441,23 @@ __device__ __forceinline__ float ak_exp(float a) {
 
 // exp((x - mx) / T).  T = 1: the fp32 difference is the correctly rounded argument.  Otherwise the difference is multiplied by
 // log2(e) / T held as two floats, one rounding more than the difference's own.  (Largest and rms error against 64 bits, T = 0.7:
-// 5.4e-6 and 1.39e-6; with the argument scaled in 64 bits and rounded twice, as before, 7.2e-6 and 1.46e-6 and four more instructions.)
-// Any T > 0: where the argument is below -200 the result is 0 whatever the low term adds, so the difference is held at `floor` there
-// and the low term stays finite - masked entries (-inf, the lowest float) and the lanes past the vocabulary would else give -inf + inf
-// from T of about 1e-16 down.  The scale is held at the largest float (T of 4e-39 and less, where any difference of more than 1e-36
-// gives 0), or the largest entry would be 0 * inf.
-struct ExpScale { float hi, lo, floor; };
+// 5.4e-6 and 1.39e-6.)
+// Any T > 0: the high term is rounded down and the low term is never 0, so that both products of a masked entry (-inf, the lowest float) or
+// of a lane past the vocabulary are -inf or finite and their sum is never -inf + inf.  The scale is held at the largest float (T of 4e-39
+// and less, where any difference of more than 1e-36 gives 0), or the largest entry would be 0 * inf.
+struct ExpScale { float hi, lo; };
 __device__ __forceinline__ ExpScale exp_scale(double invT) {
-    constexpr float FMAX = 3.4028234663852886e38f;
+    constexpr float FMAX = 3.4028234663852886e38f, TINY = 1.4e-45f;
     const double c = fmin(invT * 1.4426950408889634074, (double)FMAX);
-    const float hi = (float)c;
-    // (the reciprocal is 0 for the largest scales, whose low term is then left out: only differences that give 0 would see it)
-    return ExpScale{hi, (float)(c - (double)hi), fmaxf(-200.f * __builtin_amdgcn_rcpf(hi), -FMAX)};
+    float hi = (float)c;
+    if ((double)hi > c) hi = __uint_as_float(__float_as_uint(hi) - 1u);
+    return ExpScale{hi, fmaxf((float)(c - (double)hi), TINY)};
 }
 template <bool UNIT_T>
 __device__ __forceinline__ float ak_expx(float x, float mx, const ExpScale& k) {
     const float t = x - mx;
     if constexpr (UNIT_T) return ak_exp(t);
-    else return __builtin_amdgcn_exp2f(fmaf(t, k.hi, fmaxf(t, k.floor) * k.lo));
+    else return __builtin_amdgcn_exp2f(fmaf(t, k.hi, t * k.lo));
 }
 
 // A lane past the vocabulary asks for nothing.  (Unconditional requests clamped to the last values, the form as_load has, cost every
@@ -1714,84 +1717,169 @@ __global__ __launch_bounds__(AK_NT) void accept_rows_kernel(const float* __restr
 // ------------------------------------------------------------------------------------------
 // The same accept step with every (row, position) split over four workgroups of 256 threads, one
 // per quarter of the vocabulary (8192 entries: wavefront w of quarter q owns [8192 q + 2048 w, +2048),
-// 64 data registers per lane).  Four such workgroups fit on a CU, so the loads of one overlap the
-// arithmetic of another, and 64 rows x 6 positions give 1536 equal pieces for 1024 resident slots
-// instead of 384 items for 256.  The quarters of an item meet twice through 64-bit words in global
-// memory, each word = (launch epoch << 32 | payload), written and polled with relaxed agent-scope
-// atomics: a reader knows a word is this launch's as soon as the epoch matches, so there are no
+// 64 data registers per lane).  Four such workgroups fit on a CU.  The quarters of an item meet twice
+// through 64-bit words in global memory, each word = (launch epoch << 32 | payload), written and polled with
+// relaxed agent-scope atomics: a reader knows a word is this launch's as soon as the epoch matches, so there are no
 // flags, no fences and nothing to clear between launches (the buffer starts zeroed and epochs only
 // grow).  Sums travel as two floats (hi + lo, 48 bits) so that all four workgroups use identical values.
+//   A wavefront exponentiates against its own maximum as soon as its logits are there: those of P while Q is on its way.
 //   meeting A: each quarter's maxima m_k and sums z_k = sum exp(x - m_k) of P_j and Q_j.  With
 //              M = max m_k the normaliser is Z = sum_k z_k exp(m_k - M), and an element's probability
-//              is exp(x - m_k) * (exp(m_k - M) / Z): the per-quarter factor is folded into 1/Z, so no
-//              element is touched twice.
+//              is exp(x - m) * (exp(m - M) / Z) with the maximum m it was exponentiated against: the factor is folded into
+//              1/Z, so no element is touched twice.
 //   meeting B: each quarter's residual mass and sum min(p, q) -> Z_res, the BD term, and the quarter
 //              that holds u Z_res; only that quarter searches (wavefront, chunk, lane, element).
-// The candidate of the position is published as one more tagged word, and the workgroup (quarter 0,
-// bonus position) of every row waits for the row's gamma + 1 candidates and writes N_acc, the
+// What every thread would compute alike (four wavefronts' or quarters' maxima, factors, sums of P and Q) the lanes of a
+// wavefront compute side by side, 4 w + k for quarter k of P (w = 0) or Q (w = 1).
+// The candidate of the position and the outcome of its test are published as two more tagged words, and the workgroup (quarter 0,
+// bonus position) of every row waits for the row's gamma + 1 pairs and writes N_acc, the
 // emitted token and the mask - no second kernel.
-// Liveness: workgroups are dispatched in id order on every XCD, and a workgroup only waits for
-// workgroups with ids below its own or in its own group of four, so the oldest unfinished item
-// always has everything it waits for resident or done.  The polls are bounded all the same: after
+// A group of quarters works through consecutive items (launch_accept: how many) and requests the next item's P before it waits in
+// meeting B.
+// What bounds it: for many rows the vector units beside the stream - 940 instructions per wavefront and item (T = 0.7), 5.1 TB/s at 250 rows x
+// gamma 7 x 32000 (93.4 us; 1360 and 112 us with every thread forming every maximum, factor and quotient, both exponentials scaled and
+// logits quieted in front of every maximum); for one row the chain load 1 - exponentials 1 - meeting 1.3 - residuals 0.7 - meeting 1.1 -
+// search 0.3 - row 0.5 us behind a launch (9.4 us; 10.6); 64 rows x gamma 5 24.4 us (29.4).
+// Liveness: a workgroup only waits for its own group, or for items of groups with ids below its own; workgroups are dispatched in
+// id order, so the oldest unfinished group always has everything it waits for resident or done.  (A row that a group before this one
+// began is finished after this group's last item: that group ends at the same time.)  The polls are bounded all the same: after
 // spin_limit polls the item is marked failed (token -2) and every wave exits.
 
 constexpr int AS_NT = 256, AS_WAVES = 4, AS_CH = 8, AS_WSEG = AS_CH * 256, AS_Q = 4, AS_QSEG = AS_WAVES * AS_WSEG;
 constexpr int AS_WORDS = 10;                                   // exchange words per quarter
 constexpr int AS_XCHG_BYTES = AS_Q * AS_WORDS * 8;             // per (row, position)
-constexpr uint32_t AS_CAND_ACCEPT = 1u << 30, AS_CAND_FAIL = 1u << 29;
+constexpr int AS_SLOTS = 1024;                                 // workgroups of a launch: four on each of 256 CUs
+constexpr uint32_t AS_CAND_FAIL = 1u << 29;
 
 struct AsShared {
-    float fmx[2][AS_WAVES];
-    double dz[2][AS_WAVES];
-    double dw[2][AS_WAVES];
+    float m[2][AS_WAVES];                                      // per wavefront, P and Q: maximum, sum of exponentials
+    double z[2][AS_WAVES];
+    double w[2][AS_WAVES];                                     // .. residual mass, sum min(p, q)
     int ival[AS_WAVES];
     float xw[AS_Q][AS_WORDS];
-    int token, fail;
+    int fail;
 };
 
-__device__ __forceinline__ void as_put(unsigned long long* slot, uint32_t epoch, uint32_t payload) { tw_put(slot, epoch, payload); }
-__device__ __forceinline__ bool as_get(const unsigned long long* slot, uint32_t epoch, int spin_limit, uint32_t* payload) {
-    return tw_get(slot, epoch, spin_limit, payload);
+struct AsArgs {
+    const float *P, *Q;
+    const int32_t* d;
+    int gamma, V;
+    float T;
+    uint64_t seed;
+    uint32_t seq0;
+    unsigned long long* cand;      // two tagged words per (row, position): the candidate, the outcome of the test
+    double* bd;
+    unsigned long long* xchg;      // AS_XCHG_BYTES per (row, position); both zero-filled before their first use
+    uint32_t epoch;
+    int spin_limit, nq, per, extra;   // items of a group: per, the first `extra` groups one more
+    int32_t *n_acc, *token;
+    uint32_t* mask;
+    int32_t* hist;
+    int l;
+};
+
+// From one lane of the wavefront (uniform); sum, maximum and inclusive scan over the four lanes of a quad.
+__device__ __forceinline__ double as_lane(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ float as_lane(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+__device__ __forceinline__ float quad_max(float v) {
+    v = fmaxf(v, dpp_move<0xb1, 0xf>(v, v));                    // quad_perm 1 0 3 2, then 2 3 0 1
+    return fmaxf(v, dpp_move<0x4e, 0xf>(v, v));
+}
+__device__ __forceinline__ double quad_sum(double v) {
+    v += dpp_move<0xb1, 0xf>(v);
+    v += dpp_move<0x4e, 0xf>(v);
+    return v;
+}
+// a in lane 31 and b in lane 63: the sums over all lanes.  The halves of a and b change places first, so that one chain adds both.
+__device__ __forceinline__ double dpp_sum2(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    double v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    v += dpp_move<0x111, 0xf>(v);
+    v += dpp_move<0x112, 0xf>(v);
+    v += dpp_move<0x114, 0xf>(v);
+    v += dpp_move<0x118, 0xf>(v);
+    v += dpp_move<0x142, 0xa>(v);
+    return v;
+}
+// 1 / z to the last bit or two; 0 where z is not positive (a row without any mass)
+__device__ __forceinline__ double as_inverse(double z) {
+    double r = __builtin_amdgcn_rcp(z);
+    r = fma(r, fma(-z, r, 1.0), r);
+    r = fma(r, fma(-z, r, 1.0), r);
+    return z > 0.0 ? r : 0.0;
 }
 
-// Publish NW floats of this quarter (words first .. first + NW) and collect the same words of all nq.
-// `mine` must hold the same values in every thread.  Returns false after a timeout (sm.fail is set).
+// Poll the words first .. first + NW of all nq quarters into sm.xw.  Returns false after a timeout (sm.fail is set).
 template <int NW>
-__device__ __forceinline__ bool as_exchange(unsigned long long* slots, int q, uint32_t epoch, const float (&mine)[NW], int first,
-                                            AsShared& sm, int nq, int spin_limit) {
-    const int t = (int)threadIdx.x;
-    if (nq == 1) {                                 // the only one: nobody to meet
-        if (t < NW) sm.xw[0][first + t] = mine[t];
-        __syncthreads();
-        return true;
-    }
-    if (t < NW) as_put(slots + q * AS_WORDS + first + t, epoch, __float_as_uint(mine[t]));
-    if (t < nq * NW) {
-        const int qq = t / NW, ww = t - qq * NW;
+__device__ __forceinline__ bool as_collect(const unsigned long long* slots, const AsArgs& a, int first, AsShared& sm, int t) {
+    if (a.nq > 1 && t < 8 * a.nq && (t & 7) < NW) {
+        const int at = (t >> 3) * AS_WORDS + first + (t & 7);
         uint32_t bits = 0;
-        if (as_get(slots + qq * AS_WORDS + first + ww, epoch, spin_limit, &bits)) sm.xw[qq][first + ww] = __uint_as_float(bits);
+        if (tw_get(slots + at, a.epoch, a.spin_limit, &bits)) (&sm.xw[0][0])[at] = __uint_as_float(bits);
         else sm.fail = 1;
     }
     __syncthreads();
-    return sm.fail == 0;
+    return __builtin_amdgcn_readfirstlane(sm.fail) == 0;
+}
+__device__ __forceinline__ void as_publish(unsigned long long* slots, const AsArgs& a, int q, int word, float v, AsShared& sm) {
+    if (a.nq == 1) sm.xw[0][word] = v;                          // nobody to meet
+    else tw_put(slots + q * AS_WORDS + word, a.epoch, __float_as_uint(v));
 }
 
+// Requests of a wavefront's 2048 logits.  Only the last ones of a vocabulary need their addresses clamped (lanes past the end re-read
+// the last values; as_cut takes them out).
 __device__ __forceinline__ void as_load(const float* __restrict__ row, int V, int seg0, int lane, float (&x)[AS_CH][4]) {
+    const char* base = reinterpret_cast<const char*>(row);
+    f32x4 v[AS_CH];
+    if (seg0 + AS_WSEG <= V) {
+        base += (size_t)seg0 * 4;
+        uint32_t at = (uint32_t)lane * 16;
+        asm volatile("" : "+v"(at));            // formed here, not kept from one row to the next
 #pragma unroll
-    for (int c = 0; c < AS_CH; ++c) {           // unconditional (clamped) requests: each wait counts exactly what it needs
-        const int idx = seg0 + c * 256 + lane * 4;
-        const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + min(idx, V - 4)));
-        const bool in = idx < V;
-        x[c][0] = in ? v[0] : -INFINITY; x[c][1] = in ? v[1] : -INFINITY; x[c][2] = in ? v[2] : -INFINITY; x[c][3] = in ? v[3] : -INFINITY;
+        for (int c = 0; c < AS_CH; ++c) v[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(base + at + c * 1024));
+    } else {
+        uint32_t at = (uint32_t)(seg0 + lane * 4) * 4;
+        asm volatile("" : "+v"(at));
+#pragma unroll
+        for (int c = 0; c < AS_CH; ++c) v[c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(base + min(at + c * 1024, (uint32_t)(V - 4) * 4)));
     }
+#pragma unroll
+    for (int c = 0; c < AS_CH; ++c) { x[c][0] = v[c][0]; x[c][1] = v[c][1]; x[c][2] = v[c][2]; x[c][3] = v[c][3]; }
 }
-
-__device__ __forceinline__ float as_thread_max(const float (&x)[AS_CH][4]) {
-    float lm = -INFINITY;
+// no value is wanted of x any more (else it would be kept for the case that nothing is loaded over it)
+__device__ __forceinline__ void as_forget(float (&x)[AS_CH][4]) {
 #pragma unroll
     for (int c = 0; c < AS_CH; ++c)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) lm = fmaxf(lm, x[c][e]);
+        for (int e = 0; e < 4; ++e) asm volatile("" : "=v"(x[c][e]));
+}
+// lanes past the vocabulary (in the last wavefronts only)
+__device__ __forceinline__ void as_cut(int V, int seg0, int lane, float (&x)[AS_CH][4]) {
+    if (seg0 + AS_WSEG <= V) return;
+#pragma unroll
+    for (int c = 0; c < AS_CH; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[c][e] = seg0 + c * 256 + lane * 4 < V ? x[c][e] : -INFINITY;
+}
+
+// The instructions themselves: fmaxf and fminf put one in front of them for every operand that was loaded (it turns a signalling NaN quiet).
+__device__ __forceinline__ float as_max3(float a, float b, float c) {
+    float d;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ float as_min(float a, float b) {
+    float d;
+    asm("v_min_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ float as_thread_max(const float (&x)[AS_CH][4]) {
+    float lm = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < AS_CH; ++c) lm = as_max3(as_max3(lm, x[c][0], x[c][1]), x[c][2], x[c][3]);
     return lm;
 }
 
@@ -1801,298 +1889,312 @@ __device__ __forceinline__ double as_exp_inplace(float (&x)[AS_CH][4], float mx,
     float s = 0.f;
 #pragma unroll
     for (int c = 0; c < AS_CH; ++c) {
-        float s4 = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float v = ak_expx<UNIT_T>(x[c][e], mx, invT);
-            x[c][e] = v;
-            s4 += v;
-        }
-        s += s4;
+        for (int e = 0; e < 4; ++e) x[c][e] = ak_expx<UNIT_T>(x[c][e], mx, invT);
+        s += (x[c][0] + x[c][1]) + (x[c][2] + x[c][3]);
+        if (c & 1) __builtin_amdgcn_sched_barrier(0);           // (else the registers of the whole array are needed twice)
     }
     return (double)s;
 }
 
 // Quarter, wavefront, chunk, lane, element holding the target u * Z of the inverse CDF over scale * w.
-// tq[0..4): the quarters' totals in the common scale (identical in all four workgroups); wtot: this quarter's
-// wavefront totals of w (LDS); scale: this quarter's factor.  Only the quarter that holds the target continues;
-// it leaves the token in sm.token.  Returns (workgroup-uniform) whether this workgroup is that quarter.
+// tq: the quarters' totals (identical in all four workgroups), quarter k in lane k; tw: likewise this quarter's wavefronts'; scale: the
+// calling wavefront's factor.  Returns the token in the one lane that holds it, -1 elsewhere.
 // Rounding gaps fall back to the last index with weight, level by level.
-__device__ __forceinline__ bool as_search(const float (&w)[AS_CH][4], const double* wtot, double scale, const double (&tq)[AS_Q],
-                                          double Z, float u, int V, int q, AsShared& sm, int wave, int lane) {
+__device__ __forceinline__ int as_search(const float (&w)[AS_CH][4], double tw, double scale, double tq, double Z, float u, int V, int q,
+                                         int wave, int lane) {
     const double target = (double)u * Z;
-    int qstar = -1, qlast = 0;
-    double base = 0.0, run = 0.0;
-#pragma unroll
-    for (int k = 0; k < AS_Q; ++k) {
-        if (tq[k] > 0.0) qlast = k;
-        if (qstar < 0) {
-            if (run + tq[k] > target) { qstar = k; base = run; }
-            else run += tq[k];
-        }
-    }
+    // part of a quad's lanes that holds the target: its index, and in `base` what lies before it
     bool take_last = false;
-    if (qstar < 0) { qstar = qlast; take_last = true; }
-    if (q != qstar) return false;
-    int wstar = -1, wlast = 0;
-    double wbase = base;
+    double base = 0.0;
+    auto pick = [&](double t) -> int {
+        // inclusive scan over the quad (every lane moves: a lane that is switched off is no source)
+        const double before = dpp_move<0x90, 0xf>(t);                   // quad_perm 0 0 1 2
+        double s = t + ((lane & 3) >= 1 ? before : 0.0);
+        const double two = dpp_move<0x44, 0xf>(s);                      // quad_perm 0 1 0 1
+        s += (lane & 3) >= 2 ? two : 0.0;
+        const uint32_t hit = take_last ? 0u : (uint32_t)__ballot(base + s > target) & 15u, any = (uint32_t)__ballot(t > 0.0) & 15u;
+        int k;
+        if (hit) k = __ffs((int)hit) - 1;
+        else { k = any ? 31 - __clz((int)any) : 0; take_last = true; }
+        base += as_lane(s, k) - as_lane(t, k);
+        return k;
+    };
+    if (pick(tq) != q) return -1;
+    if (pick(tw) != wave) return -1;
+    double sc[AS_CH];                              // inclusive scans of the chunks, four side by side
 #pragma unroll
-    for (int k = 0; k < AS_WAVES; ++k) {
-        const double ww = wtot[k] * scale;
-        if (ww > 0.0) wlast = k;
-        if (wstar < 0 && !take_last) {
-            if (wbase + ww > target) wstar = k;
-            else wbase += ww;
+    for (int c = 0; c < AS_CH; ++c) {
+        if (c == AS_CH / 2) __builtin_amdgcn_sched_barrier(0);
+        sc[c] = dpp_scan((double)((w[c][0] + w[c][1]) + (w[c][2] + w[c][3])));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    int cstar = -1, clast = -1;
+    double cb = base;
+#pragma unroll
+    for (int c = 0; c < AS_CH; ++c) {
+        const double ct = as_lane(sc[c], 63) * scale;
+        if (ct > 0.0) clast = c;
+        if (cstar < 0 && !take_last) {
+            if (cb + ct > target) cstar = c;
+            else cb += ct;
         }
     }
-    if (wstar < 0) { wstar = wlast; take_last = true; }
-    if (wave == wstar) {   // wave-uniform
-        int cstar = -1, clast = -1;
-        double cb = wbase;
+    if (cstar < 0) { cstar = clast < 0 ? 0 : clast; take_last = true; }
+    float w4[4] = {0.f, 0.f, 0.f, 0.f};
+    double incl = 0.0;
 #pragma unroll
-        for (int c = 0; c < AS_CH; ++c) {
-            if (q * AS_QSEG + wave * AS_WSEG + c * 256 >= V) break;             // wave-uniform
-            const double ct = dpp_sum((double)((w[c][0] + w[c][1]) + (w[c][2] + w[c][3]))) * scale;
-            if (ct > 0.0) clast = c;
-            if (cstar < 0 && !take_last) {
-                if (cb + ct > target) cstar = c;
-                else cb += ct;
-            }
-        }
-        if (cstar < 0) { cstar = clast < 0 ? 0 : clast; take_last = true; }
-        float w4[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < AS_CH; ++c)
+        if (c == cstar) { w4[0] = w[c][0]; w4[1] = w[c][1]; w4[2] = w[c][2]; w4[3] = w[c][3]; incl = sc[c] * scale; }
+    const double mine = (double)((w4[0] + w4[1]) + (w4[2] + w4[3])) * scale;
+    unsigned long long bal = __ballot(take_last ? (mine > 0.0) : (cb + incl > target));
+    if (bal == 0ull) { take_last = true; bal = __ballot(mine > 0.0); }
+    int lstar;
+    if (bal == 0ull) lstar = 0;
+    else lstar = take_last ? (63 - __clzll((long long)bal)) : (__ffsll((long long)bal) - 1);
+    if (lane != lstar) return -1;
+    double acc = cb + incl - mine;
+    int tok = -1, lastpos = -1;
+    const int idx0 = q * AS_QSEG + wave * AS_WSEG + cstar * 256 + lane * 4;
 #pragma unroll
-        for (int c = 0; c < AS_CH; ++c)
-            if (c == cstar) { w4[0] = w[c][0]; w4[1] = w[c][1]; w4[2] = w[c][2]; w4[3] = w[c][3]; }
-        const double sc = (double)((w4[0] + w4[1]) + (w4[2] + w4[3])) * scale;
-        const double incl = dpp_scan(sc);
-        unsigned long long bal = __ballot(take_last ? (sc > 0.0) : (cb + incl > target));
-        if (bal == 0ull) { take_last = true; bal = __ballot(sc > 0.0); }
-        int lstar;
-        if (bal == 0ull) lstar = 0;
-        else lstar = take_last ? (63 - __clzll((long long)bal)) : (__ffsll((long long)bal) - 1);
-        if (lane == lstar) {
-            double acc = cb + incl - sc;
-            int tok = -1, lastpos = -1;
-            const int idx0 = q * AS_QSEG + wave * AS_WSEG + cstar * 256 + lane * 4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc += (double)w4[e] * scale;
-                if (w4[e] > 0.f) lastpos = idx0 + e;
-                if (tok < 0 && !take_last && acc > target) tok = idx0 + e;
-            }
-            if (tok < 0) tok = lastpos >= 0 ? lastpos : min(idx0, V - 1);
-            sm.token = tok;
-        }
+    for (int e = 0; e < 4; ++e) {
+        acc += (double)w4[e] * scale;
+        if (w4[e] > 0.f) lastpos = idx0 + e;
+        if (tok < 0 && !take_last && acc > target) tok = idx0 + e;
     }
-    __syncthreads();
-    return true;
+    return tok >= 0 ? tok : lastpos >= 0 ? lastpos : min(idx0, V - 1);
 }
 
+// Greedy: argmax with the lowest index on ties.  xp: the logits of this item, on return those of the next.
+__device__ __forceinline__ void accept_split_greedy(const AsArgs& a, size_t item, int b, int j, const float* next, float (&xp)[AS_CH][4], AsShared& sm,
+                                                    int q, int wave, int lane) {
+    const int seg0 = q * AS_QSEG + wave * AS_WSEG, tid = wave * 64 + lane;
+    unsigned long long* slots = a.xchg + item * (AS_Q * AS_WORDS);
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    as_cut(a.V, seg0, lane, xp);
+#pragma unroll
+    for (int c = 0; c < AS_CH; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int idx = seg0 + c * 256 + lane * 4 + e;
+            if (xp[c][e] > bv) { bv = xp[c][e]; bi = idx; }
+        }
+    if (next) as_load(next, a.V, seg0, lane, xp);
+    else as_forget(xp);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    }
+    if (lane == 0) { sm.m[0][wave] = bv; sm.ival[wave] = bi; }
+    if (tid == 0) sm.fail = 0;
+    __syncthreads();
+    float rv = sm.m[0][0];
+    int ri = sm.ival[0];
+#pragma unroll
+    for (int k = 1; k < AS_WAVES; ++k)
+        if (sm.m[0][k] > rv || (sm.m[0][k] == rv && sm.ival[k] < ri)) { rv = sm.m[0][k]; ri = sm.ival[k]; }
+    if (tid < 2) as_publish(slots, a, q, tid, tid ? __int_as_float(ri) : rv, sm);
+    const bool met = as_collect<2>(slots, a, 0, sm, tid);
+    if (tid) return;
+    if (!met) { tw_put(a.cand + 2 * item, a.epoch, AS_CAND_FAIL); return; }
+    if (q) return;
+    float gv = sm.xw[0][0];
+    int gi = __float_as_int(sm.xw[0][1]);
+    for (int k = 1; k < a.nq; ++k) {
+        const float ov = sm.xw[k][0];
+        const int oi = __float_as_int(sm.xw[k][1]);
+        if (ov > gv || (ov == gv && oi < gi)) { gv = ov; gi = oi; }
+    }
+    const bool acc = j < a.gamma ? min(max(a.d[(size_t)b * a.gamma + j], 0), a.V - 1) == gi : true;
+    tw_put(a.cand + 2 * item, a.epoch, (uint32_t)gi);
+    tw_put(a.cand + 2 * item + 1, a.epoch, acc);
+    if (j < a.gamma && a.bd) a.bd[(size_t)b * a.gamma + j] = acc ? 1.0 : 0.0;
+}
+
+// One item of quarter q.  xp: the logits of P (requested), on return those of the next item's, at next (nullptr: there is none).
+// use_q: without, the draw is from p - the bonus position, and the second pass over a position with p == q everywhere, which is asked for by
+// returning true.
 template <bool UNIT_T>
-__device__ __forceinline__ void accept_split_item(const float* __restrict__ P, const float* __restrict__ Q,
-                                                  const int32_t* __restrict__ d, int gamma, int V, float T, uint64_t seed,
-                                                  const RoundTab& rt, uint32_t seq0, unsigned long long* __restrict__ cand,
-                                                  double* __restrict__ bd, unsigned long long* __restrict__ xchg, uint32_t epoch,
-                                                  int spin_limit, AsShared& sm) {
-    const int q = blockIdx.x, nq = gridDim.x, j = blockIdx.y, b = blockIdx.z;
-    const uint32_t round = round_of(rt, b);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const size_t item = (size_t)b * (gamma + 1) + j;
-    unsigned long long* slots = xchg + item * (AS_Q * AS_WORDS);
-    const float* Prow = P + item * V;
-    const bool has_q = j < gamma;
-    const float* Qrow = has_q ? Q + ((size_t)b * gamma + j) * V : nullptr;
-    const int dtok = has_q ? min(max(d[(size_t)b * gamma + j], 0), V - 1) : -1;   // clamped: stays in bounds for any input
-    const int seg0 = q * AS_QSEG + wave * AS_WSEG;
-    float xp[AS_CH][4], xq[AS_CH][4];
-    as_load(Prow, V, seg0, lane, xp);
-    auto fail_out = [&]() { if (threadIdx.x == 0) as_put(cand + item, epoch, AS_CAND_FAIL); };
-    if (T <= 0.f) {   // greedy: argmax with the lowest index on ties
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
+__device__ __forceinline__ bool accept_split_item(const AsArgs& a, const RoundTab& rt, const ExpScale& invT, size_t item, int b, int j, bool use_q, float u_res,
+                                                  const float* next, float (&xp)[AS_CH][4], AsShared& sm, int q, int wave, int lane) {
+    const int V = a.V, seg0 = q * AS_QSEG + wave * AS_WSEG, tid = wave * 64 + lane;
+    unsigned long long* slots = a.xchg + item * (AS_Q * AS_WORDS);
+    float xq[AS_CH][4], pdl = 0.f, qdl = 0.f;
+    const bool tester = use_q && q == 0 && wave == 0;          // the wavefront that takes the test
+    if (use_q) {
+        const size_t at = (size_t)b * a.gamma + j;
+        as_load(a.Q + at * V, V, seg0, lane, xq);
+        if (tester) {
+            const int dtok = min(max(a.d[at], 0), V - 1);      // clamped: stays in bounds for any input
+            pdl = a.P[item * V + dtok]; qdl = a.Q[at * V + dtok];
+        }
+    } else {
 #pragma unroll
         for (int c = 0; c < AS_CH; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int idx = seg0 + c * 256 + lane * 4 + e;
-                if (xp[c][e] > bv) { bv = xp[c][e]; bi = idx; }
-            }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ov = __shfl_xor(bv, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        }
-        if (lane == 0) { sm.fmx[0][wave] = bv; sm.ival[wave] = bi; }
-        __syncthreads();
-        float rv = sm.fmx[0][0];
-        int ri = sm.ival[0];
-#pragma unroll
-        for (int k = 1; k < AS_WAVES; ++k)
-            if (sm.fmx[0][k] > rv || (sm.fmx[0][k] == rv && sm.ival[k] < ri)) { rv = sm.fmx[0][k]; ri = sm.ival[k]; }
-        const float mine[2] = {rv, __int_as_float(ri)};
-        if (!as_exchange<2>(slots, q, epoch, mine, 0, sm, nq, spin_limit)) { fail_out(); return; }
-        if (q == 0 && threadIdx.x == 0) {
-            float gv = sm.xw[0][0];
-            int gi = __float_as_int(sm.xw[0][1]);
-            for (int k = 1; k < nq; ++k) {
-                const float ov = sm.xw[k][0];
-                const int oi = __float_as_int(sm.xw[k][1]);
-                if (ov > gv || (ov == gv && oi < gi)) { gv = ov; gi = oi; }
-            }
-            const bool acc = has_q ? (dtok == gi) : true;
-            as_put(cand + item, epoch, (acc ? AS_CAND_ACCEPT : 0u) | (uint32_t)gi);
-            if (has_q && bd) bd[(size_t)b * gamma + j] = acc ? 1.0 : 0.0;
-        }
-        return;
+            for (int e = 0; e < 4; ++e) xq[c][e] = 0.f;
     }
-    const ExpScale invT = exp_scale(1.0 / (double)T);
-    if (has_q) as_load(Qrow, V, seg0, lane, xq);
-    float pdl = 0.f, qdl = 0.f;
-    if (has_q) { pdl = Prow[dtok]; qdl = Qrow[dtok]; }
-    // ---- local maxima
-    {
-        const float a = dpp_max(as_thread_max(xp));
-        const float c = has_q ? dpp_max(as_thread_max(xq)) : -INFINITY;
-        if (lane == 0) { sm.fmx[0][wave] = a; sm.fmx[1][wave] = c; }
+    // ---- this wavefront's maxima, exponentials and sums.  A part beyond the vocabulary (or fully masked) has no maximum: it exponentiates
+    // against 0 and contributes nothing
+    as_cut(V, seg0, lane, xp);
+    const float mp = dpp_max(as_thread_max(xp));
+    const double zp = as_exp_inplace<UNIT_T>(xp, mp > -INFINITY ? mp : 0.f, invT);
+    double zq = 0.0;
+    float mq = -INFINITY;
+    if (use_q) {
+        as_cut(V, seg0, lane, xq);
+        mq = dpp_max(as_thread_max(xq));
+        zq = as_exp_inplace<UNIT_T>(xq, mq > -INFINITY ? mq : 0.f, invT);
     }
-    __syncthreads();
-    float lmp = sm.fmx[0][0], lmq = sm.fmx[1][0];
-#pragma unroll
-    for (int k = 1; k < AS_WAVES; ++k) { lmp = fmaxf(lmp, sm.fmx[0][k]); lmq = fmaxf(lmq, sm.fmx[1][k]); }
-    // a quarter beyond the vocabulary (or fully masked) has no maximum: it exponentiates against 0 and contributes nothing
-    const float emp = lmp > -INFINITY ? lmp : 0.f, emq = lmq > -INFINITY ? lmq : 0.f;
-    // ---- local exp and sums
-    {
-        const double a = dpp_sum(as_exp_inplace<UNIT_T>(xp, emp, invT));
-        const double c = has_q ? dpp_sum(as_exp_inplace<UNIT_T>(xq, emq, invT)) : 0.0;
-        if (lane == 0) { sm.dz[0][wave] = a; sm.dz[1][wave] = c; }
-    }
+    zq = dpp_sum2(zp, zq);
+    if ((lane & 31) == 31) { sm.m[lane >> 5][wave] = lane < 32 ? mp : mq; sm.z[lane >> 5][wave] = zq; }
+    if (tid == 0) sm.fail = 0;
     __syncthreads();
     // ---- meeting A
-    double zpq[AS_Q], Zp = 0.0, Zq = 0.0, sp_mine, sq_mine;
-    float mp, mq;
+    const int k4 = lane & 3, pq = (lane >> 2) & 1;
+    // factor of part k against the common maximum: exp((m_k - M)/T); 0 for a part without a maximum
+    auto factor = [&](float m, float M) { return m > -INFINITY ? ak_expx<UNIT_T>(m, M, invT) : 0.f; };
+    const float wm = sm.m[pq][k4], wM = quad_max(wm), wf = factor(wm, wM);
     {
-        double lp = 0.0, lq = 0.0;
-#pragma unroll
-        for (int k = 0; k < AS_WAVES; ++k) { lp += sm.dz[0][k]; lq += sm.dz[1][k]; }
-        const float ph = (float)lp, qh = (float)lq;
-        const float mine[6] = {lmp, lmq, ph, (float)(lp - (double)ph), qh, (float)(lq - (double)qh)};
-        if (!as_exchange<6>(slots, q, epoch, mine, 0, sm, nq, spin_limit)) { fail_out(); return; }
-        mp = fmaxf(fmaxf(sm.xw[0][0], sm.xw[1][0]), fmaxf(sm.xw[2][0], sm.xw[3][0]));
-        mq = fmaxf(fmaxf(sm.xw[0][1], sm.xw[1][1]), fmaxf(sm.xw[2][1], sm.xw[3][1]));
-        sp_mine = 0.0; sq_mine = 0.0;
-#pragma unroll
-        for (int k = 0; k < AS_Q; ++k) {
-            // factor of quarter k: exp((m_k - M)/T); 0 for a quarter without a maximum
-            const double sp = sm.xw[k][0] > -INFINITY ? (double)ak_expx<UNIT_T>(sm.xw[k][0], mp, invT) : 0.0;
-            const double sq = sm.xw[k][1] > -INFINITY ? (double)ak_expx<UNIT_T>(sm.xw[k][1], mq, invT) : 0.0;
-            zpq[k] = ((double)sm.xw[k][2] + (double)sm.xw[k][3]) * sp;
-            Zp += zpq[k];
-            Zq += ((double)sm.xw[k][4] + (double)sm.xw[k][5]) * sq;
-            if (k == q) { sp_mine = sp; sq_mine = sq; }
-        }
+        const double s = quad_sum(sm.z[pq][k4] * (double)wf);  // the wavefronts' sums against the quarter's maximum
+        const float hi = (float)s;
+        if (tid < 8 && k4 < 3) as_publish(slots, a, q, k4 == 0 ? pq : 1 + 2 * pq + k4, k4 == 0 ? wM : k4 == 1 ? hi : (float)(s - (double)hi), sm);
     }
-    const float u_res = philox_uniform(seed, seq0 + (uint32_t)b, round, 0u, 1u);
-    if (!has_q) {   // bonus position: draw from p
-        if (as_search(xp, sm.dz[0], sp_mine, zpq, Zp, u_res, V, q, sm, wave, lane) && threadIdx.x == 0)
-            as_put(cand + item, epoch, AS_CAND_ACCEPT | (uint32_t)sm.token);
-        return;
-    }
-    const double ipz = sp_mine / Zp, iqz = sq_mine / Zq;      // this quarter's exp(m_k - M) / Z
-    const float ip_hi = (float)ipz, ip_lo = (float)(ipz - (double)ip_hi);
-    const float iq_hi = (float)iqz, iq_lo = (float)(iqz - (double)iq_hi);
-    bool accept = true;
+    const bool met = as_collect<6>(slots, a, 0, sm, tid);
+    const float qm = sm.xw[k4][pq], qM = quad_max(qm), qf = factor(qm, qM);
+    const double qz = ((double)sm.xw[k4][2 + 2 * pq] + (double)sm.xw[k4][3 + 2 * pq]) * (double)qf, inv = as_inverse(quad_sum(qz));
+    // ---- residual weights max(0, p - q) (kept in xq; without q: p) and sum min(p, q), both times Z_p / exp(m - M) with this wavefront's
+    // exp(m - M): what scales them (ipz) multiplies the sums, and q's exponentials are multiplied with the quotient of the two scales.  A
+    // wavefront whose p are all 0 has none; where the quotient exceeds the largest float, q > p or q = 0
+    const double wi = (double)wf * inv;                        // lanes (P or Q, wavefront)
+    const double ipz = as_lane(wi, wave) * (double)as_lane(qf, q);
+    double ws;
     {
-        const double pd = (double)ak_expx<UNIT_T>(pdl, mp, invT) / Zp, qd = (double)ak_expx<UNIT_T>(qdl, mq, invT) / Zq;
-        if (qd > 0.0) {
-            const double ratio = pd / qd;
-            const float u_acc = philox_uniform(seed, seq0 + (uint32_t)b, round, (uint32_t)j, 0u);
-            accept = (double)u_acc < (ratio < 1.0 ? ratio : 1.0);
-        }
-    }
-    // ---- residual weights max(0, p - q) (kept in xq) and sum min(p, q)
-    {
+        const double ratio = use_q && ipz > 0.0 ? fmin(as_lane(wi, 4 + wave) * (double)as_lane(qf, 4 + q) * as_inverse(ipz), 3.4028234663852886e38) : 0.0;
+        const float hi = (float)ratio, lo = (float)(ratio - (double)hi);
         float fw = 0.f, fm = 0.f;
 #pragma unroll
         for (int c = 0; c < AS_CH; ++c) {
-            float mn4 = 0.f;
+            float mn[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float pv = fmaf(xp[c][e], ip_lo, xp[c][e] * ip_hi), qv = fmaf(xq[c][e], iq_lo, xq[c][e] * iq_hi);
-                mn4 += fminf(pv, qv);
-                xq[c][e] = fmaxf(pv - qv, 0.f);
+                const float qv = fmaf(xq[c][e], lo, xq[c][e] * hi);
+                mn[e] = as_min(xp[c][e], qv);
+                xq[c][e] = fmaxf(xp[c][e] - qv, 0.f);
             }
             fw += (xq[c][0] + xq[c][1]) + (xq[c][2] + xq[c][3]);
-            fm += mn4;
+            fm += (mn[0] + mn[1]) + (mn[2] + mn[3]);
+            if (c & 1) __builtin_amdgcn_sched_barrier(0);
         }
-        const double tw = dpp_sum((double)fw), tm = dpp_sum((double)fm);
-        if (lane == 0) { sm.dw[0][wave] = tw; sm.dw[1][wave] = tm; }
+        asm volatile("" : "+v"(fw), "+v"(fm));                 // (the sums are finished here, not behind the requests)
+        if (next) as_load(next, V, seg0, lane, xp);
+        else as_forget(xp);
+        ws = dpp_sum2((double)fw, (double)fm) * ipz;
     }
+    if (!met) { if (tid == 0) tw_put(a.cand + 2 * item, a.epoch, AS_CAND_FAIL); return false; }
+    if ((lane & 31) == 31) sm.w[lane >> 5][wave] = ws;
     __syncthreads();
-    // ---- meeting B
-    double zrq[AS_Q], Zr = 0.0, bdj = 0.0;
-    {
-        double lr = 0.0, lm = 0.0;
-#pragma unroll
-        for (int k = 0; k < AS_WAVES; ++k) { lr += sm.dw[0][k]; lm += sm.dw[1][k]; }
-        const float rh = (float)lr, mh = (float)lm;
-        const float mine[4] = {rh, (float)(lr - (double)rh), mh, (float)(lm - (double)mh)};
-        if (!as_exchange<4>(slots, q, epoch, mine, 6, sm, nq, spin_limit)) { fail_out(); return; }
-#pragma unroll
-        for (int k = 0; k < AS_Q; ++k) {
-            zrq[k] = (double)sm.xw[k][6] + (double)sm.xw[k][7];
-            Zr += zrq[k];
-            bdj += (double)sm.xw[k][8] + (double)sm.xw[k][9];
+    ws = sm.w[pq][k4];
+    double tq = qz * inv;                                      // the quarters' shares of p
+    if (use_q) {
+        // ---- meeting B
+        {
+            const double s = quad_sum(ws);
+            const float hi = (float)s;
+            if (tid < 8 && k4 < 2) as_publish(slots, a, q, 6 + 2 * pq + k4, k4 == 0 ? hi : (float)(s - (double)hi), sm);
         }
+        if (tester) {                                          // while the words are on their way
+            const double pd = (double)ak_expx<UNIT_T>(pdl, as_lane(qM, 0), invT) * as_lane(inv, 0), qd = (double)ak_expx<UNIT_T>(qdl, as_lane(qM, 4), invT) * as_lane(inv, 4);
+            bool accept = true;
+            if (qd > 0.0) {
+                const double ratio = pd / qd;
+                uint64_t seed = a.seed;
+                asm volatile("" : "+s"(seed));                 // (the key schedule would take twenty registers through the loop)
+                const float u_acc = philox_uniform(seed, a.seq0 + (uint32_t)b, round_of(rt, b), (uint32_t)j, 0u);
+                accept = (double)u_acc < (ratio < 1.0 ? ratio : 1.0);
+            }
+            if (lane == 0) tw_put(a.cand + 2 * item + 1, a.epoch, accept);
+        }
+        if (!as_collect<4>(slots, a, 6, sm, tid)) { if (tid == 0) tw_put(a.cand + 2 * item, a.epoch, AS_CAND_FAIL); return false; }
+        tq = (double)sm.xw[k4][6 + 2 * pq] + (double)sm.xw[k4][7 + 2 * pq];
     }
-    bool mine_wins;
-    if (Zr > 0.0) mine_wins = as_search(xq, sm.dw[0], 1.0, zrq, Zr, u_res, V, q, sm, wave, lane);
-    else mine_wins = as_search(xp, sm.dz[0], sp_mine, zpq, Zp, u_res, V, q, sm, wave, lane);   // p == q: draw from p
-    if (mine_wins && threadIdx.x == 0) {
-        if (bd) bd[(size_t)b * gamma + j] = bdj;
-        as_put(cand + item, epoch, (accept ? AS_CAND_ACCEPT : 0u) | (uint32_t)sm.token);
+    const double R = quad_sum(tq);
+    if (tester && lane == 4 && a.bd) a.bd[(size_t)b * a.gamma + j] = R;
+    if (use_q && !__builtin_amdgcn_readfirstlane(as_lane(R, 0) > 0.0)) return true;
+    const int tok = as_search(xq, ws, ipz, tq, as_lane(R, 0), u_res, V, q, wave, lane);
+    if (tok >= 0) tw_put(a.cand + 2 * item, a.epoch, (uint32_t)tok);
+    return false;
+}
+
+// Row b: first failed test, emitted token, mask.  One wavefront asks for all gamma + 1 candidates and outcomes at once, one position per
+// lane (one after the other each costs a trip to memory: one row, gamma 5 11.7 -> 9.9 us).
+__device__ __forceinline__ void accept_split_row(const AsArgs& a, int b, int j) {
+    uint32_t tok = 0, acc = 1;
+    bool got = true;
+    if (j <= a.gamma) {
+        const unsigned long long* c = a.cand + 2 * ((size_t)b * (a.gamma + 1) + j);
+        got = tw_get(c, a.epoch, a.spin_limit, &tok) && !(tok & AS_CAND_FAIL) && (j == a.gamma || tw_get(c + 1, a.epoch, a.spin_limit, &acc));
+    }
+    const bool ok = __ballot(!got) == 0ull;
+    const uint32_t mk = (uint32_t)__ballot(j < a.gamma && acc), failed = ~mk & ((1u << a.gamma) - 1u);
+    const int n = failed ? __ffs((int)failed) - 1 : a.gamma;
+    const int t = ok ? __builtin_amdgcn_readlane((int)tok, n) : -2;
+    if (j == 0) {
+        a.n_acc[b] = ok ? n : 0;
+        a.token[b] = t;
+        if (a.mask) a.mask[b] = ok ? mk : 0u;
+        if (a.hist && t >= 0) a.hist[a.l + n] = t;
     }
 }
 
-// grid (4 quarters, gamma + 1 positions, rows), block 256.  cand: one tagged word per (row, position);
-// xchg: AS_XCHG_BYTES per (row, position); both zero-filled before their first use.
-__global__ __launch_bounds__(AS_NT) void accept_split_kernel(const float* __restrict__ P, const float* __restrict__ Q,
-                                                             const int32_t* __restrict__ d, int gamma, int V, float T,
-                                                             uint64_t seed, RoundTab rt, uint32_t seq0,
-                                                             unsigned long long* __restrict__ cand, double* __restrict__ bd,
-                                                             unsigned long long* __restrict__ xchg, uint32_t epoch, int spin_limit,
-                                                             int32_t* __restrict__ n_acc, int32_t* __restrict__ token,
-                                                             uint32_t* __restrict__ mask, int32_t* __restrict__ hist, int l) {
-    __shared__ AsShared sm;
-    if (threadIdx.x == 0) { sm.token = -1; sm.fail = 0; }
-    if (threadIdx.x < AS_Q * AS_WORDS) {           // a quarter without a workgroup: no maximum, no mass
-        const int w = (int)threadIdx.x % AS_WORDS;
-        (&sm.xw[0][0])[threadIdx.x] = w < 2 ? -INFINITY : 0.f;
+// grid nq (quarters the vocabulary reaches into) x groups, quarters of a group next to each other; block 256
+template <int KIND>                                // 0: T = 1, 1: other T > 0, 2: greedy
+__global__ __launch_bounds__(AS_NT, 4) void accept_split_kernel(AsArgs a, RoundTab rt) {
+    __shared__ AsShared sm[2];                     // items take them in turn: a wavefront can be one item ahead of another
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // the group's items: consecutive, as many as any other's or one more (readfirstlane: a quotient is formed in vector registers)
+    const int group = __builtin_amdgcn_readfirstlane((int)blockIdx.x / a.nq), q = (int)blockIdx.x - group * a.nq;
+    const int i0 = group * a.per + min(group, a.extra), i1 = i0 + a.per + (group < a.extra ? 1 : 0);
+    float xp[AS_CH][4];
+    as_load(a.P + (size_t)i0 * a.V, a.V, q * AS_QSEG + wave * AS_WSEG, lane, xp);
+    if (threadIdx.x < 2 * AS_Q * AS_WORDS) {       // a quarter without a workgroup: no maximum, no mass
+        const int s = (int)threadIdx.x / (AS_Q * AS_WORDS), i = (int)threadIdx.x - s * (AS_Q * AS_WORDS);
+        (&sm[s].xw[0][0])[i] = i % AS_WORDS < 2 ? -INFINITY : 0.f;
     }
+    ExpScale invT{};
+    if constexpr (KIND == 1) invT = exp_scale(1.0 / (double)a.T);
+    const int b0 = __builtin_amdgcn_readfirstlane(i0 / (a.gamma + 1));
+    int b = b0, j = i0 - b0 * (a.gamma + 1), turn = 0;
+    const bool begun = j != 0;                     // row b0 was begun by the group before
+    auto residual_draw = [&]() {
+        uint64_t seed = a.seed;
+        asm volatile("" : "+s"(seed));             // (see above)
+        return philox_uniform(seed, a.seq0 + (uint32_t)b, round_of(rt, b), 0u, 1u);
+    };
+    float u_res = KIND == 2 ? 0.f : residual_draw();
+    bool again = false;
     __syncthreads();
-    if (T == 1.0f) accept_split_item<true>(P, Q, d, gamma, V, T, seed, rt, seq0, cand, bd, xchg, epoch, spin_limit, sm);
-    else accept_split_item<false>(P, Q, d, gamma, V, T, seed, rt, seq0, cand, bd, xchg, epoch, spin_limit, sm);
-    // ---- per row: first failed test, emitted token, mask.  The first wavefront of the bonus position's first quarter asks for all
-    // gamma + 1 candidates at once, one per lane (one after the other each costs a trip to memory:
-    // one row, gamma 5 11.7 -> 9.9 us)
-    if (blockIdx.x == 0 && (int)blockIdx.y == gamma && threadIdx.x < 64) {
-        const int b = blockIdx.z, j = (int)threadIdx.x;
-        uint32_t w = 0;
-        const bool got = j > gamma || (as_get(cand + (size_t)b * (gamma + 1) + j, epoch, spin_limit, &w) && !(w & AS_CAND_FAIL));
-        const bool ok = __ballot(!got) == 0ull;
-        const uint32_t mk = (uint32_t)__ballot(j < gamma && (w & AS_CAND_ACCEPT));
-        const uint32_t failed = ~mk & ((1u << gamma) - 1u);
-        const int n = failed ? __ffs((int)failed) - 1 : gamma;
-        const int tok = ok ? (int)((uint32_t)__builtin_amdgcn_readlane((int)w, n) & 0x1fffffffu) : -2;
-        if (j == 0) {
-            n_acc[b] = ok ? n : 0;
-            token[b] = tok;
-            if (mask) mask[b] = ok ? mk : 0u;
-            if (hist && tok >= 0) hist[l + n] = tok;
+    for (int i = i0; i < i1;) {
+        int ln = lane, it = i;
+        asm volatile("" : "+v"(ln), "+s"(it));     // nothing that follows from the lane or the item is kept in registers from one item to the next
+        const float* next = it + 1 < i1 ? a.P + (size_t)(it + 1) * a.V : nullptr;
+        AsShared& s = sm[turn ^= 1];
+        if constexpr (KIND == 2) accept_split_greedy(a, it, b, j, next, xp, s, q, wave, ln);
+        else {
+            again = __builtin_amdgcn_readfirstlane((int)accept_split_item<KIND == 0>(a, rt, invT, it, b, j, j < a.gamma && !again, u_res, next, xp, s, q, wave, ln)) != 0;
+            if (again) { as_load(a.P + (size_t)it * a.V, a.V, q * AS_QSEG + wave * AS_WSEG, ln, xp); continue; }
         }
+        ++i;
+        if (j < a.gamma) { ++j; continue; }
+        if (q == 0 && wave == 0 && !(begun && b == b0)) accept_split_row(a, b, ln);
+        j = 0;
+        ++b;
+        if (KIND != 2 && i < i1) u_res = residual_draw();
     }
+    if (begun && b > b0 && q == 0 && wave == 0) accept_split_row(a, b0, lane);
 }
 
 // Per row: N_acc = first failed test, emitted token = candidate of that position, mask bits.

@@ -91,6 +91,19 @@ def test_accept_at_the_edges_of_the_vocabulary_quarters(V, T):
     assert r["ties"] <= 2
 
 
+@pytest.mark.parametrize("rows,gamma,V", [(256, 3, 16), (205, 4, 16), (500, 4, 12), (820, 4, 8), (129, 3, 8196), (37, 13, 24580), (60, 5, 24580)])
+@pytest.mark.parametrize("T", [0.0, 0.7, 1.0])
+def test_accept_with_several_items_per_group(rows, gamma, V, T):
+    """One item per group of workgroups, one more than there are groups, two and more each with rows that two groups share, more than four
+    each; on the way positions with p == q, whose draw takes a second pass, and fully separated ones."""
+    g = torch.Generator(device="cuda").manual_seed(rows * 7 + V)
+    P = torch.randn((rows, gamma + 1, V), generator=g, device="cuda") * 2
+    Q = (P[:, :gamma] + 0.5 * torch.randn((rows, gamma, V), generator=g, device="cuda")).contiguous()
+    Q[::5, 1] = P[::5, 1]                                   # p == q
+    P[3::7, 0, : V // 2], Q[3::7, 0, V // 2:] = -float("inf"), -float("inf")
+    assert check_accept(P, Q, T, seed=5, rnd=1)["ties"] <= 4
+
+
 @pytest.mark.parametrize("split", ["1", "0"])
 @pytest.mark.parametrize("T", [1e-3, 1e-15, 3e-17, 1.3e-20, 1e-30, 1e-39, 1.4e-45, 1e30])
 def test_accept_and_sampling_at_temperatures_far_from_one(T, split, monkeypatch):
