@@ -2554,7 +2554,7 @@ int32_t metasd_accept_tree(metasd_ctx* c, int32_t* n_acc_out, int32_t* token_out
         hipLaunchKernelGGL(accept_tree_walk_kernel, dim3(1), dim3(64), 0, c->stream, (const int2*)c->d_tstep(), (const int32_t*)c->d_draft(),
                            c->tshape, c->d_res(), c->d_hist() + base);
     } else {
-        int32_t* amax = reinterpret_cast<int32_t*>(c->d_cand());
+        int32_t* amax = reinterpret_cast<int32_t*>(c->d_tstep());   // (not among the tagged words of the chains: a token could be read as a tag)
         if (launch_sample(c->stream, c->d_P(), n, V, 0.f, c->cfg.seed, 0u, 0u, 0u, amax, 1, nullptr)) return c->fail(METASD_E_HIP, "launch argmax failed");
         hipLaunchKernelGGL(accept_tree_kernel, dim3(1), dim3(64), 0, c->stream, (const int32_t*)amax, (const int32_t*)c->d_draft(), c->tshape, c->d_res(),
                            c->d_hist() + base);
