@@ -9,7 +9,7 @@ SRC = os.path.join(HERE, "csrc", "metasd.hip")
 DEPS = [SRC, os.path.join(HERE, "csrc", "kernels.h"), os.path.join(HERE, "csrc", "batch.h"), os.path.join(HERE, "csrc", "prefill.h"),
         os.path.join(HERE, "csrc", "gemm_tiles.h"), os.path.join(HERE, "csrc", "step.h"), os.path.join(HERE, "csrc", "attn.h"),
         os.path.join(HERE, "csrc", "attn_plan.h"),
-        os.path.join(HERE, "csrc", "step_f32.h"),
+        os.path.join(HERE, "csrc", "step_f32.h"), os.path.join(HERE, "csrc", "chain_f32.h"),
         os.path.join(HERE, "..", "include", "metasd.h")]
 LIB = os.path.join(HERE, "libmetasd.so")
 

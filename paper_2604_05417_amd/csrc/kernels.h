@@ -1876,25 +1876,72 @@ __device__ __forceinline__ float as_min(float a, float b) {
     asm("v_min_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
     return d;
 }
-__device__ __forceinline__ float as_thread_max(const float (&x)[AS_CH][4]) {
+template <int NC>
+__device__ __forceinline__ float as_thread_max(const float (&x)[NC][4]) {
     float lm = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < AS_CH; ++c) lm = as_max3(as_max3(lm, x[c][0], x[c][1]), x[c][2], x[c][3]);
+    for (int c = 0; c < NC; ++c) lm = as_max3(as_max3(lm, x[c][0], x[c][1]), x[c][2], x[c][3]);
     return lm;
 }
 
 // x <- exp((x - mx)/T) in place (mx finite); returns this thread's sum (fp32 inside the thread).
-template <bool UNIT_T>
-__device__ __forceinline__ double as_exp_inplace(float (&x)[AS_CH][4], float mx, const ExpScale& invT) {
+template <bool UNIT_T, int NC>
+__device__ __forceinline__ double as_exp_inplace(float (&x)[NC][4], float mx, const ExpScale& invT) {
     float s = 0.f;
 #pragma unroll
-    for (int c = 0; c < AS_CH; ++c) {
+    for (int c = 0; c < NC; ++c) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[c][e] = ak_expx<UNIT_T>(x[c][e], mx, invT);
         s += (x[c][0] + x[c][1]) + (x[c][2] + x[c][3]);
         if (c & 1) __builtin_amdgcn_sched_barrier(0);           // (else the registers of the whole array are needed twice)
     }
     return (double)s;
+}
+
+// Chunk, lane and element of a wavefront's 256 NC weights (from entry `first` of the vocabulary on) at which cb + the cumulative sum of scale * w
+// exceeds target; take_last: the last one with weight.  Returns the entry in the one lane that holds it, -1 elsewhere.
+template <int NC>
+__device__ __forceinline__ int as_search_wave(const float (&w)[NC][4], double scale, double cb, double target, bool take_last, int first, int V, int lane) {
+    double sc[NC];                              // inclusive scans of the chunks, four side by side
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if (c && c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        sc[c] = dpp_scan((double)((w[c][0] + w[c][1]) + (w[c][2] + w[c][3])));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    int cstar = -1, clast = -1;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const double ct = as_lane(sc[c], 63) * scale;
+        if (ct > 0.0) clast = c;
+        if (cstar < 0 && !take_last) {
+            if (cb + ct > target) cstar = c;
+            else cb += ct;
+        }
+    }
+    if (cstar < 0) { cstar = clast < 0 ? 0 : clast; take_last = true; }
+    float w4[4] = {0.f, 0.f, 0.f, 0.f};
+    double incl = 0.0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (c == cstar) { w4[0] = w[c][0]; w4[1] = w[c][1]; w4[2] = w[c][2]; w4[3] = w[c][3]; incl = sc[c] * scale; }
+    const double mine = (double)((w4[0] + w4[1]) + (w4[2] + w4[3])) * scale;
+    unsigned long long bal = __ballot(take_last ? (mine > 0.0) : (cb + incl > target));
+    if (bal == 0ull) { take_last = true; bal = __ballot(mine > 0.0); }
+    int lstar;
+    if (bal == 0ull) lstar = 0;
+    else lstar = take_last ? (63 - __clzll((long long)bal)) : (__ffsll((long long)bal) - 1);
+    if (lane != lstar) return -1;
+    double acc = cb + incl - mine;
+    int tok = -1, lastpos = -1;
+    const int idx0 = first + cstar * 256 + lane * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        acc += (double)w4[e] * scale;
+        if (w4[e] > 0.f) lastpos = idx0 + e;
+        if (tok < 0 && !take_last && acc > target) tok = idx0 + e;
+    }
+    return tok >= 0 ? tok : lastpos >= 0 ? lastpos : min(idx0, V - 1);
 }
 
 // Quarter, wavefront, chunk, lane, element holding the target u * Z of the inverse CDF over scale * w.
@@ -1922,47 +1969,35 @@ __device__ __forceinline__ int as_search(const float (&w)[AS_CH][4], double tw, 
     };
     if (pick(tq) != q) return -1;
     if (pick(tw) != wave) return -1;
-    double sc[AS_CH];                              // inclusive scans of the chunks, four side by side
+    return as_search_wave(w, scale, base, target, take_last, q * AS_QSEG + wave * AS_WSEG, V, lane);
+}
+
+// A draw from the softmax of up to 256 NC logits (-inf past V) by one wavefront, and their argmax (lowest index on ties); the same in every lane.
+template <bool UNIT_T, int NC>
+__device__ __forceinline__ int as_wave_draw(float (&x)[NC][4], float T, float u, int V, int lane) {
+    ExpScale invT{};
+    if constexpr (!UNIT_T) invT = exp_scale(1.0 / (double)T);
+    const float mx = dpp_max(as_thread_max(x));
+    const double Z = dpp_sum(as_exp_inplace<UNIT_T>(x, mx > -INFINITY ? mx : 0.f, invT));
+    const int tok = as_search_wave(x, 1.0, 0.0, (double)u * Z, false, 0, V, lane);
+    return __builtin_amdgcn_readlane(tok, __ffsll((long long)__ballot(tok >= 0)) - 1);
+}
+template <int NC>
+__device__ __forceinline__ int as_wave_argmax(const float (&x)[NC][4], int V, int lane) {
+    float bv = -INFINITY;
+    int bi = V - 1;
 #pragma unroll
-    for (int c = 0; c < AS_CH; ++c) {
-        if (c == AS_CH / 2) __builtin_amdgcn_sched_barrier(0);
-        sc[c] = dpp_scan((double)((w[c][0] + w[c][1]) + (w[c][2] + w[c][3])));
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (x[c][e] > bv) { bv = x[c][e]; bi = c * 256 + lane * 4 + e; }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    int cstar = -1, clast = -1;
-    double cb = base;
-#pragma unroll
-    for (int c = 0; c < AS_CH; ++c) {
-        const double ct = as_lane(sc[c], 63) * scale;
-        if (ct > 0.0) clast = c;
-        if (cstar < 0 && !take_last) {
-            if (cb + ct > target) cstar = c;
-            else cb += ct;
-        }
-    }
-    if (cstar < 0) { cstar = clast < 0 ? 0 : clast; take_last = true; }
-    float w4[4] = {0.f, 0.f, 0.f, 0.f};
-    double incl = 0.0;
-#pragma unroll
-    for (int c = 0; c < AS_CH; ++c)
-        if (c == cstar) { w4[0] = w[c][0]; w4[1] = w[c][1]; w4[2] = w[c][2]; w4[3] = w[c][3]; incl = sc[c] * scale; }
-    const double mine = (double)((w4[0] + w4[1]) + (w4[2] + w4[3])) * scale;
-    unsigned long long bal = __ballot(take_last ? (mine > 0.0) : (cb + incl > target));
-    if (bal == 0ull) { take_last = true; bal = __ballot(mine > 0.0); }
-    int lstar;
-    if (bal == 0ull) lstar = 0;
-    else lstar = take_last ? (63 - __clzll((long long)bal)) : (__ffsll((long long)bal) - 1);
-    if (lane != lstar) return -1;
-    double acc = cb + incl - mine;
-    int tok = -1, lastpos = -1;
-    const int idx0 = q * AS_QSEG + wave * AS_WSEG + cstar * 256 + lane * 4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        acc += (double)w4[e] * scale;
-        if (w4[e] > 0.f) lastpos = idx0 + e;
-        if (tok < 0 && !take_last && acc > target) tok = idx0 + e;
-    }
-    return tok >= 0 ? tok : lastpos >= 0 ? lastpos : min(idx0, V - 1);
+    return __builtin_amdgcn_readfirstlane(bi);
 }
 
 // Greedy: argmax with the lowest index on ties.  xp: the logits of this item, on return those of the next.

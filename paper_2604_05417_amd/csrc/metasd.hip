@@ -24,6 +24,7 @@
 #include "gemm_tiles.h"
 #include "step.h"
 #include "step_f32.h"
+#include "chain_f32.h"
 
 using namespace msd;
 
@@ -84,10 +85,21 @@ int env_int(const char* name, int dflt) { const char* e = getenv(name); return e
 // Launch epoch of tagged exchange words (see tw_put in kernels.h): unique per launch in this process, never 0.
 // Epochs 0 (a zero-filled buffer) and 1 (the accept flag the one-workgroup accept path leaves in the upper half of a
 // candidate word) are never handed out.
-uint32_t next_epoch() {
+std::atomic<uint32_t>& epoch_counter() {
     static std::atomic<uint32_t> e{1};
+    return e;
+}
+uint32_t next_epoch() {
+    std::atomic<uint32_t>& e = epoch_counter();
     uint32_t v = ++e;
     while (v < 2) v = ++e;
+    return v;
+}
+// n consecutive ones
+uint32_t next_epochs(uint32_t n) {
+    std::atomic<uint32_t>& e = epoch_counter();
+    uint32_t v = e.fetch_add(n) + 1;
+    while (v < 2 || v + n < v) v = e.fetch_add(n) + 1;
     return v;
 }
 constexpr int KS_CAP = 8;            // split-K siblings wanted for parallelism (LDS capacity can ask for more)
@@ -195,13 +207,21 @@ bool big_pays(const metasd_model_desc& d, int pos0, int n, int nseq) {
     return small >= 25 + w + (hd > 64 ? 1.6 : 1.0) * walk * (d.n_layers - 1) / d.n_layers;
 }
 
+// Narrow fp32 models whose forward passes are one launch (chain_f32.h), and the words of an exchange region of 16 rows.
+bool chain_model(const metasd_model_desc& d) {
+    return d.dtype == METASD_F32 && d.d_model <= STEP_F32_K && d.d_ffn <= 4 * STEP_F32_K && d.d_model / d.n_heads <= 64 && d.n_layers <= CH_LAYERS;
+}
+size_t chain_region(const metasd_model_desc& d) {
+    return chain_model(d) ? chain_words(MAX_ROWS, d.d_model, d.d_ffn, d.vocab, d.n_kv_heads * (d.d_model / d.n_heads)) : 0;
+}
+
 // Word the split-K siblings of a residual GEMM set when their bounded wait for each other runs out (read back with
 // the results of every accept).
 struct GridBar { int abort; int pad[3]; };
 
 // Workspace layout shared by metasd_workspace_bytes and metasd_create.
 struct Layout {
-    size_t hist, h, h2, xn, part, gx, ssq, inv, q, ao, act, apart, rope, P, Q, cand, bd, res, draft, tstep, feat, fest, bar, xchg, tables, table_stride, total;
+    size_t hist, h, h2, xn, part, gx, ssq, inv, q, ao, act, apart, rope, P, Q, cand, bd, res, draft, tstep, feat, fest, bar, xchg, chain, tables, table_stride, total;
 };
 
 Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const metasd_model_desc* dr) {
@@ -269,6 +289,9 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
     L.tstep = take(TREE_MAX * sizeof(int2));                       // sampled tree rounds: the decision of every node
     L.bar = take(sizeof(GridBar));                                 // bd .. bar: the span read back after every round, kept small
     L.xchg = take(B * (c.gamma_max + 1) * AS_XCHG_BYTES);
+    size_t words = chain_region(t);                                // two regions of tagged words of the narrow fp32 models
+    for (int k = 0; k < c.K; ++k) words = std::max(words, chain_region(dr[k]));
+    L.chain = take(c.batch == 1 ? 2 * words * 8 : 0);
     // drafter heads: the target's feature of every processed position, and the head's estimate of the latest one
     L.feat = take(c.feature_heads ? (size_t)c.max_ctx * t.d_model * 4 : 0);
     L.fest = take(c.feature_heads ? (size_t)TREE_MAX * t.d_model * 4 : 0);   // one row per tree node (a chain uses row 0)
@@ -513,6 +536,7 @@ struct metasd_ctx {
     unsigned long long* d_gx() const { return reinterpret_cast<unsigned long long*>(ws + lay.gx); }
     float* d_ssq() const { return reinterpret_cast<float*>(ws + lay.ssq); }
     float* d_inv() const { return reinterpret_cast<float*>(ws + lay.inv); }
+    unsigned long long* d_chain() const { return reinterpret_cast<unsigned long long*>(ws + lay.chain); }
     unsigned long long* d_xchg() const { return reinterpret_cast<unsigned long long*>(ws + lay.xchg); }
     float* d_h_pp(int i) const { return reinterpret_cast<float*>(ws + (i ? lay.h2 : lay.h)); }
     void* d_q() const { return ws + lay.q; }
@@ -1010,6 +1034,48 @@ int forward_rows_f32(metasd_ctx* c, Model& M, int pos0, int m, float* logits, in
     return launch_f32_step<1, true, F32_OUT>(c, a, "gemm_f32 (head)");
 }
 
+// A forward pass, or a chain of draft steps, in one launch.  Contexts: a wavefront walks a head's positions alone, so that the separate launches, which
+// deal them out, overtake it - with heads of 32, at most one per wavefront, between 900 positions (round of 4 drafts 192 against 222 us) and
+// 1800 (266 / 208), with 16 heads between 60 (349 / 450) and 450 (514 / 460), with heads of 64 before 450 (565 / 537).  Not while launches
+// are timed one by one (metasd_profile).
+bool chain_ok(const metasd_ctx* c, const Model& M, int m, int steps, int len) {
+    const metasd_model_desc& d = M.d;
+    return c->fuse_small && c->cfg.batch == 1 && !c->tree && !M.head && !c->cfg.feature_heads && !c->prof_on && chain_model(d) && m <= MAX_ROWS &&
+           len * ((d.n_heads + CH_WAVES - 1) / CH_WAVES) * (M.hd / 32) <= 512 && (steps == 0 || d.vocab <= CH_VOCAB) &&
+           (size_t)chain_lds(m, steps, d.d_model, d.d_ffn, d.vocab, d.n_kv_heads * M.hd, M.hd, d.n_layers).end * 4 + 16 <= FULLK_LDS_MAX;
+}
+template <int MR, int KJ, int HD>
+int launch_chain_as(metasd_ctx* c, const ChainArgs& a, int groups, uint32_t lds) {
+    static const hipError_t attr = hipFuncSetAttribute((const void*)chain_f32_kernel<MR, KJ, HD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FULLK_LDS_MAX);
+    if (attr != hipSuccess) return c->fail(METASD_E_HIP, "chain_f32_kernel: cannot reserve %zu bytes of LDS", FULLK_LDS_MAX);
+    hipLaunchKernelGGL((chain_f32_kernel<MR, KJ, HD>), dim3(groups), dim3(CH_NT), lds, c->stream, a);
+    LAUNCH_CHECK(c, "chain_f32");
+    return 0;
+}
+// rows pos0 .. pos0 + m - 1 of the history; steps = 0: logits of rows first .. to out (first = m: none), else draft steps with their logits there
+int launch_chain(metasd_ctx* c, const Model& M, int pos0, int m, int first, int steps, float* out) {
+    const metasd_model_desc& d = M.d;
+    const int KVD = d.n_kv_heads * M.hd;
+    ChainArgs a{};
+    for (size_t i = 0; i < M.w.size(); ++i) a.w[i] = (const float*)M.w[i];
+    a.n_layers = d.n_layers; a.D = d.d_model; a.H = d.n_heads; a.KH = d.n_kv_heads; a.F = d.d_ffn; a.V = d.vocab; a.swiglu = d.act == METASD_SWIGLU;
+    a.max_ctx = c->cfg.max_ctx; a.eps = d.rms_eps; a.scale = 1.0f / sqrtf((float)M.hd);
+    for (int i = 0; i < M.hd / 2; ++i) a.freq[i] = std::pow((double)d.rope_theta, -2.0 * (double)i / (double)M.hd);
+    a.kv = (float*)M.kv; a.tok = c->d_hist() + pos0; a.m = m; a.pos0 = pos0; a.first = first; a.steps = steps; a.out = out;
+    a.T = c->cfg.temperature; a.seed = c->cfg.seed; a.round = (uint32_t)c->sq[0].round; a.hist = c->d_hist() + pos0 + m; a.draft = c->d_draft();
+    a.xw = c->d_chain(); a.region = chain_words(m, d.d_model, d.d_ffn, d.vocab, KVD);
+    a.tag = next_epochs(chain_exchanges(d.n_layers, steps)); a.spin_limit = std::max(0, env_int("METASD_GEMM_SPIN_LIMIT", 1 << 22)); a.abort = &c->d_bar()->abort;
+    const uint32_t lds = (uint32_t)chain_lds(m, steps, d.d_model, d.d_ffn, d.vocab, KVD, M.hd, d.n_layers).end * 4 + 16;
+    // workgroups: a unit or four per wavefront; more of them wait longer for each other (d 128: 16 of them 120 us, 8 139, 32 126; 256: 32 244, 16 271, 64
+    // 292; 512: 64 351, 32 376)
+    const int groups = std::min(64, std::max(16, d.d_model / 8));
+#define CHAIN_GO(KJ, HD) return m == 1 ? launch_chain_as<1, KJ, HD>(c, a, groups, lds) : launch_chain_as<8, KJ, HD>(c, a, groups, lds)
+    if (d.d_model <= 256) { if (M.hd == 32) CHAIN_GO(1, 32); CHAIN_GO(1, 64); }
+    if (M.hd == 32) CHAIN_GO(2, 32);
+    CHAIN_GO(2, 64);
+#undef CHAIN_GO
+}
+
 // bf16 models, general case: the two projections into the residual stream reduce their split-K partials
 // inside the GEMM and hand the next GEMM h * gain directly (EPI_RESIDUAL); the kernels that consume a
 // projection of such an input scale by 1/rms.  8 launches per layer instead of 10 (no add+norm kernels).
@@ -1213,7 +1279,8 @@ int forward_blocks(metasd_ctx* c, Model& M, int pos0, int n, float* logits, bool
         // the short-block path may leave the finished rows in the second residual buffer, which the feature copy below does not read: not
         // for the target when its features are wanted
         const bool fused = c->fuse_small && fused_small_ok(M, m) && !(is_target && c->cfg.feature_heads);
-        if (c->fuse_small && f32_step_ok(M)) rc = forward_rows_f32(c, M, pos0 + done, m, lg, first_row);
+        if (chain_ok(c, M, m, 0, pos0 + done + m)) rc = launch_chain(c, M, pos0 + done, m, lg ? first_row : m, 0, lg);
+        else if (c->fuse_small && f32_step_ok(M)) rc = forward_rows_f32(c, M, pos0 + done, m, lg, first_row);
         else if (M.d.dtype != METASD_BF16) rc = forward_rows<float>(c, M, pos0 + done, m, lg, first_row);
         else if (fused && !M.head) rc = forward_rows_fused(c, M, pos0 + done, m, lg, first_row);       // (the others carry the head's input projection)
         // (a switch that names one of the split-K forms of the residual projections asks for the path that has them)
@@ -2227,6 +2294,7 @@ int32_t metasd_create(metasd_ctx** out, const metasd_config* cfg, const metasd_m
     e = hipMemsetAsync(c->d_bar(), 0, sizeof(GridBar), c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_gx(), 0, c->lay.ssq - c->lay.gx, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_xchg(), 0, (size_t)cfg->batch * (cfg->gamma_max + 1) * AS_XCHG_BYTES, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->d_chain(), 0, lay.tables - lay.chain, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_cand(), 0, (size_t)cfg->batch * (cfg->gamma_max + 1) * 2 * sizeof(int2), c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync((void*)c->target.d_table, c->target.w.data(), c->target.w.size() * sizeof(void*), hipMemcpyHostToDevice, c->stream);
     for (int k = 0; k < cfg->K && e == hipSuccess; ++k)
@@ -2356,7 +2424,15 @@ int32_t metasd_draft(metasd_ctx* c, const int32_t* k, int32_t gamma) {
     Model& D = c->drafters[k[0]];
     const int V = D.d.vocab, l = c->sq[0].l;
     const float T = c->cfg.temperature;
-    for (int j = 0; j < gamma; ++j) {
+    // the whole chain in one launch, behind a backlog of more than the last token
+    const bool chained = !D.stream && chain_ok(c, D, 1, gamma, l + gamma);
+    if (chained) {
+        if (l - 1 > D.kvl[0])
+            if (int rc = forward(c, D, D.kvl[0], l - 1 - D.kvl[0], nullptr, false)) return rc;
+        if (int rc = launch_chain(c, D, l - 1, 1, 1, gamma, c->d_Q())) return rc;
+        D.kvl[0] = l + gamma - 1;
+    }
+    for (int j = 0; j < gamma && !chained; ++j) {
         float* Qj = c->d_Q() + (size_t)j * V;
         int rc;
         if (j == 0 && D.stream) {
