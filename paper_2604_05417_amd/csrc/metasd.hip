@@ -220,6 +220,7 @@ size_t chain_region(const metasd_model_desc& d) {
 struct GridBar { int abort; int pad[3]; };
 
 // Workspace layout shared by metasd_workspace_bytes and metasd_create.
+constexpr size_t INV_BYTES = 128;       // 1/rms of 16 rows; places of 16 rows in a plane of the cache
 struct Layout {
     size_t hist, h, h2, xn, part, gx, ssq, inv, q, ao, act, apart, rope, P, Q, cand, bd, res, draft, tstep, feat, fest, bar, xchg, chain, tables, table_stride, total;
 };
@@ -274,7 +275,7 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
     L.part = take(partmax);
     L.gx = take(gxmax);                                            // tagged partial sums of the residual GEMMs
     L.ssq = take((size_t)(dmax / 16 + 1) * 16 * 4);              // per tile group (or per tile) and row
-    L.inv = take(64);
+    L.inv = take(INV_BYTES);
     L.q = take(RM * dmax * 4);
     L.ao = take(RM * dmax * 4);
     L.act = take(RM * std::max(fmax, c.feature_heads ? 2 * dmax : 0) * 4);   // a drafter head's input rows, 2 d wide, are staged here too
@@ -734,36 +735,37 @@ StepPlan plan_step(int ntiles, int kchunks, bool pairs, bool add, int n_cu) {
     return best;
 }
 
-template <int PRO, int EPI, bool PART, int J, int U, bool HALF>
+template <int PRO, int EPI, bool PART, int J, int U, bool HALF, int NR>
 hipError_t step_allow_lds() {
-    return hipFuncSetAttribute((const void*)gemm_step_kernel<PRO, EPI, PART, J, U, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FULLK_LDS_MAX);
+    return hipFuncSetAttribute((const void*)gemm_step_kernel<PRO, EPI, PART, J, U, HALF, NR>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FULLK_LDS_MAX);
 }
-template <int PRO, int EPI, bool PART, int J, bool HALF>
+template <int PRO, int EPI, bool PART, int J, bool HALF, int NR>
 int launch_step(metasd_ctx* c, const StepArgs& a, const StepPlan& pl) {
     const int N = a.ntiles * 16;
     metasd_ctx::ProfRec* pr = c->prof_take(METASD_PROF_GEMM, (double)N * a.K * 2 + (double)a.m * a.K * 4 + (double)a.m * N * 4, N, a.K, a.m);
     const uint32_t lds = (uint32_t)step_lds(PRO == STEP_NORM, a.m, a.K);
-    constexpr int BIG = PRO == STEP_NORM ? 8 : HALF ? 3 : 4, FEW = std::min(BIG, 4);   // TERMS: the operands share the registers
-    if (pl.loads <= FEW) hipExtLaunchKernelGGL((gemm_step_kernel<PRO, EPI, PART, J, FEW, HALF>), dim3(pl.grid), dim3(1024), lds, c->stream, pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, a);
-    else hipExtLaunchKernelGGL((gemm_step_kernel<PRO, EPI, PART, J, BIG, HALF>), dim3(pl.grid), dim3(1024), lds, c->stream, pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, a);
+    constexpr int BIG = PRO == STEP_NORM ? 8 : (HALF ? 3 : 4) - (NR == 16 ? 1 : 0), FEW = std::min(BIG, 4);   // TERMS: the operands share the registers
+    if (pl.loads <= FEW) hipExtLaunchKernelGGL((gemm_step_kernel<PRO, EPI, PART, J, FEW, HALF, NR>), dim3(pl.grid), dim3(1024), lds, c->stream, pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, a);
+    else hipExtLaunchKernelGGL((gemm_step_kernel<PRO, EPI, PART, J, BIG, HALF, NR>), dim3(pl.grid), dim3(1024), lds, c->stream, pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, a);
     LAUNCH_CHECK(c, "gemm_step");
     return 0;
 }
 // the forms that stage their input may use more than 64 KiB of LDS
-template <int EPI, bool PART, int J>
+template <int EPI, bool PART, int J, int NR>
 bool step_init_one() {
-    return step_allow_lds<STEP_NORM, EPI, PART, J, 4, false>() == hipSuccess && step_allow_lds<STEP_NORM, EPI, PART, J, 8, false>() == hipSuccess;
+    return step_allow_lds<STEP_NORM, EPI, PART, J, 4, false, NR>() == hipSuccess && step_allow_lds<STEP_NORM, EPI, PART, J, 8, false, NR>() == hipSuccess;
 }
-template <int J>
-bool step_init_j() { return step_init_one<STEP_OUT, false, J>() && step_init_one<STEP_ROPE, false, J>() && step_init_one<STEP_ACT, false, J>() && (J > 2 || step_init_one<STEP_ACT, true, (J > 2 ? 1 : J)>()); }
+template <int J, int NR>
+bool step_init_j() { return step_init_one<STEP_OUT, false, J, NR>() && step_init_one<STEP_ROPE, false, J, NR>() && step_init_one<STEP_ACT, false, J, NR>(); }
 bool step_init() {
-    const bool ok = step_init_j<1>() && step_init_j<2>() && step_init_j<4>() && step_init_j<8>();
+    const bool ok = step_init_j<1, 8>() && step_init_j<2, 8>() && step_init_j<4, 8>() && step_init_j<8, 8>() && step_init_j<4, 16>() && step_init_j<8, 16>() &&
+                    step_init_one<STEP_ACT, true, 1, 8>() && step_init_one<STEP_ACT, true, 2, 8>();
     if (!ok) (void)hipGetLastError();
     return ok;
 }
 
 int step_cols(int m, int K) {           // float4 columns of a row per lane
-    const int wpr = m <= 1 ? 16 : m <= 2 ? 8 : m <= 4 ? 4 : 2;
+    const int wpr = m <= 1 ? 16 : m <= 2 ? 8 : m <= 4 ? 4 : m <= 8 ? 2 : 1;
     return (K + 256 * wpr - 1) / (256 * wpr);
 }
 bool step_ok(int m, int K) { return m <= STEP_ROWS && step_cols(m, K) <= 8 && step_lds(true, m, K) <= FULLK_LDS_MAX; }
@@ -776,13 +778,16 @@ int gemm_step_norm(metasd_ctx* c, StepArgs a, const void* W0, int n0, const void
     const StepPlan pl = plan_step(a.ntiles, a.K / 32, EPI == STEP_ACT && a.swiglu, false, c->n_cu);
     a.T = pl.T; a.S = pl.S; a.passes = pl.passes;
     const int J = step_cols(a.m, a.K);
-    if (!step_ok(a.m, a.K) || (PART && (J > 2 || a.ns < 1 || a.ns > 8)))
+    if (!step_ok(a.m, a.K) || (PART && (a.m > 8 || J > 2 || a.ns < 1 || a.ns > 8)))
         return c->fail(METASD_E_INVALID, "step GEMM: %d rows of %d, %d partials do not fit", a.m, a.K, a.ns);
-    if (J == 1) return launch_step<STEP_NORM, EPI, PART, 1, false>(c, a, pl);
-    if (PART || J == 2) return launch_step<STEP_NORM, EPI, PART, 2, false>(c, a, pl);
     if constexpr (!PART) {
-        if (J <= 4) return launch_step<STEP_NORM, EPI, PART, 4, false>(c, a, pl);
-        return launch_step<STEP_NORM, EPI, PART, 8, false>(c, a, pl);
+        if (a.m > 8) return J <= 4 ? launch_step<STEP_NORM, EPI, PART, 4, false, 16>(c, a, pl) : launch_step<STEP_NORM, EPI, PART, 8, false, 16>(c, a, pl);
+    }
+    if (J == 1) return launch_step<STEP_NORM, EPI, PART, 1, false, 8>(c, a, pl);
+    if (PART || J == 2) return launch_step<STEP_NORM, EPI, PART, 2, false, 8>(c, a, pl);
+    if constexpr (!PART) {
+        if (J <= 4) return launch_step<STEP_NORM, EPI, PART, 4, false, 8>(c, a, pl);
+        return launch_step<STEP_NORM, EPI, PART, 8, false, 8>(c, a, pl);
     }
     return 0;
 }
@@ -796,7 +801,8 @@ int gemm_step_add(metasd_ctx* c, const void* x, int m, int K, const void* W, int
     const StepPlan pl = plan_step(a.ntiles, K / 32, false, true, c->n_cu);
     a.T = pl.T; a.S = pl.S; a.passes = 1;
     if (m > STEP_ROWS) return c->fail(METASD_E_INVALID, "step GEMM: %d rows", m);
-    return pl.half ? launch_step<STEP_TERMS, STEP_ADD, false, 1, true>(c, a, pl) : launch_step<STEP_TERMS, STEP_ADD, false, 1, false>(c, a, pl);
+    if (m > 8) return pl.half ? launch_step<STEP_TERMS, STEP_ADD, false, 1, true, 16>(c, a, pl) : launch_step<STEP_TERMS, STEP_ADD, false, 1, false, 16>(c, a, pl);
+    return pl.half ? launch_step<STEP_TERMS, STEP_ADD, false, 1, true, 8>(c, a, pl) : launch_step<STEP_TERMS, STEP_ADD, false, 1, false, 8>(c, a, pl);
 }
 
 // q, k and v of layer L: q rotated in d_q, the block's K / V rows (positions pos0 ..) rotated and rounded in the cache
@@ -1197,8 +1203,19 @@ int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, 
     return 0;
 }
 
-// Short blocks (at most 8 rows) whose normalised rows fit in LDS, in general (verification, drafter heads, models wider than the path
-// above takes): 6 launches per layer (5 where attention needs no merge), none of which leaves partial sums.
+// 9 - 16 rows: the operands of a tile (16 rows of both terms, 64 bytes per input) pass through every CU beside its weights, so that a long K
+// takes longer than a split over CUs with an exchange between them.  At 12 rows: K 2048 8.7 against 12.3 us, 3072 11.5 against 13.2, 8192 18.5
+// against 14.8, 11008 28.7 against 23.
+constexpr int STEP_ADD_K = 4096;
+int residual_add(metasd_ctx* c, const void* x, int m, int K, const void* W, int N, float* h, const void* gain_next) {
+    if (m <= 8 || K <= STEP_ADD_K) return gemm_step_add(c, x, m, K, W, N, h);
+    int ntg;
+    return gemm_residual(c, x, K, m, K, W, N, (size_t)m * K, h, gain_next, (float*)c->d_xn(), c->d_ssq(), &ntg);
+}
+
+// Short blocks whose normalised rows fit in LDS, in general (8 rows of 4096 columns, 16 of 2048; verification, drafter heads, models wider than
+// the path above takes): 6 launches per layer (5 where attention needs no merge), none of which leaves partial sums.  12 rows, 1B shape, per layer:
+// 67 -> 55 us against forward_rows_residual.
 constexpr int STEP_DMIN = 512;      // from here on each of the 16 wavefronts has a chunk of the input
 int forward_rows_step(metasd_ctx* c, Model& M, int pos0, int m, float* logits, int first_row) {
     typedef bf16_t T;
@@ -1219,13 +1236,13 @@ int forward_rows_step(metasd_ctx* c, Model& M, int pos0, int m, float* logits, i
         StepArgs a = norm_in(M.layer_w(L, 0), 0);
         if ((rc = gemm_step_qkv(c, M, L, pos0, a))) return rc;
         if ((rc = attention<T>(c, M, L, pos0, m))) return rc;
-        if ((rc = gemm_step_add(c, c->d_ao(), m, DQ, M.layer_w(L, 4), D, h))) return rc;
+        if ((rc = residual_add(c, c->d_ao(), m, DQ, M.layer_w(L, 4), D, h, M.layer_w(L, 5)))) return rc;
         a = norm_in(M.layer_w(L, 5), 0);
         a.out = (float*)c->d_act(); a.N = F; a.swiglu = d.act == METASD_SWIGLU;
         if (a.swiglu) rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0);
         else rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0);
         if (rc) return rc;
-        if ((rc = gemm_step_add(c, c->d_act(), m, F, M.layer_w(L, 8), D, h))) return rc;
+        if ((rc = residual_add(c, c->d_act(), m, F, M.layer_w(L, 8), D, h, M.layer_w(L, 5)))) return rc;
     }
     if (logits) {
         StepArgs a = norm_in(M.final_norm(), first_row);
@@ -1607,8 +1624,8 @@ int forward_segs_step(metasd_ctx* c, Model& M, const Segs& sg, float* logits, in
     const int D = d.d_model, F = d.d_ffn, V = d.vocab, hd = M.hd, DQ = d.n_heads * hd, R = sg.n * sg.ms;
     hipStream_t st = c->stream;
     float* h = c->d_h();
-    long long* rowkv = reinterpret_cast<long long*>(c->d_inv());       // 8 rows: the 64 bytes of the 1/rms table, which this path does not use
-    static_assert(STEP_ROWS * sizeof(long long) <= 64, "row table");
+    long long* rowkv = reinterpret_cast<long long*>(c->d_inv());       // the 1/rms table, which this path does not use
+    static_assert(STEP_ROWS * sizeof(long long) <= INV_BYTES, "row table");
     int rc;
     hipLaunchKernelGGL(embed_seg_kernel<T>, dim3(R), dim3(256), 0, st, (const int32_t*)c->d_hist(), c->cfg.max_ctx, (const T*)M.w[0], D, h, sg);
     LAUNCH_CHECK(c, "embed (segments)");
@@ -1626,13 +1643,13 @@ int forward_segs_step(metasd_ctx* c, Model& M, const Segs& sg, float* logits, in
         a.rowkv = rowkv;
         if ((rc = gemm_step_qkv(c, M, L, 0, a))) return rc;
         if ((rc = attention_seg<T>(c, M, L, sg, at))) return rc;
-        if ((rc = gemm_step_add(c, c->d_ao(), R, DQ, M.layer_w(L, 4), D, h))) return rc;
+        if ((rc = residual_add(c, c->d_ao(), R, DQ, M.layer_w(L, 4), D, h, M.layer_w(L, 5)))) return rc;
         a = norm_in(M.layer_w(L, 5));
         a.out = (float*)c->d_act(); a.N = F; a.swiglu = d.act == METASD_SWIGLU;
         if (a.swiglu) rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 6), F, M.layer_w(L, 7), F, nullptr, 0);
         else rc = gemm_step_norm<STEP_ACT, false>(c, a, M.layer_w(L, 7), F, nullptr, 0, nullptr, 0);
         if (rc) return rc;
-        if ((rc = gemm_step_add(c, c->d_act(), R, F, M.layer_w(L, 8), D, h))) return rc;
+        if ((rc = residual_add(c, c->d_act(), R, F, M.layer_w(L, 8), D, h, M.layer_w(L, 5)))) return rc;
     }
     if (logits) {
         StepArgs a = norm_in(M.final_norm());

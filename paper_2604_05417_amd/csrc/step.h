@@ -1,4 +1,4 @@
-// Skinny GEMM of short blocks (at most 8 rows) whose K range is reduced inside the workgroup; included after kernels.h.
+// Skinny GEMM of short blocks (at most 16 rows) whose K range is reduced inside the workgroup; included after kernels.h.
 #pragma once
 
 namespace msd {
@@ -23,7 +23,7 @@ namespace msd {
 // brings the 8 features of two neighbouring chunks, multiplied with the inputs of either one (two MFMAs, each good for 8 of its rows).
 enum { STEP_NORM = 0, STEP_TERMS = 1 };
 enum { STEP_OUT = 0, STEP_ADD = 1, STEP_ACT = 2, STEP_ROPE = 3 };
-constexpr int STEP_ROWS = 8;
+constexpr int STEP_ROWS = 16;
 
 struct StepArgs {
     const float* h;                  // NORM: residual rows [m][K]
@@ -52,11 +52,15 @@ __host__ __device__ inline int step_rs(int K) { return K / 8 + 1; }
 inline size_t step_lds(bool norm, int m, int K) { return (norm ? (size_t)2 * m * step_rs(K) * 16 + 64 : 0) + (size_t)16 * 64 * 16; }
 
 // J: float4 columns of a row per lane (NORM).  U: loads of weights per group; two groups in flight.
-template <int PRO, int EPI, bool PART, int J, int U, bool HALF>
+// NR: 8, or 16 for blocks of 9 - 16 rows, whose terms are two operands.  Measured at 12 rows beside the split-K kernel with the launches behind
+// it: q | k | v of 2048 inputs and 3072 outputs 13.3 -> 8.1 us, gate | up (16384) 18.7 -> 15.1, output projection 12.3 -> 8.7.  Rows of
+// 4096 inputs do not fit: staged in two parts, q | k | v took 29.9 against 23.8 us, gate | up 39.6 against 38.2.
+template <int PRO, int EPI, bool PART, int J, int U, bool HALF, int NR>
 __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
     extern __shared__ uint4 xs[];
-    constexpr int XN = PRO == STEP_TERMS ? (HALF ? 2 * U : U) : 1;        // operands that travel with a group of weights
-    struct Group { u32x4 w[U], x[XN]; };
+    constexpr int XT = NR / 8;                                            // operands per chunk of K
+    constexpr int XN = PRO == STEP_TERMS ? (HALF ? 2 * U : U) : 1;        // chunks whose operands travel with a group of weights
+    struct Group { u32x4 w[U], x[XT * XN]; };
     const int m = a.m, K = a.K, kchunks = K >> 5, rs = step_rs(K), S = a.S, T = a.T;
     float* ssp = reinterpret_cast<float*>(xs + 2 * m * rs);
     f32x4* red = reinterpret_cast<f32x4*>(PRO == STEP_NORM ? ssp + 16 : reinterpret_cast<float*>(xs));
@@ -79,15 +83,26 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
         const int piece = HALF ? ((lane >> 3) & 1) * 64 + ((lane & 48) | (u & 1) * 8 | (lane & 7)) : lane;
         return reinterpret_cast<const u32x4*>(W) + ((size_t)tl * kchunks + c0) * 64 + piece;
     };
-    // operand column: term col / 8 of row col % 8 (columns past m repeat the last row and are never stored)
-    const int xr = min(col & 7, m - 1);
-    const u32x4* xg = reinterpret_cast<const u32x4*>(a.x + (col >> 3) * a.x_lo + (size_t)xr * K + c0 * 32 + g * 8);   // TERMS
-    const u32x4* xl = reinterpret_cast<const u32x4*>(xs) + ((col >> 3) * m + xr) * rs + g + c0 * 4;                   // NORM
+    // operand column: term col / 8 of row col % 8, or row col of either term (columns past m repeat the last row and are never stored)
+    const int xr = min(col & (NR - 1), m - 1), xt = NR == 8 ? col >> 3 : 0;
+    const u32x4* xg = reinterpret_cast<const u32x4*>(a.x + xt * a.x_lo + (size_t)xr * K + c0 * 32 + g * 8);           // TERMS
+    const u32x4* xl = reinterpret_cast<const u32x4*>(xs) + (xt * m + xr) * rs + g + c0 * 4;                           // NORM
+    const char *xhi = reinterpret_cast<const char*>(a.x), *xlo = xhi + a.x_lo * 2;       // TERMS, NR = 16: the same by bytes
+    const uint32_t xg_at = (uint32_t)(xr * K + c0 * 32 + g * 8) * 2;
+    const int xl_lo = m * rs;
     // every load is unconditional and clamped into the slice, so that each wait counts exactly the requests it needs
     auto issue = [&](Group& b, const u32x4* wp, int gi) {
         if constexpr (PRO == STEP_TERMS) {
 #pragma unroll
-            for (int u = 0; u < XN; ++u) b.x[u] = xg[(size_t)min(gi * XN + u, HALF ? 2 * last + 1 : last) * 4];
+            for (int u = 0; u < XN; ++u) {
+                const int ch = min(gi * XN + u, HALF ? 2 * last + 1 : last);
+                if constexpr (NR == 16) {
+                    b.x[2 * u] = *reinterpret_cast<const u32x4*>(xhi + (xg_at + (uint32_t)ch * 64));
+                    b.x[2 * u + 1] = *reinterpret_cast<const u32x4*>(xlo + (xg_at + (uint32_t)ch * 64));
+                } else {
+                    b.x[u] = xg[(size_t)ch * 4];
+                }
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) b.w[u] = __builtin_nontemporal_load(wp + (size_t)min(gi * U + u, last) * (HALF ? 128 : 64));
@@ -99,7 +114,7 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
         const int u = min(unit_of(0, min(wave, T - 1)), nunits - 1), q = HALF ? g & 1 : g;
         h_pre = *reinterpret_cast<const float4*>(a.out + (size_t)min(col, m - 1) * a.N + (HALF ? u * 8 : u * 16) + q * 4);
     }
-    const int lw = m <= 1 ? 0 : m <= 2 ? 1 : m <= 4 ? 2 : 3, wpr = 16 >> lw;     // wavefronts per row
+    const int lw = NR == 16 ? 4 : m <= 1 ? 0 : m <= 2 ? 1 : m <= 4 ? 2 : 3, wpr = 16 >> lw;     // wavefronts per row
     if constexpr (PRO == STEP_NORM) {
         const int row = wave >> (4 - lw), rl = min(row, m - 1), li = (wave & (wpr - 1)) * 64 + lane;
         float4 v[J], pp[PART ? J : 1][8];
@@ -143,12 +158,18 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
     } else {
         issue(ba, wp, 0);
     }
-    f32x4 acc0, acc1;                              // even and odd chunks
+    f32x4 acc0, acc1;                              // even and odd chunks; NR = 16: hi and lo terms (HALF: even and odd chunks)
     auto mul = [&](const u32x4& w, const u32x4& x, f32x4& acc) {
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
     };
     auto mul1 = [&](const Group& b, int u, int i) {
-        if constexpr (PRO == STEP_NORM) mul(b.w[u], xl[i * 4], (u & 1) ? acc1 : acc0);
+        if constexpr (PRO == STEP_NORM && NR == 16) { mul(b.w[u], xl[i * 4], acc0); mul(b.w[u], xl[xl_lo + i * 4], acc1); }
+        else if constexpr (NR == 16 && HALF) {
+            mul(b.w[u], b.x[4 * u], acc0); mul(b.w[u], b.x[4 * u + 2], acc1);
+            mul(b.w[u], b.x[4 * u + 1], acc0); mul(b.w[u], b.x[4 * u + 3], acc1);
+        }
+        else if constexpr (NR == 16) { mul(b.w[u], b.x[2 * u], acc0); mul(b.w[u], b.x[2 * u + 1], acc1); }
+        else if constexpr (PRO == STEP_NORM) mul(b.w[u], xl[i * 4], (u & 1) ? acc1 : acc0);
         else if constexpr (HALF) { mul(b.w[u], b.x[2 * u], acc0); mul(b.w[u], b.x[2 * u + 1], acc1); }
         else mul(b.w[u], b.x[u], (u & 1) ? acc1 : acc0);
     };
@@ -205,7 +226,7 @@ __global__ __launch_bounds__(1024) void gemm_step_kernel(StepArgs a) {
             for (int s = 1; s < S; ++s) y += red[(t * S + s) * 64 + lane];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                y[e] += __shfl_xor(y[e], 8, 64);
+                if constexpr (NR == 8) y[e] += __shfl_xor(y[e], 8, 64);
                 if constexpr (HALF) y[e] += __shfl_xor(y[e], 32, 64);
             }
             return y;

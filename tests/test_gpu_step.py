@@ -1,5 +1,5 @@
 """The GEMM of short blocks with its K reduction inside the workgroup (csrc/step.h) at the sizes where its split changes: block heights
-1 .. 8, K ranges that leave wavefronts without a slice or with a short one, odd numbers of 32-wide chunks (no half tiles), tile counts
+1 .. 16, K ranges that leave wavefronts without a slice or with a short one, odd numbers of 32-wide chunks (no half tiles), tile counts
 above and below the number of CUs, more tiles than one pass of a workgroup takes, GELU, grouped queries; and the same blocks through
 the kernels that take over when it is switched off.  Against the oracle, round by round."""
 import pytest
@@ -17,6 +17,10 @@ SHAPES = [
     ((512, 4, 4, 33024, W.SWIGLU, 512), (256, 4, 288, W.SWIGLU), 5),      # more pairs of tiles than one pass of 256 workgroups
     ((3072, 24, 24, 4096, W.SWIGLU, 1024), (128, 2, 160, W.SWIGLU), 7),   # 8 rows of 3072: four float4 columns and more per lane
     ((4096, 32, 8, 1024, W.SWIGLU, 512), (128, 2, 160, W.SWIGLU), 7),     # 8 rows of 4096: all eight columns, the most LDS it takes
+    ((512, 8, 8, 544, W.SWIGLU, 528), (512, 8, 544, W.GELU), 11),         # 9 - 16 rows: one chunk per wavefront, 17 chunks of d_ffn
+    ((2048, 32, 8, 1024, W.SWIGLU, 1040), (576, 9, 3104, W.GELU), 15),    # .. the most LDS it takes; half tiles and odd numbers of chunks
+    ((2048, 16, 16, 4128, W.GELU, 1040), (1024, 8, 8192, W.SWIGLU), 8),   # .. d_ffn one chunk longer than the step GEMM adds; gate | up above 256 units
+    ((2080, 65, 13, 544, W.SWIGLU, 512), (128, 2, 160, W.SWIGLU), 8),     # .. rows too wide by one chunk: the split-K path
     ((4224, 33, 11, 1024, W.SWIGLU, 512), (128, 2, 160, W.SWIGLU), 7),    # 8 rows of 4224 do not fit: verified on the split-K path
 ]
 
