@@ -89,6 +89,15 @@ __global__ void rope_kv_seg_kernel(const float* __restrict__ part, int nsplit, s
                     interleaved, q_split, nullptr, valid);
 }
 
+// grid (ceil(N / 1024), R)
+__global__ __launch_bounds__(256) void rope_kv4_seg_kernel(const float* __restrict__ part, int nsplit, size_t sstride, int N, Segs sg, int H, int KH, int hd,
+                                                           const double2* __restrict__ tab, bf16_t* __restrict__ q, bf16_t* __restrict__ kc,
+                                                           bf16_t* __restrict__ vc, size_t kv_seq_stride, int max_ctx) {
+    const int r = blockIdx.y, s = r / sg.ms, j = r - s * sg.ms;
+    const size_t so = (size_t)sg.seq[s] * kv_seq_stride;
+    rope_kv4_body(part, nsplit, sstride, N, r, gridDim.y, H, KH, hd, tab, q, kc + so, vc + so, max_ctx, (size_t)sg.pos0[s] + min(j, sg.m[s] - 1), j < sg.m[s]);
+}
+
 // The same with the cache planes of each segment given directly (kc.p[s], vc.p[s]: the planes of the segment's
 // sequence in its model, at the layer in hand).
 template <typename T>

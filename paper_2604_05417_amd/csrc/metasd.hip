@@ -1589,9 +1589,13 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
         LAUNCH_CHECK(c, "addnorm");
         if ((rc = gemm_rows<T>(c, xn, D, R, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV, &ns))) return rc;
         T* kc = (T*)M.kv + (size_t)L * 2 * plane;
-        hipLaunchKernelGGL(rope_kv_seg_kernel<T>, dim3(H + 2 * KH, R), dim3(64), 0, st, part, ns, (size_t)R * NQKV, NQKV, sg, H, KH, hd,
-                           (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, seq_stride, c->cfg.max_ctx, sizeof(T) == 2 ? 1 : 0,
-                           (split && hd >= 64) ? 1 : 0);
+        if (sizeof(T) == 2 && R >= ROPE4_ROWS && hd >= 64)
+            hipLaunchKernelGGL(rope_kv4_seg_kernel, dim3((NQKV + 1023) / 1024, R), dim3(256), 0, st, part, ns, (size_t)R * NQKV, NQKV, sg, H, KH, hd,
+                               (const double2*)c->d_rope(), (bf16_t*)c->d_q(), (bf16_t*)kc, (bf16_t*)(kc + plane), seq_stride, c->cfg.max_ctx);
+        else
+            hipLaunchKernelGGL(rope_kv_seg_kernel<T>, dim3(H + 2 * KH, R), dim3(64), 0, st, part, ns, (size_t)R * NQKV, NQKV, sg, H, KH, hd,
+                               (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, seq_stride, c->cfg.max_ctx, sizeof(T) == 2 ? 1 : 0,
+                               (split && hd >= 64) ? 1 : 0);
         LAUNCH_CHECK(c, "rope_kv (segments)");
         if ((rc = attention_seg<T>(c, M, L, sg, at))) return rc;
         if ((rc = gemm_rows_add<T>(c, c->d_ao(), R, DQ, M.layer_w(L, 4), D, h, &ns))) return rc;
@@ -1712,8 +1716,12 @@ int forward_big(metasd_ctx* c, Model& M, int seq, int pos0, int n) {
                                                                           (DQ + DKV) / 16, NQKV / 16, nullptr, (float*)c->d_q(), DQ, ep}, *pl, pr))) return rc;
             } else {
                 if ((rc = gemm_rows<T>(c, xn, D, m, D, M.layer_w(L, 1), DQ, M.layer_w(L, 2), DKV, M.layer_w(L, 3), DKV, &ns))) return rc;
-                hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, part, ns, (size_t)m * NQKV, NQKV, p0, H, KH, hd,
-                                   (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, 1, (const float*)nullptr);
+                if (m >= ROPE4_ROWS)
+                    hipLaunchKernelGGL(rope_kv4_kernel, dim3((NQKV + 1023) / 1024, m), dim3(256), 0, st, part, ns, (size_t)m * NQKV, NQKV, p0, H, KH, hd,
+                                       (const double2*)c->d_rope(), (bf16_t*)c->d_q(), kc, kc + plane, c->cfg.max_ctx);
+                else
+                    hipLaunchKernelGGL(rope_kv_kernel<T>, dim3((H + 2 * KH + 3) / 4, m), dim3(256), 0, st, part, ns, (size_t)m * NQKV, NQKV, p0, H, KH, hd,
+                                       (const double2*)c->d_rope(), (float*)c->d_q(), kc, kc + plane, c->cfg.max_ctx, 1, 1, (const float*)nullptr);
                 LAUNCH_CHECK(c, "rope_kv");
             }
             if (L + 1 == d.n_layers && !features) break;

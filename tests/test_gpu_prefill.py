@@ -76,7 +76,7 @@ HD64 = W.model_desc(3, 512, 8, 2, 736, 528, W.SWIGLU, W.BF16)
 HD128 = W.model_desc(2, 512, 4, 4, 1056, 528, W.SWIGLU, W.BF16)
 
 
-@pytest.mark.parametrize("n", [18, 33, 65, 66, 130, 257, 258, 600])
+@pytest.mark.parametrize("n", [18, 33, 65, 66, 128, 129, 130, 257, 258, 600])
 @pytest.mark.parametrize("desc", [HD64, HD128], ids=["hd64_gqa", "hd128"])
 def test_prefill_leaves_the_models_kv(desc, n):
     check_prefill(desc, n)
