@@ -183,38 +183,44 @@ __global__ void commit_tokens_kernel(const int32_t* __restrict__ n_acc, const in
 }
 
 // ------------------------------------------------------------------------------------------
-// addnorm_kernel's arithmetic (same order of additions, same results) for many rows of d = 1024 COLS columns: one
-// 256-thread workgroup per row, every thread COLS float4 columns, the row of h and all partials of a group of eight
+// addnorm_kernel's arithmetic (same order of additions, same results) for many rows of d = 1024 COLS columns (COLS = 1: at most 1024, a
+// multiple of 4): one 256-thread workgroup per row, every thread COLS float4 columns, the row of h and all partials of a group of NS
 // requested at once (up to 36 requests in flight per thread instead of 9: with one workgroup per CU the time goes with the
-// number of requests a CU keeps in flight).       grid (rows), block 256
-template <typename T, int COLS>
+// number of requests a CU keeps in flight).  NS: the smallest of 2, 4 and 8 that takes all partials at once; with eight slots whatever their
+// number (the others re-read the last one) and two barriers per column group 1499 rows of 4096 with two partials took 27.5 us, now 22.0
+// (123 MB), 256 rows with four 8.4, now 7.8.       grid (rows), block 256
+template <typename T, int COLS, int NS>
 __global__ __launch_bounds__(256) void addnorm_rows_kernel(float* __restrict__ h, const float* __restrict__ part, int nsplit, size_t sstride,
-                                                           const T* __restrict__ gain, float eps, float* __restrict__ xn, int split) {
-    __shared__ float red[4];
-    constexpr int d = 1024 * COLS;
+                                                           const T* __restrict__ gain, float eps, float* __restrict__ xn, int split, int d1) {
+    __shared__ float red[COLS][4];
+    const int d = COLS == 1 ? d1 : 1024 * COLS;
+    const bool mine = COLS > 1 || (int)threadIdx.x * 4 < d;
     const int r = blockIdx.x;
     float* hr = h + (size_t)r * d;
     const float* pr = part + (size_t)r * d;
     float4 v[COLS], gn[COLS];
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
-        const int i = threadIdx.x * 4 + 1024 * c;
+        const int i = COLS == 1 ? min((int)threadIdx.x * 4, d - 4) : (int)threadIdx.x * 4 + 1024 * c;
         v[c] = *reinterpret_cast<const float4*>(hr + i);
-        gn[c] = make_float4(El<T>::ld(gain[i]), El<T>::ld(gain[i + 1]), El<T>::ld(gain[i + 2]), El<T>::ld(gain[i + 3]));
+        if constexpr (sizeof(T) == 2) {
+            const uint2 w = *reinterpret_cast<const uint2*>(gain + i);
+            gn[c] = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u));
+        } else gn[c] = *reinterpret_cast<const float4*>(gain + i);
     }
     if (nsplit > 0) {
         float4 y[COLS];
 #pragma unroll
         for (int c = 0; c < COLS; ++c) y[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int s0 = 0; s0 < nsplit; s0 += 8) {
-            float4 p[8][COLS];
+        for (int s0 = 0; s0 < nsplit; s0 += NS) {
+            float4 p[NS][COLS];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+            for (int u = 0; u < NS; ++u)
 #pragma unroll
                 for (int c = 0; c < COLS; ++c)
-                    p[u][c] = *reinterpret_cast<const float4*>(pr + (size_t)min(s0 + u, nsplit - 1) * sstride + threadIdx.x * 4 + 1024 * c);
+                    p[u][c] = *reinterpret_cast<const float4*>(pr + (size_t)min(s0 + u, nsplit - 1) * sstride + (COLS == 1 ? min((int)threadIdx.x * 4, d - 4) : (int)threadIdx.x * 4 + 1024 * c));
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < NS; ++u) {
                 const bool on = s0 + u < nsplit;
 #pragma unroll
                 for (int c = 0; c < COLS; ++c) {
@@ -225,7 +231,7 @@ __global__ __launch_bounds__(256) void addnorm_rows_kernel(float* __restrict__ h
 #pragma unroll
         for (int c = 0; c < COLS; ++c) {
             v[c].x += y[c].x; v[c].y += y[c].y; v[c].z += y[c].z; v[c].w += y[c].w;
-            *reinterpret_cast<float4*>(hr + threadIdx.x * 4 + 1024 * c) = v[c];
+            if (mine) *reinterpret_cast<float4*>(hr + threadIdx.x * 4 + 1024 * c) = v[c];
         }
     }
     // sum of squares in addnorm_kernel's order: a thread of its 1024-thread workgroup holds one column per 4096, i.e. the
@@ -234,15 +240,17 @@ __global__ __launch_bounds__(256) void addnorm_rows_kernel(float* __restrict__ h
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
         float ss = v[c].x * v[c].x + v[c].y * v[c].y + v[c].z * v[c].z + v[c].w * v[c].w;
+        if (!mine) ss = 0.f;
         ss = wave_sum(ss);
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < 4; ++w) tot += red[w];
+        if ((threadIdx.x & 63) == 0) red[c][threadIdx.x >> 6] = ss;
     }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < COLS; ++c)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) tot += red[c][w];
     const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-    if (xn) {
+    if (xn && mine) {
 #pragma unroll
         for (int c = 0; c < COLS; ++c) {
             const int i = threadIdx.x * 4 + 1024 * c;
