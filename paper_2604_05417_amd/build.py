@@ -10,6 +10,7 @@ DEPS = [SRC, os.path.join(HERE, "csrc", "kernels.h"), os.path.join(HERE, "csrc",
         os.path.join(HERE, "csrc", "gemm_tiles.h"), os.path.join(HERE, "csrc", "step.h"), os.path.join(HERE, "csrc", "attn.h"),
         os.path.join(HERE, "csrc", "attn_plan.h"),
         os.path.join(HERE, "csrc", "step_f32.h"), os.path.join(HERE, "csrc", "chain_f32.h"),
+        os.path.join(HERE, "csrc", "chain_plan.h"),
         os.path.join(HERE, "..", "include", "metasd.h")]
 LIB = os.path.join(HERE, "libmetasd.so")
 

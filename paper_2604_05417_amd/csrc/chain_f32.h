@@ -1,6 +1,8 @@
 // Narrow fp32 models: a whole forward pass, or a whole chain of draft steps, in one launch; included after step_f32.h.
 #pragma once
 
+#include "chain_plan.h"
+
 namespace msd {
 
 // A layer of such a model is a few hundred KB that any compute unit reads in a microsecond, so its time is what stands between its four
@@ -10,14 +12,15 @@ namespace msd {
 // chip.  Weights, gains and the cached K and V of a phase do not depend on what is awaited and are requested before it.
 //   rows -> [norm, q | k | v, rotation] -> words -> [attention -> words where there are several rows -> output projection, + h] -> words -> [norm, up, activation]
 //   -> words -> [down, + h] -> words -> .. -> [norm, head] -> logits; drafting: -> words -> the draw in every workgroup -> the next step
-// Words alternate between two regions: what a workgroup writes next into a region was collected by all others before they published
-// what it has collected since.  Positions of this launch are attended to from LDS (the cache rows are written as well, for later
-// launches).  Waits are bounded: after spin_limit polls a workgroup sets *abort and all end; drafts that are then missing become token 0.
+// Exchanges take four regions of words in turn; a workgroup without units in an exchange is waited for by nobody, so what keeps the others from
+// writing over words that it still polls for are the exchanges in which every workgroup has units (chain_plan.h).  Positions of this launch are
+// attended to from LDS (the cache rows are written as well, for later launches).  Waits are bounded: after spin_limit polls a workgroup sets *abort
+// and all end; drafts that are then missing become token 0.
 // What bounds it: four (several rows: five) exchanges per layer and one per step, 0.9 - 1.1 us each, the chain of each phase's few hundred
 // instructions between them, 0.4 - 0.9 us (several rows: 1.0 - 1.7), and 2.2 us of attention at 60 positions.  Measured beside a launch per projection, a round of
 // 4 / 15 drafts of one layer and a verification of two, d 128, F = V = 512: 16 positions 176 -> 120 us, 100 positions 206 -> 130 and 597 -> 310; d 512, F 2048,
 // four layers, drafts of two, 5 drafts at 60 positions 450 -> 349.
-constexpr int CH_NT = 512, CH_WAVES = CH_NT / 64, CH_LAYERS = 8, CH_VOCAB = AS_CH * 256;
+constexpr int CH_LAYERS = 8, CH_VOCAB = AS_CH * 256;
 
 struct ChainArgs {
     const float* w[1 + 9 * CH_LAYERS + 2];         // the model's tensors in their order
@@ -33,7 +36,7 @@ struct ChainArgs {
     uint64_t seed;
     uint32_t round;
     int32_t *hist, *draft;                         // where the token of step j goes (both + j)
-    unsigned long long* xw;                        // two regions of `region` words
+    unsigned long long* xw;                        // CH_REGIONS regions of `region` words
     unsigned region;
     uint32_t tag;                                  // of the first exchange; the following ones count on
     int spin_limit;
@@ -54,7 +57,6 @@ __host__ __device__ inline ChainLds chain_lds(int m, int steps, int D, int F, in
     return o;
 }
 inline int chain_exchanges(int n_layers, int steps) { return (steps > 1 ? steps : 1) * (5 * n_layers + 1); }     // at most
-inline unsigned chain_words(int m, int D, int F, int V, int KVD) { return (unsigned)std::max(m * std::max(D + 2 * KVD, F), std::min(V, CH_VOCAB)); }
 
 template <int CTRL>
 __device__ __forceinline__ float ch_dpp(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true)); }
@@ -129,8 +131,8 @@ __device__ __forceinline__ bool ch_collect(const unsigned long long* words, int 
     return __builtin_amdgcn_readfirstlane(*fail) == 0;
 }
 
-// A wavefront's share of a projection: units gw, gw + nw, .. of NF features each, over the m rows x (LDS, ldx apart).  wptr(unit, f): the row of
-// the weights; epi(unit, r0, y): y[f] holds the sum of row r0 + lane in lanes 0 .. MR - 1.  wv: weights of U units, KB float4 columns per lane,
+// A wavefront's share of a projection: units gw, gw + nw, .. (chain_plan.h) of NF features each, over the m rows x (LDS, ldx apart).  wptr(unit, f):
+// the row of the weights; epi(unit, r0, y): y[f] holds the sum of row r0 + lane in lanes 0 .. MR - 1.  wv: weights of U units, KB float4 columns per lane,
 // the first ones requested before (ch_fetch).
 template <int U, int NF, int KB, typename WP>
 __device__ __forceinline__ void ch_fetch(float4 (&wv)[U * NF * KB], int i0, int units, int gw, int nw, int K, int k0, int lane, WP wptr) {
@@ -240,16 +242,16 @@ __global__ __launch_bounds__(CH_NT) void chain_f32_kernel(ChainArgs a) {
     // nothing that follows from the lane is kept in registers from one phase to the next (the loops over layers and steps invite that)
     auto fresh = [&]() { asm volatile("" : "+v"(lane), "+v"(tid)); };
     const int D = a.D, F = a.F, V = a.V, H = a.H, KH = a.KH, KVD = KH * HD, NQ = D + 2 * KVD;
-    const int gw = (int)blockIdx.x * CH_WAVES + wave, nw = (int)gridDim.x * CH_WAVES;
+    const int gw = chain_first(blockIdx.x, gridDim.x, wave, chain_side(a.D)), nw = (int)gridDim.x * CH_WAVES;
     const ChainLds o = chain_lds(a.m, a.steps, D, F, V, KVD, HD, a.n_layers);
     float *h = sh + o.h, *xb = sh + o.x, *qb = sh + o.q, *kvb = sh + o.kv;
     double2* tab = reinterpret_cast<double2*>(sh + o.tab);
     int *fail = reinterpret_cast<int*>(sh + o.end), *token = fail + 1;
     const int rows_all = a.m + max(a.steps - 1, 0);            // positions of the launch
     uint32_t tag = a.tag;
-    int flip = 0;
+    unsigned turn = 0;
     unsigned long long* words = a.xw;
-    auto next_exchange = [&]() { ++tag; flip ^= 1; words = a.xw + (size_t)flip * a.region; };
+    auto next_exchange = [&]() { ++tag; turn = (turn + 1) % CH_REGIONS; words = a.xw + (size_t)turn * a.region; };
     auto give_up = [&](int step) {                     // (every workgroup ends: those that wait for this one time out too)
         if (tid == 0) *a.abort = 1;
         if (a.steps && step + tid < a.steps) { a.hist[step + tid] = 0; a.draft[step + tid] = 0; }

@@ -212,7 +212,7 @@ bool chain_model(const metasd_model_desc& d) {
     return d.dtype == METASD_F32 && d.d_model <= STEP_F32_K && d.d_ffn <= 4 * STEP_F32_K && d.d_model / d.n_heads <= 64 && d.n_layers <= CH_LAYERS;
 }
 size_t chain_region(const metasd_model_desc& d) {
-    return chain_model(d) ? chain_words(MAX_ROWS, d.d_model, d.d_ffn, d.vocab, d.n_kv_heads * (d.d_model / d.n_heads)) : 0;
+    return chain_model(d) ? chain_words({MAX_ROWS, d.d_model, d.n_heads, d.n_kv_heads, d.d_model / d.n_heads, d.d_ffn, d.vocab}, CH_VOCAB) : 0;
 }
 
 // Word the split-K siblings of a residual GEMM set when their bounded wait for each other runs out (read back with
@@ -290,9 +290,9 @@ Layout make_layout(const metasd_config& c, const metasd_model_desc& t, const met
     L.tstep = take(TREE_MAX * sizeof(int2));                       // sampled tree rounds: the decision of every node
     L.bar = take(sizeof(GridBar));                                 // bd .. bar: the span read back after every round, kept small
     L.xchg = take(B * (c.gamma_max + 1) * AS_XCHG_BYTES);
-    size_t words = chain_region(t);                                // two regions of tagged words of the narrow fp32 models
+    size_t words = chain_region(t);                                // regions of tagged words of the narrow fp32 models
     for (int k = 0; k < c.K; ++k) words = std::max(words, chain_region(dr[k]));
-    L.chain = take(c.batch == 1 ? 2 * words * 8 : 0);
+    L.chain = take(c.batch == 1 ? CH_REGIONS * words * 8 : 0);
     // drafter heads: the target's feature of every processed position, and the head's estimate of the latest one
     L.feat = take(c.feature_heads ? (size_t)c.max_ctx * t.d_model * 4 : 0);
     L.fest = take(c.feature_heads ? (size_t)TREE_MAX * t.d_model * 4 : 0);   // one row per tree node (a chain uses row 0)
@@ -1069,12 +1069,10 @@ int launch_chain(metasd_ctx* c, const Model& M, int pos0, int m, int first, int 
     for (int i = 0; i < M.hd / 2; ++i) a.freq[i] = std::pow((double)d.rope_theta, -2.0 * (double)i / (double)M.hd);
     a.kv = (float*)M.kv; a.tok = c->d_hist() + pos0; a.m = m; a.pos0 = pos0; a.first = first; a.steps = steps; a.out = out;
     a.T = c->cfg.temperature; a.seed = c->cfg.seed; a.round = (uint32_t)c->sq[0].round; a.hist = c->d_hist() + pos0 + m; a.draft = c->d_draft();
-    a.xw = c->d_chain(); a.region = chain_words(m, d.d_model, d.d_ffn, d.vocab, KVD);
+    a.xw = c->d_chain(); a.region = chain_words({m, d.d_model, d.n_heads, d.n_kv_heads, M.hd, d.d_ffn, d.vocab}, CH_VOCAB);
     a.tag = next_epochs(chain_exchanges(d.n_layers, steps)); a.spin_limit = std::max(0, env_int("METASD_GEMM_SPIN_LIMIT", 1 << 22)); a.abort = &c->d_bar()->abort;
     const uint32_t lds = (uint32_t)chain_lds(m, steps, d.d_model, d.d_ffn, d.vocab, KVD, M.hd, d.n_layers).end * 4 + 16;
-    // workgroups: a unit or four per wavefront; more of them wait longer for each other (d 128: 16 of them 120 us, 8 139, 32 126; 256: 32 244, 16 271, 64
-    // 292; 512: 64 351, 32 376)
-    const int groups = std::min(64, std::max(16, d.d_model / 8));
+    const int groups = chain_groups(d.d_model);
 #define CHAIN_GO(KJ, HD) return m == 1 ? launch_chain_as<1, KJ, HD>(c, a, groups, lds) : launch_chain_as<8, KJ, HD>(c, a, groups, lds)
     if (d.d_model <= 256) { if (M.hd == 32) CHAIN_GO(1, 32); CHAIN_GO(1, 64); }
     if (M.hd == 32) CHAIN_GO(2, 32);
