@@ -4,7 +4,6 @@
 // (see check_model / the asserts next to each launcher), kernels themselves only guard ragged tails.
 #pragma once
 
-
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -1800,7 +1799,7 @@ __global__ __launch_bounds__(AK_NT) void accept_rows_kernel(const float* __restr
 constexpr int AS_NT = 256, AS_WAVES = 4, AS_CH = 8, AS_WSEG = AS_CH * 256, AS_Q = 4, AS_QSEG = AS_WAVES * AS_WSEG;
 constexpr int AS_WORDS = 10;                                   // exchange words per quarter
 constexpr int AS_XCHG_BYTES = AS_Q * AS_WORDS * 8;             // per (row, position)
-constexpr int AS_SLOTS = 1024;                                 // workgroups of a launch: four on each of 256 CUs
+constexpr int AS_SLOTS = 1024;                                 // workgroups the chip holds: four on each of 256 CUs (only the speed depends on it)
 constexpr uint32_t AS_CAND_FAIL = 1u << 29;
 
 struct AsShared {
@@ -2052,9 +2051,8 @@ __device__ __forceinline__ int as_wave_argmax(const float (&x)[NC][4], int V, in
     return __builtin_amdgcn_readfirstlane(bi);
 }
 
-// Greedy: argmax with the lowest index on ties.  xp: the logits of this item, on return those of the next.
-__device__ __forceinline__ void accept_split_greedy(const AsArgs& a, size_t item, int b, int j, const float* next, float (&xp)[AS_CH][4], AsShared& sm,
-                                                    int q, int wave, int lane) {
+// Greedy: argmax with the lowest index on ties.  xp: the logits of the item.
+__device__ __forceinline__ void accept_split_greedy(const AsArgs& a, size_t item, int b, int j, float (&xp)[AS_CH][4], AsShared& sm, int q, int wave, int lane) {
     const int seg0 = q * AS_QSEG + wave * AS_WSEG, tid = wave * 64 + lane;
     unsigned long long* slots = a.xchg + item * (AS_Q * AS_WORDS);
     float bv = -INFINITY;
@@ -2067,8 +2065,6 @@ __device__ __forceinline__ void accept_split_greedy(const AsArgs& a, size_t item
             const int idx = seg0 + c * 256 + lane * 4 + e;
             if (xp[c][e] > bv) { bv = xp[c][e]; bi = idx; }
         }
-    if (next) as_load(next, a.V, seg0, lane, xp);
-    else as_forget(xp);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const float ov = __shfl_xor(bv, o, 64);
@@ -2240,20 +2236,27 @@ __device__ __forceinline__ void accept_split_row(const AsArgs& a, int b, int j) 
 // grid nq (quarters the vocabulary reaches into) x groups, quarters of a group next to each other; block 256
 template <int KIND>                                // 0: T = 1, 1: other T > 0, 2: greedy
 __global__ __launch_bounds__(AS_NT, 4) void accept_split_kernel(AsArgs a, RoundTab rt) {
-    __shared__ AsShared sm[2];                     // items take them in turn: a wavefront can be one item ahead of another
+    __shared__ AsShared sm[KIND == 2 ? 1 : 2];     // items take them in turn: a wavefront can be one item ahead of another
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // the group's items: consecutive, as many as any other's or one more (readfirstlane: a quotient is formed in vector registers)
     const int group = __builtin_amdgcn_readfirstlane((int)blockIdx.x / a.nq), q = (int)blockIdx.x - group * a.nq;
     const int i0 = group * a.per + min(group, a.extra), i1 = i0 + a.per + (group < a.extra ? 1 : 0);
     float xp[AS_CH][4];
     as_load(a.P + (size_t)i0 * a.V, a.V, q * AS_QSEG + wave * AS_WSEG, lane, xp);
-    if (threadIdx.x < 2 * AS_Q * AS_WORDS) {       // a quarter without a workgroup: no maximum, no mass
+    if (threadIdx.x < sizeof(sm) / sizeof(sm[0]) * AS_Q * AS_WORDS) {       // a quarter without a workgroup: no maximum, no mass
         const int s = (int)threadIdx.x / (AS_Q * AS_WORDS), i = (int)threadIdx.x - s * (AS_Q * AS_WORDS);
         (&sm[s].xw[0][0])[i] = i % AS_WORDS < 2 ? -INFINITY : 0.f;
     }
     ExpScale invT{};
     if constexpr (KIND == 1) invT = exp_scale(1.0 / (double)a.T);
     const int b0 = __builtin_amdgcn_readfirstlane(i0 / (a.gamma + 1));
+    if constexpr (KIND == 2) {                     // one item (launch_accept)
+        __syncthreads();
+        const int j = i0 - b0 * (a.gamma + 1);
+        accept_split_greedy(a, i0, b0, j, xp, sm[0], q, wave, lane);
+        if (j == a.gamma && q == 0 && wave == 0) accept_split_row(a, b0, lane);
+        return;
+    }
     int b = b0, j = i0 - b0 * (a.gamma + 1), turn = 0;
     const bool begun = j != 0;                     // row b0 was begun by the group before
     auto residual_draw = [&]() {
@@ -2261,7 +2264,7 @@ __global__ __launch_bounds__(AS_NT, 4) void accept_split_kernel(AsArgs a, RoundT
         asm volatile("" : "+s"(seed));             // (see above)
         return philox_uniform(seed, a.seq0 + (uint32_t)b, round_of(rt, b), 0u, 1u);
     };
-    float u_res = KIND == 2 ? 0.f : residual_draw();
+    float u_res = residual_draw();
     bool again = false;
     __syncthreads();
     for (int i = i0; i < i1;) {
@@ -2269,17 +2272,14 @@ __global__ __launch_bounds__(AS_NT, 4) void accept_split_kernel(AsArgs a, RoundT
         asm volatile("" : "+v"(ln), "+s"(it));     // nothing that follows from the lane or the item is kept in registers from one item to the next
         const float* next = it + 1 < i1 ? a.P + (size_t)(it + 1) * a.V : nullptr;
         AsShared& s = sm[turn ^= 1];
-        if constexpr (KIND == 2) accept_split_greedy(a, it, b, j, next, xp, s, q, wave, ln);
-        else {
-            again = __builtin_amdgcn_readfirstlane((int)accept_split_item<KIND == 0>(a, rt, invT, it, b, j, j < a.gamma && !again, u_res, next, xp, s, q, wave, ln)) != 0;
-            if (again) { as_load(a.P + (size_t)it * a.V, a.V, q * AS_QSEG + wave * AS_WSEG, ln, xp); continue; }
-        }
+        again = __builtin_amdgcn_readfirstlane((int)accept_split_item<KIND == 0>(a, rt, invT, it, b, j, j < a.gamma && !again, u_res, next, xp, s, q, wave, ln)) != 0;
+        if (again) { as_load(a.P + (size_t)it * a.V, a.V, q * AS_QSEG + wave * AS_WSEG, ln, xp); continue; }
         ++i;
         if (j < a.gamma) { ++j; continue; }
         if (q == 0 && wave == 0 && !(begun && b == b0)) accept_split_row(a, b, ln);
         j = 0;
         ++b;
-        if (KIND != 2 && i < i1) u_res = residual_draw();
+        if (i < i1) u_res = residual_draw();
     }
     if (begun && b > b0 && q == 0 && wave == 0) accept_split_row(a, b0, lane);
 }

@@ -1940,7 +1940,8 @@ int launch_accept(hipStream_t st, const float* P, const float* Q, const int32_t*
         // as many quarters as the vocabulary reaches into (one: no meeting at all), and as many groups of them as the chip holds at once, so
         // that a group requests its next item while it finishes one: 64 rows, gamma 5 24.4 against 26.1 us, 700 rows x 2 of 4096 17.5 / 19.2.
         // Past four items each the groups no longer end together and one item per group is faster (250 rows, gamma 7 96.8 / 93.4, 1000 x 2 of
-        // 16000 47.3 / 49.9); greedy ones, whose items are one read, always (64 rows 13.3 / 12.9).
+        // 16000 47.3 / 49.9); greedy ones, whose items are one read, always have one (64 rows 13.3 us with several, 12.9 with
+        // one and the loop over items, 12.3 without it).
         const int nq = (V + AS_QSEG - 1) / AS_QSEG, items = rows * (gamma + 1), slots = AS_SLOTS / nq;
         const int groups = T > 0.f && items <= 4 * slots ? std::min(items, slots) : items;
         const AsArgs a{P, Q, d, gamma, V, T, seed, seq0, (unsigned long long*)cand, bd, xchg, next_epoch(), std::max(0, env_int("METASD_ACCEPT_SPIN_LIMIT", 1 << 18)),

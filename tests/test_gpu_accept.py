@@ -91,11 +91,13 @@ def test_accept_at_the_edges_of_the_vocabulary_quarters(V, T):
     assert r["ties"] <= 2
 
 
-@pytest.mark.parametrize("rows,gamma,V", [(256, 3, 16), (205, 4, 16), (500, 4, 12), (820, 4, 8), (129, 3, 8196), (37, 13, 24580), (60, 5, 24580)])
+@pytest.mark.parametrize("rows,gamma,V", [(256, 3, 16), (205, 4, 16), (500, 4, 12), (1024, 3, 8), (820, 4, 8), (129, 3, 8196), (512, 3, 8196), (37, 13, 24580),
+                                          (60, 5, 24580), (128, 7, 24580)])
 @pytest.mark.parametrize("T", [0.0, 0.7, 1.0])
 def test_accept_with_several_items_per_group(rows, gamma, V, T):
-    """One item per group of workgroups, one more than there are groups, two and more each with rows that two groups share, more than four
-    each; on the way positions with p == q, whose draw takes a second pass, and fully separated ones."""
+    """Items of a group of workgroups: one, one or two, two or three with rows that two groups share, exactly four (1024 x 4 and 512 x 4
+    items, 128 x 8 of a longer vocabulary); past that (820 x 5 items) and greedy (T = 0) one each.  On the way positions with p == q, whose draw takes a
+    second pass, and fully separated ones."""
     g = torch.Generator(device="cuda").manual_seed(rows * 7 + V)
     P = torch.randn((rows, gamma + 1, V), generator=g, device="cuda") * 2
     Q = (P[:, :gamma] + 0.5 * torch.randn((rows, gamma, V), generator=g, device="cuda")).contiguous()
