@@ -2320,7 +2320,7 @@ int32_t metasd_create(metasd_ctx** out, const metasd_config* cfg, const metasd_m
     e = hipMemsetAsync(c->d_bar(), 0, sizeof(GridBar), c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_gx(), 0, c->lay.ssq - c->lay.gx, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_xchg(), 0, (size_t)cfg->batch * (cfg->gamma_max + 1) * AS_XCHG_BYTES, c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->d_chain(), 0, lay.tables - lay.chain, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->d_chain(), 0, c->lay.feat - c->lay.chain, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_cand(), 0, (size_t)cfg->batch * (cfg->gamma_max + 1) * 2 * sizeof(int2), c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync((void*)c->target.d_table, c->target.w.data(), c->target.w.size() * sizeof(void*), hipMemcpyHostToDevice, c->stream);
     for (int k = 0; k < cfg->K && e == hipSuccess; ++k)
