@@ -102,6 +102,10 @@ uint32_t next_epochs(uint32_t n) {
     while (v < 2 || v + n < v) v = e.fetch_add(n) + 1;
     return v;
 }
+// Polls after which a workgroup gives up a wait for another one.  Split-K siblings are neighbours in the order of dispatch and wait for one
+// another's product: 2^18, a few tenths of a second.  The workgroups of a chain (chain_f32.h) need all of them resident and may wait for one that
+// has no place yet behind another stream's kernels: 2^22.
+int gemm_spin_limit(int dflt) { return std::max(0, env_int("METASD_GEMM_SPIN_LIMIT", dflt)); }
 constexpr int KS_CAP = 8;            // split-K siblings wanted for parallelism (LDS capacity can ask for more)
 constexpr int ks_cap() { return KS_CAP; }
 
@@ -688,7 +692,7 @@ int gemm_residual(metasd_ctx* c, const void* x, int ldx, int m, int K, const voi
     epi.xw = c->d_gx(); epi.h = h; epi.gain = (const bf16_t*)gain_next; epi.xsplit = xsplit; epi.ssq = ssq;
     epi.abort = &reinterpret_cast<GridBar*>(c->d_bar())->abort;
     epi.epoch = next_epoch();
-    epi.spin_limit = std::max(0, env_int("METASD_GEMM_SPIN_LIMIT", 1 << 18));
+    epi.spin_limit = gemm_spin_limit(1 << 18);
     hipExtLaunchKernelGGL((gemm_bf16_kernel<PRO_PLAIN, EPI_RESIDUAL>), dim3(groups * s.ksplit), dim3(256), (uint32_t)s.lds, c->stream,
                           pr ? pr->a : nullptr, pr ? pr->b : nullptr, 0u, (const float*)x, ldx, m, K, (const bf16_t*)W,
                           (const bf16_t*)W, (const bf16_t*)W, ntiles, ntiles, ntiles, (float*)nullptr, N, s.ksplit, s.cps, s.tpb,
@@ -1070,7 +1074,7 @@ int launch_chain(metasd_ctx* c, const Model& M, int pos0, int m, int first, int 
     a.kv = (float*)M.kv; a.tok = c->d_hist() + pos0; a.m = m; a.pos0 = pos0; a.first = first; a.steps = steps; a.out = out;
     a.T = c->cfg.temperature; a.seed = c->cfg.seed; a.round = (uint32_t)c->sq[0].round; a.hist = c->d_hist() + pos0 + m; a.draft = c->d_draft();
     a.xw = c->d_chain(); a.region = chain_words({m, d.d_model, d.n_heads, d.n_kv_heads, M.hd, d.d_ffn, d.vocab}, CH_VOCAB);
-    a.tag = next_epochs(chain_exchanges(d.n_layers, steps)); a.spin_limit = std::max(0, env_int("METASD_GEMM_SPIN_LIMIT", 1 << 22)); a.abort = &c->d_bar()->abort;
+    a.tag = next_epochs(chain_exchanges(d.n_layers, steps)); a.spin_limit = gemm_spin_limit(1 << 22); a.abort = &c->d_bar()->abort;
     const uint32_t lds = (uint32_t)chain_lds(m, steps, d.d_model, d.d_ffn, d.vocab, KVD, M.hd, d.n_layers).end * 4 + 16;
     const int groups = chain_groups(d.d_model);
 #define CHAIN_GO(KJ, HD) return m == 1 ? launch_chain_as<1, KJ, HD>(c, a, groups, lds) : launch_chain_as<8, KJ, HD>(c, a, groups, lds)
