@@ -384,6 +384,26 @@ def test_bf16_few_rows_of_several_sequences(heads, kv, B, gamma):
         assert st["max_dp"] <= 4e-3 and st["max_dq"] <= 4e-3 and st["ties_shared"] <= 1, st     # (bound: see test_gpu_attn.py)
 
 
+@pytest.mark.parametrize("d,heads,kv,ffn,act,layers,B,gamma", [(512, 8, 2, 4128, W.SWIGLU, 2, 3, 3), (1024, 8, 8, 5120, W.GELU, 2, 8, 1),
+                                                              (2048, 32, 8, 8192, W.SWIGLU, 1, 4, 3), (512, 4, 4, 4096, W.SWIGLU, 2, 3, 2)])
+def test_bf16_nine_to_sixteen_rows_of_several_sequences(d, heads, kv, ffn, act, layers, B, gamma):
+    """Verification of 9 to 16 rows over several sequences: the step GEMMs with 16 rows, the down projection of more than 4096 inputs on the
+    split-K kernel between them (and of 4096 inputs not); catch-ups with padding rows; prompts of different lengths."""
+    td = W.model_desc(layers, d, heads, kv, ffn, 1024, act, W.BF16)
+    dd = W.model_desc(1, 512, 8, 2, 4160, 1024, W.GELU, W.BF16)
+    cfg = dict(target=(td, W.gen_weights(td, 0)), drafters=[(dd, W.gen_weights(dd, 7)), (dd, W.gen_weights(dd, 8))], gamma=gamma, beta=1.0, seed=3,
+               max_ctx=120, prompt=W.prompt_tokens(40, 1024, 1))
+    prompts = [W.prompt_tokens(max(2, 40 - 11 * b), 1024, 40 + b) for b in range(B)]
+    g, seqs = batch_pair(cfg, 1.0, prompts, TOL)
+    bl = make_lockstep(g, cfg, seqs, prompts, 1.0, TOL)
+    for r in range(4):                                      # a sequence that returns to an arm has two rounds to catch up with
+        bl.round([(b + r // 2) % 2 for b in range(B)])
+    g.close()
+    for ls in bl.seqs:
+        st = ls.stats
+        assert st["max_dp"] <= TOL and st["max_dq"] <= TOL and st["ties_shared"] <= 1, st
+
+
 @pytest.mark.parametrize("grouped", ["1", "0"])
 @pytest.mark.parametrize("heads,kv", [(8, 2), (4, 4), (12, 12)])
 def test_bf16_one_long_context_among_short_ones(heads, kv, grouped, monkeypatch):
