@@ -344,7 +344,9 @@ int32_t metasd_stream_read(const void* src, size_t bytes, uint32_t* sink, void* 
 /* max_records > 0: from now on every launch of the bandwidth-bound kernels carries a pair of HIP
  * events attached to the dispatch itself (begin and end of that kernel on the context's stream).  At most
  * max_records launches are recorded; the event pool is created here, not in the hot path, and
- * the record count is reset.  0: stop recording. */
+ * the record count is reset.  0: stop recording.  Only kernels of one product each can be told apart: while
+ * recording, narrow fp32 models, whose forward pass or draft chain is otherwise one launch, take a launch per
+ * projection (same results within rounding, slower). */
 int32_t metasd_profile(metasd_ctx*, int32_t max_records);
 /* Synchronise and sum over the recorded launches of one kind: elapsed milliseconds, number of
  * launches, algorithmic bytes (weights / KV / logits each counted once per launch, plus the

@@ -1207,7 +1207,8 @@ int forward_rows_fused(metasd_ctx* c, Model& M, int pos0, int m, float* logits, 
 
 // 9 - 16 rows: the operands of a tile (16 rows of both terms, 64 bytes per input) pass through every CU beside its weights, so that a long K
 // takes longer than a split over CUs with an exchange between them.  At 12 rows: K 2048 8.7 against 12.3 us, 3072 11.5 against 13.2, 8192 18.5
-// against 14.8, 11008 28.7 against 23.
+// against 14.8, 11008 28.7 against 23 (with the normalised rows and their sums of squares that the split-K kernel also writes: they go to
+// scratch that nothing reads here - the next step GEMM normalises h - and gain_next is only there to be multiplied with).
 constexpr int STEP_ADD_K = 4096;
 int residual_add(metasd_ctx* c, const void* x, int m, int K, const void* W, int N, float* h, const void* gain_next) {
     if (m <= 8 || K <= STEP_ADD_K) return gemm_step_add(c, x, m, K, W, N, h);
@@ -1553,7 +1554,8 @@ int attention_big(metasd_ctx* c, const metasd_model_desc& d, int hd, const bf16_
 }
 
 // add the split-K partials to the residual rows and normalise: many rows of 2048, 4096 or at most 1024 columns go through the form that
-// keeps more requests in flight per CU (same arithmetic in the same order); rows of 768 columns, of whose
+// keeps more requests in flight per CU (same arithmetic in the same order; other widths, which are no models of this library's own workloads,
+// have not been measured and keep the general form); rows of 768 columns, of whose
 // 1024 threads a workgroup of the general form uses 192: 32 rows 6.6 -> 4.2 us, 288 rows 17.4 -> 4.7, 1499 rows 19.8 -> 5.7
 template <typename T>
 void launch_addnorm_many(metasd_ctx* c, int R, float* h, const float* part, int ns, int D, const T* gain, float eps, float* xn, int split) {
@@ -1620,7 +1622,7 @@ int forward_segs_t(metasd_ctx* c, Model& M, const Segs& sg, float* logits, int o
     return 0;
 }
 
-// At most 8 rows of several sequences (the drafter steps of a small batch, its verification of a token or two): the step GEMMs of
+// At most 8 rows (16 of at most 2048 columns) of several sequences (the drafter steps of a small batch, its verification): the step GEMMs of
 // forward_rows_step with the rows' places in their caches taken from a table - 5 launches per layer (6 where attention leaves records)
 // instead of 10.  One row in each of 5 sequences, 1B shape, per layer: 60 -> 43 us.
 bool segs_step_ok(const metasd_ctx* c, const Model& M, int R) {
